@@ -80,6 +80,14 @@ constexpr int BM = 256;
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kComputeUnits = 256;           // MI355X
+// Up to this many rows per expert on average the weight loads are non-temporal: an expert is one row tile then, every
+// weight is read once, and a line that will not be read again should not push others out.  A kernel of nothing but
+// loads over 2 GiB reads 7.1 TB/s with the hint and 5.9 - 6.4 without, whatever the piece per block.  Layer of the
+// Mixtral-8x7B shape, without / with, us: 16 tokens 517 / 471, 64: 506 / 466, 256: 548 / 505, 400: 568 / 537,
+// 1000: 760 / 709, 1024: 769 / 733; with several row tiles per expert the second one finds less in the L2: 1150 tokens
+// 1015 / 1038, 1536: 1063 / 1125, 4096: 2145 / 2190.  On 64 experts (2048 x 1024) the line lies at the same
+// place: 250 rows per expert 522 / 504, 375 rows 626 / 662.
+constexpr int kStreamRows = 256;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
 constexpr int kHalfTile = 128 * kRowB;       // one weight half-tile
 constexpr int kStageB = 2 * kHalfTile;       // weight stage of one half-step: two half-tiles
@@ -135,12 +143,17 @@ __device__ __forceinline__ void mfma_16x16x32(const i32x4& a, const i32x4& b) { 
 // (The compiler puts an s_nop in front of every such statement that follows another within a few instructions, because
 // M0 is on the clobber list: six per half-step.  They issue in the shadow of an MFMA: a build without the clobber,
 // and so without them, was not faster.)
-template <int R, int LDS_IMM>
+template <int R, int LDS_IMM, bool STREAM>
 __device__ __forceinline__ void mfma_16x16x32_then_load(const i32x4& a, const i32x4& b, const char* base, uint32_t offset, uint32_t lds_base) {
 #ifdef __HIP_DEVICE_COMPILE__
-    asm volatile("s_add_i32 m0, %4, %5\n\tv_mfma_f32_16x16x32_bf16 a[%6:%7], %0, %1, a[%6:%7]\n\tglobal_load_lds_dwordx4 %2, %3"
-                 ::"v"(a), "v"(b), "v"(offset), "s"(base), "s"(lds_base), "n"(LDS_IMM), "n"(R), "n"(R + 3)
-                 : "memory", "m0");
+    if constexpr (STREAM)
+        asm volatile("s_add_i32 m0, %4, %5\n\tv_mfma_f32_16x16x32_bf16 a[%6:%7], %0, %1, a[%6:%7]\n\tglobal_load_lds_dwordx4 %2, %3 nt"
+                     ::"v"(a), "v"(b), "v"(offset), "s"(base), "s"(lds_base), "n"(LDS_IMM), "n"(R), "n"(R + 3)
+                     : "memory", "m0");
+    else
+        asm volatile("s_add_i32 m0, %4, %5\n\tv_mfma_f32_16x16x32_bf16 a[%6:%7], %0, %1, a[%6:%7]\n\tglobal_load_lds_dwordx4 %2, %3"
+                     ::"v"(a), "v"(b), "v"(offset), "s"(base), "s"(lds_base), "n"(LDS_IMM), "n"(R), "n"(R + 3)
+                     : "memory", "m0");
 #endif
 }
 // The same MFMA with its accumulator tile in vector registers the compiler allocates, and a plain 16-byte load
@@ -246,18 +259,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 
+// STREAM: the weight loads carry the non-temporal hint (see kStreamRows).
 // NB: page tiles per block along the columns.  2: the 256-column block described above.  1 (MODE 1
 // only): 256 rows x 128 columns, wavefront tile 128 x 64, for launches with too few 256-wide tiles
 // to occupy the chip (few rows per expert: the launch is bound by streaming the weights, and more
 // blocks stream more).
-template <int MODE, int NB>
+template <int MODE, int NB, bool STREAM>
 __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     constexpr int S = kStages;
-    // GU1: the gate/up block with half the columns: 64 features, i.e. the 64 rows of the W1 tile and of the W3 tile that
-    // belong to them (rows sel*64 .. of both page tiles; a page tile's LDS image is linear in its rows, so half of it is
-    // one 4 KiB piece).  In LDS the stage looks like the one page tile of the narrow down block: rows 0..63 gate, 64..127 up.
-    constexpr bool GU1 = MODE == 0 && NB == 1;
-    constexpr bool TWO_WALKS = NB == 2 || GU1;   // two page tiles are walked along k
+    static_assert(MODE == 1 || NB == 2, "the narrow block is the down projection's");
+    constexpr bool TWO_WALKS = NB == 2;          // two page tiles are walked along k
     constexpr int NJ = 4 * NB;                   // 16-column MFMA tiles (B fragments) per wavefront
     constexpr int NMF = 4 * NJ;                  // MFMAs of a group: four 16-row tiles x NJ
     constexpr int kLoadsPerStage = 4 + 2 * NB;   // global_load_lds instructions per wavefront per stage
@@ -290,9 +301,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 
     // ---- weight tiles through the page table -------------------------------------
     const int32_t* trow = p.table + (size_t)(p.table_row_mod ? e % p.table_row_mod : e) * p.ppe + p.group_base;
-    const int pt0 = GU1 ? (nt >> 1) * 2 : nt * NB;
+    const int pt0 = nt * NB;
     const int pt1 = (pt0 + 1 < p.n_page_tiles) ? pt0 + 1 : pt0;   // odd tile count: the second half is masked (NB = 2)
-    const int sel = GU1 ? (nt & 1) : 0;                           // GU1: which half of the two page tiles' rows
     int bad = 0;
     auto page_addr = [&](int page) __attribute__((always_inline)) -> const char* {
         int slot = __builtin_amdgcn_readfirstlane(trow[page]);
@@ -368,12 +378,11 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // unconditional sequence per half-step under the single test of `extra`; what varies with the number of extra
     // rows is decided inside the asm statement (mfma_extra_tile_8 / _4).
     const int extra = rows_here > BM ? rows_here - BM : 0;
-    // (The 64-feature gate/up block does not split: the halves of its four column fragments are not gate/up pairs.)
     // At most 16 extra rows: ONE extra 16-row MFMA tile, rows BM .. BM + 15, and the two wavefront rows - which hold the
     // same column fragments - take half of the column fragments each (half the extra MFMAs per wavefront).  extra_which:
     // 0 = every fragment (more than 16 extra rows: wavefront row wm has the rows BM + 16 wm ..), 1 / 2 = this
     // wavefront row's half.
-    const bool split_extra = !GU1 && extra > 0 && extra <= 16;
+    const bool split_extra = extra > 0 && extra <= 16;
     const int extra_which = __builtin_amdgcn_readfirstlane(split_extra ? 1 + wm : 0);
     const char* ae_ptr = p.A;
     i32x4 AE[4];
@@ -400,7 +409,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 #pragma unroll
     for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) b_voff[o][h] = o * kHalfTile + (GU1 ? sel : h) * (kWaves * 1024) + b_off;     // GU1: both loads read piece `sel` of their tile
+        for (int h = 0; h < 2; ++h) b_voff[o][h] = o * kHalfTile + h * (kWaves * 1024) + b_off;
     auto advance_a = [&](int ia) __attribute__((always_inline)) {
         if (ia == 7) {
             a_ptr += kARowB;
@@ -419,10 +428,10 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     };
     auto load_b = [&](int slot, int kn, int odd, int i) __attribute__((always_inline)) {     // odd = kn & 1, known at compile time by the callers
         char* st = smem + slot * kStageB;
-        const TileWalk& w = (GU1 ? i < 1 : i < 2) ? w0 : w1;
+        const TileWalk& w = i < 2 ? w0 : w1;
         const int part = (i & 1) * (kWaves * 1024);                       // first or second 4 KiB of the half-tile in LDS
-        const char* b = w.tile + odd * kHalfTile + (GU1 ? sel * (kWaves * 1024) : part);
-        __builtin_amdgcn_global_load_lds((gptr_t)(b + b_off), (lptr_t)(st + (i >= 2 ? kHalfTile : 0) + part + wave * 1024), 16, 0, 0);
+        const char* b = w.tile + odd * kHalfTile + part;
+        __builtin_amdgcn_global_load_lds((gptr_t)(b + b_off), (lptr_t)(st + (i >= 2 ? kHalfTile : 0) + part + wave * 1024), 16, 0, STREAM ? 2 : 0);
         advance_b(kn, odd, i);
     };
 
@@ -435,13 +444,11 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // activations (128-byte rows, two half-steps per stage): chunk 4*hp + lane/16 in half-step parity hp.
     const int b_frag0 = (lane & 15) * kRowB + (((lane >> 4) ^ ((lane >> 2) & 2)) << 4);
     // B fragment j: MODE 0: gate rows wn*64 + (j%4)*16 of tile 0 (j < 4), the same up rows of tile 1 (j >= 4);
-    //               GU1:    gate rows wn*32 + (j%2)*16 of the stage's rows 0..63 (j < 2), the same up rows of its rows 64..127;
     //               MODE 1: rows wn*(16*NJ) + j*16 of the 128*NB rows of the block's tiles
     int b_base[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-        b_base[j] = (GU1 ? (j >> 1) * 64 + wn * 32 + (j & 1) * 16
-                         : (MODE == 0) ? (j >> 2) * 128 + wn * 64 + (j & 3) * 16 : wn * (16 * NJ) + j * 16) * kRowB;
+        b_base[j] = (MODE == 0 ? (j >> 2) * 128 + wn * 64 + (j & 3) * 16 : wn * (16 * NJ) + j * 16) * kRowB;
 
     // operand registers: two sets of four activation fragments, two sets of weight fragments
     i32x4 AX[4], AY[4], BF[2][NJ];
@@ -459,14 +466,14 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     };
     auto mfma_load_a = [&](auto i_c, auto j_c, const i32x4& a, const i32x4& b, auto ia_c) __attribute__((always_inline)) {   // + activation load instruction IA
         constexpr int IA = decltype(ia_c)::value;
-        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, IA * kWaves * 1024>(a, b, a_ptr, a_off[IA], a_wr_w);
+        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, IA * kWaves * 1024, false>(a, b, a_ptr, a_off[IA], a_wr_w);
         advance_a(IA);
     };
     auto mfma_load_b = [&](auto i_c, auto j_c, const i32x4& a, const i32x4& b, auto slot_c, auto l_c, int kn) __attribute__((always_inline)) {   // + weight load instruction L of half-step kn into slot SLOT
         constexpr int SLOT = decltype(slot_c)::value, I = decltype(l_c)::value;
         constexpr int odd = SLOT & 1;               // S is even: the parity of the half-step is that of its slot
-        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, SLOT * kStageB + (I >= 2 ? kHalfTile : 0) + (I & 1) * (kWaves * 1024)>(
-            a, b, ((GU1 ? I < 1 : I < 2) ? w0 : w1).tile, b_voff[odd][I & 1], lds_wave);
+        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, SLOT * kStageB + (I >= 2 ? kHalfTile : 0) + (I & 1) * (kWaves * 1024), STREAM>(
+            a, b, (I < 2 ? w0 : w1).tile, b_voff[odd][I & 1], lds_wave);
         advance_b(kn, odd, I);
     };
 
@@ -803,18 +810,23 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     if (bad && tid == 0 && p.status) atomicOr(p.status, 1);
 }
 
-template <int MODE, int NB>
-int launch_stages(const GemmParams& p, int grid, hipStream_t st) {
+template <int MODE, int NB, bool STREAM>
+int launch_kernel(const GemmParams& p, int grid, hipStream_t st) {
     constexpr int lds = kLdsBytes;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     MOE_HIP_TRY(attr_err);
-    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB>), dim3(grid), dim3(kThreads), lds, st, p);
+    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB, STREAM>), dim3(grid), dim3(kThreads), lds, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
+}
+
+template <int MODE, int NB>
+int launch_stages(const GemmParams& p, int grid, bool stream, hipStream_t st) {
+    return stream ? launch_kernel<MODE, NB, true>(p, grid, st) : launch_kernel<MODE, NB, false>(p, grid, st);
 }
 
 }  // namespace
@@ -826,21 +838,9 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     fill_common(p, s, g, a);
     fill_gate_up(p, s, g, a);
     const int64_t rows_each = R / s.E;
+    const bool stream = rows_each <= kStreamRows;
     const int64_t row_tiles_each = std::max<int64_t>(1, (rows_each - p.tall_rows + BM - 1) / BM);
-    // Gate/up with at most 64 rows per expert on average (the launch streams the weights once): 64-feature column tiles,
-    // twice as many blocks of half the work.  Measured on the Mixtral-8x7B shape, narrow against wide, ms for the layer: 32
-    // tokens 0.502 / 0.505, 128: 0.506 / 0.514, 256: 0.519 / 0.526, 384: 0.551 / 0.549, 512: 0.623 / 0.592, 1024: 0.83 / 0.77
-    // (with more rows a block of half the columns loads the activation rows for half the MFMAs).
-    // gate_cols: 0 = this rule, 1 / 2 = force narrow / wide.
-    const int gopt = get_opt(OPT_GATE_COLS);
-    const bool narrow_gu = gopt == 1 || (gopt == 0 && rows_each <= 64 && n_exp * row_tiles_each * p.NT < 4 * kComputeUnits);
-    int rc;
-    if (narrow_gu) {
-        p.NT = (int32_t)(2 * g.ft);
-        rc = launch_stages<0, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
-    } else {
-        rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
-    }
+    const int rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
     if (rc != MOE_OK) return rc;
     if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
     fill_down(p, s, g, a);
@@ -854,9 +854,9 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     const bool narrow = opt == 1 || (opt == 0 && n_exp * row_tiles_each * p.NT < kComputeUnits);
     if (narrow) {
         p.NT = (int32_t)g.dt;
-        return launch_stages<1, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
+        return launch_stages<1, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
     }
-    return launch_stages<1, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
+    return launch_stages<1, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
 }
 
 // y = x W^T for a dense weight matrix held as pages: the down-projection kernel with one "expert"
@@ -893,10 +893,10 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     const int wide_tiles = (p.n_page_tiles + 1) / 2;
     if ((int64_t)(a.T / BM + 1) * wide_tiles < 2 * kComputeUnits) {       // too few 256-wide tiles to fill the chip
         p.NT = p.n_page_tiles;
-        return launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
+        return launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), a.T <= 256, st);
     }
     p.NT = wide_tiles;
-    return launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
+    return launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), a.T <= 256, st);
 }
 
 
