@@ -177,7 +177,7 @@ int moe_combine(const moe_shape* s, const float* out, const int32_t* row_of,
  * and may be inspected after the stream has finished.  With bf16 data and option
  * "fuse_gather" = 1 (the default) the gate/up GEMM reads row r of its input as
  * x[row_src[r] / k], and x_perm is not written (needs T * H * 2 < 2^32, else the copy
- * is made). */
+ * is made); with f32 data it does the same and writes x_perm on the way. */
 int moe_layer(const moe_shape* s, const void* x, const void* Wr, const float* bias,
               const int32_t* page_table, const void* page_pool, int64_t pool_pages,
               float* y, void* workspace, size_t workspace_bytes, void* stream);
@@ -352,8 +352,8 @@ int moe_pre_attention(const moe_linear_shape* qkv_proj, const float* hidden, con
  *                 features).                                                 default 0
  *   "tall_tiles"  1: bf16: row tiles may be up to 32 rows higher than 256, so that a small
  *                 remainder of an expert's rows needs no tile of its own.        default 1
- *   "fuse_gather" 1: moe_layer's bf16 gate/up GEMM gathers the rows of x itself (no
- *                 x_perm copy).                                              default 1
+ *   "fuse_gather" 1: moe_layer's gate/up GEMM gathers the rows of x itself (bf16: no x_perm
+ *                 copy; f32: no copy kernel).                                default 1
  *   "chunked"     tile order of the expert GEMMs: the column tiles of an expert go to the XCDs
  *                 in chunks of about this many tiles (at most 32); 0: one by one.  default 32
  *   "tall_first"  1: inside a chunk the tall row tiles are numbered first.       default 1

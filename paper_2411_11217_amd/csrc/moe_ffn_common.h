@@ -32,8 +32,9 @@ struct GemmParams {
     int32_t* status;
     int32_t xcd_remap;
     int32_t half_tiles;       // bf16 kernel: row tiles with at most 128 rows run the half-height loop
-    const int32_t* a_gather;  // bf16 kernel, or null: row r of A is row a_gather[r] / a_div of the matrix at A (a_rows rows)
+    const int32_t* a_gather;  // or null: row r of A is row a_gather[r] / a_div of the matrix at A (a_rows rows)
     int32_t a_div, a_rows;
+    void* a_copy;             // f32 kernels, or null: the launch also writes the rows it reads here, [R][K]
     int32_t tall_rows;        // bf16 kernel: a row tile may be up to this many rows higher than BM (0 or 32), see locate_tile
     int32_t chunked;          // tile numbering: groups dealt to the XCDs in chunks of about this many tiles (0: single groups), see locate_tile
     int32_t tall_first;       // bf16 kernel: tile numbering with the tall tiles of a chunk of groups first, see locate_tile
@@ -194,6 +195,7 @@ inline void fill_gate_up(GemmParams& p, const moe_shape& s, const Geom& g, const
     p.n_cols = s.F;
     p.row_w = nullptr;
     p.a_gather = a.gather_src;
+    p.a_copy = a.gather_copy;
     p.a_div = s.k;
     p.a_rows = s.T;
 }
@@ -210,6 +212,7 @@ inline void fill_down(GemmParams& p, const moe_shape& s, const Geom& g, const Ff
     p.n_cols = s.H;
     p.row_w = a.row_w;
     p.a_gather = nullptr;
+    p.a_copy = nullptr;
 }
 
 }  // namespace moe

@@ -51,7 +51,8 @@ struct FfnArgs {
     int e_begin, e_end;        // experts processed by this launch
     int table_row_mod;         // 0: table row = e; n>0: table row = e % n (streamed slots)
     hipEvent_t mid_event;      // recorded between the gate/up and the down launch when not null
-    const int32_t* gather_src = nullptr;   // bf16 only.  Not null: x_perm is x [T][H], and row r reads x[gather_src[r] / k]
+    const int32_t* gather_src = nullptr;   // Not null: x_perm is x [T][H], and row r reads x[gather_src[r] / k]
+    void* gather_copy = nullptr;           // f32 only, with gather_src.  Not null: the gate/up launch writes the rows it reads here, [R][H]
 };
 int launch_expert_ffn(const moe_shape& s, const FfnArgs& a, hipStream_t st);
 int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, hipStream_t st);

@@ -139,6 +139,40 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
         assert_close(out.cpu().numpy()[lo:hi], o_ref[lo:hi], "bf16", f"out, expert {e} with {c} rows")
 
 
+@pytest.mark.parametrize("counts,H,F", [
+    ([1, 15, 16, 17, 31, 32, 33, 0, 64, 70], 128, 256),          # 27 rows on average: k split over the wavefronts, two k-steps for four of them
+    ([5, 0, 40], 384, 640),                                        # the same with 6 and 10 k-steps
+    ([1, 15, 16, 17, 31, 32, 33, 0, 65, 160], 128, 256),         # 37 rows on average: columns split over the wavefronts
+    ([200, 97, 0], 384, 640),
+])
+def test_f32_expert_ffn_row_counts_across_the_kernels(counts, H, F):
+    """Segments on both sides of the 16-row MFMA tiles and the 32-row blocks of the two float32 kernels, against the oracle; the layer
+    leaves the permuted rows in its workspace whether or not its GEMM gathers them."""
+    E = len(counts)
+    cfg = MoEConfig("rows32", "f32", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=96 * 1024, seed=78)
+    case = Case(cfg, shuffle_pages=True, extra_pages=1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = case.view
+    h_ref, o_ref = oracle.expert_ffn(v["x"], offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
+    w = np.random.default_rng(1).random(cfg.T, dtype=np.float32) + 0.5
+    status = torch.zeros(4, dtype=torch.int32, device="cuda")
+    h, out = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w), status=status)
+    torch.cuda.synchronize()
+    assert_status_clean(status.cpu().tolist())
+    assert_h_close(h.cpu().numpy(), h_ref, "f32", "h")
+    assert_close(out.cpu().numpy(), o_ref * w[:, None], "f32", "out * w")
+    ws = M.Workspace(case.shape)
+    ws.buf.fill_(0xFF)                                             # NaN everywhere
+    y, _ = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, workspace=ws)
+    assert torch.equal(ws.view("x_perm"), case.x[ws.view("row_src").long()])
+    M.set_option("fuse_gather", 0)
+    try:
+        y0, _ = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev)
+    finally:
+        M.set_option("fuse_gather", 1)
+    assert torch.equal(y0, y)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,H,E,k", [(1, 128, 1, 1), (17, 128, 3, 3), (100, 384, 16, 4), (33, 1024, 17, 2), (250, 256, 32, 8),
                                      (47, 640, 33, 5), (130, 2048, 64, 64), (2000, 512, 8, 2)])
