@@ -304,8 +304,8 @@ int moe_linear_pages_required(const moe_linear_shape* s, int64_t* pages);
 int moe_linear_pack(const moe_linear_shape* s, const void* W, const int32_t* page_table, int64_t pool_pages,
                     void* pages_out);
 /* out[t][n] = sum_k x[t][k] W[n][k].  x: device bf16[T][K]; page_table: device
- * int32[pages]; out: device float[T][N]; workspace: device, MOE_LINEAR_WORKSPACE_BYTES;
- * status: device int32[4] or NULL (bit 0 of [0]: a page-table entry outside the pool). */
+ * int32[pages]; out: device float[T][N]; workspace: device, MOE_LINEAR_WORKSPACE_BYTES
+ * (checked, not used); status: device int32[4] or NULL (bit 0 of [0]: a page-table entry outside the pool). */
 int moe_linear(const moe_linear_shape* s, const void* x, const int32_t* page_table, const void* page_pool,
                int64_t pool_pages, float* out, void* workspace, size_t workspace_bytes, int32_t* status, void* stream);
 /* s = hidden + delta (hidden may be NULL: s = delta), written to hidden_out when not

@@ -17,19 +17,6 @@ using namespace moe;
 
 namespace {
 
-__global__ void set_bounds_kernel(int32_t* offsets, int32_t T) {
-    if (threadIdx.x == 0) {
-        offsets[0] = 0;
-        offsets[1] = T;
-    }
-}
-
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;      // NaN stays NaN
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;                        // round to nearest, ties to even
-}
-
 // One block per row.  s = hidden + delta is written as f32 and kept in registers for the second
 // pass (H <= 256 * 4 * kMaxVec elements), so the row is read once.
 constexpr int kNormThreads = 256;
@@ -87,11 +74,8 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float4* __restrict
 }
 
 int enqueue_linear(const moe_linear_shape& s, const void* x, const int32_t* table, const void* pool, int64_t pool_pages,
-                   float* out, void* workspace, int32_t* status, hipStream_t st) {
-    int32_t* bounds = (int32_t*)workspace;
-    hipLaunchKernelGGL(set_bounds_kernel, dim3(1), dim3(64), 0, st, bounds, s.T);
-    MOE_HIP_TRY(hipGetLastError());
-    LinearArgs a{x, s.T, s.K, s.N, bounds, table, (const char*)pool, pool_pages, s.page_bytes, linear_pages(s), out, status};
+                   float* out, void* out16, int32_t* status, hipStream_t st) {
+    LinearArgs a{x, s.T, s.K, s.N, table, (const char*)pool, pool_pages, s.page_bytes, linear_pages(s), out, (uint16_t*)out16, status};
     return launch_linear_bf16(a, st);
 }
 
@@ -105,6 +89,14 @@ int enqueue_add_rmsnorm(int32_t T, int32_t H, const float* hidden, const float* 
 
 }  // namespace
 
+int moe::launch_cast_bf16(int64_t n, const float* in, void* out, hipStream_t st) {
+    const int64_t n_vec = n / 4;
+    const int grid = (int)std::min<int64_t>((n_vec + 255) / 256, 65536);
+    hipLaunchKernelGGL(cast_bf16_kernel, dim3(grid), dim3(256), 0, st, (const float4*)in, (uint2*)out, n_vec);
+    MOE_HIP_TRY(hipGetLastError());
+    return MOE_OK;
+}
+
 extern "C" {
 
 int moe_linear(const moe_linear_shape* s, const void* x, const int32_t* page_table, const void* page_pool,
@@ -114,7 +106,7 @@ int moe_linear(const moe_linear_shape* s, const void* x, const int32_t* page_tab
     if (s->T == 0) return MOE_OK;
     if (!x || !page_table || !page_pool || !out || !workspace || pool_pages <= 0) return MOE_ERR_INVALID_ARG;
     if (workspace_bytes < MOE_LINEAR_WORKSPACE_BYTES) return MOE_ERR_WORKSPACE_TOO_SMALL;
-    return enqueue_linear(*s, x, page_table, page_pool, pool_pages, out, workspace, status, (hipStream_t)stream);
+    return enqueue_linear(*s, x, page_table, page_pool, pool_pages, out, nullptr, status, (hipStream_t)stream);
 }
 
 int moe_add_rmsnorm(int32_t T, int32_t H, const float* hidden, const float* delta, const float* gamma, float eps,
@@ -129,11 +121,7 @@ int moe_cast_bf16(int64_t n, const float* in, void* out, void* stream) {
     if (n < 0 || n % 4 != 0) return MOE_ERR_INVALID_ARG;
     if (n == 0) return MOE_OK;
     if (!in || !out) return MOE_ERR_INVALID_ARG;
-    const int64_t n_vec = n / 4;
-    const int grid = (int)std::min<int64_t>((n_vec + 255) / 256, 65536);
-    hipLaunchKernelGGL(cast_bf16_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const float4*)in, (uint2*)out, n_vec);
-    MOE_HIP_TRY(hipGetLastError());
-    return MOE_OK;
+    return launch_cast_bf16(n, in, out, (hipStream_t)stream);
 }
 
 int moe_post_attention(const moe_shape* s, const moe_linear_shape* o_proj, const void* attn, const float* hidden,
@@ -151,7 +139,7 @@ int moe_post_attention(const moe_shape* s, const moe_linear_shape* o_proj, const
     if (!attn || !hidden || !o_table || !norm_gamma || !Wr || !page_table || !page_pool || !hidden_mid || !x_moe || !y ||
         !workspace || pool_pages <= 0 || !(eps >= 0.f))
         return MOE_ERR_INVALID_ARG;
-    // workspace: [the MoE layer's workspace][bounds of the linear][O-projection output f32 [T][H]]
+    // workspace: [the MoE layer's workspace][256 bytes, unused][O-projection output f32 [T][H]]
     const size_t layer_bytes = (layer_workspace_bytes(*s) + 255) / 256 * 256;
     const size_t need = layer_bytes + 256 + (size_t)s->T * s->H * 4;
     if (workspace_bytes < need) return MOE_ERR_WORKSPACE_TOO_SMALL;
@@ -159,7 +147,7 @@ int moe_post_attention(const moe_shape* s, const moe_linear_shape* o_proj, const
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
     float* o = (float*)(ws + layer_bytes + 256);
-    rc = enqueue_linear(*o_proj, attn, o_table, page_pool, pool_pages, o, ws + layer_bytes, nullptr, st);
+    rc = enqueue_linear(*o_proj, attn, o_table, page_pool, pool_pages, o, nullptr, nullptr, st);
     if (rc != MOE_OK) return rc;
     rc = enqueue_add_rmsnorm(s->T, s->H, hidden, o, norm_gamma, eps, hidden_mid, x_moe, st);
     if (rc != MOE_OK) return rc;
@@ -181,10 +169,7 @@ int moe_pre_attention(const moe_linear_shape* qkv_proj, const float* hidden, con
     hipStream_t st = (hipStream_t)stream;
     rc = enqueue_add_rmsnorm(qkv_proj->T, qkv_proj->K, hidden, delta, norm_gamma, eps, hidden_out, x_norm, st);
     if (rc != MOE_OK) return rc;
-    rc = enqueue_linear(*qkv_proj, x_norm, qkv_table, page_pool, pool_pages, qkv, workspace, nullptr, st);
-    if (rc != MOE_OK) return rc;
-    if (qkv_bf16) return moe_cast_bf16((int64_t)qkv_proj->T * qkv_proj->N, qkv, qkv_bf16, stream);
-    return MOE_OK;
+    return enqueue_linear(*qkv_proj, x_norm, qkv_table, page_pool, pool_pages, qkv, qkv_bf16, nullptr, st);
 }
 
 int moe_post_attention_workspace_bytes(const moe_shape* s, size_t* bytes) {

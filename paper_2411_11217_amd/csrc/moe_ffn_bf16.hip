@@ -86,8 +86,11 @@ constexpr int kComputeUnits = 256;           // MI355X
 // Mixtral-8x7B shape, without / with, us: 16 tokens 517 / 471, 64: 506 / 466, 256: 548 / 505, 400: 568 / 537,
 // 1000: 760 / 709, 1024: 769 / 733; with several row tiles per expert the second one finds less in the L2: 1150 tokens
 // 1015 / 1038, 1536: 1063 / 1125, 4096: 2145 / 2190.  On 64 experts (2048 x 1024) the line lies at the same
-// place: 250 rows per expert 522 / 504, 375 rows 626 / 662.
+// place: 250 rows per expert 522 / 504, 375 rows 626 / 662.  And only where the experts' weights exceed the 256 MiB
+// last-level cache: smaller ones may still be there from the call before, and the hint keeps them out (8 experts of
+// 1024 x 2816, 138 MB, 100 tokens: 53 us without, 56 with).
 constexpr int kStreamRows = 256;
+constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
 constexpr int kHalfTile = 128 * kRowB;       // one weight half-tile
 constexpr int kStageB = 2 * kHalfTile;       // weight stage of one half-step: two half-tiles
@@ -97,13 +100,6 @@ constexpr int kStageA = 256 * kARowB;        // activation stage of one k-step
 constexpr int kStagesA = 3;                  // depth of the activation ring
 constexpr int kRingA = kStages * kStageB;    // LDS offset of the activation ring (the weight ring sits at 0)
 constexpr int kLdsBytes = kRingA + kStagesA * kStageA;   // 160 KiB: all of a compute unit's LDS
-
-// silu(g) * u with the hardware exp2 and reciprocal (1 ulp each): far below the resolution of
-// the bf16 result; an IEEE division would cost a dozen instructions per element
-__device__ __forceinline__ float silu_mul(float g, float u) {
-    const float e = __builtin_amdgcn_exp2f(g * -1.44269504088896340736f);
-    return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
-}
 
 // wait until at most N of my vector-memory loads are outstanding and all my LDS fetches are back
 template <int N>
@@ -735,7 +731,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                     if (decltype(full)::value || row < rows_here) {
 #pragma unroll
                         for (int j = 0; j < NP; ++j)
-                            h[(int64_t)row * p.ldo + j * 16] = (__bf16)silu_mul(v[j][r], v[j + NP][r]);
+                            h[(int64_t)row * p.ldo + j * 16] = (__bf16)silu_mul_bf16(v[j][r], v[j + NP][r]);
                     }
                 }
             });
@@ -753,7 +749,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 #pragma unroll
                     for (int j = 0; j < NP; ++j)
                         if (!split_extra || (j >> 1) == wm)          // split: this wavefront row's gate fragments only
-                            h[(int64_t)row * p.ldo + j * 16] = (__bf16)silu_mul(accE[j][r], accE[j + NP][r]);
+                            h[(int64_t)row * p.ldo + j * 16] = (__bf16)silu_mul_bf16(accE[j][r], accE[j + NP][r]);
                 }
             }
         }
@@ -838,7 +834,14 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     fill_common(p, s, g, a);
     fill_gate_up(p, s, g, a);
     const int64_t rows_each = R / s.E;
-    const bool stream = rows_each <= kStreamRows;
+    const bool stream = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
+    if (rows_kernel_takes((int)rows_each)) {
+        const int rc = launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, stream, st);
+        if (rc != MOE_OK) return rc;
+        if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
+        fill_down(p, s, g, a);
+        return launch_down_rows_bf16(p, s.H, R, (int)rows_each, n_exp, stream, st);
+    }
     const int64_t row_tiles_each = std::max<int64_t>(1, (rows_each - p.tall_rows + BM - 1) / BM);
     const int rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
     if (rc != MOE_OK) return rc;
@@ -860,12 +863,12 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
 }
 
 // y = x W^T for a dense weight matrix held as pages: the down-projection kernel with one "expert"
-// that owns all T rows (offsets = {0, T}) and no row weight.
+// that owns all T rows and no row weight.
 int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     GemmParams p{};
     p.A = (const char*)a.x;
     p.lda_bytes = (int64_t)a.K * 2;
-    p.offsets = a.offsets;
+    p.dense_rows = a.T;
     p.table = a.page_table;
     p.pool = a.pool;
     p.page_bytes = a.page_bytes;
@@ -890,13 +893,21 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     p.tall_first = get_opt(OPT_TALL_FIRST);
     p.balance = get_opt(OPT_BALANCE);
     p.chunked = std::min(std::max(get_opt(OPT_CHUNKED), 0), 32);
+    if (linear_rows_kernel_takes(a.N, a.T)) {
+        p.out16 = a.out16;
+        return launch_linear_rows_bf16(p, a.N, a.T, st);
+    }
     const int wide_tiles = (p.n_page_tiles + 1) / 2;
+    int rc;
     if ((int64_t)(a.T / BM + 1) * wide_tiles < 2 * kComputeUnits) {       // too few 256-wide tiles to fill the chip
         p.NT = p.n_page_tiles;
-        return launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), a.T <= 256, st);
+        rc = launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), false, st);
+    } else {
+        p.NT = wide_tiles;
+        rc = launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), false, st);
     }
-    p.NT = wide_tiles;
-    return launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), a.T <= 256, st);
+    if (rc != MOE_OK || !a.out16) return rc;
+    return launch_cast_bf16((int64_t)a.T * a.N, a.out, a.out16, st);
 }
 
 

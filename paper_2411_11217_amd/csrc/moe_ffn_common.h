@@ -11,7 +11,8 @@ namespace moe {
 struct GemmParams {
     const char* A;            // activations, dtype [R][K] row-major
     int64_t lda_bytes;
-    const int32_t* offsets;   // [E+1]
+    const int32_t* offsets;   // [E+1], or null: one segment of dense_rows rows
+    int32_t dense_rows;
     const int32_t* table;     // page table
     const char* pool;
     int64_t page_bytes;
@@ -26,6 +27,7 @@ struct GemmParams {
     int32_t e_begin, e_end;   // experts covered by the launch
     int32_t table_row_mod;    // 0: table row = e; n > 0: table row = e % n
     void* out;
+    uint16_t* out16;          // MODE 1 of the bf16 kernel for few rows, or null: a bf16 copy of out
     int32_t ldo;              // elements
     int32_t n_cols;           // valid output columns
     const float* row_w;
@@ -74,8 +76,12 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
     const int e_l = p.e_begin + lane;
     int seg0 = 0, cnt = 0;
     if (e_l < p.e_end) {
-        seg0 = p.offsets[e_l];
-        cnt = p.offsets[e_l + 1] - seg0;
+        if (p.offsets) {
+            seg0 = p.offsets[e_l];
+            cnt = p.offsets[e_l + 1] - seg0;
+        } else {
+            cnt = p.dense_rows;
+        }
     }
     const int stride = p.xcd_remap ? 8 : 1;
     int x = p.xcd_remap ? (int)(blockIdx.x & 7) : 0;                 // my chunks: those whose number is x modulo stride
@@ -144,18 +150,19 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
     return t;
 }
 
-// Address of tile number ti of the group; a page-table entry outside the pool is
-// never followed: slot 0 is read instead and *bad is raised.
-__device__ __forceinline__ const char* tile_address(const GemmParams& p, const int32_t* trow, int64_t ti, int* bad) {
-    const int page = (int)(ti / p.tpp);
-    const int within = (int)(ti - (int64_t)page * p.tpp);
-    int slot = trow[page];
-    if ((unsigned)slot >= (unsigned)p.pool_pages) {
-        *bad = 1;
-        slot = 0;
-    }
-    return p.pool + (int64_t)slot * p.page_bytes + (int64_t)within * p.tile_bytes;
+// silu(g) * u for the bf16 kernels, with the hardware exp2 and reciprocal (1 ulp each): far below the resolution of
+// the bf16 result; an IEEE division would cost a dozen instructions per element
+__device__ __forceinline__ float silu_mul_bf16(float g, float u) {
+    const float e = __builtin_amdgcn_exp2f(g * -1.44269504088896340736f);
+    return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
 }
+
+// the kernel for few rows per expert (moe_ffn_rows_bf16.hip); p as filled for the launch, NT is set there
+bool rows_kernel_takes(int rows_each);
+int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, bool stream, hipStream_t st);
+int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, bool stream, hipStream_t st);
+bool linear_rows_kernel_takes(int N, int T);
+int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st);
 
 inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const FfnArgs& a) {
     p.offsets = a.offsets;

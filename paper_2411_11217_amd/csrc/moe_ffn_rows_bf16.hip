@@ -1,0 +1,309 @@
+// a3 and the dense linear map for launches with few rows per expert, bf16 operands, fp32 accumulation, on
+// v_mfma_f32_16x16x32_bf16.  The launch is bound by reading every weight once, and what counts is how many bytes are under
+// way and how short a block's way to its first load is.
+//
+// A block owns a row tile (16 * RT rows) x 16 * CW * FC columns (MODE 0: features, gate and up).  The CW wavefronts split the
+// columns; a wavefront's 16 weight rows of a half-tile are 1 KiB in a row in the page, exactly one 16-byte load per lane and
+// exactly its MFMA operand, so the weights go from the page straight into registers, D k-steps ahead (STREAM: with the
+// non-temporal hint).  The activations, which all wavefronts share, are loaded as far ahead into registers and pass through a
+// double-buffered LDS stage (one k-step, 128-byte rows, the chunk swizzle of moe_ffn_bf16.hip), one barrier per k-step.
+// All loads are the compiler's own, in one order, so its counted waits keep D - 1 k-steps under way across the barriers.
+// Rows beyond the tile's last pair of 16-row MFMA tiles are neither loaded nor multiplied (a copy of the loop per pair:
+// branches inside it would put an LDS latency in front of every MFMA).  Few registers and little LDS: two or more blocks share
+// a compute unit and cover each other's start and end.
+//
+// RG > 1 (linear map): RG groups of CW wavefronts share the columns and split the row tiles.  Every output is the same chain of
+// MFMAs along k as in moe_ffn_bf16.hip: the same bits.
+#include "moe_ffn_common.h"
+
+namespace moe {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kComputeUnits = 256;                   // MI355X
+constexpr int kHalfTileBytes = 128 * 64;             // 32 k of a page tile
+constexpr int kTileBytes = 2 * kHalfTileBytes;
+
+// Block -> (expert, row tile, column tile): the tiles are numbered expert by expert, inside an expert in runs of eight column
+// tiles (block b runs on XCD b % 8), the row tiles of a run one after the other, so that those of a column tile meet
+// in one L2.  One expert per lane, a prefix sum and a ballot; every wavefront does it on its own.  The order of
+// locate_tile costs a few microseconds of integer arithmetic per block, which these short blocks would feel.
+struct RowsTile {
+    int e, nt, row0, rows_here;
+};
+template <int BM>
+__device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& t) {
+    const int lane = threadIdx.x & 63, id = blockIdx.x;
+    int seg, rows, m, rel;
+    if (p.offsets) {
+        const int e_l = p.e_begin + lane;
+        int seg0 = 0, cnt = 0;
+        if (e_l < p.e_end) {
+            seg0 = p.offsets[e_l];
+            cnt = p.offsets[e_l + 1] - seg0;
+        }
+        const int m_l = (cnt + BM - 1) / BM;
+        const int incl = lane_prefix_sum(m_l * p.NT, lane);
+        const unsigned long long holds = __ballot(id < incl);
+        if (!holds) return false;
+        const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)holds) - 1);
+        seg = __builtin_amdgcn_readlane(seg0, src);
+        rows = __builtin_amdgcn_readlane(cnt, src);
+        m = __builtin_amdgcn_readlane(m_l, src);
+        rel = id - __builtin_amdgcn_readlane(incl, src) + m * p.NT;
+        t.e = p.e_begin + src;
+    } else {
+        seg = 0;
+        rows = p.dense_rows;
+        m = (rows + BM - 1) / BM;
+        rel = id;
+        t.e = 0;
+        if (id >= m * p.NT) return false;
+    }
+    const int run = rel / (8 * m), in_run = rel - run * 8 * m;
+    const int width = min(8, p.NT - run * 8);        // column tiles of this run
+    const int mt = in_run / width;
+    t.nt = run * 8 + in_run - mt * width;
+    t.row0 = seg + mt * BM;
+    t.rows_here = min(BM, rows - mt * BM);
+    return true;
+}
+
+template <int N>
+struct Num {
+    static constexpr int value = N;
+};
+
+// FC: fragments of 16 columns per wavefront (MODE 0: of 16 features, gate and up)
+template <int MODE, int RT, int CW, int FC, int RG, int D, bool STREAM>
+__global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p) {
+    constexpr int BM = 16 * RT, NB = MODE == 0 ? 2 * FC : FC, kCols = 16 * CW * FC;
+    constexpr int kPass = 8 * CW * RG;               // rows that one load instruction per thread fetches
+    constexpr int AJ = (BM + kPass - 1) / kPass, kStage = AJ * kPass * 128;
+    static_assert(RT % 2 == 0 && RT <= 8 && 128 % kCols == 0 && (kPass <= BM || RG == 1 || kPass >= 16 * RG), "");
+    __shared__ __attribute__((aligned(1024))) char smem[2 * kStage];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cw = RG == 1 ? wave : wave % CW, rg = RG == 1 ? 0 : wave / CW;
+    const int r = lane & 15, g = lane >> 4;
+
+    RowsTile tc;
+    if (!locate_rows_tile<BM>(p, tc)) return;
+    const int nt = tc.nt, row0 = tc.row0, rows_here = tc.rows_here;
+    const int32_t* trow = p.table + (size_t)(p.table_row_mod ? tc.e % p.table_row_mod : tc.e) * p.ppe + p.group_base;
+
+    // activations: 16 bytes of rows tid / 8 + kPass * j
+    uint32_t a_off[AJ];
+#pragma unroll
+    for (int j = 0; j < AJ; ++j) {
+        const int row = min(j * kPass + (tid >> 3), rows_here - 1);
+        const int src = p.a_gather ? min(max(p.a_gather[row0 + row] / p.a_div, 0), p.a_rows - 1) : row;
+        a_off[j] = (uint32_t)src * (uint32_t)p.lda_bytes + (tid & 7) * 16;
+    }
+    const char* a_base = p.a_gather ? p.A : p.A + (int64_t)row0 * p.lda_bytes;
+    const int a_wr = (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    const int a_rd[2] = {r * 128 + ((g ^ ((r >> 1) & 7)) << 4), r * 128 + (((4 + g) ^ ((r >> 1) & 7)) << 4)};
+
+    // weights: one page tile is walked along k, MODE 0 two (the W1 and the W3 tile of the same features)
+    int bad = 0, page, within, page1 = 0, within1 = 0;
+    const char* tile[MODE == 0 ? 2 : 1];
+    auto page_addr = [&](int pg) __attribute__((always_inline)) -> const char* {
+        int slot = __builtin_amdgcn_readfirstlane(trow[pg]);
+        if ((unsigned)slot >= (unsigned)p.pool_pages) {   // never follow an entry outside the pool
+            bad = 1;
+            slot = 0;
+        }
+        return p.pool + (int64_t)slot * p.page_bytes;
+    };
+    constexpr int kColTiles = 128 / kCols;                // blocks per page tile along the columns
+    {
+        const int t0 = (nt / kColTiles) * (MODE == 0 ? 2 : 1) * p.KT;
+        page = t0 / p.tpp;
+        within = t0 - page * p.tpp;
+        tile[0] = page_addr(page) + (int64_t)within * kTileBytes;
+        if (MODE == 0) {
+            page1 = (t0 + p.KT) / p.tpp;
+            within1 = t0 + p.KT - page1 * p.tpp;
+            tile[MODE == 0] = page_addr(page1) + (int64_t)within1 * kTileBytes;
+        }
+    }
+    auto advance = [&]() __attribute__((always_inline)) {
+        tile[0] += kTileBytes;
+        if (++within == p.tpp) {
+            within = 0;
+            tile[0] = page_addr(++page);
+        }
+        if (MODE == 0) {
+            tile[MODE == 0] += kTileBytes;
+            if (++within1 == p.tpp) {
+                within1 = 0;
+                tile[MODE == 0] = page_addr(++page1);
+            }
+        }
+    };
+    const uint32_t b_off = ((nt % kColTiles) * kCols + cw * 16 * FC + r) * 64 + ((g ^ ((r >> 2) & 2)) << 4);
+
+    // row group rg: row tiles rg * (NRT / RG) ..
+    constexpr int TPW = (RT + RG - 1) / RG;
+    f32x4 acc[TPW][NB];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int tile0 = 0, tiles_mine = TPW;                 // this wavefront's first row tile and their number
+
+    // the loop for NRT row tiles: rows beyond them are neither loaded nor multiplied
+    auto main_loop = [&](auto nrt_c) __attribute__((always_inline)) {
+        constexpr int NRT = decltype(nrt_c)::value, NA = (16 * NRT + kPass - 1) / kPass, NT = (NRT + RG - 1) / RG;
+        static_assert(RG * NT * 16 <= AJ * kPass, "every row tile that is multiplied lies inside the stage");
+        tile0 = rg * NT;
+        tiles_mine = NT;
+        i32x4 areg[D][NA], breg[D][2][NB];
+        int kt_load = 0;                             // k-step that the next load_b fetches
+        auto load_a = [&](int s, int slot) __attribute__((always_inline)) {
+            const char* base = a_base + (int64_t)min(s, p.KT - 1) * 128;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) areg[slot][j] = *(const i32x4*)(base + a_off[j]);
+        };
+        auto load_b = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int hp = 0; hp < 2; ++hp)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const i32x4* src = (const i32x4*)(tile[MODE == 0 ? b / FC : 0] + (MODE == 0 ? b % FC : b) * 1024 + hp * kHalfTileBytes + b_off);
+                    if constexpr (STREAM) breg[slot][hp][b] = __builtin_nontemporal_load(src);
+                    else breg[slot][hp][b] = *src;
+                }
+            if (++kt_load < p.KT) advance();
+        };
+        int buf = 0;
+        auto step = [&](int s, int slot, bool more) __attribute__((always_inline)) {     // slot: known at compile time
+            char* st = smem + buf;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) *(i32x4*)(st + a_wr + j * kPass * 128) = areg[slot][j];
+            __syncthreads();
+            if (more) load_a(s + D, slot);
+            i32x4 a[2][NT];
+#pragma unroll
+            for (int hp = 0; hp < 2; ++hp)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) a[hp][i] = *(const i32x4*)(st + a_rd[hp] + (tile0 + i) * 2048);
+#pragma unroll
+            for (int hp = 0; hp < 2; ++hp)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[hp][i]), __builtin_bit_cast(bf16x8, breg[slot][hp][b]), acc[i][b], 0, 0, 0);
+            if (more) load_b(slot);
+            buf ^= kStage;
+        };
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            load_a(u, u);
+            load_b(u);
+        }
+        int s = 0;
+        for (; s + 2 * D <= p.KT; s += D)
+#pragma unroll
+            for (int u = 0; u < D; ++u) step(s + u, u, true);
+#pragma unroll
+        for (int u = 0; u < 2 * D - 1; ++u)
+            if (s + u < p.KT) step(s + u, u % D, s + u + D < p.KT);
+    };
+    if (RT > 6 && rows_here > 96) main_loop(Num<RT>{});
+    else if (RT > 4 && rows_here > 64) main_loop(Num<RT < 6 ? RT : 6>{});
+    else if (RT > 2 && rows_here > 32) main_loop(Num<RT < 4 ? RT : 4>{});
+    else main_loop(Num<2>{});
+
+    const int col = nt * kCols + cw * 16 * FC + r;
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = (tile0 + i) * 16 + g * 4 + v;
+            if (row >= rows_here || (RG > 1 && i >= tiles_mine)) continue;
+            const int64_t o = (int64_t)(row0 + row) * p.ldo + col;
+            if (MODE == 0) {
+#pragma unroll
+                for (int f = 0; f < FC; ++f) ((__bf16*)p.out)[o + f * 16] = (__bf16)silu_mul_bf16(acc[i][f][v], acc[i][NB - FC + f][v]);
+            } else {
+                const float wgt = p.row_w ? p.row_w[row0 + row] : 1.0f;
+#pragma unroll
+                for (int f = 0; f < FC; ++f) {
+                    const float y = acc[i][f][v] * wgt;
+                    ((float*)p.out)[o + f * 16] = y;
+                    if (p.out16) p.out16[o + f * 16] = (uint16_t)f32_to_bf16_bits(y);
+                }
+            }
+        }
+    if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
+}
+
+template <int MODE, int RT, int CW, int FC, int RG, int D, bool STREAM>
+int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
+    p.NT = cols / (16 * CW * FC);
+    hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D, STREAM>), dim3(p.NT * (R / (16 * RT) + n_exp)), dim3(64 * CW * RG), 0, st, p);
+    MOE_HIP_TRY(hipGetLastError());
+    return MOE_OK;
+}
+
+}  // namespace
+
+// Where the expert GEMMs take this kernel: up to 80 rows per expert on average (of all experts: the launches of a streamed
+// layer take what the resident layer's single launch takes).  us for the layer, moe_ffn_bf16.hip's kernel / this one:
+// Mixtral-8x7B shape (2 of 8 experts) 1 token 196 / 165, 4: 364 / 355, 16: 469 / 455, 64: 477 / 466, 150: 485 / 478, 256 (64
+// rows each): 522 / 511, 288: 532 / 520, 400 (100 rows): 552 / 560; 64 experts of 2048 x 1024, 8 per token, 20 tokens 192 /
+// 183, 400: 241 / 235, 600 (75 rows): 252 / 247, 777 (97 rows): 259 / 262; DBRX shape 120 tokens 1089 / 1036, 250: 1129 / 1096.
+// What is left is the weights' way from HBM: 6.3 - 6.5 TB/s in the gate/up launch, whatever the depth and the block.
+constexpr int kRowsKernelMax = 80;
+// Up to here 64-row blocks with half the columns; 45 .. 72 rows need two of them per expert for some experts, and the second
+// one reads the weights again (176 tokens of the Mixtral-8x7B shape, 44 rows: 489 against 503 with 128-row blocks).
+constexpr int kRows64Max = 44;
+
+bool rows_kernel_takes(int rows_each) { return rows_each <= kRowsKernelMax; }
+
+template <bool STREAM>
+static int gate_up(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st) {
+    if (rows_each <= kRows64Max) return launch_rows<0, 4, 4, 1, 1, 4, STREAM>(p, F, R, n_exp, st);
+    return launch_rows<0, 8, 8, 1, 1, 2, STREAM>(p, F, R, n_exp, st);
+}
+
+template <bool STREAM>
+static int down(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st) {
+    if (rows_each <= kRows64Max) return launch_rows<1, 4, 4, 2, 1, 4, STREAM>(p, H, R, n_exp, st);
+    return launch_rows<1, 8, 8, 1, 1, 4, STREAM>(p, H, R, n_exp, st);
+}
+
+int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, bool stream, hipStream_t st) {
+    return stream ? gate_up<true>(p, F, R, rows_each, n_exp, st) : gate_up<false>(p, F, R, rows_each, n_exp, st);
+}
+
+int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, bool stream, hipStream_t st) {
+    return stream ? down<true>(p, H, R, rows_each, n_exp, st) : down<false>(p, H, R, rows_each, n_exp, st);
+}
+
+// Where the dense linear map takes it: one row tile, or as many blocks of 64 columns and 128 rows as run at once.  One weight
+// matrix alone has too few columns to fill the chip; us for the pre-attention task (norm and bf16 copy included), 256-row
+// blocks of moe_ffn_bf16.hip / this kernel, both with temporal loads: 4096 x 6144 (Mixtral-8x7B shape) 1 token 31 / 23, 60: 39 /
+// 24, 100: 38 / 33, 256: 54 / 38; 2048 x 3072 300 tokens 36 / 24, 640: 39 / 27; 6144 x 9216 50 tokens 53 / 36, 128: 53 / 49.
+// Blocks of 32 columns as long as they make one round of blocks, else of 64 (with non-temporal loads: 4096 x 6144 60 tokens
+// 27 / 30, 100: 39 / 42, but 200: 73 / 48; 6144 x 9216 50 tokens 60 / 42); the fewer columns, the more wavefronts along the
+// rows.  Temporal loads: one matrix fits the 256 MiB last-level cache, and a call that finds it there is that much
+// shorter (6144 x 9216, 128 tokens: 68 us with the hint, 48 without).
+// Groups of wavefronts that split k instead were faster still with 65 .. 128 rows (4096 x 6144 100 tokens 33 against 39 with
+// the hint), but they change the order of the sums, which the O projection hands on to a rounding and the router.
+bool linear_rows_kernel_takes(int N, int T) { return T <= 128 || N / 64 * ((T + 127) / 128) <= kComputeUnits; }
+
+int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
+    const bool few_columns = N / 32 * ((T + 127) / 128) <= kComputeUnits;
+    if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8, false>(p, N, T, 1, st);
+    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 8, false>(p, N, T, 1, st);
+    if (few_columns) return launch_rows<1, 8, 2, 1, 4, 4, false>(p, N, T, 1, st);
+    return launch_rows<1, 8, 4, 1, 2, 4, false>(p, N, T, 1, st);
+}
+
+}  // namespace moe

@@ -29,6 +29,12 @@ void set_hip_error(hipError_t e);
 int get_opt(int id);
 enum Opt { OPT_XCD_REMAP = 0, OPT_PROFILE, OPT_DOWN_COLS, OPT_HALF_TILES, OPT_FUSE_GATHER, OPT_TALL_TILES, OPT_TALL_FIRST, OPT_CHUNKED, OPT_BALANCE, OPT_GATE_COLS, OPT_COUNT };
 
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
+    uint32_t u = __float_as_uint(f);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;      // NaN stays NaN
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;                        // round to nearest, ties to even
+}
+
 // ---- kernel launchers (each returns MOE_OK or MOE_ERR_HIP) -----------------
 int launch_route(const moe_shape& s, const void* x, const void* Wr, const float* bias,
                  int32_t* ids, float* w, float* logits, hipStream_t st);
@@ -58,17 +64,18 @@ int launch_expert_ffn(const moe_shape& s, const FfnArgs& a, hipStream_t st);
 int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, hipStream_t st);
 int launch_expert_ffn_f32(const moe_shape& s, const Geom& g, const FfnArgs& a, hipStream_t st);
 
-// Dense y = x W^T over paged weights (bf16 in, f32 out); offsets: device int32[2] = {0, T}.
+// Dense y = x W^T over paged weights (bf16 in, f32 out).
 struct LinearArgs {
     const void* x;             // bf16 [T][K]
     int T, K, N;
-    const int32_t* offsets;
     const int32_t* page_table; // device [pages]
     const char* pool;
     int64_t pool_pages, page_bytes, pages;
     float* out;                // [T][N]
+    uint16_t* out16;           // bf16 [T][N] or null: out rounded to nearest even as well
     int32_t* status;           // [4] or null
 };
+int launch_cast_bf16(int64_t n, const float* in, void* out, hipStream_t st);
 int launch_linear_bf16(const LinearArgs& a, hipStream_t st);
 
 int launch_combine(const moe_shape& s, const float* out, const int32_t* row_of, const float* topk_w,

@@ -198,9 +198,12 @@ inline int gemm_grid(int NT, int R, int BM, int n_experts, int chunked) {
     const int64_t plain_groups = (NT + 7) / 8;
     int64_t slack = 0;
     if (chunked > 0) {
-        for (int m = 1; m <= kMaxRowBlockedTiles; ++m) {
+        // no expert has more than R / BM + 1 row tiles
+        const int m_max = R / BM + 1 < kMaxRowBlockedTiles ? R / BM + 1 : kMaxRowBlockedTiles;
+        for (int m = 1; m <= m_max; ++m) {
             const ChunkPlan c = plan_chunks(m, false, NT, chunked);
-            for (int xrel = 0; xrel < 8; ++xrel) {
+            const int positions = c.nb == 1 ? 1 : 8;       // one row block: the XCD of the first chunk has the most
+            for (int xrel = 0; xrel < positions; ++xrel) {
                 int64_t tiles = 0;
                 for (int b = 0; b < c.nb; ++b) tiles += share_of_block(c, b, xrel, 8).tiles;
                 if (tiles - plain_groups * m > slack) slack = tiles - plain_groups * m;

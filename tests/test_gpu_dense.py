@@ -48,6 +48,24 @@ def test_linear_matches_the_oracle(T, K, N, page):
     assert_close(out.cpu().numpy()[rows], ref, "bf16", f"linear {T}x{K}x{N}")
 
 
+@pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 96, 97, 128, 129, 300])
+@pytest.mark.parametrize("K,N", [(128, 128), (384, 640), (256, 9216)])
+def test_linear_with_few_rows(T, K, N):
+    # row counts around the row-tile pairs and blocks; two, four and six k-steps; column tiles of
+    # 32 and of 64, one and several row tiles; the bf16 copy of the pre-attention task
+    g = torch.Generator().manual_seed(T + K)
+    x = torch.randn((T, K), generator=g)
+    W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
+    ls = M.make_linear_shape(T, K, N, 3 * 16384)
+    table, pool = paged_linear(ls, W)
+    gamma = torch.ones(K)
+    _, xn, qkv, qkv16 = M.moe_pre_attention(ls, None, x.cuda(), gamma.cuda(), 1e-5, table, pool)
+    out = M.moe_linear(ls, xn, table, pool)
+    torch.cuda.synchronize()
+    assert torch.equal(out, qkv) and torch.equal(qkv16, qkv.to(torch.bfloat16))
+    assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
+
+
 def test_linear_empty_and_errors():
     ls = M.make_linear_shape(0, 128, 128, 16384)
     lib = M.binding._lib()

@@ -140,6 +140,34 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
 
 
 @pytest.mark.parametrize("counts,H,F", [
+    ([1, 16, 17, 31, 32, 33, 0, 48, 63, 64, 65, 128, 129], 256, 384),       # 48 rows on average: 128-row blocks
+    ([1, 15, 0, 33, 64, 65, 100, 17], 128, 640),                              # 36 rows: 64-row blocks, two and ten k-steps
+    ([95, 96, 97, 112, 113, 127, 40, 1, 60], 128, 256),                      # 82 rows: beyond the kernel for few rows
+    ([95, 96, 97, 112, 113, 127, 40, 1, 34], 384, 128),                      # 79 rows
+    ([300, 3, 0, 1], 256, 256),                                               # 76 rows, three row tiles of one expert
+])
+def test_bf16_expert_ffn_with_few_rows_per_expert(counts, H, F):
+    """Segments on both sides of the 16-row MFMA tiles, the row-tile pairs and the blocks of the kernel for few rows per expert."""
+    E = len(counts)
+    cfg = MoEConfig("few", "bf16", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=48 * 1024, seed=79)
+    case = Case(cfg, shuffle_pages=True, extra_pages=1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = case.view
+    h_ref, o_ref = oracle.expert_ffn(v["x"], offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
+    w = np.random.default_rng(1).random(cfg.T, dtype=np.float32) + 0.5
+    status = torch.zeros(4, dtype=torch.int32, device="cuda")
+    h, out = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w), status=status)
+    torch.cuda.synchronize()
+    assert_status_clean(status.cpu().tolist())
+    for e, c in enumerate(counts):
+        lo, hi = int(offsets[e]), int(offsets[e + 1])
+        if c:
+            assert_h_close(h.float().cpu().numpy()[lo:hi], h_ref[lo:hi], "bf16", f"h, expert {e} with {c} rows")
+            assert_close(out.cpu().numpy()[lo:hi], o_ref[lo:hi] * w[lo:hi, None], "bf16", f"out, expert {e} with {c} rows")
+    run_layer(case)
+
+
+@pytest.mark.parametrize("counts,H,F", [
     ([1, 15, 16, 17, 31, 32, 33, 0, 64, 70], 128, 256),          # 27 rows on average: k split over the wavefronts, two k-steps for four of them
     ([5, 0, 40], 384, 640),                                        # the same with 6 and 10 k-steps
     ([1, 15, 16, 17, 31, 32, 33, 0, 65, 160], 128, 256),         # 37 rows on average: columns split over the wavefronts
