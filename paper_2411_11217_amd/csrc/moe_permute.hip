@@ -1,20 +1,17 @@
 // a2. Permutation of routed rows by expert: a stable counting sort of the flat
 // indices i = t*k + slot by expert id, in two small kernels plus a row copy.
 //
-//   count   : every block owns kChunk consecutive flat indices; per wavefront
-//             and per expert the population count of a ballot gives how many
-//             of its 64 entries go to that expert; the counts are staged in LDS
-//             and the block's totals go to block_counts[block][E].  Skipped when
-//             one block holds all indices.
-//   place   : same chunking.  Thread e first adds up block_counts[.][e]: the sum over
-//             the blocks before its own is the block's base inside expert e, the sum
-//             over all blocks is counts[e], whose exclusive scan is offsets[] (block 0
-//             writes both).  With more than kScanInPlace blocks a one-block scan kernel
-//             does these sums once instead (block_base, counts, offsets).  The rank of an
-//             entry inside its expert is offsets[e] + base + (entries of earlier wavefront
-//             passes of the block, from LDS) + popcount(ballot & lanes below).
-//             No atomics: the placement is a pure function of the input, hence
-//             stable (ascending flat index inside an expert) and reproducible.
+//   place   : every block owns kChunk consecutive flat indices.  Lanes of a wavefront pass with the same expert find each
+//             other with six ballots (one per bit of the id); the mask gives an entry's rank among them and their number,
+//             staged in LDS per pass.  Up to kCountInPlace blocks, every block also counts the ids of all the others itself
+//             (integer sums in LDS): those before its own chunk give its base inside every expert, all of them give
+//             counts[], whose scan over the lanes is offsets[] (block 0 writes both).  The rank of an entry inside its
+//             expert is offsets[e] + base + (entries of earlier wavefront passes of the block) + its rank in its pass.
+//   count   : with more blocks, a launch of its own counts every block's chunk (block_counts[block][E]) and the placing
+//             blocks add these up; with more than kScanInPlace blocks a one-block scan kernel does the sums once
+//             instead (block_base, counts, offsets).
+//             The placement is a pure function of the input, hence stable (ascending flat index inside an
+//             expert) and reproducible.
 //   gather  : x_perm[row] = x[row_src[row] / k], 16 bytes per lane, one block per row.
 #include "moe_internal.h"
 
@@ -25,33 +22,56 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kPasses = 4;
 constexpr int kChunk = kThreads * kPasses;   // flat indices per block
+// Up to this many blocks the placing blocks read all ids instead of a count launch (4.7 us and more).
+constexpr int kCountInPlace = 16;
 constexpr int kScanInPlace = 256;            // up to this many blocks every placing block sums the block counts itself
 
 __device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
     return __popcll(mask & ((1ull << lane) - 1ull));
 }
 
+// lanes of the wavefront with the same id as this one (0: this lane's id is not an expert)
+__device__ __forceinline__ uint64_t same_expert(int id, bool valid) {
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const bool bit = (id >> b) & 1;
+        const uint64_t set = __ballot(bit);
+        m &= bit ? set : ~set;
+    }
+    return valid ? m : 0;
+}
+static_assert(MOE_MAX_EXPERTS == 64, "an expert id has six bits");
+
+// cnt[pass * kWaves + wave][e] = entries for expert e of every wavefront pass of this block's chunk, and each entry's
+// rank among those of its pass.  Ends with a barrier.
+__device__ __forceinline__ void count_chunk(const int (&my_id)[kPasses], int E, int32_t (*cnt)[MOE_MAX_EXPERTS], int (&my_rank)[kPasses]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < kPasses * kWaves * MOE_MAX_EXPERTS; i += kThreads) cnt[0][i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const uint64_t m = same_expert(my_id[p], my_id[p] >= 0 && my_id[p] < E);
+        my_rank[p] = lanes_below(m, lane);
+        if (m && my_rank[p] == 0) cnt[p * kWaves + wave][my_id[p]] = __popcll(m);
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(kThreads) void count_kernel(const int32_t* __restrict__ ids, int R, int E,
                                                          int32_t* __restrict__ block_counts) {
     __shared__ int32_t cnt[kPasses * kWaves][MOE_MAX_EXPERTS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int base = blockIdx.x * kChunk;
-    int my_id[kPasses];
+    int my_id[kPasses], my_rank[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {               // all loads under way at once
         const int i = base + p * kThreads + threadIdx.x;
         my_id[p] = i < R ? ids[i] : -1;
     }
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-        for (int e = 0; e < E; ++e) {
-            const uint64_t m = __ballot(my_id[p] == e);
-            if (lane == 0) cnt[p * kWaves + wave][e] = __popcll(m);
-        }
-    }
-    __syncthreads();
+    count_chunk(my_id, E, cnt, my_rank);
     for (int e = threadIdx.x; e < E; e += kThreads) {
         int sum = 0;
+#pragma unroll
         for (int j = 0; j < kPasses * kWaves; ++j) sum += cnt[j][e];
         block_counts[(size_t)blockIdx.x * E + e] = sum;
     }
@@ -84,9 +104,9 @@ __global__ __launch_bounds__(64) void scan_kernel(const int32_t* __restrict__ bl
     }
 }
 
-// block_base != null: the scan kernel has run (block_base, counts, offsets are inputs).  Else they are
-// formed here from block_counts[nblocks][E] (nblocks == 1: from this block's own counts), and block 0
-// writes counts[], offsets[] and clears status[0..3] when status is not null.
+// block_base != null: the scan kernel has run (block_base, counts, offsets are inputs).  Else they are formed here, from
+// block_counts[nblocks][E] or, when that is null, from the ids themselves, and block 0 writes counts[], offsets[] and clears
+// status[0..3] when status is not null.
 __global__ __launch_bounds__(kThreads) void place_kernel(const int32_t* __restrict__ ids,
                                                          const float* __restrict__ topk_w, int R, int E,
                                                          const int32_t* __restrict__ block_counts, int nblocks,
@@ -96,16 +116,17 @@ __global__ __launch_bounds__(kThreads) void place_kernel(const int32_t* __restri
                                                          float* __restrict__ row_w, int32_t* __restrict__ status) {
     __shared__ int32_t cnt[kPasses * kWaves][MOE_MAX_EXPERTS];
     __shared__ int32_t start[MOE_MAX_EXPERTS];
-    __shared__ int32_t total[MOE_MAX_EXPERTS];
+    __shared__ int32_t others[kWaves][2][MOE_MAX_EXPERTS];     // ids of the chunks before / behind this block's, per wavefront
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int base = blockIdx.x * kChunk;
+    const bool count_ids = !block_base && !block_counts && nblocks > 1;
     // sums over the other blocks' counts (loads under way during the ballots below)
     int before = 0, all = 0;
     if (threadIdx.x < E) {
         const int e = threadIdx.x;
         if (block_base) {
             before = offsets[e] + block_base[(size_t)blockIdx.x * E + e];
-        } else if (nblocks > 1) {
+        } else if (block_counts) {
             for (int b = 0; b < nblocks; ++b) {
                 const int c = block_counts[(size_t)b * E + e];
                 all += c;
@@ -122,42 +143,61 @@ __global__ __launch_bounds__(kThreads) void place_kernel(const int32_t* __restri
         my_id[p] = i < R ? ids[i] : -1;
         my_w[p] = (row_w && i < R) ? topk_w[i] : 0.f;
     }
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-        const int id = my_id[p];
-        my_rank[p] = 0;
-        for (int e = 0; e < E; ++e) {
-            const uint64_t m = __ballot(id == e);
-            if (lane == 0) cnt[p * kWaves + wave][e] = __popcll(m);
-            if (id == e) my_rank[p] = lanes_below(m, lane);
-        }
-    }
-    __syncthreads();
-    // exclusive running sum over the (pass, wavefront) order in which flat indices grow
-    for (int e = threadIdx.x; e < E; e += kThreads) {
-        int run = 0;
-        for (int j = 0; j < kPasses * kWaves; ++j) {
-            const int c = cnt[j][e];
-            cnt[j][e] = run;
-            run += c;
-        }
-        total[e] = nblocks > 1 ? all : run;
-        start[e] = before;
-    }
-    if (!block_base) {
+    if (count_ids) {
+        for (int i = threadIdx.x; i < kWaves * 2 * MOE_MAX_EXPERTS; i += kThreads) others[0][0][i] = 0;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int run = 0;
-            for (int e = 0; e < E; ++e) {
-                start[e] += run;
-                if (blockIdx.x == 0) {
-                    offsets[e] = run;
-                    counts[e] = total[e];
-                }
-                run += total[e];
+        for (int b = 0; b < nblocks; ++b) {
+            if (b == (int)blockIdx.x) continue;
+            int id[kPasses];
+#pragma unroll
+            for (int p = 0; p < kPasses; ++p) {
+                const int i = b * kChunk + p * kThreads + threadIdx.x;
+                id[p] = i < R ? ids[i] : -1;
             }
-            if (blockIdx.x == 0) offsets[E] = run;
+#pragma unroll
+            for (int p = 0; p < kPasses; ++p)
+                if (id[p] >= 0 && id[p] < E) atomicAdd(&others[wave][b > (int)blockIdx.x][id[p]], 1);
         }
+    }
+    count_chunk(my_id, E, cnt, my_rank);
+    // exclusive running sum over the (pass, wavefront) order in which flat indices grow; then the experts' starts
+    if (wave == 0) {
+        int run = 0;
+        if (lane < E) {
+            int c[kPasses * kWaves];
+#pragma unroll
+            for (int j = 0; j < kPasses * kWaves; ++j) c[j] = cnt[j][lane];
+#pragma unroll
+            for (int j = 0; j < kPasses * kWaves; ++j) {
+                cnt[j][lane] = run;
+                run += c[j];
+            }
+        }
+        if (!block_base) {
+            int total = block_counts ? all : run;
+            if (count_ids && lane < E) {
+#pragma unroll
+                for (int q = 0; q < kWaves; ++q) before += others[q][0][lane];
+                total += before;
+#pragma unroll
+                for (int q = 0; q < kWaves; ++q) total += others[q][1][lane];
+            }
+            int incl = total;                            // lanes beyond the experts add zeros
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int u = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += u;
+            }
+            before += incl - total;
+            if (blockIdx.x == 0) {
+                if (lane < E) {
+                    offsets[lane] = incl - total;
+                    counts[lane] = total;
+                }
+                if (lane == E - 1) offsets[E] = incl;
+            }
+        }
+        start[lane] = before;
     }
     __syncthreads();
 #pragma unroll
@@ -195,9 +235,10 @@ int launch_permute(const moe_shape& s, const int32_t* ids, const float* topk_w, 
                    int32_t* status_to_clear, hipStream_t st) {
     const int R = s.T * s.k;
     const int nblocks = std::max((R + kChunk - 1) / kChunk, 1);      // R == 0: one block writes the zero counts
-    int32_t* block_counts = (int32_t*)ws;
+    int32_t* block_counts = nullptr;
     int32_t* block_base = nullptr;
-    if (nblocks > 1) {
+    if (nblocks > kCountInPlace) {
+        block_counts = (int32_t*)ws;
         hipLaunchKernelGGL(count_kernel, dim3(nblocks), dim3(kThreads), 0, st, ids, R, s.E, block_counts);
         MOE_HIP_TRY(hipGetLastError());
     }

@@ -22,7 +22,7 @@
 // wavefront with a halving butterfly (63 cross-lane moves: lane j ends up with
 // the sum of value j) and over the four wavefronts through LDS.
 //
-// In both, the selection and the softmax are done by one lane per token.
+// In both, the selection and the softmax are done by one lane per (token, expert).
 #include "moe_internal.h"
 
 namespace moe {
@@ -38,32 +38,47 @@ __device__ __forceinline__ void load8(const float* base, size_t elem, float (&v)
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// Top-k of lg[0..E) by descending value (strict >: the lower index keeps a tie) and the softmax
-// over the selected values, for token tok.
-__device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int tok, int32_t* __restrict__ ids,
+// Top-k of lg[0 .. E) by descending value (the lower index keeps a tie) and the softmax over the selected values, for token
+// tok, by EP lanes of one wavefront (EP = experts padded to a power of two; lane `le` of the group holds expert le): k rounds
+// of a maximum over the lanes and a ballot for its first holder.  One lane per token took k * E steps of LDS latency
+// each: with 64 experts, 8 per token, 20 of the launch's 34 us.  A NaN is selected only when no free expert precedes it, as
+// a scan that keeps the first and replaces it by what compares greater would do.  Every lane of the wavefront calls this; `live`: the token exists.
+template <int EP>
+__device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int tok, bool live, int32_t* __restrict__ ids,
                                              float* __restrict__ w) {
-    uint64_t taken = 0;
-    float first = 0.f, den = 0.f;
+    const int lane = threadIdx.x & 63, le = lane & (EP - 1);
+    auto group = [&](uint64_t m) __attribute__((always_inline)) {    // this group's bits of a ballot
+        return EP == 64 ? m : (m >> (lane - le)) & ((1ull << (EP & 63)) - 1);
+    };
+    const float v = le < E ? lg[le] : 0.f;
+    const bool nan = v != v;
+    const uint64_t nans = group(__ballot(nan));
+    bool free_e = le < E;
+    float first = 0.f, den = 0.f, my_p = 0.f;
+    int my_id = 0;
     for (int s = 0; s < k; ++s) {
-        int best = -1;
-        float bv = 0.f;
-        for (int e = 0; e < E; ++e) {
-            const bool free_e = !((taken >> e) & 1ull);
-            const float v = lg[e];
-            if (free_e && (best < 0 || v > bv)) {
-                best = e;
-                bv = v;
-            }
-        }
-        taken |= 1ull << best;
+        const int f0 = __ffsll((long long)group(__ballot(free_e))) - 1;      // s < k <= E: there is one
+        float bv = free_e && !nan ? v : -INFINITY;
+#pragma unroll
+        for (int m = EP / 2; m >= 1; m >>= 1) bv = fmaxf(bv, __shfl_xor(bv, m, 64));
+        const int top = __ffsll((long long)group(__ballot(free_e && !nan && v == bv))) - 1;
+        const bool take_nan = (nans >> f0) & 1;
+        const int best = take_nan ? f0 : top;
+        if (take_nan) bv = NAN;
+        free_e = free_e && le != best;
         if (s == 0) first = bv;
         const float p = __expf(bv - first);
         den += p;
-        ids[(size_t)tok * k + s] = best;
-        w[(size_t)tok * k + s] = p;                           // normalised below
+        if (le == s) {
+            my_id = best;
+            my_p = p;
+        }
     }
     const float inv = 1.0f / den;
-    for (int s = 0; s < k; ++s) w[(size_t)tok * k + s] *= inv;
+    if (live && le < k) {
+        ids[(size_t)tok * k + le] = my_id;
+        w[(size_t)tok * k + le] = my_p * inv;
+    }
 }
 
 // NE: 16-expert tiles (experts padded to 16, 32 or 64); NW: wavefronts of a block.
@@ -73,7 +88,7 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
                                                          float* __restrict__ w, float* __restrict__ logits,
                                                          int T, int H, int E, int k) {
     constexpr int EP = NE * 16;
-    constexpr int UB = NE <= 2 ? 4 : 2;                      // units whose loads are in flight together
+    constexpr int UB = 4;                                    // units whose loads are in flight together
     __shared__ float s_part[NW][16][EP];
     __shared__ float s_logit[16][EP];
     const int lane = threadIdx.x & 63;
@@ -132,7 +147,8 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
         if (logits && e < E && t0 + t < T) logits[(size_t)(t0 + t) * E + e] = sum;
     }
     __syncthreads();
-    if (threadIdx.x < 16 && t0 + threadIdx.x < T) select_top_k(s_logit[threadIdx.x], E, k, t0 + threadIdx.x, ids, w);
+    constexpr int TW = 64 / EP;                              // tokens a wavefront selects for at a time
+    for (int t = wave * TW + lane / EP; t < 16; t += NW * TW) select_top_k<EP>(s_logit[t], E, k, t0 + t, t0 + t < T, ids, w);
 }
 
 // EP: experts padded to a compile-time bound (a power of two, 8..64).
@@ -194,7 +210,7 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x,
         if (logits && e < E && t0 + t < T) logits[(size_t)(t0 + t) * E + e] = sum;
     }
     __syncthreads();
-    if (threadIdx.x < TPB && t0 + threadIdx.x < T) select_top_k(s_logit + threadIdx.x * EP, E, k, t0 + threadIdx.x, ids, w);
+    if (wave == 0) select_top_k<EP>(s_logit + lane / EP * EP, E, k, t0 + lane / EP, t0 + lane / EP < T, ids, w);
 }
 
 template <int EP>

@@ -216,6 +216,55 @@ def test_router_shapes(T, H, E, k, dtype):
     compare_routing(cfg, ids.cpu().numpy(), w.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("E,k", [(1, 1), (5, 5), (8, 3), (17, 4), (64, 8)])
+def test_router_selects_like_a_scan_with_ties_infinities_and_nan(E, k, dtype):
+    """The selected experts are those of k scans over the logits that keep the first free one and replace it by what compares
+    greater: the lower index of equal logits (repeated router rows), infinities, NaN only when no free expert precedes it."""
+    T, H = 35, 128
+    g = torch.Generator().manual_seed(E)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Wr = torch.randn(((E + 1) // 2, H), generator=g).to(dt).repeat(2, 1)[:E].contiguous()      # every logit twice
+    x = torch.randn((T, H), generator=g).to(dt)
+    bias = torch.zeros(E)
+    for e, v in ((1, float("inf")), (3, float("-inf")), (4, float("nan")), (E - 1, float("-inf"))):
+        if e < E:
+            bias[e] = v
+    s = M.make_shape(T, H, 128, E, k, dtype, 65536)
+    for b in (None, bias, bias.roll(1), torch.full((E,), float("nan"))):
+        ids, w, logits = M.moe_route(s, x.cuda(), Wr.cuda(), bias=None if b is None else b.cuda(), want_logits=True)
+        lg, ids = logits.cpu().tolist(), ids.cpu().tolist()
+        for t in range(T):
+            free, want = list(range(E)), []
+            for _ in range(k):
+                best = free[0]
+                for e in free:
+                    if lg[t][e] > lg[t][best]:
+                        best = e
+                free.remove(best)
+                want.append(best)
+            assert ids[t] == want, (t, lg[t])
+        if b is None:
+            sel = torch.softmax(torch.gather(logits.cpu().double(), 1, torch.tensor(ids)), 1)
+            assert (w.cpu().double() - sel).abs().max() <= 2e-6      # __expf and a reciprocal: a few units of 2^-23
+
+
+def test_permutation_leaves_out_ids_that_are_no_experts():
+    E, k = 5, 2
+    for T in (40, 1500, 9000):                                         # one block, blocks that count in place, a count launch
+        rng = np.random.default_rng(T)
+        ids = rng.integers(-2, E + 2, size=(T, k)).astype(np.int32)
+        ids[0] = (-1, 64)
+        pm = M.moe_permute(M.MoEShape(T, 128, 128, E, k, M.DTYPE_BF16, 16384), _dev_i32(ids))
+        flat = ids.reshape(-1)
+        ok = (flat >= 0) & (flat < E)
+        counts = np.bincount(flat[ok], minlength=E)
+        assert np.array_equal(pm["counts"].cpu().numpy(), counts)
+        assert np.array_equal(pm["offsets"].cpu().numpy(), np.r_[0, np.cumsum(counts)])
+        order = np.flatnonzero(ok)[np.argsort(flat[ok], kind="stable")]
+        assert np.array_equal(pm["row_src"].cpu().numpy()[:ok.sum()], order)
+
+
 @pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1000, 1, 1), (512, 3, 2), (513, 3, 2), (4096, 8, 2), (16384, 64, 1),
                                    (5000, 16, 4), (40000, 64, 2), (131072, 8, 2), (140000, 5, 2)])
 def test_permutation_block_counts(T, E, k):
