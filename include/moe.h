@@ -345,7 +345,7 @@ int moe_pre_attention(const moe_linear_shape* qkv_proj, const float* hidden, con
  * measured best.  No option changes a result bit.
  *   "xcd_remap"   1: column-tile groups of the expert GEMMs are dealt round robin to the
  *                 8 XCDs; 0: block b computes tile b.                       default 1
- *   "half_tiles"  1: bf16 row tiles with at most 128 rows run shorter loops.   default 1
+ *   "half_tiles"  1: bf16 row tiles with at most 192 rows run shorter loops.   default 1
  *   "down_cols"   column tiles of the bf16 down GEMM: 0 = by grid size, 1 = 128 wide,
  *                 2 = 256 wide.                                              default 0
  *   "gate_cols"   accepted and ignored (the bf16 gate/up GEMM has one width of column tiles, 128

@@ -99,6 +99,7 @@ constexpr int kARowB = 128;                  // bytes of one activation row in a
 constexpr int kStageA = 256 * kARowB;        // activation stage of one k-step
 constexpr int kStagesA = 3;                  // depth of the activation ring
 constexpr int kRingA = kStages * kStageB;    // LDS offset of the activation ring (the weight ring sits at 0)
+constexpr int kShortTiles = 6;                // most row tiles of a wavefront in the loop of a short row tile
 constexpr int kLdsBytes = kRingA + kStagesA * kStageA;   // 160 KiB: all of a compute unit's LDS
 
 // wait until at most N of my vector-memory loads are outstanding and all my LDS fetches are back
@@ -447,9 +448,9 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         b_base[j] = (MODE == 0 ? (j >> 2) * 128 + wn * 64 + (j & 3) * 16 : wn * (16 * NJ) + j * 16) * kRowB;
 
     // operand registers: two sets of four activation fragments, two sets of weight fragments
-    i32x4 AX[4], AY[4], BF[2][NJ];
+    i32x4 AX[kShortTiles], AY[kShortTiles], BF[2][NJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) AX[i] = AY[i] = i32x4{0, 0, 0, 0};
+    for (int i = 0; i < kShortTiles; ++i) AX[i] = AY[i] = i32x4{0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < NJ; ++j) BF[0][j] = BF[1][j] = i32x4{0, 0, 0, 0};   // the first rotated MFMA group adds 0 * 0
 
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         advance_b(kn, odd, I);
     };
 
-    // The main loop for a tile of 256 rows (HALF = false) or of at most 128 rows (HALF = true).
+    // The main loop for a tile of 256 rows (HALF = false) or of at most 192 rows (HALF = true).
     //
     // 256 rows: wavefront (wm, wn) owns rows wm*128 .. +127: row tiles 0..3 through the fragment set AX,
     // 4..7 through AY.  A half-step on weight-ring slot U (a compile-time constant: every weight address
@@ -488,6 +489,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     //   group 1: the second half of the column fragments of half-step k-1; fetches all fragments of k;
     //            issues the activation loads (even half-steps only: rows 128..255 are not loaded at all);
     //   group 2: the first half of the column fragments of half-step k; issues the weight loads.
+    // 129 .. 192 rows: the same with five or six row tiles per wavefront.
     // At most 64 rows: the same with the wavefronts wm = 1 taking part in the loads only; at most 32
     // rows: two row tiles instead of four.  Measured in cycles of a full tile: 0.6 for the first, and
     // the launches of the Mixtral-8x7B-shaped workload (whose short tiles have 4 to 31 rows) got 2-3 %
@@ -506,9 +508,9 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         constexpr bool HALF = decltype(half_tile_c)::value;
         constexpr bool TALL = decltype(tall_c)::value;
         static_assert(!(HALF && TALL), "tall tiles run the full loop");
-        constexpr int RT = decltype(rt_c)::value;       // short tiles: row tiles a wavefront computes (4, 2)
-        constexpr int NA = decltype(na_c)::value;       // short tiles: activation load instructions per k-step (4, 2, 1: 32 rows each)
-        constexpr int WROWS = HALF ? 64 : 128;          // rows of a wavefront
+        constexpr int RT = decltype(rt_c)::value;       // short tiles: row tiles a wavefront computes (6, 5, 4, 2)
+        constexpr int NA = decltype(na_c)::value;       // short tiles: activation load instructions per k-step (6, 5, 4, 2, 1: 32 rows each)
+        constexpr int WROWS = !HALF ? 128 : RT > 4 ? 16 * RT : 64;      // rows of a wavefront
         const bool wact = !HALF || wm == 0 || rows_here > 64;    // a short tile with at most 64 rows is the upper wavefronts' alone
         int a_frag[2];                    // includes the activation stage being read: moves on after every odd half-step
 #pragma unroll
@@ -687,26 +689,30 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(accE[j]));      // read only behind the drain
     };
-    // A row tile with at most 128 rows takes the half-height loop; any other whose last rows are missing
+    // A row tile with at most 192 rows takes a loop of its height; any other whose last rows are missing
     // runs the full loop on repeated rows (skipping single MFMAs would take a branch each: a wavefront
     // issues about one instruction in four clocks, and the branches cost more than the MFMAs they skip).
-    // Short tiles: at most 128 rows: both wavefront rows, 64 rows each; at most 64: the upper wavefront row
-    // alone (the other wavefronts only load); at most 32: two row tiles instead of four.
-    const bool half_tile = p.half_tiles && rows_here <= 128;
+    // Short tiles: 129 .. 192 rows: both wavefront rows, five or six row tiles each; 65 .. 128: four row tiles each; at
+    // most 64: the upper wavefront row alone (the other wavefronts only load); at most 32: two row tiles instead of four.
+    // us for the layer with the full loop / with five or six row tiles: DBRX shape, 550 tokens (138 rows per expert) 1338 /
+    // 1222, 700 tokens 1394 / 1307; Mixtral-8x7B shape, 600 tokens 644 / 592; 64 experts of 2048 x 1024, 1200 tokens 421 / 397.
+    const bool half_tile = p.half_tiles && rows_here <= 32 * kShortTiles;
     using std::integral_constant;
     if (!half_tile && extra) main_loop(std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::true_type{});
     else if (!half_tile) main_loop(std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
+    else if (rows_here > 160) main_loop(std::true_type{}, integral_constant<int, 6>{}, integral_constant<int, 6>{}, std::false_type{});
+    else if (rows_here > 128) main_loop(std::true_type{}, integral_constant<int, 5>{}, integral_constant<int, 5>{}, std::false_type{});
     else if (rows_here > 64) main_loop(std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
     else if (rows_here > 32) main_loop(std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 2>{}, std::false_type{});
     else main_loop(std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 1>{}, std::false_type{});
     const bool wact = !half_tile || wm == 0 || rows_here > 64;        // this wavefront has rows
-    const int row_tiles = !half_tile ? 8 : (rows_here > 32 ? 4 : 2);   // and this many row tiles
+    const int row_tiles = !half_tile ? 8 : rows_here > 160 ? 6 : rows_here > 128 ? 5 : rows_here > 32 ? 4 : 2;   // and this many row tiles
 
     // ---- epilogue ---------------------------------------------------------------------
     // accumulator register r of lane l in MFMA tile (i, j) is the element at row i*16 + (l/16)*4 + r,
     // column l%16 of that 16 x 16 tile
     const int col_l = lane & 15;
-    const int a_row_base = wm * (half_tile ? 64 : 128) + (lane >> 4) * 4;
+    const int a_row_base = wm * (row_tiles > 4 ? 16 * row_tiles : 64) + (lane >> 4) * 4;
     const bool full_rows = rows_here >= BM;
     // store(i, v): the 4 x NJ x 16 values of row tile i of this wavefront
     auto for_row_tiles = [&](auto n_c, auto&& store) __attribute__((always_inline)) {
@@ -740,6 +746,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         else if (!wact) {
         } else if (row_tiles == 2) store_rows(std::false_type{}, std::integral_constant<int, 2>{});
         else if (row_tiles == 4) store_rows(std::false_type{}, std::integral_constant<int, 4>{});
+        else if (row_tiles == 5) store_rows(std::false_type{}, std::integral_constant<int, 5>{});
+        else if (row_tiles == 6) store_rows(std::false_type{}, std::integral_constant<int, 6>{});
         else store_rows(std::false_type{}, std::integral_constant<int, 8>{});
         if (extra) {                           // the extra row tile of a tall tile
 #pragma unroll
@@ -784,6 +792,8 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
             else if (!wact) {
             } else if (row_tiles == 2) store_rows(std::false_type{}, std::integral_constant<int, 2>{});
             else if (row_tiles == 4) store_rows(std::false_type{}, std::integral_constant<int, 4>{});
+            else if (row_tiles == 5) store_rows(std::false_type{}, std::integral_constant<int, 5>{});
+            else if (row_tiles == 6) store_rows(std::false_type{}, std::integral_constant<int, 6>{});
             else store_rows(std::false_type{}, std::integral_constant<int, 8>{});
             if (extra) {                       // the extra row tile of a tall tile
 #pragma unroll

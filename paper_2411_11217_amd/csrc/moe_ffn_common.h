@@ -33,7 +33,7 @@ struct GemmParams {
     const float* row_w;
     int32_t* status;
     int32_t xcd_remap;
-    int32_t half_tiles;       // bf16 kernel: row tiles with at most 128 rows run the half-height loop
+    int32_t half_tiles;       // bf16 kernel: row tiles with at most 192 rows run the loop of their height
     const int32_t* a_gather;  // or null: row r of A is row a_gather[r] / a_div of the matrix at A (a_rows rows)
     int32_t a_div, a_rows;
     void* a_copy;             // f32 kernels, or null: the launch also writes the rows it reads here, [R][K]
