@@ -88,7 +88,9 @@ constexpr int kComputeUnits = 256;           // MI355X
 // 1015 / 1038, 1536: 1063 / 1125, 4096: 2145 / 2190.  On 64 experts (2048 x 1024) the line lies at the same
 // place: 250 rows per expert 522 / 504, 375 rows 626 / 662.  And only where the experts' weights exceed the 256 MiB
 // last-level cache: smaller ones may still be there from the call before, and the hint keeps them out (8 experts of
-// 1024 x 2816, 138 MB, 100 tokens: 53 us without, 56 with).
+// 1024 x 2816, 138 MB, 100 tokens: 53 us without, 56 with).  An expert that has several row tiles all the same reads without
+// the hint: its tiles share the weights through the L2 (8 experts of 2048 x 4096, 400 tokens, 40 % of them on one
+// expert: layer 129 us with the hint for all, 106 this way).
 constexpr int kStreamRows = 256;
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
@@ -256,12 +258,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 
-// STREAM: the weight loads carry the non-temporal hint (see kStreamRows).
 // NB: page tiles per block along the columns.  2: the 256-column block described above.  1 (MODE 1
 // only): 256 rows x 128 columns, wavefront tile 128 x 64, for launches with too few 256-wide tiles
 // to occupy the chip (few rows per expert: the launch is bound by streaming the weights, and more
 // blocks stream more).
-template <int MODE, int NB, bool STREAM>
+template <int MODE, int NB>
 __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     constexpr int S = kStages;
     static_assert(MODE == 1 || NB == 2, "the narrow block is the down projection's");
@@ -423,12 +424,15 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         __builtin_amdgcn_global_load_lds((gptr_t)(a_ptr + a_off[ia]), (lptr_t)(smem + a_wr + (ia * kWaves + wave) * 1024), 16, 0, 0);
         advance_a(ia);
     };
-    auto load_b = [&](int slot, int kn, int odd, int i) __attribute__((always_inline)) {     // odd = kn & 1, known at compile time by the callers
+    auto load_b = [&](auto stream_c, int slot, int kn, int odd, int i) __attribute__((always_inline)) {     // odd = kn & 1, known at compile time by the callers
         char* st = smem + slot * kStageB;
         const TileWalk& w = i < 2 ? w0 : w1;
         const int part = (i & 1) * (kWaves * 1024);                       // first or second 4 KiB of the half-tile in LDS
         const char* b = w.tile + odd * kHalfTile + part;
-        __builtin_amdgcn_global_load_lds((gptr_t)(b + b_off), (lptr_t)(st + (i >= 2 ? kHalfTile : 0) + part + wave * 1024), 16, 0, STREAM ? 2 : 0);
+        const gptr_t src = (gptr_t)(b + b_off);
+        const lptr_t dst = (lptr_t)(st + (i >= 2 ? kHalfTile : 0) + part + wave * 1024);
+        if constexpr (decltype(stream_c)::value) __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
+        else __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
         advance_b(kn, odd, i);
     };
 
@@ -466,10 +470,10 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
         mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, IA * kWaves * 1024, false>(a, b, a_ptr, a_off[IA], a_wr_w);
         advance_a(IA);
     };
-    auto mfma_load_b = [&](auto i_c, auto j_c, const i32x4& a, const i32x4& b, auto slot_c, auto l_c, int kn) __attribute__((always_inline)) {   // + weight load instruction L of half-step kn into slot SLOT
+    auto mfma_load_b = [&](auto i_c, auto j_c, const i32x4& a, const i32x4& b, auto slot_c, auto l_c, auto stream_c, int kn) __attribute__((always_inline)) {   // + weight load instruction L of half-step kn into slot SLOT
         constexpr int SLOT = decltype(slot_c)::value, I = decltype(l_c)::value;
         constexpr int odd = SLOT & 1;               // S is even: the parity of the half-step is that of its slot
-        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, SLOT * kStageB + (I >= 2 ? kHalfTile : 0) + (I & 1) * (kWaves * 1024), STREAM>(
+        mfma_16x16x32_then_load<(decltype(i_c)::value * NJ + decltype(j_c)::value) * 4, SLOT * kStageB + (I >= 2 ? kHalfTile : 0) + (I & 1) * (kWaves * 1024), decltype(stream_c)::value>(
             a, b, (I < 2 ? w0 : w1).tile, b_voff[odd][I & 1], lds_wave);
         advance_b(kn, odd, I);
     };
@@ -503,8 +507,9 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // test cost two of them (to the block and back) plus the branch around its load: measured per half-step about as
     // much as the eight extra MFMAs themselves (a tall tile took 15 % longer than a full one for 12.5 % more MFMAs with
     // the extra tile's loads taken out, and still 15 % longer with half the extra MFMAs).
-    auto main_loop = [&](auto half_tile_c, auto rt_c, auto na_c, auto tall_c) __attribute__((always_inline)) {
+    auto main_loop = [&](auto stream_c, auto half_tile_c, auto rt_c, auto na_c, auto tall_c) __attribute__((always_inline)) {
         using std::integral_constant;
+        constexpr bool ST = decltype(stream_c)::value;  // the weight loads carry the non-temporal hint (see kStreamRows)
         constexpr bool HALF = decltype(half_tile_c)::value;
         constexpr bool TALL = decltype(tall_c)::value;
         static_assert(!(HALF && TALL), "tall tiles run the full loop");
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                     constexpr int m = decltype(mc)::value;
                     constexpr int r = m / NJ, j = (r & 1) ? NJ - 1 - m % NJ : m % NJ;   // back and forth: one operand stays at each row change
                     constexpr bool ld = LB && m >= LB0 && (m - LB0) % LBS == 0 && (m - LB0) / LBS < 2 * NB;
-                    if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, AX[r], BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, (m - LB0) / LBS>{}, kn);
+                    if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, AX[r], BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, (m - LB0) / LBS>{}, integral_constant<bool, ST>{}, kn);
                     else mfma(integral_constant<int, r>{}, integral_constant<int, j>{}, AX[r], BF[HP][j]);
                     MOE_FENCE();
                     if (m < 4) {
@@ -607,7 +612,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                     constexpr int r = m / NH, j = (r & 1) ? NH - 1 - m % NH : m % NH;
                     constexpr bool ld = LB && m % LBS == 0 && m / LBS < 2 * NB;
                     const i32x4& a_cur = HP ? AY[r] : AX[r];
-                    if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, a_cur, BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, ld ? m / LBS : 0>{}, kn);
+                    if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, a_cur, BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, ld ? m / LBS : 0>{}, integral_constant<bool, ST>{}, kn);
                     else mfma(integral_constant<int, r>{}, integral_constant<int, j>{}, a_cur, BF[HP][j]);
                     MOE_FENCE();
                 });
@@ -618,7 +623,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                 }
                 if (LB) {
 #pragma unroll
-                    for (int i = 0; i < 2 * NB; ++i) load_b(nslot, kn, nslot & 1, i);
+                    for (int i = 0; i < 2 * NB; ++i) load_b(integral_constant<bool, ST>{}, nslot, kn, nslot & 1, i);
                 }
             }
             if (HALF && LA && HP) {            // a short tile has no second load part: the sources of the k-step two ahead move on here
@@ -655,7 +660,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                 advance_a(7);
             }
 #pragma unroll
-            for (int i = 0; i < kLB; ++i) load_b(s, s, s & 1, i);
+            for (int i = 0; i < kLB; ++i) load_b(integral_constant<bool, ST>{}, s, s, s & 1, i);
         }
         // the accumulators are cleared while the first stages are on their way
         static_for<32 * NJ>([&](auto rc) __attribute__((always_inline)) { acc_zero<decltype(rc)::value>(); });
@@ -698,13 +703,17 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // 1222, 700 tokens 1394 / 1307; Mixtral-8x7B shape, 600 tokens 644 / 592; 64 experts of 2048 x 1024, 1200 tokens 421 / 397.
     const bool half_tile = p.half_tiles && rows_here <= 32 * kShortTiles;
     using std::integral_constant;
-    if (!half_tile && extra) main_loop(std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::true_type{});
-    else if (!half_tile) main_loop(std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
-    else if (rows_here > 160) main_loop(std::true_type{}, integral_constant<int, 6>{}, integral_constant<int, 6>{}, std::false_type{});
-    else if (rows_here > 128) main_loop(std::true_type{}, integral_constant<int, 5>{}, integral_constant<int, 5>{}, std::false_type{});
-    else if (rows_here > 64) main_loop(std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
-    else if (rows_here > 32) main_loop(std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 2>{}, std::false_type{});
-    else main_loop(std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 1>{}, std::false_type{});
+    auto run = [&](auto stream_c) __attribute__((always_inline)) {
+        if (!half_tile && extra) main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::true_type{});
+        else if (!half_tile) main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
+        else if (rows_here > 160) main_loop(stream_c, std::true_type{}, integral_constant<int, 6>{}, integral_constant<int, 6>{}, std::false_type{});
+        else if (rows_here > 128) main_loop(stream_c, std::true_type{}, integral_constant<int, 5>{}, integral_constant<int, 5>{}, std::false_type{});
+        else if (rows_here > 64) main_loop(stream_c, std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
+        else if (rows_here > 32) main_loop(stream_c, std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 2>{}, std::false_type{});
+        else main_loop(stream_c, std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 1>{}, std::false_type{});
+    };
+    if (p.stream && tc.mtiles == 1) run(std::true_type{});
+    else run(std::false_type{});
     const bool wact = !half_tile || wm == 0 || rows_here > 64;        // this wavefront has rows
     const int row_tiles = !half_tile ? 8 : rows_here > 160 ? 6 : rows_here > 128 ? 5 : rows_here > 32 ? 4 : 2;   // and this many row tiles
 
@@ -816,23 +825,18 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     if (bad && tid == 0 && p.status) atomicOr(p.status, 1);
 }
 
-template <int MODE, int NB, bool STREAM>
-int launch_kernel(const GemmParams& p, int grid, hipStream_t st) {
+template <int MODE, int NB>
+int launch_stages(const GemmParams& p, int grid, hipStream_t st) {
     constexpr int lds = kLdsBytes;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     MOE_HIP_TRY(attr_err);
-    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB, STREAM>), dim3(grid), dim3(kThreads), lds, st, p);
+    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB>), dim3(grid), dim3(kThreads), lds, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
-}
-
-template <int MODE, int NB>
-int launch_stages(const GemmParams& p, int grid, bool stream, hipStream_t st) {
-    return stream ? launch_kernel<MODE, NB, true>(p, grid, st) : launch_kernel<MODE, NB, false>(p, grid, st);
 }
 
 }  // namespace
@@ -844,16 +848,16 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     fill_common(p, s, g, a);
     fill_gate_up(p, s, g, a);
     const int64_t rows_each = R / s.E;
-    const bool stream = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
+    p.stream = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
     if (rows_kernel_takes((int)rows_each)) {
-        const int rc = launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, stream, st);
+        const int rc = launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, st);
         if (rc != MOE_OK) return rc;
         if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
         fill_down(p, s, g, a);
-        return launch_down_rows_bf16(p, s.H, R, (int)rows_each, n_exp, stream, st);
+        return launch_down_rows_bf16(p, s.H, R, (int)rows_each, n_exp, st);
     }
     const int64_t row_tiles_each = std::max<int64_t>(1, (rows_each - p.tall_rows + BM - 1) / BM);
-    const int rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
+    const int rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
     if (rc != MOE_OK) return rc;
     if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
     fill_down(p, s, g, a);
@@ -867,9 +871,9 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     const bool narrow = opt == 1 || (opt == 0 && n_exp * row_tiles_each * p.NT < kComputeUnits);
     if (narrow) {
         p.NT = (int32_t)g.dt;
-        return launch_stages<1, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
+        return launch_stages<1, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
     }
-    return launch_stages<1, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), stream, st);
+    return launch_stages<1, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
 }
 
 // y = x W^T for a dense weight matrix held as pages: the down-projection kernel with one "expert"
@@ -911,10 +915,10 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     int rc;
     if ((int64_t)(a.T / BM + 1) * wide_tiles < 2 * kComputeUnits) {       // too few 256-wide tiles to fill the chip
         p.NT = p.n_page_tiles;
-        rc = launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), false, st);
+        rc = launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
     } else {
         p.NT = wide_tiles;
-        rc = launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), false, st);
+        rc = launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
     }
     if (rc != MOE_OK || !a.out16) return rc;
     return launch_cast_bf16((int64_t)a.T * a.N, a.out, a.out16, st);

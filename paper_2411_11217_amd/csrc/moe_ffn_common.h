@@ -40,11 +40,13 @@ struct GemmParams {
     int32_t tall_rows;        // bf16 kernel: a row tile may be up to this many rows higher than BM (0 or 32), see locate_tile
     int32_t chunked;          // tile numbering: groups dealt to the XCDs in chunks of about this many tiles (0: single groups), see locate_tile
     int32_t tall_first;       // bf16 kernel: tile numbering with the tall tiles of a chunk of groups first, see locate_tile
+    int32_t stream;           // bf16 kernels: weights of experts with one row tile are loaded with the non-temporal hint
     int32_t balance;          // 1: no XCD runs more than an eighth of the launch's tiles, see stolen_tile
 };
 
 struct TileCoord {
     int e, mt, nt, row0, rows_here;
+    int mtiles;               // row tiles of the expert
     bool valid;
 };
 
@@ -143,6 +145,7 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
     const RowSpan rs = rows_of_tile(seg, rows, te.mt, BM, p.tall_rows);
     t.nt = te.nt;
     t.mt = te.mt;
+    t.mtiles = mtiles;
     t.e = p.e_begin + src;
     t.row0 = rs.row0;
     t.rows_here = rs.rows_here;
@@ -159,8 +162,8 @@ __device__ __forceinline__ float silu_mul_bf16(float g, float u) {
 
 // the kernel for few rows per expert (moe_ffn_rows_bf16.hip); p as filled for the launch, NT is set there
 bool rows_kernel_takes(int rows_each);
-int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, bool stream, hipStream_t st);
-int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, bool stream, hipStream_t st);
+int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st);
+int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st);
 bool linear_rows_kernel_takes(int N, int T);
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st);
 

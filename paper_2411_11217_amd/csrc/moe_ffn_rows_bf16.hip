@@ -4,7 +4,7 @@
 //
 // A block owns a row tile (16 * RT rows) x 16 * CW * FC columns (MODE 0: features, gate and up).  The CW wavefronts split the
 // columns; a wavefront's 16 weight rows of a half-tile are 1 KiB in a row in the page, exactly one 16-byte load per lane and
-// exactly its MFMA operand, so the weights go from the page straight into registers, D k-steps ahead (STREAM: with the
+// exactly its MFMA operand, so the weights go from the page straight into registers, D k-steps ahead (p.stream: with the
 // non-temporal hint).  The activations, which all wavefronts share, are loaded as far ahead into registers and pass through a
 // double-buffered LDS stage (one k-step, 128-byte rows, the chunk swizzle of moe_ffn_bf16.hip), one barrier per k-step.
 // All loads are the compiler's own, in one order, so its counted waits keep D - 1 k-steps under way across the barriers.
@@ -33,6 +33,7 @@ constexpr int kTileBytes = 2 * kHalfTileBytes;
 // locate_tile costs a few microseconds of integer arithmetic per block, which these short blocks would feel.
 struct RowsTile {
     int e, nt, row0, rows_here;
+    int mtiles;               // row tiles of the expert
 };
 template <int BM>
 __device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& t) {
@@ -69,6 +70,7 @@ __device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& 
     t.nt = run * 8 + in_run - mt * width;
     t.row0 = seg + mt * BM;
     t.rows_here = min(BM, rows - mt * BM);
+    t.mtiles = m;
     return true;
 }
 
@@ -78,7 +80,7 @@ struct Num {
 };
 
 // FC: fragments of 16 columns per wavefront (MODE 0: of 16 features, gate and up)
-template <int MODE, int RT, int CW, int FC, int RG, int D, bool STREAM>
+template <int MODE, int RT, int CW, int FC, int RG, int D>
 __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p) {
     constexpr int BM = 16 * RT, NB = MODE == 0 ? 2 * FC : FC, kCols = 16 * CW * FC;
     constexpr int kPass = 8 * CW * RG;               // rows that one load instruction per thread fetches
@@ -156,7 +158,8 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
     int tile0 = 0, tiles_mine = TPW;                 // this wavefront's first row tile and their number
 
     // the loop for NRT row tiles: rows beyond them are neither loaded nor multiplied
-    auto main_loop = [&](auto nrt_c) __attribute__((always_inline)) {
+    auto main_loop = [&](auto stream_c, auto nrt_c) __attribute__((always_inline)) {
+        constexpr bool STREAM = decltype(stream_c)::value;
         constexpr int NRT = decltype(nrt_c)::value, NA = (16 * NRT + kPass - 1) / kPass, NT = (NRT + RG - 1) / RG;
         static_assert(RG * NT * 16 <= AJ * kPass, "every row tile that is multiplied lies inside the stage");
         tile0 = rg * NT;
@@ -214,10 +217,14 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         for (int u = 0; u < 2 * D - 1; ++u)
             if (s + u < p.KT) step(s + u, u % D, s + u + D < p.KT);
     };
-    if (RT > 6 && rows_here > 96) main_loop(Num<RT>{});
-    else if (RT > 4 && rows_here > 64) main_loop(Num<RT < 6 ? RT : 6>{});
-    else if (RT > 2 && rows_here > 32) main_loop(Num<RT < 4 ? RT : 4>{});
-    else main_loop(Num<2>{});
+    auto run = [&](auto stream_c) __attribute__((always_inline)) {
+        if (RT > 6 && rows_here > 96) main_loop(stream_c, Num<RT>{});
+        else if (RT > 4 && rows_here > 64) main_loop(stream_c, Num<RT < 6 ? RT : 6>{});
+        else if (RT > 2 && rows_here > 32) main_loop(stream_c, Num<RT < 4 ? RT : 4>{});
+        else main_loop(stream_c, Num<2>{});
+    };
+    if (RG == 1 && p.stream && tc.mtiles == 1) run(Num<RG == 1>{});        // RG > 1: the linear map, never streamed
+    else run(Num<0>{});
 
     const int col = nt * kCols + cw * 16 * FC + r;
 #pragma unroll
@@ -243,10 +250,10 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
     if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
 }
 
-template <int MODE, int RT, int CW, int FC, int RG, int D, bool STREAM>
+template <int MODE, int RT, int CW, int FC, int RG, int D>
 int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
     p.NT = cols / (16 * CW * FC);
-    hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D, STREAM>), dim3(p.NT * (R / (16 * RT) + n_exp)), dim3(64 * CW * RG), 0, st, p);
+    hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D>), dim3(p.NT * (R / (16 * RT) + n_exp)), dim3(64 * CW * RG), 0, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }
@@ -266,24 +273,14 @@ constexpr int kRows64Max = 44;
 
 bool rows_kernel_takes(int rows_each) { return rows_each <= kRowsKernelMax; }
 
-template <bool STREAM>
-static int gate_up(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st) {
-    if (rows_each <= kRows64Max) return launch_rows<0, 4, 4, 1, 1, 4, STREAM>(p, F, R, n_exp, st);
-    return launch_rows<0, 8, 8, 1, 1, 2, STREAM>(p, F, R, n_exp, st);
+int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st) {
+    if (rows_each <= kRows64Max) return launch_rows<0, 4, 4, 1, 1, 4>(p, F, R, n_exp, st);
+    return launch_rows<0, 8, 8, 1, 1, 2>(p, F, R, n_exp, st);
 }
 
-template <bool STREAM>
-static int down(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st) {
-    if (rows_each <= kRows64Max) return launch_rows<1, 4, 4, 2, 1, 4, STREAM>(p, H, R, n_exp, st);
-    return launch_rows<1, 8, 8, 1, 1, 4, STREAM>(p, H, R, n_exp, st);
-}
-
-int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, bool stream, hipStream_t st) {
-    return stream ? gate_up<true>(p, F, R, rows_each, n_exp, st) : gate_up<false>(p, F, R, rows_each, n_exp, st);
-}
-
-int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, bool stream, hipStream_t st) {
-    return stream ? down<true>(p, H, R, rows_each, n_exp, st) : down<false>(p, H, R, rows_each, n_exp, st);
+int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st) {
+    if (rows_each <= kRows64Max) return launch_rows<1, 4, 4, 2, 1, 4>(p, H, R, n_exp, st);
+    return launch_rows<1, 8, 8, 1, 1, 4>(p, H, R, n_exp, st);
 }
 
 // Where the dense linear map takes it: one row tile, or as many blocks of 64 columns and 128 rows as run at once.  One weight
@@ -300,10 +297,10 @@ bool linear_rows_kernel_takes(int N, int T) { return T <= 128 || N / 64 * ((T + 
 
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
     const bool few_columns = N / 32 * ((T + 127) / 128) <= kComputeUnits;
-    if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8, false>(p, N, T, 1, st);
-    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 8, false>(p, N, T, 1, st);
-    if (few_columns) return launch_rows<1, 8, 2, 1, 4, 4, false>(p, N, T, 1, st);
-    return launch_rows<1, 8, 4, 1, 2, 4, false>(p, N, T, 1, st);
+    if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8>(p, N, T, 1, st);
+    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 8>(p, N, T, 1, st);
+    if (few_columns) return launch_rows<1, 8, 2, 1, 4, 4>(p, N, T, 1, st);
+    return launch_rows<1, 8, 4, 1, 2, 4>(p, N, T, 1, st);
 }
 
 }  // namespace moe
