@@ -94,6 +94,13 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
 
     RowsTile tc;
     if (!locate_rows_tile<BM>(p, tc)) return;
+    // diagnostic: some blocks report the shader clock they saw, as in moe_ffn_bf16.hip
+    const bool clock_probe = p.status && (blockIdx.x & 511) == 256 && threadIdx.x == 0;
+    long long probe_c = 0, probe_w = 0;
+    if (clock_probe) {
+        probe_c = clock64();
+        probe_w = wall_clock64();
+    }
     const int nt = tc.nt, row0 = tc.row0, rows_here = tc.rows_here;
     const int32_t* trow = p.table + (size_t)(p.table_row_mod ? tc.e % p.table_row_mod : tc.e) * p.ppe + p.group_base;
 
@@ -247,6 +254,10 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
                 }
             }
         }
+    if (clock_probe) {
+        const long long dc = clock64() - probe_c, dw = wall_clock64() - probe_w;
+        if (dw > 0) p.status[2 + MODE] = (int32_t)(dc * 100 / dw);       // MHz
+    }
     if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
 }
 

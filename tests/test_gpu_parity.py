@@ -145,6 +145,7 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
     ([95, 96, 97, 112, 113, 127, 40, 1, 60], 128, 256),                      # 82 rows: beyond the kernel for few rows
     ([95, 96, 97, 112, 113, 127, 40, 1, 34], 384, 128),                      # 79 rows
     ([300, 3, 0, 1], 256, 256),                                               # 76 rows, three row tiles of one expert
+    ([130, 161, 176, 191, 145, 0], 256, 384),                                 # 133 rows: five and six row tiles per wavefront
 ])
 def test_bf16_expert_ffn_with_few_rows_per_expert(counts, H, F):
     """Segments on both sides of the 16-row MFMA tiles, the row-tile pairs and the blocks of the kernel for few rows per expert."""
