@@ -907,7 +907,7 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     p.tall_first = get_opt(OPT_TALL_FIRST);
     p.balance = get_opt(OPT_BALANCE);
     p.chunked = std::min(std::max(get_opt(OPT_CHUNKED), 0), 32);
-    if (linear_rows_kernel_takes(a.N, a.T)) {
+    if (linear_takes_rows_kernel(a.T, a.K, a.N)) {
         p.out16 = a.out16;
         return launch_linear_rows_bf16(p, a.N, a.T, st);
     }

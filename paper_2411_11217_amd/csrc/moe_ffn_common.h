@@ -164,7 +164,6 @@ __device__ __forceinline__ float silu_mul_bf16(float g, float u) {
 bool rows_kernel_takes(int rows_each);
 int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st);
 int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st);
-bool linear_rows_kernel_takes(int N, int T);
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st);
 
 inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const FfnArgs& a) {

@@ -294,18 +294,14 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
     return launch_rows<1, 8, 8, 1, 1, 4>(p, H, R, n_exp, st);
 }
 
-// Where the dense linear map takes it: one row tile, or as many blocks of 64 columns and 128 rows as run at once.  One weight
-// matrix alone has too few columns to fill the chip; us for the pre-attention task (norm and bf16 copy included), 256-row
-// blocks of moe_ffn_bf16.hip / this kernel, both with temporal loads: 4096 x 6144 (Mixtral-8x7B shape) 1 token 31 / 23, 60: 39 /
-// 24, 100: 38 / 33, 256: 54 / 38; 2048 x 3072 300 tokens 36 / 24, 640: 39 / 27; 6144 x 9216 50 tokens 53 / 36, 128: 53 / 49.
-// Blocks of 32 columns as long as they make one round of blocks, else of 64 (with non-temporal loads: 4096 x 6144 60 tokens
-// 27 / 30, 100: 39 / 42, but 200: 73 / 48; 6144 x 9216 50 tokens 60 / 42); the fewer columns, the more wavefronts along the
-// rows.  Temporal loads: one matrix fits the 256 MiB last-level cache, and a call that finds it there is that much
-// shorter (6144 x 9216, 128 tokens: 68 us with the hint, 48 without).
+// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here).  32 columns as long as they
+// make one round of blocks, else 64 (with non-temporal loads: 4096 x 6144 60 tokens 27 / 30, 100: 39 / 42, but 200: 73 / 48; 6144 x
+// 9216 50 tokens 60 / 42); the fewer columns, the more wavefronts along the rows.
+// Temporal loads, us without / with the non-temporal hint, weights where the call before left them (one matrix fits the 256 MiB
+// last-level cache) | weights from HBM: 4096 x 6144 64 tokens 17 / 21 | 21 / 22, 128: 26 / 34 | 30 / 36; 6144 x 9216 64 tokens 30 /
+// 35 | 38 / 37, 128: 40 / 59 | 58 / 60; 2048 x 3072 128 tokens 15 / - | 17 / 20.
 // Groups of wavefronts that split k instead were faster still with 65 .. 128 rows (4096 x 6144 100 tokens 33 against 39 with
 // the hint), but they change the order of the sums, which the O projection hands on to a rounding and the router.
-bool linear_rows_kernel_takes(int N, int T) { return T <= 128 || N / 64 * ((T + 127) / 128) <= kComputeUnits; }
-
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
     const bool few_columns = N / 32 * ((T + 127) / 128) <= kComputeUnits;
     if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8>(p, N, T, 1, st);

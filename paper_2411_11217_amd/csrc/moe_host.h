@@ -42,4 +42,22 @@ void copy_tile(char* page_tile, char* dense, int64_t ld, int esize, bool to_page
 int validate_linear(const moe_linear_shape* s);
 int64_t linear_pages(const moe_linear_shape& s);
 
+// Where the dense linear map takes the kernel for few rows (csrc/moe_ffn_rows_bf16.hip): as long as its blocks of 64 columns
+// and 128 rows make one round on the 256 compute units, and with a short k and few rows.
+//   One matrix alone has too few columns to fill the chip with 256-row blocks (moe_ffn_bf16.hip).  us, those blocks / this
+// kernel, weights where the call before left them | weights from HBM (copies that exceed the last-level cache in turn): 4096 x
+// 6144 (K x N) 1 token - | 45 / 15, 100: - | 47 / 30; 6144 x 9216 16 tokens 33 / 21 | 48 / 29, 100: 41 / 39 | 59 / 50;
+// 4096 x 16384 (one full round) 16 tokens 25 / 22 | 42 / 27, 64: 31 / 24 | 40 / 30, 128: 32 / 32 | 46 / 42; 8192 x 1024 600
+// tokens 75 / 47 | 76 / 50.
+//   Beyond one round a block's way through all of k is paid for twice: 4096 x 18432 16 tokens 26 / 33 | 38 / 39, 128: 33 / 51 | 48
+// / 73; 4096 x 32000 64 tokens 44 / 46 | 50 / 55, 100: 47 / 64 | 53 / 75; 4096 x 128256 128 tokens 224 / 304.
+//   A short way makes the other kernel's blocks (one per compute unit, set-up and tile search of 2 us) the longer ones again:
+// 1024 x 65536 32 tokens 28 / 25 | 33 / 29, 64: 31 / 30 | 36 / 36, 128: 34 / 36 | 39 / 50; 1024 x 18432 32 tokens 12 / 12 | 17 / 14;
+// 1536 x 18432 32 tokens 14 / 15 | 21 / 19, 1536 x 65536: 37 / 33 | 44 / 41; 2048 x 32768 32 tokens 24 / 23 | 28 / 27, but 2048 x 18432: 16
+// / 19 | 22 / 23.
+inline bool linear_takes_rows_kernel(int T, int K, int N) {
+    constexpr int64_t kComputeUnits = 256;           // MI355X
+    return (int64_t)(N / 64) * (((int64_t)T + 127) / 128) <= kComputeUnits || (K <= 1536 && T <= 32);
+}
+
 }  // namespace moe

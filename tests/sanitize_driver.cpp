@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "moe.h"
+#include "moe_host.h"
 #include "moe_tile_order.h"
 
 extern "C" {
@@ -275,8 +276,24 @@ static void tile_orders() {
     std::printf("tile order: %d random cases and 6 fixed ones ok\n", cases);
 }
 
+// Beyond one round of 256 blocks of 64 columns x 128 rows the linear map must not take the kernel for few rows (it was
+// 1.1 to 1.6 times the other kernel's time there), up to one round it must.
+static void linear_rule() {
+    using moe::linear_takes_rows_kernel;
+    for (int K : {1664, 2048, 4096, 16384})
+        for (int T : {1, 64, 65, 128}) {
+            CHECK(linear_takes_rows_kernel(T, K, 16384));
+            CHECK(linear_takes_rows_kernel(T, K, 128));
+            for (int N : {16512, 18432, 32000, 128256}) CHECK(!linear_takes_rows_kernel(T, K, N));
+        }
+    CHECK(linear_takes_rows_kernel(256, 4096, 8192) && !linear_takes_rows_kernel(257, 4096, 8192));
+    CHECK(linear_takes_rows_kernel(32, 1536, 65536) && !linear_takes_rows_kernel(33, 1536, 65536));
+    CHECK(!linear_takes_rows_kernel(2147483647, 128, 2147483520));
+}
+
 int main() {
     tile_orders();
+    linear_rule();
     // packer: tiles that fill their pages exactly, pages with padding at the end of a group, one tile per page
     packer_round_trip(MOE_DTYPE_F32, 128, 256, 3, 2 * 32768);
     packer_round_trip(MOE_DTYPE_F32, 256, 128, 2, 5 * 32768);

@@ -49,10 +49,11 @@ def test_linear_matches_the_oracle(T, K, N, page):
 
 
 @pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 96, 97, 128, 129, 300])
-@pytest.mark.parametrize("K,N", [(128, 128), (384, 640), (256, 9216)])
+@pytest.mark.parametrize("K,N", [(128, 128), (384, 640), (256, 9216), (1152, 16512)])
 def test_linear_with_few_rows(T, K, N):
     # row counts around the row-tile pairs and blocks; two, four and six k-steps; column tiles of
-    # 32 and of 64, one and several row tiles; the bf16 copy of the pre-attention task
+    # 32 and of 64, one and several row tiles; the bf16 copy of the pre-attention task; 16512 columns: the kernel with
+    # 256-row blocks from 33 rows on
     g = torch.Generator().manual_seed(T + K)
     x = torch.randn((T, K), generator=g)
     W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
