@@ -41,7 +41,7 @@ __device__ __forceinline__ void load8(const float* base, size_t elem, float (&v)
 // Top-k of lg[0 .. E) by descending value (the lower index keeps a tie) and the softmax over the selected values, for token
 // tok, by EP lanes of one wavefront (EP = experts padded to a power of two; lane `le` of the group holds expert le): k rounds
 // of a maximum over the lanes and a ballot for its first holder.  One lane per token took k * E steps of LDS latency
-// each: with 64 experts, 8 per token, 777 tokens the launch took 34 us, now 19.  A NaN is selected only when no free expert precedes it, as
+// each: with 64 experts, 8 per token, 777 tokens the launch took 34 us, now 17.  A NaN is selected only when no free expert precedes it, as
 // a scan that keeps the first and replaces it by what compares greater would do.  Every lane of the wavefront calls this; `live`: the token exists.
 template <int EP>
 __device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int tok, bool live, int32_t* __restrict__ ids,
@@ -88,7 +88,10 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
                                                          float* __restrict__ w, float* __restrict__ logits,
                                                          int T, int H, int E, int k) {
     constexpr int EP = NE * 16;
-    constexpr int UB = 4;                                    // units whose loads are in flight together
+    // Units whose loads are in flight together.  Beyond 32 experts two: with four a wavefront needs 193 registers and only one
+    // block fits a compute unit; 65536 tokens of 2048, 64 experts, 8 per token: 251 us with four, 156 with two, 777 tokens 17
+    // either way; 65536 tokens, 33 experts, 5 per token: 172 and 105.
+    constexpr int UB = NE <= 2 ? 4 : 2;
     __shared__ float s_part[NW][16][EP];
     __shared__ float s_logit[16][EP];
     const int lane = threadIdx.x & 63;

@@ -194,6 +194,24 @@ def test_pipeline_pool_size_and_argument_errors_without_gpu():
     assert lib.moe_pipeline_destroy(None) == B.ERR_INVALID_ARG
 
 
+def test_router_blocks_for_many_experts_share_a_compute_unit():
+    """The bf16 router is bound by loads in flight: beyond 32 experts its blocks have eight wavefronts, and two of them must fit
+    the 512 registers of each SIMD (at most 128 per wavefront).  Read from the compiler's resource remarks."""
+    import shutil
+    import subprocess
+    from paper_2411_11217_amd import build as hip_build
+    hipcc = os.environ.get("HIPCC", "hipcc")
+    if not shutil.which(hipcc):
+        pytest.skip("no hipcc")
+    r = subprocess.run([hipcc] + hip_build.FLAGS + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                                                     os.path.join(hip_build.CSRC, "moe_route.hip"), "-o", os.devnull],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    kernels = re.findall(r"Function Name: (\S+).*?Occupancy \[waves/SIMD\]: (\d+)", r.stderr, re.S)
+    waves = {name: int(n) for name, n in kernels if "route_mfma_kernelILi4E" in name}
+    assert len(waves) == 1 and min(waves.values()) >= 4, kernels
+
+
 def test_host_packer_and_oracle_under_the_host_sanitizers(tmp_path):
     """The host-only translation unit of the library (csrc/moe_host.cpp: shape checks, page geometry, packer) and the C
     oracle, built with the host compiler's address and undefined-behaviour sanitizers and run on exact-size heap
