@@ -27,10 +27,9 @@ constexpr int kComputeUnits = 256;                   // MI355X
 constexpr int kHalfTileBytes = 128 * 64;             // 32 k of a page tile
 constexpr int kTileBytes = 2 * kHalfTileBytes;
 
-// Block -> (expert, row tile, column tile): the tiles are numbered expert by expert, inside an expert in runs of eight column
-// tiles (block b runs on XCD b % 8), the row tiles of a run one after the other, so that those of a column tile meet
-// in one L2.  One expert per lane, a prefix sum and a ballot; every wavefront does it on its own.  The order of
-// locate_tile costs a few microseconds of integer arithmetic per block, which these short blocks would feel.
+// Block -> (expert, row tile, column tile), in the order of rows_tile_in_expert (moe_tile_order.h).  One expert per lane, a
+// prefix sum and a ballot; every wavefront does it on its own.  The order of locate_tile costs a few microseconds of
+// integer arithmetic per block, which these short blocks would feel.
 struct RowsTile {
     int e, nt, row0, rows_here;
     int mtiles;               // row tiles of the expert
@@ -64,12 +63,10 @@ __device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& 
         t.e = 0;
         if (id >= m * p.NT) return false;
     }
-    const int run = rel / (8 * m), in_run = rel - run * 8 * m;
-    const int width = min(8, p.NT - run * 8);        // column tiles of this run
-    const int mt = in_run / width;
-    t.nt = run * 8 + in_run - mt * width;
-    t.row0 = seg + mt * BM;
-    t.rows_here = min(BM, rows - mt * BM);
+    const TileInExpert te = rows_tile_in_expert(rel, m, p.NT);
+    t.nt = te.nt;
+    t.row0 = seg + te.mt * BM;
+    t.rows_here = min(BM, rows - te.mt * BM);
     t.mtiles = m;
     return true;
 }
@@ -264,7 +261,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
 template <int MODE, int RT, int CW, int FC, int RG, int D>
 int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
     p.NT = cols / (16 * CW * FC);
-    hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D>), dim3(p.NT * (R / (16 * RT) + n_exp)), dim3(64 * CW * RG), 0, st, p);
+    hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D>), dim3(rows_grid(p.NT, R, 16 * RT, n_exp)), dim3(64 * CW * RG), 0, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }

@@ -213,4 +213,20 @@ inline int gemm_grid(int NT, int R, int BM, int n_experts, int chunked) {
     return (int)(8 * (plain_groups * M + slack * n_experts));
 }
 
+// The order of the kernel for few rows per expert (moe_ffn_rows_bf16.hip).  Its tiles are numbered expert by expert, inside an
+// expert of m row tiles in runs of eight column tiles, the row tiles of a run one after the other.  Block b runs on XCD b % 8:
+// in a run of eight the row tiles of a column tile meet in one L2, in a last run of fewer columns they do not.
+// -> row tile and column tile of tile number rel (0 <= rel < m * NT) of the expert.
+MOE_HD TileInExpert rows_tile_in_expert(int rel, int m, int NT) {
+    const int run = rel / (8 * m), in_run = rel - run * 8 * m;
+    const int left = NT - run * 8, width = left < 8 ? left : 8;       // column tiles of this run
+    TileInExpert t;
+    t.mt = in_run / width;
+    t.nt = run * 8 + in_run - t.mt * width;
+    return t;
+}
+
+// its grid: the experts have at most R / BM + n_experts row tiles of BM rows
+inline int rows_grid(int NT, int R, int BM, int n_experts) { return NT * (R / BM + n_experts); }
+
 }  // namespace moe

@@ -273,7 +273,39 @@ static void tile_orders() {
     tile_order({1024, 1024, 1024, 1024}, 16, 256, 32, 32, 8, true);
     tile_order({4096}, 24, 256, 32, 32, 8, true);
     tile_order({300, 200, 100}, 4, 64, 0, 32, 8, false);                 // the f32 kernel's row tile
+    // the float32 kernels: row tiles of 32 rows, none of them tall, column tiles of 64 or 16 features or columns
+    std::uniform_int_distribution<int> any_nt(1, 1000), rows32(0, 300), many32(0, 3000);
+    for (int rep = 0; rep < 200; ++rep) {
+        std::vector<int> counts((size_t)(1 + (int)(g_rng() % 17)));
+        for (int& c : counts) c = pick(g_rng) < 2 ? 0 : pick(g_rng) < 8 ? rows32(g_rng) : many32(g_rng);
+        tile_order(counts, rep % 4 == 0 ? 1 + (int)(g_rng() % 24) : any_nt(g_rng), 32, 0, rep % 2 ? 32 : 0, rep % 5 ? 8 : 1, false, rep % 3 != 0);
+        ++cases;
+    }
     std::printf("tile order: %d random cases and 6 fixed ones ok\n", cases);
+}
+
+// The order of the kernel for few rows per expert: every (expert, row tile, column tile) exactly once, inside the grid.
+static void rows_order() {
+    using namespace moe;
+    std::uniform_int_distribution<int> few(0, 100), many(0, 700), any_nt(1, 300);
+    for (int rep = 0; rep < 400; ++rep) {
+        const int BM = rep % 2 ? 64 : 128, NT = rep % 5 == 0 ? 1 + rep % 9 : any_nt(g_rng), E = 1 + (int)(g_rng() % 17);
+        int R = 0, total = 0;
+        for (int e = 0; e < E; ++e) {
+            const int c = g_rng() % 5 == 0 ? 0 : g_rng() % 4 ? few(g_rng) : many(g_rng), m = (c + BM - 1) / BM;
+            std::vector<char> seen((size_t)m * (size_t)NT, 0);
+            for (int rel = 0; rel < m * NT; ++rel) {
+                const TileInExpert t = rows_tile_in_expert(rel, m, NT);
+                CHECK(t.mt >= 0 && t.mt < m && t.nt >= 0 && t.nt < NT);
+                char& flag = seen[(size_t)t.mt * (size_t)NT + (size_t)t.nt];
+                CHECK(flag == 0);
+                flag = 1;
+            }
+            R += c;
+            total += m * NT;
+        }
+        CHECK(rows_grid(NT, R, BM, E) >= total);
+    }
 }
 
 // Beyond one round of 256 blocks of 64 columns x 128 rows the linear map must not take the kernel for few rows (it was
@@ -293,6 +325,7 @@ static void linear_rule() {
 
 int main() {
     tile_orders();
+    rows_order();
     linear_rule();
     // packer: tiles that fill their pages exactly, pages with padding at the end of a group, one tile per page
     packer_round_trip(MOE_DTYPE_F32, 128, 256, 3, 2 * 32768);

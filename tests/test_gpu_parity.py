@@ -20,6 +20,7 @@ MED = {
     "bf16_two_experts_ragged": MoEConfig("m1", "bf16", T=700, H=256, F=384, E=2, k=1, page_bytes=64 * 1024, seed=21),
     "bf16_top2_of_4": MoEConfig("m2", "bf16", T=333, H=384, F=512, E=4, k=2, page_bytes=48 * 1024, seed=22),
     "bf16_top4_of_16": MoEConfig("m3", "bf16", T=200, H=256, F=256, E=16, k=4, page_bytes=32 * 1024, seed=23),
+    "bf16_top4_of_16_more_rows": MoEConfig("m6", "bf16", T=420, H=256, F=256, E=16, k=4, page_bytes=32 * 1024, seed=26),   # beyond the kernel for few rows
     "f32_top2_of_5": MoEConfig("m4", "f32", T=150, H=128, F=256, E=5, k=2, page_bytes=96 * 1024, seed=24),
     "bf16_skewed": MoEConfig("m5", "bf16", T=600, H=256, F=256, E=8, k=2, page_bytes=64 * 1024, seed=25,
                              bias=((0, 3.0), (7, -3.0))),
@@ -97,7 +98,6 @@ def run_layer(case: Case, ref=None):
 
 @pytest.mark.parametrize("down_cols", [0, 1, 2])
 def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
-    # (the gate/up launch takes the same choice of column tiles as the down launch: by grid size, narrow, wide)
     """Segments of 1 .. 300 rows, one per expert, on both sides of every threshold of the bf16 kernel's row-tile
     variants (32, 64, 128, 192 rows, the 256-row tile boundary, tiles that take a remainder of up to 32 rows along) and an
     empty one, against the oracle row by row; with the tall tiles switched off every bit stays the same."""
@@ -111,24 +111,20 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
     x_bits = v["x"]                                     # [T, H] in the oracle's storage form; k = 1: rows are tokens
     h_ref, o_ref = oracle.expert_ffn(x_bits, offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
     M.set_option("down_cols", down_cols)
-    M.set_option("gate_cols", down_cols)
     try:
         status = torch.zeros(4, dtype=torch.int32, device="cuda")
         h, out = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, status=status)
         torch.cuda.synchronize()
     finally:
         M.set_option("down_cols", 0)
-        M.set_option("gate_cols", 0)
     assert_status_clean(status.cpu().tolist())
     M.set_option("down_cols", down_cols)
-    M.set_option("gate_cols", down_cols)
     M.set_option("tall_tiles", 0)
     try:
         h0, out0 = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, status=status)
         torch.cuda.synchronize()
     finally:
         M.set_option("down_cols", 0)
-        M.set_option("gate_cols", 0)
         M.set_option("tall_tiles", 1)
     assert torch.equal(h0, h) and torch.equal(out0, out)
     for e, c in enumerate(counts):
@@ -306,7 +302,7 @@ def test_reduced_cases_stagewise_and_layer(name, down_cols):
 @pytest.mark.parametrize("name", ["bf16_top2_of_4", "bf16_two_experts_ragged", "f32_top2_of_5"])
 @pytest.mark.parametrize("option,default,other", [("xcd_remap", 1, 0), ("fuse_gather", 1, 0), ("half_tiles", 1, 0), ("tall_tiles", 1, 0),
                                                   ("down_cols", 0, 1), ("down_cols", 0, 2), ("chunked", 32, 0), ("chunked", 32, 8),
-                                                  ("tall_first", 1, 0), ("balance", 1, 0), ("gate_cols", 0, 1), ("gate_cols", 0, 2)])
+                                                  ("tall_first", 1, 0), ("balance", 1, 0)])
 def test_kernel_options_give_identical_bits(option, default, other, name):
     # which block computes which tile, the tile variant, and who gathers the rows of x do not change any arithmetic
     case = Case(MED[name])
@@ -434,8 +430,12 @@ def test_identical_experts_and_single_expert_invariants():
     assert ws2.view("counts").cpu().numpy().sum() == cfg.T * cfg.k
 
 
-def test_streamed_pages_match_resident_pages_bitwise():
-    cfg = scaled(MED["bf16_top4_of_16"], T=300)
+@pytest.mark.parametrize("name,T", [("bf16_top4_of_16", 300),              # 75 rows per expert: the kernel for few rows
+                                    ("bf16_top4_of_16_more_rows", 420),    # 105: the 256-row blocks
+                                    ("f32_top2_of_5", 150),                # 60: the float32 kernel that splits the columns
+                                    ("f32_top2_of_5", 40)])                # 16: the one that splits k
+def test_streamed_pages_match_resident_pages_bitwise(name, T):
+    cfg = scaled(MED[name], T=T)
     res = Case(cfg)
     y_res, ws_res = M.moe_layer(res.shape, res.x, res.Wr, res.pw.table_dev, res.pw.pages_dev)
     torch.cuda.synchronize()
@@ -444,10 +444,14 @@ def test_streamed_pages_match_resident_pages_bitwise():
     st = M.Streamer(res.shape, host.pages_host, host.table_host)
     try:
         for _ in range(2):          # the second call reuses slots that the first one filled
-            y_st, ws_st = M.moe_layer_streamed(st, res.x, res.Wr)
+            ws_st = M.Workspace(res.shape)
+            ws_st.buf.fill_(0xFF)                                             # NaN everywhere
+            y_st, _ = M.moe_layer_streamed(st, res.x, res.Wr, workspace=ws_st)
             torch.cuda.synchronize()
             assert_status_clean(ws_st.view("status").cpu().tolist())
             assert torch.equal(y_st, y_res)
+            if cfg.dtype == "f32":                                            # every expert's launch writes its rows of x_perm
+                assert torch.equal(ws_st.view("x_perm"), res.x[ws_st.view("row_src").long() // cfg.k])
         x_perm = res.x[ws_res.view("row_src").long() // cfg.k].contiguous()   # moe_layer gathered inside its GEMM
         h, out = M.moe_expert_ffn_streamed(st, x_perm, ws_res.view("offsets"), row_w=ws_res.view("row_w"))
         torch.cuda.synchronize()
@@ -455,14 +459,15 @@ def test_streamed_pages_match_resident_pages_bitwise():
     finally:
         st.close()
     ref = res.oracle_layer()
-    assert_close(y_res.cpu().numpy(), ref["y"], "bf16", "streamed case vs oracle")
+    assert_close(y_res.cpu().numpy(), ref["y"], cfg.dtype, "streamed case vs oracle")
 
 
 @pytest.mark.parametrize("resident", ["none", "some", "all"])
-def test_multi_layer_weight_paging_matches_resident_layers_bitwise(resident):
+@pytest.mark.parametrize("tokens", [96, 200])              # 48 and 100 rows per expert: either bf16 kernel
+def test_multi_layer_weight_paging_matches_resident_layers_bitwise(resident, tokens):
     """Three layers, four micro-batches, two passes (the second starts with the first layer already
     prefetched): every output equals moe_layer on that layer's resident pages, bit for bit."""
-    base = scaled(MED["bf16_top2_of_4"], T=96)
+    base = scaled(MED["bf16_top2_of_4"], T=tokens)
     s = shape_of(base)
     gu, d = M.pages_required(s)
     ppe = gu + d

@@ -16,7 +16,7 @@ import torch
 import oracle
 import paper_2411_11217_amd as M
 from moe_workloads import CONFIGS, prompt_lengths, scaled
-from util import Case, assert_close, assert_h_close, check_permutation_valid, compare_routing, say, assert_status_clean
+from util import Case, assert_close, assert_h_close, check_permutation_valid, compare_routing, say, shape_of, assert_status_clean
 
 pytestmark = pytest.mark.gpu
 
@@ -195,6 +195,28 @@ def test_mixtral_8x7b_around_the_ridge(T):
     M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, workspace=ws, y=y)
     torch.cuda.synchronize()
     check_full(case, y, ws, cfg.name)
+
+
+@pytest.fixture(scope="module")
+def mixtral_8x7b_t700():
+    return Case(scaled(CONFIGS["c3_mixtral8x7b_t4096"], name="few_rows", T=700))
+
+
+@pytest.mark.parametrize("T", [4, 100, 160, 400, 580, 700])
+def test_mixtral_8x7b_with_one_row_tile_per_expert(mixtral_8x7b_t700, T):
+    # the weights exceed the last-level cache and the experts have one row tile each: the kernels' loops with non-temporal
+    # weight loads.  1, 25 and 40 rows per expert on average: the blocks of 64 rows of the kernel for few rows, with one and
+    # two pairs of row tiles; 100, 145 and 175: the short loops of the 256-row blocks with four, five and six row tiles
+    import copy
+    case = copy.copy(mixtral_8x7b_t700)
+    case.cfg = scaled(case.cfg, name=f"few_rows_t{T}", T=T)
+    case.shape = shape_of(case.cfg)
+    case.x = case.x[:T].contiguous()
+    case.view = dict(case.view, x=case.view["x"][:T])
+    ws, y = nan_filled_outputs(case)
+    M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, workspace=ws, y=y)
+    torch.cuda.synchronize()
+    check_full(case, y, ws, case.cfg.name)
 
 
 def test_mixtral_8x7b_prefill_micro_batch():

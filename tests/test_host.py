@@ -172,6 +172,9 @@ def test_null_and_small_workspace_errors_without_gpu():
     assert lib.moe_route(ctypes.byref(s0), None, None, None, None, None, None, None) == 0   # T == 0: nothing to do
     assert lib.moe_set_option(b"no_such_option", 1) == B.ERR_INVALID_ARG
     assert M.get_option("xcd_remap") in (0, 1)
+    M.set_option("gate_cols", 1)                       # accepted although it has no effect any more
+    assert M.get_option("gate_cols") == 1
+    M.set_option("gate_cols", 0)
 
 
 def test_pipeline_pool_size_and_argument_errors_without_gpu():
