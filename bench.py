@@ -26,7 +26,7 @@ PEAK_CLOCK_MHZ = 2400.0       # the clock the published peaks are quoted at
 
 # HBM traffic per launch of the gate/up GEMM on the default workload, in bytes, from the
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised under profiles/ (None: not measured).
-MEASURED_TRAFFIC = {"c3_mixtral8x7b_t4096": 3.416e9, "c4_mixtral8x22b_t8192_skew": 2.112e10}
+MEASURED_TRAFFIC = {"c3_mixtral8x7b_t4096": 3.416e9, "c2_mixtral8x7b_t256": 1.914e9, "c4_mixtral8x22b_t8192_skew": 2.112e10}
 
 
 def cpu_model() -> str:
@@ -200,16 +200,20 @@ def main():
     if stages:
         t_gu = stages["gemm_gate_up"] * 1e-3
         achieved = flops_gu / t_gu / 1e12
-        kernel = "ffn_gemm_bf16<0>" if cfg.R // cfg.E > 80 else "ffn_rows_bf16<0>"      # the library's own line between the two
+        each = cfg.R // cfg.E                              # the library's own lines between its kernels
+        kernel = ("ffn_gemm_bf16<0>" if each > 80 else "ffn_rows_bf16<0>") if cfg.dtype == "bf16" else \
+            "ffn_rows_f32<0>" if each > 32 else "ffn_few_rows_f32<0>"
         roofline = {"bound": "mfma", "kernel": kernel + " (gate/up expert GEMM + SwiGLU epilogue)",
                     "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": MEASURED_TRAFFIC.get(args.config),
                     "avg_launch_ms": round(stages["gemm_gate_up"], 4), "launches_timed": n_prof}
         # Few rows per expert (at most half a row tile on average): the launch streams the weights once and HBM is its
-        # roof.  Algorithmic bytes: both weight matrices of every expert, x, and h written.
+        # roof.  Algorithmic bytes: both weight matrices of every expert, x, and h written (f32: and the permuted rows).
         esize = 2 if cfg.dtype == "bf16" else 4
         if cfg.R <= 128 * cfg.E:
             gu_bytes = 2.0 * cfg.E * cfg.H * cfg.F * esize + cfg.T * cfg.H * esize + cfg.R * cfg.F * esize
+            if cfg.dtype == "f32" and M.get_option("fuse_gather"):
+                gu_bytes += cfg.R * cfg.H * esize
             gbs = gu_bytes / t_gu / 1e9
             roofline.update({"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                              "frac": round(gbs / PEAK_HBM_GBS, 4), "mfma_tflops": round(achieved, 2)})
@@ -226,8 +230,8 @@ def main():
         R, H, F, T, E, b = cfg.R, cfg.H, cfg.F, cfg.T, cfg.E, (2 if cfg.dtype == "bf16" else 4)
         alg_bytes = {   # algorithmic HBM bytes of the copy-like stages
             "route": T * H * b + E * H * b + 8 * R,
-            # index arrays only when the gate/up GEMM gathers the rows of x itself (bf16, the default)
-            "permute": 12 * R + (0 if cfg.dtype == "bf16" and M.get_option("fuse_gather") else T * H * b + R * H * b),
+            # index arrays only when the gate/up GEMM gathers the rows of x itself (the default)
+            "permute": 12 * R + (0 if M.get_option("fuse_gather") else T * H * b + R * H * b),
             "combine": 4 * R * H + 4 * R + 4 * T * H,
         }
         extra = {
@@ -438,6 +442,13 @@ def rate_probes(args, M):
         rates[blocks] = round(buf.numel() / t / 1e12, 3)
     out["hbm_read_tbs"] = max(rates.values())
     out["hbm_read_tbs_by_blocks"] = rates
+    # the same with the non-temporal hint, as the weight loads of launches with few rows per expert carry it
+    rates = {}
+    for blocks in (1024, 2048, 4096):
+        t = timed(lambda: M.probe_stream_read(buf, blocks=blocks, non_temporal=True), 10)
+        rates[blocks] = round(buf.numel() / t / 1e12, 3)
+    out["hbm_read_nt_tbs"] = max(rates.values())
+    out["hbm_read_nt_tbs_by_blocks"] = rates
     del buf
     # matrix rate: a dense bf16 product of 2048 x 8192 x 32768 through the paged linear map (the down-projection kernel on
     # full, equal tiles: eight row tiles, 128 column tiles, a reduction twice as long as the layer's gate/up product)

@@ -161,7 +161,10 @@ int moe_permute(const moe_shape* s, const int32_t* topk_ids, const float* topk_w
  * out: device float[R][H]; status: device int32[4] or NULL (see moe_workspace_layout.status).
  * The kernels only ever OR error bits into status[0] and overwrite status[2], status[3];
  * they never clear: the CALLER zeroes the four words before the call (moe_layer does that
- * for its own status words, in one of its kernels). */
+ * for its own status words, in one of its kernels).
+ * A row's h and out do not depend on how many rows its call has with bf16 data: every sum is one chain along the
+ * reduction.  With f32 data they do in their last bits: up to 32 rows per expert on average (T * k / E) the
+ * reduction is cut into four partial sums.  Streamed and resident calls of one shape give the same bits. */
 int moe_expert_ffn(const moe_shape* s, const void* x_perm, const int32_t* offsets,
                    const int32_t* page_table, const void* page_pool, int64_t pool_pages,
                    const float* row_w, void* h_ws, float* out, int32_t* status, void* stream);
@@ -370,8 +373,10 @@ int moe_get_option(const char* name, int* value);
  * with profiled rates of the hardware): moe_probe_stream_read launches `blocks` blocks that together read
  * `bytes` bytes (a multiple of 16, 16-byte aligned) from device memory at src once and discard them; timing the
  * launch gives the read rate device memory sustains for a kernel of nothing but coalesced loads.  sink: device
- * int32 or NULL (never written for real data).  Enqueue only, no synchronisation. */
+ * int32 or NULL (never written for real data).  Enqueue only, no synchronisation.  The _nt variant's loads carry the
+ * non-temporal hint, as the weight loads of launches with few rows per expert do. */
 int moe_probe_stream_read(const void* src, size_t bytes, int32_t blocks, int32_t* sink, void* stream);
+int moe_probe_stream_read_nt(const void* src, size_t bytes, int32_t blocks, int32_t* sink, void* stream);
 
 /* ------------------------------------------------------------------ stage timing
  * For measurements only.  While option "profile" is 1, moe_layer records HIP

@@ -91,6 +91,7 @@ _SIGNATURES = {
     "moe_get_option": (ctypes.c_int, [ctypes.c_char_p, _vp]),
     "moe_profile_read": (ctypes.c_int, [_vp, _vp]),
     "moe_probe_stream_read": (ctypes.c_int, [_vp, _sz, ctypes.c_int32, _vp, _vp]),
+    "moe_probe_stream_read_nt": (ctypes.c_int, [_vp, _sz, ctypes.c_int32, _vp, _vp]),
 }
 EXPORTED_SYMBOLS = tuple(_SIGNATURES)
 
@@ -354,10 +355,11 @@ def moe_layer(s: MoEShape, x, Wr, page_table, page_pool, bias=None, workspace: O
     return y, workspace
 
 
-def probe_stream_read(buf: torch.Tensor, blocks: int = 2048, stream=None):
+def probe_stream_read(buf: torch.Tensor, blocks: int = 2048, stream=None, non_temporal: bool = False):
     """Enqueues one launch that reads all of the device tensor buf once (measurement helper)."""
     nbytes = buf.numel() * buf.element_size()
-    _check(_lib().moe_probe_stream_read(buf.data_ptr(), nbytes, int(blocks), None, _stream(stream)), "moe_probe_stream_read")
+    fn = _lib().moe_probe_stream_read_nt if non_temporal else _lib().moe_probe_stream_read
+    _check(fn(buf.data_ptr(), nbytes, int(blocks), None, _stream(stream)), "moe_probe_stream_read")
 
 
 STATIC_SCRATCH_BYTES = 32 << 20

@@ -2,8 +2,8 @@
 // post-attention task is the O projection followed by the MoE FFN, the pre-attention task a
 // normalisation followed by the QKV projection.  Their weights are paged like the experts':
 //
-//   moe_linear       y = x W^T over paged W, on the matrix cores (the down-projection kernel of
-//                    the expert FFN with a single row segment)
+//   moe_linear       y = x W^T over paged W, on the matrix cores (a down-projection kernel of the
+//                    expert FFN with a single row segment)
 //   moe_add_rmsnorm  s = hidden + delta (the residual stream, f32);  x = bf16(s / rms(s) * gamma)
 //   moe_cast_bf16    f32 -> bf16, round to nearest even
 //   moe_post_attention / moe_pre_attention   the two tasks as sequences of the above and moe_layer

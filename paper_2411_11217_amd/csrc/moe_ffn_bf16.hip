@@ -80,17 +80,18 @@ constexpr int BM = 256;
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kComputeUnits = 256;           // MI355X
-// Up to this many rows per expert on average the weight loads are non-temporal: an expert is one row tile then, every
-// weight is read once, and a line that will not be read again should not push others out.  A kernel of nothing but
-// loads over 2 GiB reads 7.1 TB/s with the hint and 5.9 - 6.4 without, whatever the piece per block.  Layer of the
-// Mixtral-8x7B shape, without / with, us: 16 tokens 517 / 471, 64: 506 / 466, 256: 548 / 505, 400: 568 / 537,
-// 1000: 760 / 709, 1024: 769 / 733; with several row tiles per expert the second one finds less in the L2: 1150 tokens
-// 1015 / 1038, 1536: 1063 / 1125, 4096: 2145 / 2190.  On 64 experts (2048 x 1024) the line lies at the same
-// place: 250 rows per expert 522 / 504, 375 rows 626 / 662.  And only where the experts' weights exceed the 256 MiB
-// last-level cache: smaller ones may still be there from the call before, and the hint keeps them out (8 experts of
-// 1024 x 2816, 138 MB, 100 tokens: 53 us without, 56 with).  An expert that has several row tiles all the same reads without
-// the hint: its tiles share the weights through the L2 (8 experts of 2048 x 4096, 400 tokens, 40 % of them on one
-// expert: layer 129 us with the hint for all, 106 this way).
+// Up to this many rows per expert on average the weight loads are non-temporal, here and in moe_ffn_rows_bf16.hip: an expert
+// is one row tile then, every weight is read once, and a line that will not be read again should not push others out.  A
+// kernel of nothing but loads reads 7.1 TB/s with the hint and 6.2 without (moe_probe_stream_read_nt).  Layer without / with,
+// us: Mixtral-8x7B shape 16 tokens 481 / 434, 64: 487 / 444, 256: 520 / 491 (these in the other kernel), 400: 544 / 529, 700:
+// 635 / 609, 1000: 735 / 700, 1024: 748 / 717; 64 experts of 2048 x 1024 100 tokens 172 / 158, 777: 222 / 203, 2000 (250 rows per
+// expert): 469 / 445; DBRX shape 100 tokens 1090 / 991, 400: 1206 / 1139, 900: 1474 / 1427.  With more rows hardly an expert has
+// one row tile: 1536 tokens of the Mixtral-8x7B shape 1076 / 1075.  An expert that has several row tiles all the same reads
+// without the hint: its tiles share the weights through the L2 (8 experts of 2048 x 4096, 400 tokens, 40 % of them on one
+// expert: 129 us with the hint for all, 106 this way).
+// And only where the experts' weights exceed the 256 MiB last-level cache: smaller ones may still be there from the call
+// before, and the hint keeps them out (8 experts of 1024 x 2816, 138 MB, 100 tokens: 53 without, 56 with).  Where other
+// weights pass in between it is the other way round (ten such layers in turn, 8 tokens 49 / 47, 100: 55 / 53, 400: 70 / 69).
 constexpr int kStreamRows = 256;
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
@@ -488,12 +489,12 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     //            fragments of k and the activation fragments of row tiles 0..3; issues the activation loads;
     //   group 2: row tiles 0..3 of half-step k; fetches the activation fragments of row tiles 4..7;
     //            issues the weight loads.
-    // Short tiles.  At most 128 rows: wavefront (wm, wn) owns rows wm*64 .. +63, four row tiles; the two
+    // Short tiles.  65 .. 128 rows: wavefront (wm, wn) owns rows wm*64 .. +63, four row tiles; the two
     // fragment sets alternate between half-steps, and the groups split the columns instead:
     //   group 1: the second half of the column fragments of half-step k-1; fetches all fragments of k;
-    //            issues the activation loads (even half-steps only: rows 128..255 are not loaded at all);
+    //            issues the activation loads (even half-steps only: rows beyond the tile's last 32 are not loaded at all);
     //   group 2: the first half of the column fragments of half-step k; issues the weight loads.
-    // 129 .. 192 rows: the same with five or six row tiles per wavefront.
+    // 129 .. 192 rows: the same with five or six row tiles per wavefront (rows wm*80 .. or wm*96 ..).
     // At most 64 rows: the same with the wavefronts wm = 1 taking part in the loads only; at most 32
     // rows: two row tiles instead of four.  Measured in cycles of a full tile: 0.6 for the first, and
     // the launches of the Mixtral-8x7B-shaped workload (whose short tiles have 4 to 31 rows) got 2-3 %
@@ -876,8 +877,8 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     return launch_stages<1, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
 }
 
-// y = x W^T for a dense weight matrix held as pages: the down-projection kernel with one "expert"
-// that owns all T rows and no row weight.
+// y = x W^T for a dense weight matrix held as pages: one of the two down-projection kernels (linear_takes_rows_kernel in
+// moe_host.h) with one "expert" that owns all T rows and no row weight.
 int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     GemmParams p{};
     p.A = (const char*)a.x;

@@ -10,14 +10,17 @@
 //   ffn_rows_f32: a block owns 32 rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the
 //     columns and share the activations, which go through LDS (two stages of one 64-wide k-step; the registers hold the
 //     next one), one barrier per k-step.  17 KiB of LDS and few registers: four and more blocks share a compute unit, hide
-//     each other's latency and keep the end of a launch short (a k-step is 1024 MFMA cycles per wavefront in MODE 0).
+//     each other's latency and keep the end of a launch short (a k-step is 64 MFMAs of 32 cycles per wavefront in MODE 0).
 //     Blocks of 64 rows read the weights half as often and were slower up to thousands of tokens, 32 / 64 rows, us for the
 //     layer of 1024 x 2816 (8 experts, 2 per token): 260 tokens 175 / 216, 500: 241 / 287, 1000: 396 / 424, 2000: 685 / 734,
 //     8000: 2441 / 2396 (113 / 116 TFLOP/s for the layer).  The MFMAs of a row tile run in a row: with those of the two row
 //     tiles alternating (longer distance between two on one accumulator) 1000 tokens took 427.
 //   ffn_few_rows_f32: at most 32 rows x 16 columns (MODE 0: 16 features), the wavefronts split k instead: every fourth
 //     k-step each, activations straight from memory, no barrier until the four partial tiles are added through LDS in a
-//     fixed order.  Four times the blocks, each a quarter as long: with a few rows per expert the launch is latency.
+//     fixed order.  Four times the blocks, each a quarter as long: with a few rows per expert the launch is latency.  The order
+//     of the sums differs from ffn_rows_f32's, so a row's last bits depend on the rows per expert of the call.  The same four
+//     partial sums in ffn_rows_f32 would make them equal and cost it 4 - 10 % (in registers three instead of four wavefronts fit a
+//     SIMD, in LDS as much: 1024 x 2816, 700 tokens 282 / 301, 4000 tokens 1248 / 1361 us for the layer).
 //
 // Against one kernel with 64-row x 256-column blocks and both operands staged through LDS behind a barrier each way: 256 x
 // 512, 64 tokens: both launches 94 -> 16 us, the layer 116 -> 30 us; 1024 x 2816, 700 tokens: 782 -> 270 us, 812 -> 296 us.

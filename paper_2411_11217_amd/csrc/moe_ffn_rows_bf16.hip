@@ -273,7 +273,13 @@ int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
 // Mixtral-8x7B shape (2 of 8 experts) 1 token 196 / 165, 4: 364 / 355, 16: 469 / 455, 64: 477 / 466, 150: 485 / 478, 256 (64
 // rows each): 522 / 511, 288: 532 / 520, 400 (100 rows): 552 / 560; 64 experts of 2048 x 1024, 8 per token, 20 tokens 192 /
 // 183, 400: 241 / 235, 600 (75 rows): 252 / 247, 777 (97 rows): 259 / 262; DBRX shape 120 tokens 1089 / 1036, 250: 1129 / 1096.
-// What is left is the weights' way from HBM: 6.3 - 6.5 TB/s in the gate/up launch, whatever the depth and the block.
+// What is left is the weights' way from HBM: with 4, 36 and 256 tokens of the Mixtral-8x7B shape 6.5, 6.7 and 5.8 TB/s in the
+// gate/up launch, 6.2, 6.6 and 5.9 in the down launch, whatever the depth and the block.
+// The average is all the host knows.  An expert with more rows than a block reads its weights once per row tile, 1.1 to 2.3 times
+// over the fabric.  Skewed routing (40 % of the rows on one expert, or one expert with every token) is still 2 - 25 % faster this
+// way; with every token on the same k experts two of the shapes lose, all other experts being empty: DBRX shape 80 tokens 395 /
+// 439, 130: 452 / 534, 176: 470 / 563, 256: 521 / 539, 300: 674 / 649; Mixtral-8x22B shape 130 tokens 365 / 465, 200 and more: within 4 %
+// (8x7B shape 130 tokens 284 / 265, 300: 382 / 320).
 constexpr int kRowsKernelMax = 80;
 // Up to here 64-row blocks with half the columns; 45 .. 72 rows need two of them per expert for some experts, and the second
 // one reads the weights again (176 tokens of the Mixtral-8x7B shape, 44 rows: 489 against 503 with 128-row blocks).

@@ -520,3 +520,23 @@ def test_layer_can_be_captured_in_a_hip_graph_and_replayed():
             g.replay()
             st.synchronize()
             assert torch.equal(y, want), rep
+
+
+@pytest.mark.parametrize("non_temporal", [False, True])
+@pytest.mark.parametrize("n16,blocks", [(1, 1), (1, 7), (1023, 1), (1025, 1), (4099, 3), (100000, 64)])
+def test_stream_probe_reads_every_word_once(n16, blocks, non_temporal):
+    # the probe folds what it reads into one word per lane and reports a single value: put it at the ends and around the unrolled stretch
+    lib = M.binding._lib()
+    fn = lib.moe_probe_stream_read_nt if non_temporal else lib.moe_probe_stream_read
+    buf = torch.zeros(n16 * 4, dtype=torch.int32, device="cuda")
+    sink = torch.zeros(1, dtype=torch.int32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    for at in sorted({0, n16 // 2, n16 - 1, min(1024, n16 - 1)}):
+        buf.zero_()
+        sink.zero_()
+        assert fn(buf.data_ptr(), n16 * 16, blocks, sink.data_ptr(), st) == 0
+        assert sink.item() == 0
+        buf[at * 4 + at % 4] = 0x5EEDF00D
+        assert fn(buf.data_ptr(), n16 * 16, blocks, sink.data_ptr(), st) == 0
+        assert sink.item() == 1
+    assert fn(buf.data_ptr(), 8, blocks, None, st) == -1 and fn(buf.data_ptr() + 4, 16, 1, None, st) == -1
