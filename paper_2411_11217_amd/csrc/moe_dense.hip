@@ -169,7 +169,13 @@ int moe_pre_attention(const moe_linear_shape* qkv_proj, const float* hidden, con
     hipStream_t st = (hipStream_t)stream;
     rc = enqueue_add_rmsnorm(qkv_proj->T, qkv_proj->K, hidden, delta, norm_gamma, eps, hidden_out, x_norm, st);
     if (rc != MOE_OK) return rc;
-    return enqueue_linear(*qkv_proj, x_norm, qkv_table, page_pool, pool_pages, qkv, qkv_bf16, nullptr, st);
+    // The projection writes the bf16 copy while other blocks still read x_norm: a copy that goes to the same memory is made
+    // by a launch of its own.
+    const int64_t T = qkv_proj->T, n = T * qkv_proj->N;
+    const bool same_memory = qkv_bf16 && overlap(x_norm, T * qkv_proj->K * 2, qkv_bf16, n * 2);
+    rc = enqueue_linear(*qkv_proj, x_norm, qkv_table, page_pool, pool_pages, qkv, same_memory ? nullptr : qkv_bf16, nullptr, st);
+    if (rc != MOE_OK || !same_memory) return rc;
+    return launch_cast_bf16(n, qkv, qkv_bf16, st);
 }
 
 int moe_post_attention_workspace_bytes(const moe_shape* s, size_t* bytes) {

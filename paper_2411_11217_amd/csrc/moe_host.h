@@ -38,6 +38,12 @@ int check_table_host(const moe_shape& s, const Geom& g, const int32_t* table, in
 // and its page image.
 void copy_tile(char* page_tile, char* dense, int64_t ld, int esize, bool to_page);
 
+// Whether two buffers of na and nb bytes share any of them.
+inline bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
+    const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+    return p < q ? q - p < (uintptr_t)na : p - q < (uintptr_t)nb;
+}
+
 // Dense paged matrices (moe_linear): MOE_OK or an error; pages of one matrix (shape must be valid).
 int validate_linear(const moe_linear_shape* s);
 int64_t linear_pages(const moe_linear_shape& s);

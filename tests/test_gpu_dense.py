@@ -1,5 +1,7 @@
 """GPU parity of the dense neighbours of the layer (paged linear map, residual + RMS norm, cast) against
 oracle/dense.py, through the C ABI, and of the two task calls against the sequence of their stages."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -65,6 +67,29 @@ def test_linear_with_few_rows(T, K, N):
     torch.cuda.synchronize()
     assert torch.equal(out, qkv) and torch.equal(qkv16, qkv.to(torch.bfloat16))
     assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
+
+
+def test_pre_attention_bf16_copy_over_the_normalised_rows():
+    # a caller that has no use for x_norm lets the bf16 copy of the projection take its memory (100 and 400 rows: the kernel that
+    # writes the copy itself, 4000: the one that does not)
+    K = N = 1280
+    g = torch.Generator().manual_seed(3)
+    ls1 = M.make_linear_shape(1, K, N, 65536)
+    W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
+    table, pool = paged_linear(ls1, W)
+    gamma = torch.ones(K, device="cuda")
+    lib = M.binding._lib()
+    for T in (100, 400, 4000):
+        ls = M.make_linear_shape(T, K, N, 65536)
+        x = torch.randn((T, K), generator=g).cuda()
+        hidden, _, qkv, qkv16 = M.moe_pre_attention(ls, None, x, gamma, 1e-5, table, pool)
+        h2, q2, both = torch.empty_like(hidden), torch.empty_like(qkv), torch.empty_like(qkv16)
+        ws = torch.empty(16, dtype=torch.uint8, device="cuda")
+        rc = lib.moe_pre_attention(ctypes.byref(ls), None, x.data_ptr(), gamma.data_ptr(), 1e-5, table.data_ptr(), pool.data_ptr(), pool.shape[0],
+                                   h2.data_ptr(), both.data_ptr(), q2.data_ptr(), both.data_ptr(), ws.data_ptr(), 16,
+                                   torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.equal(h2, hidden) and torch.equal(q2, qkv) and torch.equal(both, qkv16)
 
 
 def test_linear_empty_and_errors():
