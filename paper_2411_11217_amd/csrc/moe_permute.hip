@@ -7,7 +7,7 @@
 //             (integer sums in LDS): those before its own chunk give its base inside every expert, all of them give
 //             counts[], whose scan over the lanes is offsets[] (block 0 writes both).  The rank of an entry inside its
 //             expert is offsets[e] + base + (entries of earlier wavefront passes of the block) + its rank in its pass.
-//   count   : with more blocks, a launch of its own counts every block's chunk (block_counts[block][E]) and the placing
+//   count   : with more blocks, or when row_of takes the memory of the ids, a launch of its own counts every block's chunk (block_counts[block][E]) and the placing
 //             blocks add these up; with more than kScanInPlace blocks a one-block scan kernel does the sums once
 //             instead (block_base, counts, offsets).
 //             The placement is a pure function of the input, hence stable (ascending flat index inside an
@@ -237,7 +237,10 @@ int launch_permute(const moe_shape& s, const int32_t* ids, const float* topk_w, 
     const int nblocks = std::max((R + kChunk - 1) / kChunk, 1);      // R == 0: one block writes the zero counts
     int32_t* block_counts = nullptr;
     int32_t* block_base = nullptr;
-    if (nblocks > kCountInPlace) {
+    // Blocks that count all ids themselves read them while others write row_of: a row_of in the memory of the ids gets the
+    // count launch, behind which a block reads its own chunk alone, before it writes it.
+    const bool same_memory = overlap(ids, (int64_t)R * 4, row_of, (int64_t)R * 4);
+    if (nblocks > kCountInPlace || (nblocks > 1 && same_memory)) {
         block_counts = (int32_t*)ws;
         hipLaunchKernelGGL(count_kernel, dim3(nblocks), dim3(kThreads), 0, st, ids, R, s.E, block_counts);
         MOE_HIP_TRY(hipGetLastError());

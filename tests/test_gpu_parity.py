@@ -2,6 +2,8 @@
 element, on the same seeded inputs, through the C ABI.  Stage tests feed each
 GPU stage the ORACLE's upstream results so that a near tie in the router cannot
 cascade; the layer test runs the fused call end to end."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -277,6 +279,24 @@ def test_permutation_block_counts(T, E, k):
     for name in ("counts", "offsets", "row_src", "row_of"):
         assert np.array_equal(pm[name].cpu().numpy(), ref[name]), name
     assert np.array_equal(pm["row_w"].cpu().numpy(), w.reshape(-1)[ref["row_src"]])
+
+
+@pytest.mark.parametrize("T,E,k", [(300, 8, 2), (2500, 16, 4), (8192, 8, 2), (2048, 64, 8), (20000, 8, 2)])
+def test_permutation_may_put_row_of_over_the_ids(T, E, k):
+    rng = np.random.default_rng(T)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    ref = oracle.permute(ids, E)
+    s = M.MoEShape(T, 128, 128, E, k, M.DTYPE_BF16, 16384)
+    lib = M.binding._lib()
+    both = _dev_i32(ids)
+    counts, offsets, row_src = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * k))
+    ws = torch.empty(max(M.workspace_layout(s).permute_bytes, 16), dtype=torch.uint8, device="cuda")
+    rc = lib.moe_permute(ctypes.byref(s), both.data_ptr(), None, None, counts.data_ptr(), offsets.data_ptr(), row_src.data_ptr(), both.data_ptr(),
+                         None, None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    for name, t in (("counts", counts), ("offsets", offsets), ("row_src", row_src), ("row_of", both.reshape(-1))):
+        assert np.array_equal(t.cpu().numpy(), ref[name]), name
 
 
 def test_c1_stagewise_and_layer():
