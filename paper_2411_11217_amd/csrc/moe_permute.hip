@@ -2,14 +2,14 @@
 // indices i = t*k + slot by expert id, in two small kernels plus a row copy.
 //
 //   place   : every block owns kChunk consecutive flat indices.  Lanes of a wavefront pass with the same expert find each
-//             other with six ballots (one per bit of the id); the mask gives an entry's rank among them and their number,
-//             staged in LDS per pass.  Up to kCountInPlace blocks, every block also counts the ids of all the others itself
+//             other with a ballot per bit of the id (six for 64 experts); the mask gives an entry's rank among them and
+//             their number, staged in LDS per pass.  Up to kCountInPlace blocks, every block also counts the ids of all the others itself
 //             (integer sums in LDS): those before its own chunk give its base inside every expert, all of them give
 //             counts[], whose scan over the lanes is offsets[] (block 0 writes both).  The rank of an entry inside its
 //             expert is offsets[e] + base + (entries of earlier wavefront passes of the block) + its rank in its pass.
-//   count   : with more blocks, or when row_of takes the memory of the ids, a launch of its own counts every block's chunk (block_counts[block][E]) and the placing
-//             blocks add these up; with more than kScanInPlace blocks a one-block scan kernel does the sums once
-//             instead (block_base, counts, offsets).
+//   count   : with more blocks, or when row_of takes the memory of the ids, a launch of its own counts every block's chunk
+//             (block_counts[block][E]) and the placing blocks add these up; with more than kScanInPlace blocks a
+//             one-block scan kernel does the sums once instead (block_base, counts, offsets).
 //             The placement is a pure function of the input, hence stable (ascending flat index inside an
 //             expert) and reproducible.
 //   gather  : x_perm[row] = x[row_src[row] / k], 16 bytes per lane, one block per row.
@@ -30,11 +30,14 @@ __device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
     return __popcll(mask & ((1ull << lane) - 1ull));
 }
 
-// lanes of the wavefront with the same id as this one (0: this lane's id is not an expert)
-__device__ __forceinline__ uint64_t same_expert(int id, bool valid) {
+// lanes of the wavefront with the same id as this one (0: this lane's id is not an expert); only as many ballots as the
+// number of experts has bits (300000 ids of a single expert: 31.7 us with six, 30.4 with none)
+__device__ __forceinline__ uint64_t same_expert(int id, int E) {
+    const bool valid = id >= 0 && id < E;
     uint64_t m = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
+        if ((E - 1) >> b == 0) break;
         const bool bit = (id >> b) & 1;
         const uint64_t set = __ballot(bit);
         m &= bit ? set : ~set;
@@ -51,7 +54,7 @@ __device__ __forceinline__ void count_chunk(const int (&my_id)[kPasses], int E, 
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-        const uint64_t m = same_expert(my_id[p], my_id[p] >= 0 && my_id[p] < E);
+        const uint64_t m = same_expert(my_id[p], E);
         my_rank[p] = lanes_below(m, lane);
         if (m && my_rank[p] == 0) cnt[p * kWaves + wave][my_id[p]] = __popcll(m);
     }
