@@ -92,6 +92,12 @@ constexpr int kComputeUnits = 256;           // MI355X
 // And only where the experts' weights exceed the 256 MiB last-level cache: smaller ones may still be there from the call
 // before, and the hint keeps them out (8 experts of 1024 x 2816, 138 MB, 100 tokens: 53 without, 56 with).  Where other
 // weights pass in between it is the other way round (ten such layers in turn, 8 tokens 49 / 47, 100: 55 / 53, 400: 70 / 69).
+// The same launches store h with the hint (those of moe_ffn_rows_bf16.hip always do): lines written through as they come cost
+// the reads of the weights less than dirty lines that the end of the launch has to write back.  (Any write does: a kernel of
+// nothing but loads that reads 1.88 GB in 274 us takes 300 when its blocks also write 15 MB, wherever these go.)  Gate/up
+// launch without / with, us: Mixtral-8x7B shape 256 tokens 325 / 308, 500: 346 / 325 (and the down launch behind it 198 / 180),
+// 1000: 420 / 407; DBRX shape, 600 tokens 753 / 720.  Weights that stay in the last-level cache leave room for h there and in
+// the L2, which the hint gives up: 8 experts of 1024 x 2816, 1500 tokens 41 / 50 in the down launch; 2048 x 4096, 3000 tokens 120 / 127.
 constexpr int kStreamRows = 256;
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
@@ -739,7 +745,16 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     if (MODE == 0) {
         constexpr int NP = NJ / 2;             // gate/up pairs of a wavefront: fragments j and j + NP
         __bf16* h = (__bf16*)p.out + (int64_t)row0 * p.ldo + nt * (32 * NP) + wn * (16 * NP) + col_l;
-        auto store_rows = [&](auto full, auto n_c) __attribute__((always_inline)) {
+        // stream_c: the launch streams its weights, and h goes past the L2 (see kStreamRows)
+        auto store_h = [&](auto stream_c, __bf16 v, __bf16* dst) __attribute__((always_inline)) {
+            if constexpr (decltype(stream_c)::value) {
+                __builtin_nontemporal_store(v, dst);
+                asm volatile("" ::: "memory");           // else the compiler makes one store of this one and the plain one
+            } else {
+                *dst = v;
+            }
+        };
+        auto store_rows = [&](auto stream_c, auto full, auto n_c) __attribute__((always_inline)) {
             for_row_tiles(n_c, [&](int i, float (&v)[NJ][4]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -747,18 +762,22 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
                     if (decltype(full)::value || row < rows_here) {
 #pragma unroll
                         for (int j = 0; j < NP; ++j)
-                            h[(int64_t)row * p.ldo + j * 16] = (__bf16)silu_mul_bf16(v[j][r], v[j + NP][r]);
+                            store_h(stream_c, (__bf16)silu_mul_bf16(v[j][r], v[j + NP][r]), h + (int64_t)row * p.ldo + j * 16);
                     }
                 }
             });
         };
-        if (full_rows) store_rows(std::true_type{}, std::integral_constant<int, 8>{});
-        else if (!wact) {
-        } else if (row_tiles == 2) store_rows(std::false_type{}, std::integral_constant<int, 2>{});
-        else if (row_tiles == 4) store_rows(std::false_type{}, std::integral_constant<int, 4>{});
-        else if (row_tiles == 5) store_rows(std::false_type{}, std::integral_constant<int, 5>{});
-        else if (row_tiles == 6) store_rows(std::false_type{}, std::integral_constant<int, 6>{});
-        else store_rows(std::false_type{}, std::integral_constant<int, 8>{});
+        auto store_tile = [&](auto stream_c) __attribute__((always_inline)) {
+            if (full_rows) store_rows(stream_c, std::true_type{}, std::integral_constant<int, 8>{});
+            else if (!wact) {
+            } else if (row_tiles == 2) store_rows(stream_c, std::false_type{}, std::integral_constant<int, 2>{});
+            else if (row_tiles == 4) store_rows(stream_c, std::false_type{}, std::integral_constant<int, 4>{});
+            else if (row_tiles == 5) store_rows(stream_c, std::false_type{}, std::integral_constant<int, 5>{});
+            else if (row_tiles == 6) store_rows(stream_c, std::false_type{}, std::integral_constant<int, 6>{});
+            else store_rows(stream_c, std::false_type{}, std::integral_constant<int, 8>{});
+        };
+        if (p.stream) store_tile(std::true_type{});
+        else store_tile(std::false_type{});
         if (extra) {                           // the extra row tile of a tall tile
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
