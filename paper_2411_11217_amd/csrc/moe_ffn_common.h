@@ -153,6 +153,57 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
     return t;
 }
 
+// Block -> (expert, row tile, column tile), in the order of rows_tile_in_expert (moe_tile_order.h).  One expert per lane, a
+// prefix sum and a ballot; every wavefront does it on its own.  The order of locate_tile costs a few microseconds of
+// integer arithmetic per block, which the short blocks that use this one would feel.
+struct RowsTile {
+    int e, nt, row0, rows_here;
+    int mtiles;               // row tiles of the expert
+};
+// EVEN: the row tiles of an expert differ by 16 rows at most, instead of all but the last having BM.
+template <int BM, bool EVEN = false>
+__device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& t) {
+    const int lane = threadIdx.x & 63, id = blockIdx.x;
+    int seg, rows, m, rel;
+    if (p.offsets) {
+        const int e_l = p.e_begin + lane;
+        int seg0 = 0, cnt = 0;
+        if (e_l < p.e_end) {
+            seg0 = p.offsets[e_l];
+            cnt = p.offsets[e_l + 1] - seg0;
+        }
+        const int m_l = (cnt + BM - 1) / BM;
+        const int incl = lane_prefix_sum(m_l * p.NT, lane);
+        const unsigned long long holds = __ballot(id < incl);
+        if (!holds) return false;
+        const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)holds) - 1);
+        seg = __builtin_amdgcn_readlane(seg0, src);
+        rows = __builtin_amdgcn_readlane(cnt, src);
+        m = __builtin_amdgcn_readlane(m_l, src);
+        rel = id - __builtin_amdgcn_readlane(incl, src) + m * p.NT;
+        t.e = p.e_begin + src;
+    } else {
+        seg = 0;
+        rows = p.dense_rows;
+        m = (rows + BM - 1) / BM;
+        rel = id;
+        t.e = 0;
+        if (id >= m * p.NT) return false;
+    }
+    const TileInExpert te = rows_tile_in_expert(rel, m, p.NT);
+    t.nt = te.nt;
+    int first = te.mt * BM, height = BM;
+    if constexpr (EVEN) {
+        const int n16 = (rows + 15) >> 4, base = n16 / m, more = n16 - base * m;
+        first = 16 * (te.mt * base + min(te.mt, more));
+        height = 16 * (base + (te.mt < more));
+    }
+    t.row0 = seg + first;
+    t.rows_here = min(height, rows - first);
+    t.mtiles = m;
+    return true;
+}
+
 // silu(g) * u for the bf16 kernels, with the hardware exp2 and reciprocal (1 ulp each): far below the resolution of
 // the bf16 result; an IEEE division would cost a dozen instructions per element
 __device__ __forceinline__ float silu_mul_bf16(float g, float u) {

@@ -1,29 +1,33 @@
-// a3 for float32 storage: the same grouped SwiGLU FFN over the same page format, on v_mfma_f32_16x16x4_f32 (256 FLOP per
-// clock and compute unit, a sixteenth of the bf16 rate: with more than a few rows per expert the matrix cores are the bound,
-// 157 TFLOP/s nominal; with fewer it is the weights' way from HBM).
+// a3 for float32 storage: the same grouped SwiGLU FFN over the same page format.  With more than a few rows per expert the
+// matrix cores are the bound, with fewer it is the weights' way from HBM.
 //
-// In both kernels a lane's share of an operand is a 16-byte chunk (four consecutive k of one row): lane l holds chunk
-// 4q + l / 16 of row l % 16, and four MFMAs take one element of the four each, so that MFMA j adds the k = 16q + 4g + j
-// (g = 0 .. 3).  Activations and weights use the same map, so no element needs to move between lanes.  The weight chunks go
-// from the page straight into registers: a weight element is used by one wavefront alone, LDS would only cost a round trip.
-//
-//   ffn_rows_f32: a block owns 32 rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the
-//     columns and share the activations, which go through LDS (two stages of one 64-wide k-step; the registers hold the
-//     next one), one barrier per k-step.  17 KiB of LDS and few registers: four and more blocks share a compute unit, hide
-//     each other's latency and keep the end of a launch short (a k-step is 64 MFMAs of 32 cycles per wavefront in MODE 0).
-//     Blocks of 64 rows read the weights half as often and were slower up to thousands of tokens, 32 / 64 rows, us for the
-//     layer of 1024 x 2816 (8 experts, 2 per token): 260 tokens 175 / 216, 500: 241 / 287, 1000: 396 / 424, 2000: 685 / 734,
-//     8000: 2441 / 2396 (113 / 116 TFLOP/s for the layer).  The MFMAs of a row tile run in a row: with those of the two row
-//     tiles alternating (longer distance between two on one accumulator) 1000 tokens took 427.
-//   ffn_few_rows_f32: at most 32 rows x 16 columns (MODE 0: 16 features), the wavefronts split k instead: every fourth
+//   ffn_split_f32: float32 products on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, 16 times the rate of the float32 MFMA).
+//     Every value is a sum of three bf16, x = x0 + x1 + x2 with 24 bits together, and a product is the six partial products
+//     x2 y0 + x0 y2 + x1 y1 + x1 y0 + x0 y1 + x0 y0; what is left out is below 2^-25 of it.  The six MFMAs of 32 k add up in
+//     registers of their own, from zero, and a float32 addition takes the sum over: with all six on the accumulator itself
+//     every MFMA rounds at the size of the accumulator.  Relative error against float64 of h / of out for a given h: float32 MFMA 8.7e-7 / 9.5e-7,
+//     six MFMAs on the accumulator 7.3e-7 / 5.8e-7, this way 1.8e-7 / 1.5e-7 (1024 x 2816; 256 x 512: 4.2e-7 / 4.1e-7, 3.4e-7 /
+//     2.4e-7, 1.1e-7 / 0.8e-7).  Infinities and values that bf16 rounds to one give NaN (inf - inf), and parts of tiny
+//     values leave the range of bf16: a wavefront whose sums hold anything that is not finite, or not zero and below 2^-80,
+//     computes its tile again on the float32 MFMA, operands straight from memory.
+//     A block owns 16 RT rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the columns; a
+//     weight element is used by one wavefront alone and goes from the page straight into registers, where it is split.
+//     The activations are split once per block and pass through LDS (two stages; the registers hold the next step or two), one
+//     barrier per step of 32 k.  Splitting eight values takes 44 vector instructions, as long as 11 MFMAs: the more rows
+//     a block has, the more MFMAs share the split of its weights, and blocks of other wavefronts on the same SIMD fill
+//     the matrix cores meanwhile (three per SIMD).  Few columns (MODE 1): KG = 2, two groups of four wavefronts with 32 k of a step each.
+//     1024 x 2816, 700 tokens, against the float32 MFMA with blocks of 32 rows: gate/up 177 / 111 us, down 107 / 77, layer 289 / 202;
+//     8000 tokens 2440 / 1580; 256 x 512, 1100 tokens 64 / 47.  Matrix cores busy 0.57 of the gate/up launch.
+//   ffn_few_rows_f32: at most 32 rows x 16 columns (MODE 0: 16 features) on v_mfma_f32_16x16x4_f32, the wavefronts split k instead: every fourth
 //     k-step each, activations straight from memory, no barrier until the four partial tiles are added through LDS in a
-//     fixed order.  Four times the blocks, each a quarter as long: with a few rows per expert the launch is latency.  The order
-//     of the sums differs from ffn_rows_f32's, so a row's last bits depend on the rows per expert of the call.  The same four
-//     partial sums in ffn_rows_f32 would make them equal and cost it 4 - 10 % (in registers three instead of four wavefronts fit a
-//     SIMD, in LDS as much: 1024 x 2816, 700 tokens 282 / 301, 4000 tokens 1248 / 1361 us for the layer).
-//
-// Against one kernel with 64-row x 256-column blocks and both operands staged through LDS behind a barrier each way: 256 x
-// 512, 64 tokens: both launches 94 -> 16 us, the layer 116 -> 30 us; 1024 x 2816, 700 tokens: 782 -> 270 us, 812 -> 296 us.
+//     fixed order.  A lane's share of an operand is a 16-byte chunk (four consecutive k of one row): lane l holds chunk 4q +
+//     l / 16 of row l % 16, and four MFMAs take one element of the four each, so that MFMA j adds the k = 16q + 4g + j (g = 0 .. 3);
+//     activations and weights use the same map, so no element needs to move between lanes.  Four times the
+//     blocks, each a quarter as long: with a few rows per expert the launch is latency.
+// The two kernels add in different orders, so a row's last bits depend on the rows per expert of the call.
+#include <mutex>
+#include <type_traits>
+
 #include "moe_ffn_common.h"
 
 namespace moe {
@@ -32,13 +36,18 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
+constexpr int kComputeUnits = 256;                   // MI355X
 constexpr int kTileBytes = 128 * 64 * 4;             // a page tile: 128 rows of 256 bytes
-constexpr int kRows = 32;                            // rows of a block, of either kernel
-// Up to this many rows per expert on average the blocks of ffn_few_rows_f32 take the launch, us for the layer, ffn_few_rows
-// / ffn_rows: 256 x 512 (8 experts, 2 per token) 64 tokens 30 / 43, 130 tokens 35 / 44, 260 tokens (65 rows) 42 / 45, 500
-// tokens 51 / 50; 1024 x 2816 8 tokens 83 / 119, 100 tokens 112 / 147, 130 tokens 158 / 153, 260 tokens 203 / 175: beyond 32
-// rows an expert's weights are read once per row tile by either, and the activations once per 16 columns instead of 64.
-constexpr int kFewRows = 32;
+constexpr int kFewRows = 32;                         // rows of a block of ffn_few_rows_f32
+
+// Where ffn_split_f32 takes a launch: with more than 32 rows per expert on average (beyond, an expert's weights are read once per row
+// tile by the other kernel, and its activations once per 16 columns), and with more than 16 where its blocks of 64 columns
+// make a round on the 256 compute units.  us for the launch, ffn_few_rows / ffn_split: gate/up of 1024 x 2816 (8 experts, 2 per
+// token; 352 blocks) 50 tokens 53 / 55, 70: 61 / 55, 110: 69 / 55, 128: 86 / 59; its down launch (128 blocks) 70: 34 / 46, 110: 40 / 48,
+// 128: 55 / 49; 256 x 512 (64 and 32 blocks) 110 tokens 13 / 16 and 11 / 16.
+inline bool split_takes(int rows_each, int64_t column_blocks) {
+    return rows_each > kFewRows || (rows_each > kFewRows / 2 && column_blocks >= kComputeUnits);
+}
 
 // The tiles of one column tile along k, `step` tiles at a time; a page-table look-up only where a page begins.  An entry
 // outside the pool is never followed: slot 0 is read instead and *bad is raised.
@@ -81,114 +90,279 @@ __device__ __forceinline__ int64_t source_row(const GemmParams& p, int r) {
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
-// NB weight fragments per wavefront: MODE 0 the gate rows and the up rows of 16 features, MODE 1 16 columns
-template <int MODE>
-__global__ __launch_bounds__(kThreads) void ffn_rows_f32(const GemmParams p) {
-    constexpr int RT = kRows / 16, NB = MODE == 0 ? 2 : 1;
-    constexpr int kStride = 68;                      // floats per LDS row (64 + pad, 16-byte aligned)
-    __shared__ __attribute__((aligned(16))) float sA[2][kRows * kStride];
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+
+__device__ __forceinline__ int pack_bf16(float a, float b) {          // both rounded to nearest even
+    int v = 0;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(v) : "v"(a), "v"(b));
+#endif
+    return v;
+}
+
+// eight values, each as a sum of three bf16: part[0] + part[1] + part[2]
+__device__ __forceinline__ void split_bf16(const f32x4& lo, const f32x4& hi, i32x4 (&part)[3]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float a = j < 2 ? lo[2 * j] : hi[2 * j - 4], b = j < 2 ? lo[2 * j + 1] : hi[2 * j - 3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int v = pack_bf16(a, b);
+            part[q][j] = v;
+            a -= __builtin_bit_cast(float, v << 16);
+            b -= __builtin_bit_cast(float, v & (int)0xffff0000);
+        }
+    }
+}
+
+// RT: row tiles of 16; KG: groups of four wavefronts, each takes 32 k of a step
+template <int MODE, int RT, int KG>
+__global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(const GemmParams p) {
+    constexpr int NB = MODE == 0 ? 2 : 1, BM = 16 * RT, AJ = (BM + 63) / 64;
+    constexpr int kPlane = BM * 64, kSplitStage = 3 * kPlane;     // LDS bytes of one part of 32 k: rows of 32 bf16; of all three
+    constexpr int D = MODE == 0 ? 1 : 2;             // steps whose loads are under way
+    constexpr int kStage = KG * kSplitStage;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];      // two stages
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3), kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
     const int r = lane & 15, g = lane >> 4;
 
-    const TileCoord tc = locate_tile<kRows>(p);
-    if (!tc.valid) return;
+    RowsTile tc;
+    if (!locate_rows_tile<BM, true>(p, tc)) return;
     const int nt = tc.nt, row0 = tc.row0, rows_here = tc.rows_here;
-    const int nrt = (rows_here + 15) >> 4;           // row tiles with rows
     const int32_t* trow = p.table + (size_t)(p.table_row_mod ? tc.e % p.table_row_mod : tc.e) * p.ppe + p.group_base;
     int bad = 0;
     TileWalk w[NB];
+    auto weights_start = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) w[b].start(p, trow, ((nt >> 1) * NB + b) * p.KT, bad);
+        for (int b = 0; b < NB; ++b) w[b].start(p, trow, ((nt >> 1) * NB + b) * p.KT, bad);
+    };
+    weights_start();
     const int n = (nt & 1) * 64 + wave * 16 + r;
-    const int boff[2] = {chunk_offset(n, 0, g), chunk_offset(n, 1, g)};
+    const int boff[2] = {chunk_offset(n, 0, g), chunk_offset(n, 1, g)};     // half a k-step on: 128 bytes more
 
-    const char* asrc[RT];                            // this thread's 16 bytes of rows tid / 16 + 16 j of the stage
+    // this thread's chunks, a 64-byte piece apart, of rows tid / 4 and 64 + tid / 4 (KG = 2: the second group the other 32 k)
+    const int a_row = (tid >> 2) & 63, a_ch = tid & 3;
+    const char* asrc[AJ];
 #pragma unroll
-    for (int j = 0; j < RT; ++j)
-        asrc[j] = p.A + source_row(p, row0 + min(j * 16 + (tid >> 4), rows_here - 1)) * p.lda_bytes + (tid & 15) * 16;
-    const int a_wr = (tid >> 4) * kStride + (tid & 15) * 4;
-
-    f32x4 areg[RT], breg[2][NB][4], acc[RT][NB];
-    auto load = [&](int kt, int set) __attribute__((always_inline)) {        // k-step kt: activations, and weights into set
-#pragma unroll
-        for (int j = 0; j < RT; ++j) areg[j] = *(const f32x4*)(asrc[j] + (int64_t)kt * 256);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) breg[set][b][q] = *(const f32x4*)(w[b].tile + boff[q & 1] + (q >> 1) * 128);
-    };
+    for (int j = 0; j < AJ; ++j)
+        asrc[j] = p.A + source_row(p, row0 + min(j * 64 + a_row, rows_here - 1)) * p.lda_bytes + a_ch * 16 + kg * 128;
+    const int a_wr = kg * kSplitStage + a_row * 64 + ((a_ch ^ ((a_row >> 2) & 2)) << 4);
+    const int a_rd = kg * kSplitStage + r * 64 + ((g ^ ((r >> 2) & 2)) << 4);
     const bool copy = p.a_copy && nt == 0;           // the first column tile's blocks write the rows out as well
-    auto store_a = [&](int kt, int set) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < RT; ++j) *(f32x4*)(&sA[set][j * 16 * kStride + a_wr]) = areg[j];
-        if (copy) {
-#pragma unroll
-            for (int j = 0; j < RT; ++j) {
-                const int row = j * 16 + (tid >> 4);
-                if (row < rows_here) *(f32x4*)((char*)p.a_copy + (int64_t)(row0 + row) * p.lda_bytes + (int64_t)kt * 256 + (tid & 15) * 16) = areg[j];
-            }
-        }
-    };
+
+    f32x4 acc[RT][NB];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto step = [&](int kt, int set) __attribute__((always_inline)) {        // set = kt & 1, known at compile time
-        if (kt + 1 < p.KT) {
+
+    // NRT: row tiles that are loaded and multiplied.  A step is 32 * KG k.
+    auto main_loop = [&](auto nrt_c) __attribute__((always_inline)) {
+        constexpr int NRT = decltype(nrt_c)::value, NA = NRT > 4 ? 2 : 1;
+        const int steps = 2 * p.KT / KG;             // even: KT is
+        f32x4 areg[D][NA][2], breg[D][NB][2];
+        i32x4 bpart[1][NB][3];
+        auto load = [&](int s, int slot) __attribute__((always_inline)) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) w[b].next(p, trow, 1, bad);
-            load(kt + 1, set ^ 1);
-        }
+            for (int j = 0; j < NA; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+                for (int c = 0; c < 2; ++c) areg[slot][j][c] = *(const f32x4*)(asrc[j] + (int64_t)s * (128 * KG) + c * 64);
+            if (s > 0 && (KG == 2 || !(s & 1))) {
 #pragma unroll
-            for (int i = 0; i < RT; ++i)
-                if (i < nrt) {
-                    const f32x4 a = *(const f32x4*)(&sA[set][(i * 16 + r) * kStride + (q * 4 + g) * 4]);
+                for (int b = 0; b < NB; ++b) w[b].next(p, trow, 1, bad);
+            }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) breg[slot][b][c] = *(const f32x4*)(w[b].tile + boff[c] + (KG == 2 ? kg : s & 1) * 128);
+        };
+        auto copy_rows = [&](int s, int slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < NA; ++j) {
+                const int row = j * 64 + a_row;
+                char* dst = (char*)p.a_copy + (int64_t)(row0 + row) * p.lda_bytes + a_ch * 16 + kg * 128 + (int64_t)s * (128 * KG);
+                if (row < rows_here) {
+                    *(f32x4*)dst = areg[slot][j][0];
+                    *(f32x4*)(dst + 64) = areg[slot][j][1];
+                }
+            }
+        };
+        auto split = [&](int slot, char* st, i32x4 (&bp)[NB][3]) __attribute__((always_inline)) {   // a step's loads: activations to st, weights to bp
+#pragma unroll
+            for (int j = 0; j < NA; ++j) {
+                i32x4 part[3];
+                split_bf16(areg[slot][j][0], areg[slot][j][1], part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (BM % 64 == 0 || j * 64 + a_row < BM) *(i32x4*)(st + q * kPlane + j * 4096 + a_wr) = part[q];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                split_bf16(breg[slot][b][0], breg[slot][b][1], bp[b]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto multiply = [&](const char* st, const i32x4 (&bp)[NB][3]) __attribute__((always_inline)) {
+            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};      // the small products first
+            constexpr int G = MODE == 0 ? 1 : 2;     // row tiles at a time: four independent chains, or two
+            i32x4 a[2][G][3];
+            auto fetch = [&](int i, int set) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < G; ++t)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[set][t][q] = *(const i32x4*)(st + q * kPlane + (i + t) * 1024 + a_rd);
+            };
+            f32x4 sum[2][G][NB];
+            auto add = [&](int i, int set) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < G; ++t)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        acc[i + t][b] += sum[set][t][b];
+                        asm volatile("" : "+v"(acc[i + t][b]));      // here, and not behind the loop with all sums kept until there
+                    }
+            };
+            fetch(0, 0);
+#pragma unroll
+            for (int i = 0; i < NRT; i += G) {
+                const int set = (i / G) & 1;
+                if (i + G < NRT) fetch(i + G, set ^ 1);
+#pragma unroll
+                for (int pr = 0; pr < 6; ++pr)
+#pragma unroll
+                    for (int t = 0; t < G; ++t)
 #pragma unroll
                         for (int b = 0; b < NB; ++b)
-                            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], breg[set][b][q][j], acc[i][b], 0, 0, 0);
-                }
-        if (kt + 1 < p.KT) {
-            store_a(kt + 1, set ^ 1);                // last read in step kt - 1: everyone has passed the barrier behind it
+                            sum[set][t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[set][t][pa[pr]]), __builtin_bit_cast(bf16x8, bp[b][pb[pr]]), pr == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[set][t][b], 0, 0, 0);
+                if (i > 0) add(i - G, set ^ 1);      // behind the MFMAs of the next row tiles: their latency has passed
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            add(NRT - G, (NRT / G - 1) & 1);
+        };
+        // the vector operations of the split between the MFMAs
+        auto interleave = [&]() __attribute__((always_inline)) {
+#ifdef ILV
+            constexpr int kMfmas = NRT * NB * 6, kOps = (NA + NB) * 44, kEach = (kOps + kMfmas - 1) / kMfmas + ILV;
+#pragma unroll
+            for (int i = 0; i < kMfmas; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, kEach, 0);
+            }
+#endif
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+        if (copy) copy_rows(0, 0);
+        split(0, smem, bpart[0]);
+        if (D < steps) load(D, 0);
+        __syncthreads();
+        for (int s = 0; s < steps; s += 2) {
+            multiply(smem, bpart[0]);
+            if (copy) copy_rows(s + 1, D - 1);
+            split(D - 1, smem + kStage, bpart[0]);   // last read in step s - 1: everyone has passed the barrier behind it
+            if (s + 1 + D < steps) load(s + 1 + D, D - 1);
             __syncthreads();
+            multiply(smem + kStage, bpart[0]);
+            if (s + 2 < steps) {
+                if (copy) copy_rows(s + 2, 0);
+                split(0, smem, bpart[0]);
+                if (s + 2 + D < steps) load(s + 2 + D, 0);
+                __syncthreads();
+            }
         }
     };
-    load(0, 0);
-    store_a(0, 0);
-    __syncthreads();
-    for (int kt = 0; kt < p.KT; kt += 2) {           // KT is even (H and F are multiples of 128)
-        step(kt, 0);
-        step(kt + 1, 1);
+    if (RT > 6 && rows_here > 96) main_loop(std::integral_constant<int, RT>{});
+    else if (RT > 4 && rows_here > 64) main_loop(std::integral_constant<int, RT < 6 ? RT : 6>{});
+    else if (rows_here > 32) main_loop(std::integral_constant<int, 4>{});
+    else main_loop(std::integral_constant<int, 2>{});
+    if constexpr (KG == 2) {                         // the second group's sums are added to the first's
+        __syncthreads();
+        f32x4* part = (f32x4*)smem + (tid & 255);
+        if (kg == 1) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) part[(i * NB + b) * 256] = acc[i][b];
+        }
+        __syncthreads();
+        if (kg == 1) {
+            if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[i][b] += part[(i * NB + b) * 256];
     }
 
     // register v of lane (r, g): row i * 16 + g * 4 + v, column r
     const int col = nt * 64 + wave * 16 + r;
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
+    auto store = [&](int i, const f32x4 (&a)[NB]) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = i * 16 + g * 4 + v;
             if (row >= rows_here) continue;
             float* o = (float*)p.out + (int64_t)(row0 + row) * p.ldo + col;
-            if (MODE == 0) *o = silu_mul(acc[i][0][v], acc[i][NB - 1][v]);
-            else *o = acc[i][0][v] * (p.row_w ? p.row_w[row0 + row] : 1.0f);
+            if (MODE == 0) *o = silu_mul(a[0][v], a[NB - 1][v]);
+            else *o = a[0][v] * (p.row_w ? p.row_w[row0 + row] : 1.0f);
         }
-    if (bad && tid == 0 && p.status) atomicOr(p.status, 1);
+    };
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float m = fabsf(acc[i][b][v]);
+                odd = odd || !(m < INFINITY) || (m < 0x1p-80f && m != 0.f);
+            }
+    if (__builtin_expect(__ballot(odd) == 0, 1)) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) store(i, acc[i]);
+    } else {
+        for (int i = 0; i * 16 < rows_here; ++i) {
+            const char* arow = p.A + source_row(p, row0 + min(i * 16 + r, rows_here - 1)) * p.lda_bytes + g * 16;
+            f32x4 sum[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            weights_start();
+            for (int kt = 0; kt < p.KT; ++kt) {
+                if (kt > 0) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) w[b].next(p, trow, 1, bad);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 a = *(const f32x4*)(arow + (int64_t)kt * 256 + q * 64);
+                    f32x4 wt[NB];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) wt[b] = *(const f32x4*)(w[b].tile + boff[q & 1] + (q >> 1) * 128);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) sum[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], wt[b][j], sum[b], 0, 0, 0);
+                }
+            }
+            store(i, sum);
+        }
+    }
+    if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
 }
 
 template <int MODE>
 __global__ __launch_bounds__(kThreads) void ffn_few_rows_f32(const GemmParams p) {
-    constexpr int RT = kRows / 16, NB = MODE == 0 ? 2 : 1, W = kThreads / 64;
+    constexpr int RT = kFewRows / 16, NB = MODE == 0 ? 2 : 1, W = kThreads / 64;
     __shared__ float part[W][RT][NB][4][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
 
-    const TileCoord tc = locate_tile<kRows>(p);
+    const TileCoord tc = locate_tile<kFewRows>(p);
     if (!tc.valid) return;
     const int nt = tc.nt, row0 = tc.row0, rows_here = tc.rows_here;
     const bool two = rows_here > 16;
@@ -273,15 +447,42 @@ __global__ __launch_bounds__(kThreads) void ffn_few_rows_f32(const GemmParams p)
     if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
 }
 
-// cols: output columns (MODE 0: features) of the launch; rows_each: rows per expert on average (of all experts, so that the
-// experts of a streamed layer, one launch each, take the same kernel as the resident layer's single launch)
+template <int MODE, int RT, int KG>
+int launch_split(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
+    constexpr int lds = 2 * KG * 3 * RT * 16 * 64;
+    p.NT = cols / 64;
+    const int grid = rows_grid(p.NT, R, 16 * RT, n_exp);
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute((const void*)ffn_split_f32<MODE, RT, KG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    MOE_HIP_TRY(attr_err);
+    hipLaunchKernelGGL((ffn_split_f32<MODE, RT, KG>), dim3(grid), dim3(kThreads * KG), lds, st, p);
+    MOE_HIP_TRY(hipGetLastError());
+    return MOE_OK;
+}
+
+// cols: output columns (MODE 0: features) of the launch.  The rules go by the rows per expert on average (of all experts, so
+// that the experts of a streamed layer, one launch each, take the same kernel as the resident layer's single launch).
 template <int MODE>
-int launch_mode(GemmParams& p, int cols, int R, int rows_each, int n_exp, hipStream_t st) {
-    const bool few = rows_each <= kFewRows;
-    p.NT = cols / (few ? 16 : 64);
-    const dim3 grid(gemm_grid(p.NT, R, kRows, n_exp, p.chunked)), block(kThreads);
-    if (few) hipLaunchKernelGGL((ffn_few_rows_f32<MODE>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((ffn_rows_f32<MODE>), grid, block, 0, st, p);
+int launch_mode(GemmParams& p, int cols, int R, int E, int n_exp, hipStream_t st) {
+    const int rows_each = R / E;
+    const int64_t column_blocks = (int64_t)(cols / 64) * E;
+    if (split_takes(rows_each, column_blocks)) {
+        // us for the launch of 1024 x 2816, 64 rows and KG = 2 / 128 rows and KG = 2 / 64 rows and KG = 1: 150 tokens 50 / 52 / 78, 700:
+        // 76 / 78 / 91, 1000: 113 / 134 / 110, 4000: 318 / 385 / 311
+        if constexpr (MODE == 1) {
+            return launch_split<1, 4, 2>(p, cols, R, n_exp, st);
+        } else {
+            // 128 rows halve what a block spends on splitting weights, 64 make more blocks: 1024 x 2816 (352 blocks for up to 128 rows
+            // each) 300 tokens 78 / 77, 700: 110 / 114, 4000: 449 / 474; 256 x 512, 300 tokens (64 blocks) 23 / 18, 1000: 26 / 21
+            if (column_blocks * ((rows_each + 127) / 128) >= kComputeUnits) return launch_split<0, 8, 1>(p, cols, R, n_exp, st);
+            return launch_split<0, 4, 1>(p, cols, R, n_exp, st);
+        }
+    }
+    p.NT = cols / 16;
+    hipLaunchKernelGGL((ffn_few_rows_f32<MODE>), dim3(gemm_grid(p.NT, R, kFewRows, n_exp, p.chunked)), dim3(kThreads), 0, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }
@@ -293,11 +494,11 @@ int launch_expert_ffn_f32(const moe_shape& s, const Geom& g, const FfnArgs& a, h
     GemmParams p{};
     fill_common(p, s, g, a);
     fill_gate_up(p, s, g, a);
-    int rc = launch_mode<0>(p, s.F, R, R / s.E, n_exp, st);
+    int rc = launch_mode<0>(p, s.F, R, s.E, n_exp, st);
     if (rc != MOE_OK) return rc;
     if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
     fill_down(p, s, g, a);
-    return launch_mode<1>(p, s.H, R, R / s.E, n_exp, st);
+    return launch_mode<1>(p, s.H, R, s.E, n_exp, st);
 }
 
 int launch_expert_ffn(const moe_shape& s, const FfnArgs& a, hipStream_t st) {

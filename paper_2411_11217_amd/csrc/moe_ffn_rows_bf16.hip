@@ -27,50 +27,6 @@ constexpr int kComputeUnits = 256;                   // MI355X
 constexpr int kHalfTileBytes = 128 * 64;             // 32 k of a page tile
 constexpr int kTileBytes = 2 * kHalfTileBytes;
 
-// Block -> (expert, row tile, column tile), in the order of rows_tile_in_expert (moe_tile_order.h).  One expert per lane, a
-// prefix sum and a ballot; every wavefront does it on its own.  The order of locate_tile costs a few microseconds of
-// integer arithmetic per block, which these short blocks would feel.
-struct RowsTile {
-    int e, nt, row0, rows_here;
-    int mtiles;               // row tiles of the expert
-};
-template <int BM>
-__device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& t) {
-    const int lane = threadIdx.x & 63, id = blockIdx.x;
-    int seg, rows, m, rel;
-    if (p.offsets) {
-        const int e_l = p.e_begin + lane;
-        int seg0 = 0, cnt = 0;
-        if (e_l < p.e_end) {
-            seg0 = p.offsets[e_l];
-            cnt = p.offsets[e_l + 1] - seg0;
-        }
-        const int m_l = (cnt + BM - 1) / BM;
-        const int incl = lane_prefix_sum(m_l * p.NT, lane);
-        const unsigned long long holds = __ballot(id < incl);
-        if (!holds) return false;
-        const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)holds) - 1);
-        seg = __builtin_amdgcn_readlane(seg0, src);
-        rows = __builtin_amdgcn_readlane(cnt, src);
-        m = __builtin_amdgcn_readlane(m_l, src);
-        rel = id - __builtin_amdgcn_readlane(incl, src) + m * p.NT;
-        t.e = p.e_begin + src;
-    } else {
-        seg = 0;
-        rows = p.dense_rows;
-        m = (rows + BM - 1) / BM;
-        rel = id;
-        t.e = 0;
-        if (id >= m * p.NT) return false;
-    }
-    const TileInExpert te = rows_tile_in_expert(rel, m, p.NT);
-    t.nt = te.nt;
-    t.row0 = seg + te.mt * BM;
-    t.rows_here = min(BM, rows - te.mt * BM);
-    t.mtiles = m;
-    return true;
-}
-
 template <int N>
 struct Num {
     static constexpr int value = N;

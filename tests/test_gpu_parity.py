@@ -11,7 +11,7 @@ import torch
 import oracle
 import paper_2411_11217_amd as M
 from moe_workloads import CONFIGS, MoEConfig, scaled
-from util import Case, assert_close, assert_h_close, check_permutation_valid, compare_routing, say, shape_of, assert_status_clean
+from util import F32_REL_RMS, Case, assert_close, assert_h_close, assert_status_clean, check_permutation_valid, compare_routing, rel_rms, say, shape_of
 
 pytestmark = pytest.mark.gpu
 
@@ -198,6 +198,65 @@ def test_f32_expert_ffn_row_counts_across_the_kernels(counts, H, F):
     finally:
         M.set_option("fuse_gather", 1)
     assert torch.equal(y0, y)
+
+
+@pytest.mark.parametrize("counts,H,F", [
+    ([1, 16, 17, 33, 64, 65, 96, 97, 128, 129, 300, 0], 128, 256),    # the split kernel's row tiles and loops; two and four k-steps
+    ([260, 31, 111], 384, 640),                                         # six and ten k-steps, three row tiles of an expert
+    ([20] * 63 + [70], 128, 256),                                       # few rows, but column blocks for every compute unit: gate/up alone
+    ([150, 40, 9, 260], 256, 4224),                                     # 264 column blocks: the blocks of 128 rows
+])
+def test_f32_split_products(counts, H, F):
+    """The float32 kernel on the bf16 matrix cores against the oracle.  Its sums over k take one float32 rounding (2^-24) per 32 k
+    at the size of the result and six at the size of 32 terms: below 1e-6 relative RMS with up to 132 such steps."""
+    E = len(counts)
+    cfg = MoEConfig("split32", "f32", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=96 * 1024, seed=79)
+    case = Case(cfg, shuffle_pages=True, extra_pages=1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = case.view
+    h_ref, o_ref = oracle.expert_ffn(v["x"], offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
+    status = torch.zeros(4, dtype=torch.int32, device="cuda")
+    h, out = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, status=status)
+    torch.cuda.synchronize()
+    assert_status_clean(status.cpu().tolist())
+    assert rel_rms(h.cpu().numpy(), h_ref) < 1e-6
+    assert rel_rms(out.cpu().numpy(), o_ref) < 1e-6
+    for e, c in enumerate(counts):
+        lo, hi = int(offsets[e]), int(offsets[e + 1])
+        if c:
+            assert_close(out.cpu().numpy()[lo:hi], o_ref[lo:hi], "f32", f"out, expert {e} with {c} rows")
+
+
+def test_f32_split_products_of_extreme_values():
+    """Infinities, NaN, values that bf16 rounds to infinity and values whose low parts leave its range: what the float32 products
+    give, row by row, and nothing of it in other rows."""
+    counts, H, F = [100, 40], 128, 256
+    cfg = MoEConfig("extreme32", "f32", T=sum(counts), H=H, F=F, E=2, k=1, page_bytes=96 * 1024, seed=80)
+    case = Case(cfg)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    x = case.x.clone()
+    x[3, 5] = float("inf")
+    x[20, 7] = float("-inf")
+    x[21, 8] = float("nan")
+    x[40, 9], x[40, 10] = 3.4e38, -3.4e38
+    x[60] *= 2.0 ** -118
+    x[110, 100] = float("inf")
+    h, _ = M.moe_expert_ffn(case.shape, x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev)
+    torch.cuda.synchronize()
+    ref = torch.empty_like(h, device="cpu")
+    for e in range(2):
+        r = slice(int(offsets[e]), int(offsets[e + 1]))
+        g, u = x[r].cpu() @ case.inp["W1"][e].T, x[r].cpu() @ case.inp["W3"][e].T
+        ref[r] = g / (1 + torch.exp(-g)) * u
+    h = h.cpu()
+    assert torch.equal(torch.isnan(h), torch.isnan(ref)) and torch.equal(torch.isinf(h), torch.isinf(ref))
+    assert torch.equal(torch.sign(h[torch.isinf(h)]), torch.sign(ref[torch.isinf(ref)]))
+    plain = [i for i in range(140) if i not in (3, 20, 21, 40, 60, 110)]
+    assert torch.isfinite(h[plain]).all() and rel_rms(h[plain].numpy(), ref[plain].numpy()) < 1e-6
+    assert rel_rms(h[40][torch.isfinite(ref[40])].numpy(), ref[40][torch.isfinite(ref[40])].numpy()) < F32_REL_RMS
+    g64 = x[60].cpu().double() @ case.inp["W1"][0].T.double()
+    u64 = x[60].cpu().double() @ case.inp["W3"][0].T.double()
+    assert np.abs(h[60].double().numpy() - (0.5 * g64 * u64).numpy()).max() <= 2.0 ** -149     # underflows: silu(g) = g / 2 there
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
