@@ -274,19 +274,23 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
     return launch_rows<1, 8, 8, 1, 1, 4>(p, H, R, n_exp, st);
 }
 
-// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here).  32 columns as long as they
-// make one round of blocks, else 64 (with non-temporal loads: 4096 x 6144 60 tokens 27 / 30, 100: 39 / 42, but 200: 73 / 48; 6144 x
-// 9216 50 tokens 60 / 42); the fewer columns, the more wavefronts along the rows.
+// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here).  Up to 64 rows 32 columns as long as
+// they make one round of blocks, else 64 (6144 x 9216 50 tokens 60 / 42 us), and with 32 columns two row groups.  More rows: blocks
+// of 64 rows x 64 columns as long as they make one round.  Blocks of 128 rows x 32 columns, whose four row groups each loaded the
+// weights, brought 32 KB per k-step to a compute unit where these bring 16; us for the pre-attention task, those / these, weights where
+// the call before left them | from HBM: 4096 x 6144 70 tokens 31 / 27 | 36 / 29, 100: 32 / 27 | 37 / 31, 128: 33 / 27 | 39 / 34; 2048 x 3072 300
+// tokens (128 rows x 64 columns before) 23 / 22 | 24 / 22; the post-attention task of the Mixtral-8x7B shape, 100 tokens 490 / 478.  Beyond one round 128 rows x 64 columns:
+// 4096 x 6144 192 tokens 36 with 64 rows, 35 with 128; 6144 x 9216 70 tokens 56 and 45.
 // Temporal loads, us without / with the non-temporal hint, weights where the call before left them (one matrix fits the 256 MiB
-// last-level cache) | weights from HBM: 4096 x 6144 64 tokens 17 / 21 | 21 / 22, 128: 26 / 34 | 30 / 36; 6144 x 9216 64 tokens 30 /
-// 35 | 38 / 37, 128: 40 / 59 | 58 / 60; 2048 x 3072 128 tokens 15 / - | 17 / 20.
-// Groups of wavefronts that split k instead were faster still with 65 .. 128 rows (4096 x 6144 100 tokens 33 against 39 with
+// last-level cache) | weights from HBM: 4096 x 6144 64 tokens 17 / 21 | 21 / 22; 6144 x 9216 64 tokens 30 / 35 | 38 / 37, 128: 40 /
+// 59 | 58 / 60.
+// Groups of wavefronts that split k were faster than the blocks of 128 rows x 32 columns too (4096 x 6144 100 tokens 33 against 39 with
 // the hint), but they change the order of the sums, which the O projection hands on to a rounding and the router.
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
     const bool few_columns = N / 32 * ((T + 127) / 128) <= kComputeUnits;
     if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8>(p, N, T, 1, st);
     if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 8>(p, N, T, 1, st);
-    if (few_columns) return launch_rows<1, 8, 2, 1, 4, 4>(p, N, T, 1, st);
+    if (N / 64 * ((T + 63) / 64) <= kComputeUnits) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
     return launch_rows<1, 8, 4, 1, 2, 4>(p, N, T, 1, st);
 }
 
