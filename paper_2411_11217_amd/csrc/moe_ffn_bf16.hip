@@ -870,11 +870,11 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     const int64_t rows_each = R / s.E;
     p.stream = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
     if (rows_kernel_takes((int)rows_each)) {
-        const int rc = launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, st);
+        int rc = thin_takes_gate_up(s) ? launch_gate_up_thin_bf16(p, s.F, R, n_exp, st) : launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, st);
         if (rc != MOE_OK) return rc;
         if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
         fill_down(p, s, g, a);
-        return launch_down_rows_bf16(p, s.H, R, (int)rows_each, n_exp, st);
+        return thin_takes_down(s) ? launch_down_thin_bf16(p, s.H, R, n_exp, st) : launch_down_rows_bf16(p, s.H, R, (int)rows_each, n_exp, st);
     }
     const int64_t row_tiles_each = std::max<int64_t>(1, (rows_each - p.tall_rows + BM - 1) / BM);
     const int rc = launch_stages<0, 2>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);

@@ -216,6 +216,11 @@ bool rows_kernel_takes(int rows_each);
 int launch_gate_up_rows_bf16(GemmParams& p, int F, int R, int rows_each, int n_exp, hipStream_t st);
 int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp, hipStream_t st);
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st);
+// the one for a handful of tokens (moe_ffn_thin_bf16.hip)
+bool thin_takes_gate_up(const moe_shape& s);
+bool thin_takes_down(const moe_shape& s);
+int launch_gate_up_thin_bf16(GemmParams& p, int F, int R, int n_exp, hipStream_t st);
+int launch_down_thin_bf16(GemmParams& p, int H, int R, int n_exp, hipStream_t st);
 
 inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const FfnArgs& a) {
     p.offsets = a.offsets;

@@ -201,6 +201,46 @@ def test_f32_expert_ffn_row_counts_across_the_kernels(counts, H, F):
 
 
 @pytest.mark.parametrize("counts,H,F", [
+    ([1, 0, 3], 128, 128),                     # two k-steps each way
+    ([16], 512, 640),                            # as many k-steps as are under way, and two more
+    ([0, 7, 2, 0, 1], 1024, 1152),               # twice as many, and two more
+    ([2, 13, 0], 1536, 384),
+])
+def test_bf16_handful_of_tokens(counts, H, F):
+    """The kernel for at most 16 tokens against the oracle, and bit by bit against the kernel that takes over with more; one expert
+    may have more rows than a tile when the offsets do not come from a routing."""
+    E, T = len(counts), sum(counts)
+    cfg = MoEConfig("thin", "bf16", T=T + 17, H=H, F=F, E=E, k=1, page_bytes=48 * 1024, seed=81)
+    case = Case(cfg, shuffle_pages=True, extra_pages=1)
+    few = M.make_shape(T, H, F, E, 1, "bf16", cfg.page_bytes)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = case.view
+    h_ref, o_ref = oracle.expert_ffn(v["x"][:T], offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
+    x = case.x[:T].contiguous()
+    w = np.random.default_rng(2).random(T, dtype=np.float32) + 0.5
+    status = torch.zeros(4, dtype=torch.int32, device="cuda")
+    h, out = M.moe_expert_ffn(few, x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w), status=status)
+    torch.cuda.synchronize()
+    assert_status_clean(status.cpu().tolist())
+    assert_h_close(h.float().cpu().numpy(), h_ref, "bf16", "h")
+    assert_close(out.cpu().numpy(), o_ref * w[:, None], "bf16", "out * w")
+    more = offsets.copy()
+    more[-1] += 17                                       # 17 rows more behind those of the last expert: beyond this kernel
+    w2 = np.concatenate([w, np.ones(17, np.float32)])
+    h2, out2 = M.moe_expert_ffn(case.shape, case.x, _dev_i32(more), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w2))
+    assert torch.equal(h2[:T], h) and torch.equal(out2[:T], out)
+    if T * 2 > 16:                                       # all rows of two per token on one expert: two row tiles
+        twice = M.make_shape(T, H, F, E, min(E, 2), "bf16", cfg.page_bytes)
+        R = twice.R
+        one = np.zeros(E + 1, np.int32)
+        one[1:] = R
+        h3, out3 = M.moe_expert_ffn(twice, case.x[:R].contiguous(), _dev_i32(one), case.pw.table_dev, case.pw.pages_dev)
+        h4, out4 = M.moe_expert_ffn(M.make_shape(R + 17, H, F, E, 1, "bf16", cfg.page_bytes), torch.cat([case.x[:R], case.x[:17]]),
+                                    _dev_i32(np.concatenate([[0], np.full(E, R + 17, np.int32)]).astype(np.int32)), case.pw.table_dev, case.pw.pages_dev)
+        assert torch.equal(h4[:R], h3) and torch.equal(out4[:R], out3)
+
+
+@pytest.mark.parametrize("counts,H,F", [
     ([1, 16, 17, 33, 64, 65, 96, 97, 128, 129, 300, 0], 128, 256),    # the split kernel's row tiles and loops; two and four k-steps
     ([260, 31, 111], 384, 640),                                         # six and ten k-steps, three row tiles of an expert
     ([20] * 63 + [70], 128, 256),                                       # few rows, but column blocks for every compute unit: gate/up alone
