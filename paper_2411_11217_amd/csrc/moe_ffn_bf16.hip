@@ -881,15 +881,16 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     if (rc != MOE_OK) return rc;
     if (a.mid_event) MOE_HIP_TRY(hipEventRecord(a.mid_event, st));
     fill_down(p, s, g, a);
-    // Down projection with few row tiles: 256-wide column tiles would leave compute units without a block,
-    // so the columns are cut into 128-wide tiles instead.  The routing result is not known here; the choice
+    // Down projection with few row tiles: 256-wide column tiles would leave compute units without a block, so the columns are cut
+    // into 128-wide tiles as long as these make no more than one round.  The routing result is not known here; the choice
     // goes by the row tiles an even split of the rows over the experts would give (the grid is sized by the
-    // upper bound as ever).  Measured on the Mixtral-8x7B shape, narrow against wide: 768 tokens 0.23 / 0.29
-    // ms, 1024 tokens 0.26 / 0.32, 1280 tokens 0.45 / 0.38, 2048 tokens 0.48 / 0.38.
+    // upper bound as ever).  us for the launch, narrow / wide: Mixtral-8x7B shape 1000 tokens (256 narrow tiles) 247 / 312, 1200 (512) 453 / 367;
+    // Mixtral-8x22B shape 600 tokens (384) 384 / 295, 1000: 472 / 377; 2048 x 4096 1500 tokens (256) 74 / 92, 2500 (384) 108 / 95; 1024 x 2816
+    // 2000 tokens (128) 55 / 69; DBRX shape 600 tokens (768) 435 / 405.
     // down_cols: 0 = this rule, 1 / 2 = force NB.
     const int opt = get_opt(OPT_DOWN_COLS);
-    const bool narrow = opt == 1 || (opt == 0 && n_exp * row_tiles_each * p.NT < kComputeUnits);
-    if (narrow) {
+    const int64_t narrow_tiles = n_exp * row_tiles_each * (int64_t)g.dt;
+    if (opt == 1 || (opt == 0 && narrow_tiles <= kComputeUnits)) {
         p.NT = (int32_t)g.dt;
         return launch_stages<1, 1>(p, gemm_grid(p.NT, R, BM, n_exp, p.chunked), st);
     }
