@@ -269,8 +269,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 // only): 256 rows x 128 columns, wavefront tile 128 x 64, for launches with too few 256-wide tiles
 // to occupy the chip (few rows per expert: the launch is bound by streaming the weights, and more
 // blocks stream more).
-template <int MODE, int NB>
+// TR: most rows of a row tile without its extra ones.  128 (the linear map with NB = 1): twice the blocks, none but the loops of
+// short tiles.
+template <int MODE, int NB, int TR>
 __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
+    static_assert(TR == BM || (TR == 128 && NB == 1), "");
     constexpr int S = kStages;
     static_assert(MODE == 1 || NB == 2, "the narrow block is the down projection's");
     constexpr bool TWO_WALKS = NB == 2;          // two page tiles are walked along k
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     const int wm = wave >> 1, wn = wave & 1;
 
     // ---- which tile is mine -------------------------------------------------
-    const TileCoord tc = locate_tile<BM>(p);
+    const TileCoord tc = locate_tile<TR>(p);
     if (!tc.valid) return;
     // diagnostic: some blocks report the shader clock they saw (cycle counter against the 100 MHz
     // constant counter over the whole tile); the chip is power limited under this kernel
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // extra rows when the MFMAs of this block were put under a branch on the number of extra rows).  So: one
     // unconditional sequence per half-step under the single test of `extra`; what varies with the number of extra
     // rows is decided inside the asm statement (mfma_extra_tile_8 / _4).
-    const int extra = rows_here > BM ? rows_here - BM : 0;
+    const int extra = TR == BM && rows_here > BM ? rows_here - BM : 0;
     // At most 16 extra rows: ONE extra 16-row MFMA tile, rows BM .. BM + 15, and the two wavefront rows - which hold the
     // same column fragments - take half of the column fragments each (half the extra MFMAs per wavefront).  extra_which:
     // 0 = every fragment (more than 16 extra rows: wavefront row wm has the rows BM + 16 wm ..), 1 / 2 = this
@@ -708,14 +711,16 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     // most 64: the upper wavefront row alone (the other wavefronts only load); at most 32: two row tiles instead of four.
     // us for the layer with the full loop / with five or six row tiles: DBRX shape, 550 tokens (138 rows per expert) 1338 /
     // 1222, 700 tokens 1394 / 1307; Mixtral-8x7B shape, 600 tokens 644 / 592; 64 experts of 2048 x 1024, 1200 tokens 421 / 397.
-    const bool half_tile = p.half_tiles && rows_here <= 32 * kShortTiles;
+    const bool half_tile = TR < BM || (p.half_tiles && rows_here <= 32 * kShortTiles);
     using std::integral_constant;
     auto run = [&](auto stream_c) __attribute__((always_inline)) {
-        if (!half_tile && extra) main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::true_type{});
-        else if (!half_tile) main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
-        else if (rows_here > 160) main_loop(stream_c, std::true_type{}, integral_constant<int, 6>{}, integral_constant<int, 6>{}, std::false_type{});
-        else if (rows_here > 128) main_loop(stream_c, std::true_type{}, integral_constant<int, 5>{}, integral_constant<int, 5>{}, std::false_type{});
-        else if (rows_here > 64) main_loop(stream_c, std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
+        if constexpr (TR == BM) {
+            if (!half_tile && extra) return main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::true_type{});
+            if (!half_tile) return main_loop(stream_c, std::false_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
+            if (rows_here > 160) return main_loop(stream_c, std::true_type{}, integral_constant<int, 6>{}, integral_constant<int, 6>{}, std::false_type{});
+            if (rows_here > 128) return main_loop(stream_c, std::true_type{}, integral_constant<int, 5>{}, integral_constant<int, 5>{}, std::false_type{});
+        }
+        if (rows_here > 64) main_loop(stream_c, std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, std::false_type{});
         else if (rows_here > 32) main_loop(stream_c, std::true_type{}, integral_constant<int, 4>{}, integral_constant<int, 2>{}, std::false_type{});
         else main_loop(stream_c, std::true_type{}, integral_constant<int, 2>{}, integral_constant<int, 1>{}, std::false_type{});
     };
@@ -845,16 +850,16 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     if (bad && tid == 0 && p.status) atomicOr(p.status, 1);
 }
 
-template <int MODE, int NB>
+template <int MODE, int NB, int TR = BM>
 int launch_stages(const GemmParams& p, int grid, hipStream_t st) {
     constexpr int lds = kLdsBytes;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_err = hipFuncSetAttribute((const void*)ffn_gemm_bf16<MODE, NB, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     MOE_HIP_TRY(attr_err);
-    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB>), dim3(grid), dim3(kThreads), lds, st, p);
+    hipLaunchKernelGGL((ffn_gemm_bf16<MODE, NB, TR>), dim3(grid), dim3(kThreads), lds, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }
@@ -936,7 +941,17 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     int rc;
     if ((int64_t)(a.T / BM + 1) * wide_tiles < 2 * kComputeUnits) {       // too few 256-wide tiles to fill the chip
         p.NT = p.n_page_tiles;
-        rc = launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
+        // Row tiles of 128 as long as they make one round: a tile of 256 rows x 128 columns is a chain of some 0.6 us per k-step
+        // whatever else the chip does, one of 128 rows 0.4.  us for the pre-attention task, 256 / 128 rows: 4096 x 6144 270 tokens (144
+        // tiles of 128) 60 / 42, 300: 53 / 45, 512: 56 / 46; 6144 x 9216 256 tokens (144) 72 / 57; 2048 x 3072 700 tokens (144) 38 / 34,
+        // 1000 (192) 40 / 34.  Not for the experts' down launch, whose experts are a tile each and would read their weights twice: 2048 x 4096 1024
+        // tokens 70 us for the launch, 86 with tiles of 128.
+        if (p.half_tiles && a.T > 128 && (int64_t)((a.T + 127) / 128) * p.NT <= kComputeUnits) {
+            p.tall_rows = 0;
+            rc = launch_stages<1, 1, 128>(p, gemm_grid(p.NT, a.T, 128, 1, p.chunked), st);
+        } else {
+            rc = launch_stages<1, 1>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);
+        }
     } else {
         p.NT = wide_tiles;
         rc = launch_stages<1, 2>(p, gemm_grid(p.NT, a.T, BM, 1, p.chunked), st);

@@ -69,6 +69,24 @@ def test_linear_with_few_rows(T, K, N):
     assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
 
 
+@pytest.mark.parametrize("T,K,N", [(129, 128, 9216), (192, 640, 12800), (256, 256, 9216), (257, 384, 6144), (385, 128, 6144), (512, 256, 6144)])
+def test_linear_row_tiles_of_128(T, K, N):
+    # one round of blocks of 128 rows x 128 columns: against the oracle, and bit by bit against row tiles of 256
+    g = torch.Generator().manual_seed(T + K)
+    x = torch.randn((T, K), generator=g).to(torch.bfloat16)
+    W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
+    ls = M.make_linear_shape(T, K, N, 3 * 16384)
+    table, pool = paged_linear(ls, W)
+    out = M.moe_linear(ls, x.cuda(), table, pool)
+    M.set_option("half_tiles", 0)
+    try:
+        out256 = M.moe_linear(ls, x.cuda(), table, pool)
+    finally:
+        M.set_option("half_tiles", 1)
+    assert torch.equal(out, out256)
+    assert_close(out.cpu().numpy(), dense.linear(bits(x), bits(W)), "bf16", f"linear {T}x{K}x{N}")
+
+
 def test_pre_attention_bf16_copy_over_the_normalised_rows():
     # a caller that has no use for x_norm lets the bf16 copy of the projection take its memory (100 and 400 rows: the kernel that
     # writes the copy itself, 4000: the one that does not)
