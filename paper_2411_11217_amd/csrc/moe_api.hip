@@ -105,16 +105,21 @@ static int layer_body(const moe_shape& s, const void* x, const void* Wr, const f
     float* row_w = (float*)(ws + L.row_w);
     const int ps = prof_slot();
     prof_mark(ps, 0, st);
-    int rc = launch_route(s, x, Wr, bias, ids, w, nullptr, st);
-    if (rc != MOE_OK) return rc;
-    prof_mark(ps, 1, st);
     // The gate/up GEMM gathers the rows of x by itself: bf16 with 32-bit byte offsets into x, and x_perm stays unwritten;
     // f32 with 64-bit addresses, and the blocks of the first column tile write x_perm as they read.
     const bool bf16 = s.dtype == MOE_DTYPE_BF16;
     const bool fuse = get_opt(OPT_FUSE_GATHER) && (!bf16 || (int64_t)s.T * s.H * 2 < ((int64_t)1 << 32));
-    rc = launch_permute(s, ids, w, fuse ? nullptr : x, counts, offsets, row_src, row_of, row_w,
-                        fuse ? nullptr : ws + L.x_perm, ws + L.scan, status, st);   // also clears the status words (in a kernel: the call can be graph-captured)
+    // the status words are cleared by the router or the permutation (in a kernel: the call can be graph-captured)
+    const PlaceOut place{counts, offsets, row_src, row_of, row_w, status};
+    const bool places = fuse && route_places(s);
+    int rc = launch_route(s, x, Wr, bias, ids, w, nullptr, st, places ? &place : nullptr);
     if (rc != MOE_OK) return rc;
+    prof_mark(ps, 1, st);
+    if (!places) {
+        rc = launch_permute(s, ids, w, fuse ? nullptr : x, counts, offsets, row_src, row_of, row_w,
+                            fuse ? nullptr : ws + L.x_perm, ws + L.scan, status, st);
+        if (rc != MOE_OK) return rc;
+    }
     prof_mark(ps, 2, st);
     rc = ffn(fuse ? x : ws + L.x_perm, fuse ? row_src : nullptr, fuse && !bf16 ? ws + L.x_perm : nullptr, offsets, row_w,
              ws + L.h, (float*)(ws + L.out), status, prof_event(ps, 3));

@@ -36,8 +36,16 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 }
 
 // ---- kernel launchers (each returns MOE_OK or MOE_ERR_HIP) -----------------
+// What the permutation writes (moe_permute of the C ABI, without the copy of x).
+struct PlaceOut {
+    int32_t *counts, *offsets, *row_src, *row_of;
+    float* row_w;
+    int32_t* status;           // int32[4], cleared
+};
+// Whether the router can place the rows as well: one block owns all tokens.
+bool route_places(const moe_shape& s);
 int launch_route(const moe_shape& s, const void* x, const void* Wr, const float* bias,
-                 int32_t* ids, float* w, float* logits, hipStream_t st);
+                 int32_t* ids, float* w, float* logits, hipStream_t st, const PlaceOut* place = nullptr);     // place: only with route_places
 
 size_t permute_workspace_bytes(const moe_shape& s);
 int launch_permute(const moe_shape& s, const int32_t* ids, const float* topk_w, const void* x,

@@ -13,7 +13,7 @@
 //             The placement is a pure function of the input, hence stable (ascending flat index inside an
 //             expert) and reproducible.
 //   gather  : x_perm[row] = x[row_src[row] / k], 16 bytes per lane, one block per row.
-#include "moe_internal.h"
+#include "moe_place.h"
 
 namespace moe {
 namespace {
@@ -25,26 +25,6 @@ constexpr int kChunk = kThreads * kPasses;   // flat indices per block
 // Up to this many blocks the placing blocks read all ids instead of a count launch (4.7 us and more).
 constexpr int kCountInPlace = 16;
 constexpr int kScanInPlace = 256;            // up to this many blocks every placing block sums the block counts itself
-
-__device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
-    return __popcll(mask & ((1ull << lane) - 1ull));
-}
-
-// lanes of the wavefront with the same id as this one (0: this lane's id is not an expert); only as many ballots as the
-// number of experts has bits (300000 ids of a single expert: 31.7 us with six, 30.4 with none)
-__device__ __forceinline__ uint64_t same_expert(int id, int E) {
-    const bool valid = id >= 0 && id < E;
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        if ((E - 1) >> b == 0) break;
-        const bool bit = (id >> b) & 1;
-        const uint64_t set = __ballot(bit);
-        m &= bit ? set : ~set;
-    }
-    return valid ? m : 0;
-}
-static_assert(MOE_MAX_EXPERTS == 64, "an expert id has six bits");
 
 // cnt[pass * kWaves + wave][e] = entries for expert e of every wavefront pass of this block's chunk, and each entry's
 // rank among those of its pass.  Ends with a barrier.

@@ -23,7 +23,11 @@
 // the sum of value j) and over the four wavefronts through LDS.
 //
 // In both, the selection and the softmax are done by one lane per (token, expert).
-#include "moe_internal.h"
+//
+// With at most 16 tokens of bf16 data one block has all of them, and in moe_layer it does the permutation too, with the
+// counting sort of moe_permute.hip on the ids that it has in LDS: a launch less, which is 4 to 5 us of a call that can
+// be as short as 30.
+#include "moe_place.h"
 
 namespace moe {
 namespace {
@@ -46,7 +50,7 @@ __device__ __forceinline__ void load8(const float* base, size_t elem, float (&v)
 // a scan that keeps the first and replaces it by what compares greater would do.  Every lane of the wavefront calls this; `live`: the token exists.
 template <int EP>
 __device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int tok, bool live, int32_t* __restrict__ ids,
-                                             float* __restrict__ w) {
+                                             float* __restrict__ w, int32_t* s_ids = nullptr, float* s_w = nullptr) {
     const int lane = threadIdx.x & 63, le = lane & (EP - 1);
     auto group = [&](uint64_t m) __attribute__((always_inline)) {    // this group's bits of a ballot
         return EP == 64 ? m : (m >> (lane - le)) & ((1ull << (EP & 63)) - 1);
@@ -79,15 +83,75 @@ __device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int 
     if (live && le < k) {
         ids[(size_t)tok * k + le] = my_id;
         w[(size_t)tok * k + le] = my_p * inv;
+        if (s_ids) {
+            s_ids[tok * k + le] = my_id;
+            s_w[tok * k + le] = my_p * inv;
+        }
     }
 }
 
-// NE: 16-expert tiles (experts padded to 16, 32 or 64); NW: wavefronts of a block.
-template <int NE, int NW>
+// The permutation of R <= 1024 rows by one block of NW wavefronts that has their ids and weights in LDS.  cnt: 16 x
+// MOE_MAX_EXPERTS words of LDS, start: MOE_MAX_EXPERTS.  Starts and ends its use of them behind barriers of its own.
+template <int NW>
+__device__ __forceinline__ void place_rows(const int32_t* s_ids, const float* s_w, int R, int E, int32_t (*cnt)[MOE_MAX_EXPERTS],
+                                           int32_t* start, const PlaceOut& o) {
+    constexpr int P = 16 / NW;                               // wavefront passes: 16 of them cover the rows
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 16 * MOE_MAX_EXPERTS; i += NW * 64) cnt[0][i] = 0;
+    if (o.status && threadIdx.x < 4) o.status[threadIdx.x] = 0;
+    __syncthreads();
+    int my_id[P], my_rank[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int i = (p * NW + wave) * 64 + lane;
+        my_id[p] = i < R ? s_ids[i] : -1;
+        const uint64_t m = same_expert(my_id[p], E);
+        my_rank[p] = lanes_below(m, lane);
+        if (m && my_rank[p] == 0) cnt[p * NW + wave][my_id[p]] = __popcll(m);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int run = 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int c = cnt[j][lane];                      // zero beyond the experts
+            cnt[j][lane] = run;
+            run += c;
+        }
+        int incl = run;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += u;
+        }
+        start[lane] = incl - run;
+        if (lane < E) {
+            o.offsets[lane] = incl - run;
+            o.counts[lane] = run;
+        }
+        if (lane == E - 1) o.offsets[E] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int i = (p * NW + wave) * 64 + lane, e = my_id[p];
+        if (e >= 0) {
+            const int r = start[e] + cnt[p * NW + wave][e] + my_rank[p];
+            o.row_of[i] = r;
+            o.row_src[r] = i;
+            o.row_w[r] = s_w[i];
+        }
+    }
+}
+
+// NE: 16-expert tiles (experts padded to 16, 32 or 64); NW: wavefronts of a block; PLACE: the one block of the launch places
+// the rows as well.
+template <int NE, int NW, bool PLACE>
 __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restrict__ x, const char* __restrict__ Wr,
                                                          const float* __restrict__ bias, int32_t* __restrict__ ids,
                                                          float* __restrict__ w, float* __restrict__ logits,
-                                                         int T, int H, int E, int k) {
+                                                         int T, int H, int E, int k, const PlaceOut place) {
     constexpr int EP = NE * 16;
     // Units whose loads are in flight together.  Beyond 32 experts two: with four a wavefront needs 193 registers and only one
     // block fits a compute unit; 65536 tokens of 2048, 64 experts, 8 per token: 251 us with four, 156 with two, 777 tokens 17
@@ -95,6 +159,8 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
     constexpr int UB = NE <= 2 ? 4 : 2;
     __shared__ float s_part[NW][16][EP];
     __shared__ float s_logit[16][EP];
+    __shared__ int32_t s_ids[PLACE ? 16 * MOE_MAX_EXPERTS : 1];
+    __shared__ float s_w[PLACE ? 16 * MOE_MAX_EXPERTS : 1];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * 16;
@@ -152,7 +218,12 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
     }
     __syncthreads();
     constexpr int TW = 64 / EP;                              // tokens a wavefront selects for at a time
-    for (int t = wave * TW + lane / EP; t < 16; t += NW * TW) select_top_k<EP>(s_logit[t], E, k, t0 + t, t0 + t < T, ids, w);
+    for (int t = wave * TW + lane / EP; t < 16; t += NW * TW)
+        select_top_k<EP>(s_logit[t], E, k, t0 + t, t0 + t < T, ids, w, PLACE ? s_ids : nullptr, PLACE ? s_w : nullptr);
+    if constexpr (PLACE) {
+        static_assert(sizeof(s_part) >= 16 * MOE_MAX_EXPERTS * 4 && sizeof(s_logit) >= MOE_MAX_EXPERTS * 4, "");
+        place_rows<NW>(s_ids, s_w, T * k, E, (int32_t(*)[MOE_MAX_EXPERTS])s_part, (int32_t*)s_logit, place);
+    }
 }
 
 // EP: experts padded to a compile-time bound (a power of two, 8..64).
@@ -230,23 +301,30 @@ int launch_f32(const moe_shape& s, const void* x, const void* Wr, const float* b
 
 template <int NE, int NW>
 int launch_bf16(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
-                float* logits, hipStream_t st) {
+                float* logits, hipStream_t st, const PlaceOut* place) {
     const dim3 grid((s.T + 15) / 16), block(NW * 64);
-    hipLaunchKernelGGL((route_mfma_kernel<NE, NW>), grid, block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits,
-                       s.T, s.H, s.E, s.k);
+    if (place)
+        hipLaunchKernelGGL((route_mfma_kernel<NE, NW, true>), dim3(1), block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits,
+                           s.T, s.H, s.E, s.k, *place);
+    else
+        hipLaunchKernelGGL((route_mfma_kernel<NE, NW, false>), grid, block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits,
+                           s.T, s.H, s.E, s.k, PlaceOut{});
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }
 
 }  // namespace
 
+bool route_places(const moe_shape& s) { return s.dtype == MOE_DTYPE_BF16 && s.T > 0 && s.T <= 16; }
+
 int launch_route(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
-                 float* logits, hipStream_t st) {
+                 float* logits, hipStream_t st, const PlaceOut* place) {
     if (s.T == 0) return MOE_OK;
+    if (place && !route_places(s)) return MOE_ERR_INVALID_ARG;
     if (s.dtype == MOE_DTYPE_BF16) {
-        if (s.E <= 16) return launch_bf16<1, 16>(s, x, Wr, bias, ids, w, logits, st);
-        if (s.E <= 32) return launch_bf16<2, 16>(s, x, Wr, bias, ids, w, logits, st);
-        return launch_bf16<4, 8>(s, x, Wr, bias, ids, w, logits, st);
+        if (s.E <= 16) return launch_bf16<1, 16>(s, x, Wr, bias, ids, w, logits, st, place);
+        if (s.E <= 32) return launch_bf16<2, 16>(s, x, Wr, bias, ids, w, logits, st, place);
+        return launch_bf16<4, 8>(s, x, Wr, bias, ids, w, logits, st, place);
     }
     if (s.E <= 8) return launch_f32<8>(s, x, Wr, bias, ids, w, logits, st);
     if (s.E <= 16) return launch_f32<16>(s, x, Wr, bias, ids, w, logits, st);

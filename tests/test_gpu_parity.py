@@ -200,6 +200,29 @@ def test_f32_expert_ffn_row_counts_across_the_kernels(counts, H, F):
     assert torch.equal(y0, y)
 
 
+@pytest.mark.parametrize("T", [1, 3, 16, 17])
+@pytest.mark.parametrize("E,k", [(1, 1), (5, 2), (17, 17), (33, 4), (64, 64), (64, 8)])
+def test_layer_places_the_rows_of_a_handful_of_tokens(T, E, k):
+    """With at most 16 tokens the router's block also does the permutation: what the layer leaves in its workspace is what the two
+    calls give, bit by bit, and its output that of the stages."""
+    cfg = MoEConfig("place", "bf16", T=T, H=256, F=128, E=E, k=k, page_bytes=32 * 1024, seed=83)
+    case = Case(cfg)
+    s = case.shape
+    ids, w, _ = M.moe_route(s, case.x, case.Wr)
+    pm = M.moe_permute(s, ids, x=case.x, topk_w=w)
+    h, out = M.moe_expert_ffn(s, pm["x_perm"], pm["offsets"], case.pw.table_dev, case.pw.pages_dev, row_w=pm["row_w"])
+    y_ref = M.moe_combine(s, out, pm["row_of"])
+    ws = M.Workspace(s)
+    ws.buf.fill_(0xFF)
+    y, _ = M.moe_layer(s, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ws.view("topk_ids").reshape(-1), ids.reshape(-1)) and torch.equal(ws.view("topk_w").reshape(-1), w.reshape(-1))
+    for name in ("counts", "offsets", "row_src", "row_of", "row_w"):
+        assert torch.equal(ws.view(name).reshape(-1), pm[name].reshape(-1)), name
+    assert_status_clean(ws.view("status").tolist())
+    assert torch.equal(y, y_ref)
+
+
 @pytest.mark.parametrize("counts,H,F", [
     ([1, 0, 3], 128, 128),                     # two k-steps each way
     ([16], 512, 640),                            # as many k-steps as are under way, and two more
