@@ -218,8 +218,9 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
     }
     __syncthreads();
     constexpr int TW = 64 / EP;                              // tokens a wavefront selects for at a time
-    for (int t = wave * TW + lane / EP; t < 16; t += NW * TW)
-        select_top_k<EP>(s_logit[t], E, k, t0 + t, t0 + t < T, ids, w, PLACE ? s_ids : nullptr, PLACE ? s_w : nullptr);
+    const int live = min(16, T - t0);
+    for (int t = wave * TW; t < live; t += NW * TW)          // the whole wavefront, as long as its first token exists
+        select_top_k<EP>(s_logit[t + lane / EP], E, k, t0 + t + lane / EP, t + lane / EP < live, ids, w, PLACE ? s_ids : nullptr, PLACE ? s_w : nullptr);
     if constexpr (PLACE) {
         static_assert(sizeof(s_part) >= 16 * MOE_MAX_EXPERTS * 4 && sizeof(s_logit) >= MOE_MAX_EXPERTS * 4, "");
         place_rows<NW>(s_ids, s_w, T * k, E, (int32_t(*)[MOE_MAX_EXPERTS])s_part, (int32_t*)s_logit, place);
