@@ -148,10 +148,9 @@ __device__ __forceinline__ void place_rows(const int32_t* s_ids, const float* s_
 // NE: 16-expert tiles (experts padded to 16, 32 or 64); NW: wavefronts of a block; PLACE: the one block of the launch places
 // the rows as well.
 template <int NE, int NW, bool PLACE>
-__global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restrict__ x, const char* __restrict__ Wr,
-                                                         const float* __restrict__ bias, int32_t* __restrict__ ids,
-                                                         float* __restrict__ w, float* __restrict__ logits,
-                                                         int T, int H, int E, int k, const PlaceOut place) {
+__device__ __forceinline__ void route_mfma(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
+                                           int32_t* __restrict__ ids, float* __restrict__ w, float* __restrict__ logits,
+                                           int T, int H, int E, int k, const PlaceOut& place) {
     constexpr int EP = NE * 16;
     // Units whose loads are in flight together.  Beyond 32 experts two: with four a wavefront needs 193 registers and only one
     // block fits a compute unit; 65536 tokens of 2048, 64 experts, 8 per token: 251 us with four, 156 with two, 777 tokens 17
@@ -225,6 +224,20 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restr
         static_assert(sizeof(s_part) >= 16 * MOE_MAX_EXPERTS * 4 && sizeof(s_logit) >= MOE_MAX_EXPERTS * 4, "");
         place_rows<NW>(s_ids, s_w, T * k, E, (int32_t(*)[MOE_MAX_EXPERTS])s_part, (int32_t*)s_logit, place);
     }
+}
+
+template <int NE, int NW>
+__global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
+                                                             int32_t* __restrict__ ids, float* __restrict__ w, float* __restrict__ logits,
+                                                             int T, int H, int E, int k) {
+    route_mfma<NE, NW, false>(x, Wr, bias, ids, w, logits, T, H, E, k, PlaceOut{});
+}
+
+template <int NE, int NW>
+__global__ __launch_bounds__(NW * 64) void route_place_kernel(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
+                                                              int32_t* __restrict__ ids, float* __restrict__ w, int T, int H, int E, int k,
+                                                              const PlaceOut place) {
+    route_mfma<NE, NW, true>(x, Wr, bias, ids, w, nullptr, T, H, E, k, place);
 }
 
 // EP: experts padded to a compile-time bound (a power of two, 8..64).
@@ -305,11 +318,11 @@ int launch_bf16(const moe_shape& s, const void* x, const void* Wr, const float* 
                 float* logits, hipStream_t st, const PlaceOut* place) {
     const dim3 grid((s.T + 15) / 16), block(NW * 64);
     if (place)
-        hipLaunchKernelGGL((route_mfma_kernel<NE, NW, true>), dim3(1), block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits,
-                           s.T, s.H, s.E, s.k, *place);
+        hipLaunchKernelGGL((route_place_kernel<NE, NW>), dim3(1), block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, s.T, s.H, s.E,
+                           s.k, *place);
     else
-        hipLaunchKernelGGL((route_mfma_kernel<NE, NW, false>), grid, block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits,
-                           s.T, s.H, s.E, s.k, PlaceOut{});
+        hipLaunchKernelGGL((route_mfma_kernel<NE, NW>), grid, block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits, s.T, s.H,
+                           s.E, s.k);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }
@@ -321,7 +334,7 @@ bool route_places(const moe_shape& s) { return s.dtype == MOE_DTYPE_BF16 && s.T 
 int launch_route(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
                  float* logits, hipStream_t st, const PlaceOut* place) {
     if (s.T == 0) return MOE_OK;
-    if (place && !route_places(s)) return MOE_ERR_INVALID_ARG;
+    if (place && (!route_places(s) || logits)) return MOE_ERR_INVALID_ARG;
     if (s.dtype == MOE_DTYPE_BF16) {
         if (s.E <= 16) return launch_bf16<1, 16>(s, x, Wr, bias, ids, w, logits, st, place);
         if (s.E <= 32) return launch_bf16<2, 16>(s, x, Wr, bias, ids, w, logits, st, place);
