@@ -9,6 +9,7 @@ import of a symbol fails loudly; there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -128,13 +129,16 @@ def _check(status: int, where: str):
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the current stream's handle, without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t: Optional[torch.Tensor], dtype, shape, name: str) -> Optional[int]:
     if t is None:
         return None
+    if t.is_cuda and t.dtype is dtype and (shape is None or t.shape == shape) and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name}: must be a CUDA/HIP device tensor")
     if t.dtype != dtype:
@@ -163,6 +167,12 @@ def tile_bytes(s: MoEShape) -> int:
 
 def pages_required(s: MoEShape):
     """(pages_gu, pages_d) per expert."""
+    return _pages_required(s.T, s.H, s.F, s.E, s.k, s.dtype, s.page_bytes)
+
+
+@functools.lru_cache(maxsize=256)                    # a function of the sizes alone; an invalid shape raises every time
+def _pages_required(*fields):
+    s = MoEShape(*fields)
     a, b = _i64(0), _i64(0)
     _check(_lib().moe_pages_required(ctypes.byref(s), ctypes.byref(a), ctypes.byref(b)), "moe_pages_required")
     return a.value, b.value
@@ -268,13 +278,18 @@ def moe_permute(s: MoEShape, topk_ids, x=None, topk_w=None, stream=None):
     row_of = torch.empty(R, dtype=torch.int32, device=dev)
     row_w = torch.empty(R, dtype=torch.float32, device=dev) if topk_w is not None else None
     x_perm = torch.empty((R, s.H), dtype=s.torch_dtype, device=dev) if x is not None else None
-    wsb = workspace_layout(s).permute_bytes
-    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
+    wsb = max(_permute_bytes(s.T, s.H, s.F, s.E, s.k, s.dtype, s.page_bytes), 16)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
     _check(_lib().moe_permute(ctypes.byref(s), pi, pw, px, counts.data_ptr(), offsets.data_ptr(), row_src.data_ptr(),
                               row_of.data_ptr(), None if row_w is None else row_w.data_ptr(),
-                              None if x_perm is None else x_perm.data_ptr(), ws.data_ptr(), ws.numel(),
+                              None if x_perm is None else x_perm.data_ptr(), ws.data_ptr(), wsb,
                               _stream(stream)), "moe_permute")
     return dict(counts=counts, offsets=offsets, row_src=row_src, row_of=row_of, row_w=row_w, x_perm=x_perm)
+
+
+@functools.lru_cache(maxsize=256)
+def _permute_bytes(*fields):
+    return workspace_layout(MoEShape(*fields)).permute_bytes
 
 
 def moe_expert_ffn(s: MoEShape, x_perm, offsets, page_table, page_pool, row_w=None, status=None, stream=None):
@@ -541,6 +556,12 @@ def make_linear_shape(T, K, N, page_bytes) -> LinearShape:
 
 
 def linear_pages_required(ls: LinearShape) -> int:
+    return _linear_pages_required(ls.T, ls.K, ls.N, ls.dtype, ls.page_bytes)
+
+
+@functools.lru_cache(maxsize=256)
+def _linear_pages_required(*fields):
+    ls = LinearShape(*fields)
     v = _i64(0)
     _check(_lib().moe_linear_pages_required(ctypes.byref(ls), ctypes.byref(v)), "moe_linear_pages_required")
     return int(v.value)
@@ -562,8 +583,8 @@ def moe_linear(ls: LinearShape, x, page_table, page_pool, status=None, stream=No
     pp = _dev(page_pool, torch.uint8, None, "page_pool")
     ps = _dev(status, torch.int32, (4,), "status")
     out = torch.empty((ls.T, ls.N), dtype=torch.float32, device=x.device)
-    ws = torch.empty(16, dtype=torch.uint8, device=x.device)
-    _check(_lib().moe_linear(ctypes.byref(ls), px, pt, pp, int(page_pool.shape[0]), out.data_ptr(), ws.data_ptr(), 16, ps,
+    # the workspace is checked and not used: the output stands in for one
+    _check(_lib().moe_linear(ctypes.byref(ls), px, pt, pp, int(page_pool.shape[0]), out.data_ptr(), out.data_ptr(), 16, ps,
                              _stream(stream)), "moe_linear")
     return out
 
@@ -632,9 +653,9 @@ def moe_pre_attention(qkv_proj: LinearShape, hidden, delta, norm_gamma, eps, qkv
     x_norm = torch.empty((T, H), dtype=torch.bfloat16, device=dev)
     qkv = torch.empty((T, qkv_proj.N), dtype=torch.float32, device=dev)
     qkv16 = torch.empty((T, qkv_proj.N), dtype=torch.bfloat16, device=dev) if want_bf16 else None
-    ws = torch.empty(16, dtype=torch.uint8, device=dev)
+    # the workspace is checked and not used: an output stands in for one
     _check(_lib().moe_pre_attention(ctypes.byref(qkv_proj), ph, pd, pg, float(eps), pt, pp, int(page_pool.shape[0]),
                                     hidden_out.data_ptr(), x_norm.data_ptr(), qkv.data_ptr(),
-                                    None if qkv16 is None else qkv16.data_ptr(), ws.data_ptr(), 16, _stream(stream)),
+                                    None if qkv16 is None else qkv16.data_ptr(), qkv.data_ptr(), 16, _stream(stream)),
            "moe_pre_attention")
     return hidden_out, x_norm, qkv, qkv16
