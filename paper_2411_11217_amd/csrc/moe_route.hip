@@ -26,7 +26,7 @@
 //
 // With at most 16 tokens of bf16 data one block has all of them, and in moe_layer it does the permutation too, with the
 // counting sort of moe_permute.hip on the ids that it has in LDS: a launch less, which is 4 to 5 us of a call that can
-// be as short as 30.
+// be as short as 30.  With f32 data the same is done for short rows (route_place_f32_kernel).
 #include "moe_place.h"
 
 namespace moe {
@@ -240,25 +240,19 @@ __global__ __launch_bounds__(NW * 64) void route_place_kernel(const char* __rest
     route_mfma<NE, NW, true>(x, Wr, bias, ids, w, nullptr, T, H, E, k, place);
 }
 
-// EP: experts padded to a compile-time bound (a power of two, 8..64).
+// EP: experts padded to a compile-time bound (a power of two, 8..64).  The logits of the 64 / EP tokens from t0 on, over the chunks
+// of eight elements first, first + step, ..: lane j of a wavefront gets the sum of value j = token * EP + expert over its lanes.
 template <int EP>
-__global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x, const float* __restrict__ Wr,
-                                                    const float* __restrict__ bias, int32_t* __restrict__ ids,
-                                                    float* __restrict__ w, float* __restrict__ logits,
-                                                    int T, int H, int E, int k) {
-    constexpr int TPB = 64 / EP;                      // tokens per block
-    __shared__ float s_part[4][64];
-    __shared__ float s_logit[64];
+__device__ __forceinline__ float partial_logits(const float* __restrict__ x, const float* __restrict__ Wr, int t0, int T, int H, int E,
+                                                int first, int step) {
+    constexpr int TPB = 64 / EP;                      // tokens
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.x * TPB;
-
     float acc[64];                                    // value v = t * EP + e
 #pragma unroll
     for (int v = 0; v < 64; ++v) acc[v] = 0.f;
 
     const int chunks = H >> 3;
-    for (int c = threadIdx.x; c < chunks; c += 256) {
+    for (int c = first; c < chunks; c += step) {
         float xv[TPB][8];
 #pragma unroll
         for (int t = 0; t < TPB; ++t) {
@@ -289,7 +283,21 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x,
             acc[i] = keep + __shfl_xor(give, m, 64);
         }
     }
-    s_part[wave][lane] = acc[0];                      // lane j: value j summed over this wavefront's part of H
+    return acc[0];
+}
+
+template <int EP>
+__global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x, const float* __restrict__ Wr,
+                                                    const float* __restrict__ bias, int32_t* __restrict__ ids,
+                                                    float* __restrict__ w, float* __restrict__ logits,
+                                                    int T, int H, int E, int k) {
+    constexpr int TPB = 64 / EP;                      // tokens per block
+    __shared__ float s_part[4][64];
+    __shared__ float s_logit[64];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int t0 = blockIdx.x * TPB;
+    s_part[wave][lane] = partial_logits<EP>(x, Wr, t0, T, H, E, threadIdx.x, 256);
     __syncthreads();
     if (threadIdx.x < 64) {
         const int v = threadIdx.x, t = v / EP, e = v % EP;
@@ -302,9 +310,42 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x,
     if (wave == 0) select_top_k<EP>(s_logit + lane / EP * EP, E, k, t0 + lane / EP, t0 + lane / EP < T, ids, w);
 }
 
+// Few tokens of a short row: a row has one chunk of eight elements per lane at most, so a wavefront of the kernel above has all the
+// work of its block.  Here it is one of the kPlaceWaves of the only block, which then places the rows as well.  The same bits.
+constexpr int kPlaceWaves = 8, kPlaceElements = 512;
+constexpr int experts_padded(int E) { return E <= 8 ? 8 : E <= 16 ? 16 : E <= 32 ? 32 : 64; }
+
+template <int EP>
+__global__ __launch_bounds__(kPlaceWaves * 64) void route_place_f32_kernel(const float* __restrict__ x, const float* __restrict__ Wr,
+                                                                          const float* __restrict__ bias, int32_t* __restrict__ ids,
+                                                                          float* __restrict__ w, int T, int H, int E, int k, const PlaceOut place) {
+    constexpr int TPB = 64 / EP;                      // tokens per wavefront
+    __shared__ float s_logit[kPlaceWaves][64];
+    __shared__ int32_t s_ids[kPlaceWaves * TPB * EP];  // k <= E <= EP
+    __shared__ float s_w[kPlaceWaves * TPB * EP];
+    __shared__ int32_t s_cnt[16][MOE_MAX_EXPERTS], s_start[MOE_MAX_EXPERTS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t0 = wave * TPB;
+    if (t0 < T) {
+        const int e = lane % EP;
+        float sum = partial_logits<EP>(x, Wr, t0, T, H, E, lane, 64);
+        if (bias != nullptr && e < E) sum += bias[e];
+        s_logit[wave][lane] = sum;                    // read by this wavefront alone
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        select_top_k<EP>(s_logit[wave] + lane / EP * EP, E, k, t0 + lane / EP, t0 + lane / EP < T, ids, w, s_ids, s_w);
+    }
+    place_rows<kPlaceWaves>(s_ids, s_w, T * k, E, s_cnt, s_start, place);
+}
+
 template <int EP>
 int launch_f32(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
-               float* logits, hipStream_t st) {
+               float* logits, hipStream_t st, const PlaceOut* place) {
+    if (place) {
+        hipLaunchKernelGGL((route_place_f32_kernel<EP>), dim3(1), dim3(kPlaceWaves * 64), 0, st, (const float*)x, (const float*)Wr, bias, ids, w,
+                           s.T, s.H, s.E, s.k, *place);
+        MOE_HIP_TRY(hipGetLastError());
+        return MOE_OK;
+    }
     constexpr int tokens_per_block = 64 / EP;
     const dim3 grid((s.T + tokens_per_block - 1) / tokens_per_block), block(256);
     hipLaunchKernelGGL((route_kernel<EP>), grid, block, 0, st, (const float*)x, (const float*)Wr, bias, ids, w, logits, s.T,
@@ -329,7 +370,11 @@ int launch_bf16(const moe_shape& s, const void* x, const void* Wr, const float* 
 
 }  // namespace
 
-bool route_places(const moe_shape& s) { return s.dtype == MOE_DTYPE_BF16 && s.T > 0 && s.T <= 16; }
+bool route_places(const moe_shape& s) {
+    if (s.T <= 0) return false;
+    if (s.dtype == MOE_DTYPE_BF16) return s.T <= 16;
+    return s.H <= kPlaceElements && s.T <= kPlaceWaves * 64 / experts_padded(s.E);
+}
 
 int launch_route(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
                  float* logits, hipStream_t st, const PlaceOut* place) {
@@ -340,10 +385,10 @@ int launch_route(const moe_shape& s, const void* x, const void* Wr, const float*
         if (s.E <= 32) return launch_bf16<2, 16>(s, x, Wr, bias, ids, w, logits, st, place);
         return launch_bf16<4, 8>(s, x, Wr, bias, ids, w, logits, st, place);
     }
-    if (s.E <= 8) return launch_f32<8>(s, x, Wr, bias, ids, w, logits, st);
-    if (s.E <= 16) return launch_f32<16>(s, x, Wr, bias, ids, w, logits, st);
-    if (s.E <= 32) return launch_f32<32>(s, x, Wr, bias, ids, w, logits, st);
-    return launch_f32<64>(s, x, Wr, bias, ids, w, logits, st);
+    if (s.E <= 8) return launch_f32<8>(s, x, Wr, bias, ids, w, logits, st, place);
+    if (s.E <= 16) return launch_f32<16>(s, x, Wr, bias, ids, w, logits, st, place);
+    if (s.E <= 32) return launch_f32<32>(s, x, Wr, bias, ids, w, logits, st, place);
+    return launch_f32<64>(s, x, Wr, bias, ids, w, logits, st, place);
 }
 
 }  // namespace moe

@@ -200,12 +200,13 @@ def test_f32_expert_ffn_row_counts_across_the_kernels(counts, H, F):
     assert torch.equal(y0, y)
 
 
-@pytest.mark.parametrize("T", [1, 3, 16, 17])
-@pytest.mark.parametrize("E,k", [(1, 1), (5, 2), (17, 17), (33, 4), (64, 64), (64, 8)])
-def test_layer_places_the_rows_of_a_handful_of_tokens(T, E, k):
-    """With at most 16 tokens the router's block also does the permutation: what the layer leaves in its workspace is what the two
-    calls give, bit by bit, and its output that of the stages."""
-    cfg = MoEConfig("place", "bf16", T=T, H=256, F=128, E=E, k=k, page_bytes=32 * 1024, seed=83)
+@pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 3), ("bf16", 16), ("bf16", 17), ("f32", 1), ("f32", 8), ("f32", 9), ("f32", 31),
+                                     ("f32", 32), ("f32", 63), ("f32", 64), ("f32", 65)])
+@pytest.mark.parametrize("E,k", [(1, 1), (5, 2), (8, 8), (16, 3), (17, 17), (33, 4), (64, 64), (64, 8)])
+def test_layer_places_the_rows_of_a_handful_of_tokens(dtype, T, E, k):
+    """With few tokens (bf16: 16, f32: 512 over the padded number of experts) the router's block also does the permutation: what
+    the layer leaves in its workspace is what the two calls give, bit by bit, and its output that of the stages."""
+    cfg = MoEConfig("place", dtype, T=T, H=256, F=128, E=E, k=k, page_bytes=32 * 1024, seed=83)
     case = Case(cfg)
     s = case.shape
     ids, w, _ = M.moe_route(s, case.x, case.Wr)
