@@ -202,7 +202,7 @@ def main():
         achieved = flops_gu / t_gu / 1e12
         each = cfg.R // cfg.E                              # the library's own lines between its kernels
         kernel = ("ffn_gemm_bf16<0>" if each > 80 else "ffn_rows_bf16<0>") if cfg.dtype == "bf16" else \
-            "ffn_rows_f32<0>" if each > 32 else "ffn_few_rows_f32<0>"
+            "ffn_split_f32<0>" if each > 32 else "ffn_few_rows_f32<0>"
         roofline = {"bound": "mfma", "kernel": kernel + " (gate/up expert GEMM + SwiGLU epilogue)",
                     "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": MEASURED_TRAFFIC.get(args.config),

@@ -17,7 +17,8 @@
 //     a block has, the more MFMAs share the split of its weights, and blocks of other wavefronts on the same SIMD fill
 //     the matrix cores meanwhile (three per SIMD).  Few columns (MODE 1): KG = 2, two groups of four wavefronts with 32 k of a step each.
 //     1024 x 2816, 700 tokens, against the float32 MFMA with blocks of 32 rows: gate/up 177 / 111 us, down 107 / 77, layer 289 / 202;
-//     8000 tokens 2440 / 1580; 256 x 512, 1100 tokens 64 / 47.  Matrix cores busy 0.57 of the gate/up launch.
+//     8000 tokens 2440 / 1580; 256 x 512, 1100 tokens 64 / 47.  700 tokens: matrix cores busy 0.54 and 0.40 of the launches' cycles,
+//     vector instructions 0.63 and 0.59.
 //   ffn_few_rows_f32: at most 32 rows x 16 columns (MODE 0: 16 features) on v_mfma_f32_16x16x4_f32, the wavefronts split k instead: every fourth
 //     k-step each, activations straight from memory, no barrier until the four partial tiles are added through LDS in a
 //     fixed order.  A lane's share of an operand is a 16-byte chunk (four consecutive k of one row): lane l holds chunk 4q +
@@ -242,17 +243,6 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
                 __builtin_amdgcn_sched_barrier(0);
             }
             add(NRT - G, (NRT / G - 1) & 1);
-        };
-        // the vector operations of the split between the MFMAs
-        auto interleave = [&]() __attribute__((always_inline)) {
-#ifdef ILV
-            constexpr int kMfmas = NRT * NB * 6, kOps = (NA + NB) * 44, kEach = (kOps + kMfmas - 1) / kMfmas + ILV;
-#pragma unroll
-            for (int i = 0; i < kMfmas; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, kEach, 0);
-            }
-#endif
         };
 #pragma unroll
         for (int d = 0; d < D; ++d) load(d, d);
