@@ -9,7 +9,8 @@
 //     six MFMAs on the accumulator 7.3e-7 / 5.8e-7, this way 1.8e-7 / 1.5e-7 (1024 x 2816; 256 x 512: 4.2e-7 / 4.1e-7, 3.4e-7 /
 //     2.4e-7, 1.1e-7 / 0.8e-7).  Infinities and values that bf16 rounds to one give NaN (inf - inf), and parts of tiny
 //     values leave the range of bf16: a wavefront whose sums hold anything that is not finite, or not zero and below 2^-80,
-//     computes its tile again on the float32 MFMA, operands straight from memory.
+//     computes its tile again on the float32 MFMA, operands straight from memory.  (A sum of 2^-80 or more from values below 2^-110,
+//     whose third part is not a normal bf16 any more, needs factors beyond 2^30 on the other side.)
 //     A block owns 16 RT rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the columns; a
 //     weight element is used by one wavefront alone and goes from the page straight into registers, where it is split.
 //     The activations are split once per block and pass through LDS (two stages; the registers hold the next step or two), one
