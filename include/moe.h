@@ -164,7 +164,8 @@ int moe_permute(const moe_shape* s, const int32_t* topk_ids, const float* topk_w
  * for its own status words, in one of its kernels).
  * A row's h and out do not depend on how many rows its call has with bf16 data: every sum is one chain along the
  * reduction.  With f32 data they do in their last bits: the kernels for few and for more rows per expert on average
- * (T * k / E) add in different orders.  Streamed and resident calls of one shape give the same bits. */
+ * (T * k / E) add in different orders.  What the other rows hold changes no bit of a row.  Streamed and resident calls
+ * of one shape give the same bits. */
 int moe_expert_ffn(const moe_shape* s, const void* x_perm, const int32_t* offsets,
                    const int32_t* page_table, const void* page_pool, int64_t pool_pages,
                    const float* row_w, void* h_ws, float* out, int32_t* status, void* stream);

@@ -8,9 +8,9 @@
 //     every MFMA rounds at the size of the accumulator.  Relative error against float64 of h / of out for a given h: float32 MFMA 8.7e-7 / 9.5e-7,
 //     six MFMAs on the accumulator 7.3e-7 / 5.8e-7, this way 1.8e-7 / 1.5e-7 (1024 x 2816; 256 x 512: 4.2e-7 / 4.1e-7, 3.4e-7 /
 //     2.4e-7, 1.1e-7 / 0.8e-7).  Infinities and values that bf16 rounds to one give NaN (inf - inf), and parts of tiny
-//     values leave the range of bf16: a wavefront whose sums hold anything that is not finite, or not zero and below 2^-80,
-//     computes its tile again on the float32 MFMA, operands straight from memory.  (A sum of 2^-80 or more from values below 2^-110,
-//     whose third part is not a normal bf16 any more, needs factors beyond 2^30 on the other side.)
+//     values leave the range of bf16: a sum that is not finite, or not zero and below 2^-80, is replaced by that of the float32 MFMA, operands straight
+//     from memory.  A wavefront does that for the row tiles of 16 that hold such a sum, and stores those sums alone.  (A sum of 2^-80 or more
+//     from values below 2^-110, whose third part is not a normal bf16 any more, needs factors beyond 2^30 on the other side.)
 //     A block owns 16 RT rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the columns; a
 //     weight element is used by one wavefront alone and goes from the page straight into registers, where it is split.
 //     The activations are split once per block and pass through LDS (two stages; the registers hold the next step or two), one
@@ -292,54 +292,77 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
 
     // register v of lane (r, g): row i * 16 + g * 4 + v, column r
     const int col = nt * 64 + wave * 16 + r;
-    auto store = [&](int i, const f32x4 (&a)[NB]) __attribute__((always_inline)) {
+    auto store = [&](int i, const f32x4 (&a)[NB], uint32_t rows) __attribute__((always_inline)) {       // rows: bit v for register v
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = i * 16 + g * 4 + v;
-            if (row >= rows_here) continue;
+            if (row >= rows_here || !((rows >> v) & 1)) continue;
             float* o = (float*)p.out + (int64_t)(row0 + row) * p.ldo + col;
             if (MODE == 0) *o = silu_mul(a[0][v], a[NB - 1][v]);
             else *o = a[0][v] * (p.row_w ? p.row_w[row0 + row] : 1.0f);
         }
     };
-    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) store(i, acc[i], 15);
+    // Odd sums: not finite, or not zero and below 2^-80.  Only these are replaced, so that a row's bits depend on its own values alone
+    // and not on what else is in its tile.
+    float least = INFINITY, finite = 0.f;            // the smallest magnitude that is not zero; 0, or NaN
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float m = fabsf(acc[i][b][v]);
-                odd = odd || !(m < INFINITY) || (m < 0x1p-80f && m != 0.f);
+            for (int b = 0; b < NB; ++b) {
+                least = fminf(least, acc[i][b][v] == 0.f ? INFINITY : fabsf(acc[i][b][v]));
+                finite = fmaf(acc[i][b][v], 0.f, finite);
             }
-    if (__builtin_expect(__ballot(odd) == 0, 1)) {
+    if (__builtin_expect(__ballot(least < 0x1p-80f || finite != 0.f) != 0, 0)) {
+        uint32_t odd = 0;                            // bit 4 i + v: register v of row tile i
 #pragma unroll
-        for (int i = 0; i < RT; ++i) store(i, acc[i]);
-    } else {
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const float m = fabsf(acc[i][b][v]);
+                    odd |= (uint32_t)(!(m < INFINITY) || (m < 0x1p-80f && m != 0.f)) << (4 * i + v);
+                }
         for (int i = 0; i * 16 < rows_here; ++i) {
+            const uint32_t mine = (odd >> (4 * i)) & 15;
+            if (!__ballot(mine != 0)) continue;
             const char* arow = p.A + source_row(p, row0 + min(i * 16 + r, rows_here - 1)) * p.lda_bytes + g * 16;
-            f32x4 sum[NB];
+            f32x4 sum[NB], a[2][4], wt[2][NB][4];
 #pragma unroll
             for (int b = 0; b < NB; ++b) sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
             weights_start();
-            for (int kt = 0; kt < p.KT; ++kt) {
+            auto load = [&](int kt, int slot) __attribute__((always_inline)) {
                 if (kt > 0) {
 #pragma unroll
                     for (int b = 0; b < NB; ++b) w[b].next(p, trow, 1, bad);
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 a = *(const f32x4*)(arow + (int64_t)kt * 256 + q * 64);
-                    f32x4 wt[NB];
+                    a[slot][q] = *(const f32x4*)(arow + (int64_t)kt * 256 + q * 64);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) wt[b] = *(const f32x4*)(w[b].tile + boff[q & 1] + (q >> 1) * 128);
+                    for (int b = 0; b < NB; ++b) wt[slot][b][q] = *(const f32x4*)(w[b].tile + boff[q & 1] + (q >> 1) * 128);
+                }
+            };
+            auto multiply = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) sum[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], wt[b][j], sum[b], 0, 0, 0);
-                }
+                        for (int b = 0; b < NB; ++b) sum[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[slot][q][j], wt[slot][b][q][j], sum[b], 0, 0, 0);
+            };
+            load(0, 0);
+            for (int kt = 0; kt < p.KT; kt += 2) {   // KT is even
+                load(kt + 1, 1);
+                multiply(0);
+                if (kt + 2 < p.KT) load(kt + 2, 0);
+                multiply(1);
             }
-            store(i, sum);
+            store(i, sum, mine);
         }
     }
     if (bad && lane == 0 && p.status) atomicOr(p.status, 1);

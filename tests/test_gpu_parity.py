@@ -323,6 +323,23 @@ def test_f32_split_products_of_extreme_values():
     assert np.abs(h[60].double().numpy() - (0.5 * g64 * u64).numpy()).max() <= 2.0 ** -149     # underflows: silu(g) = g / 2 there
 
 
+@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([150, 40, 9, 260], 256, 4224)])       # gate/up: 64 and 128 rows a block
+@pytest.mark.parametrize("scale", [float("inf"), float("nan"), 2.0 ** -45, 2.0 ** -100])
+def test_f32_rows_do_not_depend_on_their_neighbours(counts, H, F, scale):
+    """Rows of infinities, NaN or tiny values (2^-45: sums of the down launch alone) change no bit of h and out of any other row."""
+    cfg = MoEConfig("neighbours32", "f32", T=sum(counts), H=H, F=F, E=len(counts), k=1, page_bytes=96 * 1024, seed=85)
+    case = Case(cfg)
+    offsets = _dev_i32(np.concatenate([[0], np.cumsum(counts)]))
+    h0, out0 = M.moe_expert_ffn(case.shape, case.x, offsets, case.pw.table_dev, case.pw.pages_dev)
+    rows = torch.tensor([3, 20, 21, 60, counts[0] + 1, sum(counts) - 1])
+    x = case.x.clone()
+    x[rows] *= scale
+    h, out = M.moe_expert_ffn(case.shape, x, offsets, case.pw.table_dev, case.pw.pages_dev)
+    others = torch.ones(sum(counts), dtype=torch.bool)
+    others[rows] = False
+    assert torch.equal(h.cpu()[others], h0.cpu()[others]) and torch.equal(out.cpu()[others], out0.cpu()[others])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,H,E,k", [(1, 128, 1, 1), (17, 128, 3, 3), (100, 384, 16, 4), (33, 1024, 17, 2), (250, 256, 32, 8),
                                      (47, 640, 33, 5), (130, 2048, 64, 64), (2000, 512, 8, 2)])
