@@ -165,7 +165,11 @@ int moe_permute(const moe_shape* s, const int32_t* topk_ids, const float* topk_w
  * A row's h and out do not depend on how many rows its call has with bf16 data: every sum is one chain along the
  * reduction.  With f32 data they do in their last bits: the kernels for few and for more rows per expert on average
  * (T * k / E) add in different orders.  What the other rows hold changes no bit of a row.  Streamed and resident calls
- * of one shape give the same bits. */
+ * of one shape give the same bits.
+ * With f32 data all finite operands, subnormals among them, have the accuracy of float32 products.  (The kernel for more
+ * rows splits its operands into bf16.  Sums that are Inf, NaN or so small that the split could show in them, below K *
+ * 2^-108 times the largest magnitudes of their row and column, it forms again from float32 products: a call in which
+ * most sums are of that kind takes about twice as long.) */
 int moe_expert_ffn(const moe_shape* s, const void* x_perm, const int32_t* offsets,
                    const int32_t* page_table, const void* page_pool, int64_t pool_pages,
                    const float* row_w, void* h_ws, float* out, int32_t* status, void* stream);

@@ -7,10 +7,14 @@
 //     registers of their own, from zero, and a float32 addition takes the sum over: with all six on the accumulator itself
 //     every MFMA rounds at the size of the accumulator.  Relative error against float64 of h / of out for a given h: float32 MFMA 8.7e-7 / 9.5e-7,
 //     six MFMAs on the accumulator 7.3e-7 / 5.8e-7, this way 1.8e-7 / 1.5e-7 (1024 x 2816; 256 x 512: 4.2e-7 / 4.1e-7, 3.4e-7 /
-//     2.4e-7, 1.1e-7 / 0.8e-7).  Infinities and values that bf16 rounds to one give NaN (inf - inf), and parts of tiny
-//     values leave the range of bf16: a sum that is not finite, or not zero and below 2^-80, is replaced by that of the float32 MFMA, operands straight
-//     from memory.  A wavefront does that for the row tiles of 16 that hold such a sum, and stores those sums alone.  (A sum of 2^-80 or more
-//     from values below 2^-110, whose third part is not a normal bf16 any more, needs factors beyond 2^30 on the other side.)
+//     2.4e-7, 1.1e-7 / 0.8e-7).
+//     What the parts cannot hold: infinities and values that bf16 rounds to one give NaN (inf - inf), and of a value below
+//     2^-110 up to 2^-134 is lost, half the last bit of a bf16 subnormal (neither the conversion nor the MFMA flushes them).  A sum of K
+//     products loses at most K 2^-134 (X + W) of that, with X and W the largest magnitudes of its row and its column, which the threads
+//     note as they split (a v_max3 for two values: 2 - 3 % of the layer), and less than K 2^-146 in products that underflow.  A sum that
+//     is not finite, or below 2^26 times these with neither its row nor its column zero, is replaced by that of the float32 MFMA, operands straight from
+//     memory: a wavefront does that for the row tiles of 16 that hold such a sum, and stores those sums alone.  With X = W = 1 and K = 1024
+//     the limit is 2^-97; ordinary sums meet it when they cancel to 0 exactly, one in some 30 million.
 //     A block owns 16 RT rows x 64 columns (MODE 0: 64 features, gate and up).  The four wavefronts split the columns; a
 //     weight element is used by one wavefront alone and goes from the page straight into registers, where it is split.
 //     The activations are split once per block and pass through LDS (two stages; the registers hold the next step or two), one
@@ -95,7 +99,6 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f +
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-
 __device__ __forceinline__ int pack_bf16(float a, float b) {          // both rounded to nearest even
     int v = 0;
 #ifdef __HIP_DEVICE_COMPILE__
@@ -104,11 +107,19 @@ __device__ __forceinline__ int pack_bf16(float a, float b) {          // both ro
     return v;
 }
 
-// eight values, each as a sum of three bf16: part[0] + part[1] + part[2]
-__device__ __forceinline__ void split_bf16(const f32x4& lo, const f32x4& hi, i32x4 (&part)[3]) {
+// the largest of m, |a| and |b|; a NaN among them does not matter here
+__device__ __forceinline__ void raise_to(float& m, float a, float b) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+#endif
+}
+
+// eight values, each as a sum of three bf16: part[0] + part[1] + part[2]; top: raised to the largest magnitude among them
+__device__ __forceinline__ void split_bf16(const f32x4& lo, const f32x4& hi, i32x4 (&part)[3], float& top) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         float a = j < 2 ? lo[2 * j] : hi[2 * j - 4], b = j < 2 ? lo[2 * j + 1] : hi[2 * j - 3];
+        raise_to(top, a, b);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const int v = pack_bf16(a, b);
@@ -143,7 +154,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
     };
     weights_start();
     const int n = (nt & 1) * 64 + wave * 16 + r;
-    const int boff[2] = {chunk_offset(n, 0, g), chunk_offset(n, 1, g)};     // half a k-step on: 128 bytes more
+    const int boff = chunk_offset(n, 0, g);          // the next chunk: bit 6 the other way; half a k-step on: 128 bytes more
 
     // this thread's chunks, a 64-byte piece apart, of rows tid / 4 and 64 + tid / 4 (KG = 2: the second group the other 32 k)
     const int a_row = (tid >> 2) & 63, a_ch = tid & 3;
@@ -160,6 +171,11 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float a_top[AJ], w_top[NB];                      // largest magnitudes of this thread's activations (by row) and weights
+#pragma unroll
+    for (int j = 0; j < AJ; ++j) a_top[j] = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) w_top[b] = 0.f;
 
     // NRT: row tiles that are loaded and multiplied.  A step is 32 * KG k.
     auto main_loop = [&](auto nrt_c) __attribute__((always_inline)) {
@@ -177,18 +193,24 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
                 for (int b = 0; b < NB; ++b) w[b].next(p, trow, 1, bad);
             }
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NB; ++b) {
+                int o = boff;
+                asm("" : "+v"(o) : "s"(s));          // both offsets are formed here, and not kept through the loop
 #pragma unroll
-                for (int c = 0; c < 2; ++c) breg[slot][b][c] = *(const f32x4*)(w[b].tile + boff[c] + (KG == 2 ? kg : s & 1) * 128);
+                for (int c = 0; c < 2; ++c) breg[slot][b][c] = *(const f32x4*)(w[b].tile + (o ^ (c * 64)) + (KG == 2 ? kg : s & 1) * 128);
+            }
         };
         auto copy_rows = [&](int s, int slot) __attribute__((always_inline)) {
+            char* dst = (char*)p.a_copy + (int64_t)row0 * p.lda_bytes + (int64_t)s * (128 * KG);
+            int first = a_row;
+            asm("" : "+v"(first) : "s"(s));          // as above
 #pragma unroll
             for (int j = 0; j < NA; ++j) {
-                const int row = j * 64 + a_row;
-                char* dst = (char*)p.a_copy + (int64_t)(row0 + row) * p.lda_bytes + a_ch * 16 + kg * 128 + (int64_t)s * (128 * KG);
+                const int row = j * 64 + first;
+                const uint32_t o = (uint32_t)row * (uint32_t)p.lda_bytes + a_ch * 16 + kg * 128;
                 if (row < rows_here) {
-                    *(f32x4*)dst = areg[slot][j][0];
-                    *(f32x4*)(dst + 64) = areg[slot][j][1];
+                    *(f32x4*)(dst + o) = areg[slot][j][0];
+                    *(f32x4*)(dst + o + 64) = areg[slot][j][1];
                 }
             }
         };
@@ -196,7 +218,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
 #pragma unroll
             for (int j = 0; j < NA; ++j) {
                 i32x4 part[3];
-                split_bf16(areg[slot][j][0], areg[slot][j][1], part);
+                split_bf16(areg[slot][j][0], areg[slot][j][1], part, a_top[j]);
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     if (BM % 64 == 0 || j * 64 + a_row < BM) *(i32x4*)(st + q * kPlane + j * 4096 + a_wr) = part[q];
@@ -204,7 +226,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
             }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                split_bf16(breg[slot][b][0], breg[slot][b][1], bp[b]);
+                split_bf16(breg[slot][b][0], breg[slot][b][1], bp[b], w_top[b]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -270,32 +292,58 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
     else if (RT > 4 && rows_here > 64) main_loop(std::integral_constant<int, RT < 6 ? RT : 6>{});
     else if (rows_here > 32) main_loop(std::integral_constant<int, 4>{});
     else main_loop(std::integral_constant<int, 2>{});
+    // the thread's coordinates once more: kept through the loop they would take registers that it does not have
+    int tid_e = tid;
+    asm volatile("" : "+v"(tid_e));
+    const int lane_e = tid_e & 63, r_e = lane_e & 15, g_e = lane_e >> 4, row_e = (tid_e >> 2) & 63;
+    // what the four threads of a row, the four lanes of a column and the two groups have seen; stage 0 was last read before
+    // the last barrier of the loop, with KG = 2 the second group's sums lie there
+    float* s_top = (float*)(smem + (KG == 2 ? RT * NB * 4096 : 0));          // [KG][BM] rows, KG = 2: [NB][256] weights of the second group
+#pragma unroll
+    for (int j = 0; j < AJ; ++j) {
+        a_top[j] = fmaxf(a_top[j], __shfl_xor(a_top[j], 1, 64));
+        a_top[j] = fmaxf(a_top[j], __shfl_xor(a_top[j], 2, 64));
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        w_top[b] = fmaxf(w_top[b], __shfl_xor(w_top[b], 16, 64));
+        w_top[b] = fmaxf(w_top[b], __shfl_xor(w_top[b], 32, 64));
+    }
+    if (KG == 2) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < AJ; ++j)
+        if ((tid_e & 3) == 0 && (BM % 64 == 0 || j * 64 + row_e < BM)) s_top[kg * BM + j * 64 + row_e] = j * 64 + row_e < rows_here ? a_top[j] : 0.f;
     if constexpr (KG == 2) {                         // the second group's sums are added to the first's
-        __syncthreads();
-        f32x4* part = (f32x4*)smem + (tid & 255);
+        f32x4* part = (f32x4*)smem + (tid_e & 255);
         if (kg == 1) {
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int b = 0; b < NB; ++b) part[(i * NB + b) * 256] = acc[i][b];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) s_top[KG * BM + b * 256 + (tid_e & 255)] = w_top[b];
         }
         __syncthreads();
         if (kg == 1) {
-            if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
+            if (bad && lane_e == 0 && p.status) atomicOr(p.status, 1);
             return;
         }
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[i][b] += part[(i * NB + b) * 256];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w_top[b] = fmaxf(w_top[b], s_top[KG * BM + b * 256 + tid_e]);
+    } else {
+        __syncthreads();
     }
 
-    // register v of lane (r, g): row i * 16 + g * 4 + v, column r
-    const int col = nt * 64 + wave * 16 + r;
+    // register v: row i * 16 + g_e * 4 + v, column r_e
+    const int col = nt * 64 + wave * 16 + r_e;
     auto store = [&](int i, const f32x4 (&a)[NB], uint32_t rows) __attribute__((always_inline)) {       // rows: bit v for register v
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = i * 16 + g * 4 + v;
+            const int row = i * 16 + g_e * 4 + v;
             if (row >= rows_here || !((rows >> v) & 1)) continue;
             float* o = (float*)p.out + (int64_t)(row0 + row) * p.ldo + col;
             if (MODE == 0) *o = silu_mul(a[0][v], a[NB - 1][v]);
@@ -304,33 +352,53 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
     };
 #pragma unroll
     for (int i = 0; i < RT; ++i) store(i, acc[i], 15);
-    // Odd sums: not finite, or not zero and below 2^-80.  Only these are replaced, so that a row's bits depend on its own values alone
-    // and not on what else is in its tile.
-    float least = INFINITY, finite = 0.f;            // the smallest magnitude that is not zero; 0, or NaN
+    // Odd: a sum that is not finite, or below the limit where what the parts of its operands and its products lost may show (see
+    // the top of the file; nothing is lost where the row or the column is zero).  Only these are replaced, so that a row's bits depend on
+    // its own values alone and not on what else is in its tile.
+    const float per_unit = (float)p.KT * 64.f * 0x1p-108f;
+    float w_limit[NB], least = INFINITY, finite = 0.f;        // least: a sum's distance from its limit; finite: 0, or NaN
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+    for (int b = 0; b < NB; ++b) w_limit[b] = w_top[b] == 0.f ? -INFINITY : per_unit * (w_top[b] + 0x1p-12f);
+    auto row_limits = [&](int i) __attribute__((always_inline)) {
+        f32x4 t = *(const f32x4*)(s_top + i * 16 + g_e * 4);
+        if (KG == 2) {
+            const f32x4 u = *(const f32x4*)(s_top + BM + i * 16 + g_e * 4);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] = fmaxf(t[v], u[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[v] = t[v] == 0.f ? -INFINITY : per_unit * t[v];
+        return t;
+    };
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const f32x4 limit = row_limits(i);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                least = fminf(least, acc[i][b][v] == 0.f ? INFINITY : fabsf(acc[i][b][v]));
+                least = fminf(least, fabsf(acc[i][b][v]) - (limit[v] + w_limit[b]));
                 finite = fmaf(acc[i][b][v], 0.f, finite);
             }
-    if (__builtin_expect(__ballot(least < 0x1p-80f || finite != 0.f) != 0, 0)) {
+    }
+    if (__builtin_expect(__ballot(least < 0.f || finite != 0.f) != 0, 0)) {
         uint32_t odd = 0;                            // bit 4 i + v: register v of row tile i
 #pragma unroll
-        for (int i = 0; i < RT; ++i)
+        for (int i = 0; i < RT; ++i) {
+            const f32x4 limit = row_limits(i);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     const float m = fabsf(acc[i][b][v]);
-                    odd |= (uint32_t)(!(m < INFINITY) || (m < 0x1p-80f && m != 0.f)) << (4 * i + v);
+                    odd |= (uint32_t)(!(m < INFINITY) || m - (limit[v] + w_limit[b]) < 0.f) << (4 * i + v);
                 }
+        }
         for (int i = 0; i * 16 < rows_here; ++i) {
             const uint32_t mine = (odd >> (4 * i)) & 15;
             if (!__ballot(mine != 0)) continue;
-            const char* arow = p.A + source_row(p, row0 + min(i * 16 + r, rows_here - 1)) * p.lda_bytes + g * 16;
+            const char* arow = p.A + source_row(p, row0 + min(i * 16 + r_e, rows_here - 1)) * p.lda_bytes + g_e * 16;
+            const int n_e = (nt & 1) * 64 + wave * 16 + r_e, boff_e[2] = {chunk_offset(n_e, 0, g_e), chunk_offset(n_e, 1, g_e)};
             f32x4 sum[NB], a[2][4], wt[2][NB][4];
 #pragma unroll
             for (int b = 0; b < NB; ++b) sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -344,7 +412,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
                 for (int q = 0; q < 4; ++q) {
                     a[slot][q] = *(const f32x4*)(arow + (int64_t)kt * 256 + q * 64);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) wt[slot][b][q] = *(const f32x4*)(w[b].tile + boff[q & 1] + (q >> 1) * 128);
+                    for (int b = 0; b < NB; ++b) wt[slot][b][q] = *(const f32x4*)(w[b].tile + boff_e[q & 1] + (q >> 1) * 128);
                 }
             };
             auto multiply = [&](int slot) __attribute__((always_inline)) {
@@ -365,7 +433,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
             store(i, sum, mine);
         }
     }
-    if (bad && lane == 0 && p.status) atomicOr(p.status, 1);
+    if (bad && lane_e == 0 && p.status) atomicOr(p.status, 1);
 }
 
 template <int MODE>

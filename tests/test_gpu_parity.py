@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import paper_2411_11217_amd as M
-from moe_workloads import CONFIGS, MoEConfig, scaled
+from moe_workloads import CONFIGS, MoEConfig, make_inputs, scaled
 from util import F32_REL_RMS, Case, assert_close, assert_h_close, assert_status_clean, check_permutation_valid, compare_routing, rel_rms, say, shape_of
 
 pytestmark = pytest.mark.gpu
@@ -321,6 +321,39 @@ def test_f32_split_products_of_extreme_values():
     g64 = x[60].cpu().double() @ case.inp["W1"][0].T.double()
     u64 = x[60].cpu().double() @ case.inp["W3"][0].T.double()
     assert np.abs(h[60].double().numpy() - (0.5 * g64 * u64).numpy()).max() <= 2.0 ** -149     # underflows: silu(g) = g / 2 there
+
+
+@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([150, 40, 9, 260], 256, 4224)])       # gate/up: 64 and 128 rows a block
+@pytest.mark.parametrize("sx,s1,s3,s2", [
+    (-118, 50, 118, 0),                        # x: third parts below the last bit of a bf16 subnormal; sums of 2^-68 and of 1
+    (-136, 120, 120, 0),                       # x: float32 subnormals, most of them no bf16 at all
+    (50, -118, 0, 0),                          # W1
+    (-59, 0, 0, 118),                          # h, in the down launch
+    (-68, 0, 0, 120),                          # h: float32 subnormals
+])
+def test_f32_split_products_of_small_operands(counts, H, F, sx, s1, s3, s2):
+    """Operands whose low parts no bf16 holds, against factors that make their sums ordinary numbers: as accurate as float32
+    products.  Relative RMS below 2e-6: a chain of F / 4 = 1056 float32 roundings at most, 2^-24 * sqrt(1056 / 3) if they are
+    random."""
+    E = len(counts)
+    cfg = MoEConfig("small32", "f32", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=96 * 1024, seed=84)
+    inp = make_inputs(cfg, threads=16)
+    for name, e in (("x", sx), ("W1", s1), ("W3", s3), ("W2", s2)):
+        inp[name] = inp[name] * 2.0 ** e
+    case = Case(cfg, inputs=inp)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    w = np.random.default_rng(3).random(cfg.T, dtype=np.float32) + 0.5
+    h, out = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w))
+    h, out = h.cpu(), out.cpu()
+    for e in range(E):
+        r = slice(int(offsets[e]), int(offsets[e + 1]))
+        g, u = inp["x"][r].double() @ inp["W1"][e].T.double(), inp["x"][r].double() @ inp["W3"][e].T.double()
+        h_ref = g / (1 + torch.exp(-g)) * u
+        o_ref = (h[r].double() @ inp["W2"][e].T.double()) * torch.from_numpy(w[r]).double()[:, None]
+        h_rms = float(h_ref.square().mean().sqrt())
+        # h itself may be a float32 subnormal: one unit of those, for the rounding of silu(g) and of the product
+        assert float((h[r].double() - h_ref).square().mean().sqrt()) < 2e-6 * h_rms + 2.0 ** -149, f"h, expert {e}"
+        assert rel_rms(out[r].numpy(), o_ref.numpy()) < 2e-6, f"out, expert {e}"
 
 
 @pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([150, 40, 9, 260], 256, 4224)])       # gate/up: 64 and 128 rows a block
