@@ -944,9 +944,13 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
         // Row tiles of 128 as long as they make one round: a tile of 256 rows x 128 columns is a chain of some 0.6 us per k-step
         // whatever else the chip does, one of 128 rows 0.4.  us for the pre-attention task, 256 / 128 rows: 4096 x 6144 270 tokens (144
         // tiles of 128) 60 / 42, 300: 53 / 45, 512: 56 / 46; 6144 x 9216 256 tokens (144) 72 / 57; 2048 x 3072 700 tokens (144) 38 / 34,
-        // 1000 (192) 40 / 34.  Not for the experts' down launch, whose experts are a tile each and would read their weights twice: 2048 x 4096 1024
+        // 1000 (192) 40 / 34.  With up to 160 rows, a short tile of 256, they read the weights twice to have twice the blocks, which wide
+        // matrices with a long k do not win back: 129 rows, 4096 x 13312 (208 tiles of 128) 37 / 34, 4096 x 14336 (224) 37 / 37, 4096 x 15360 (240) 37 / 38, 4096 x
+        // 16384 (256) 35 / 40, 6144 x 13312 50 / 50, 6144 x 16384 47 / 55, but 2048 x 16384 21.4 / 20.4; 161 rows 4096 x 16384 39 / 36.
+        // Not for the experts' down launch, whose experts are a tile each and would read their weights twice: 2048 x 4096 1024
         // tokens 70 us for the launch, 86 with tiles of 128.
-        if (p.half_tiles && a.T > 128 && (int64_t)((a.T + 127) / 128) * p.NT <= kComputeUnits) {
+        const int64_t half_tiles = (int64_t)((a.T + 127) / 128) * p.NT;
+        if (p.half_tiles && a.T > 128 && half_tiles <= kComputeUnits && (a.T > 160 || half_tiles <= 224 || p.KT <= 32)) {
             p.tall_rows = 0;
             rc = launch_stages<1, 1, 128>(p, gemm_grid(p.NT, a.T, 128, 1, p.chunked), st);
         } else {
