@@ -8,6 +8,7 @@
 // expert has at most 16 rows (others, from offsets that no routing made, take several row tiles).  us for the launch, D = 8 / 12 / 16:
 // down of the Mixtral-8x7B shape, one token 45 / 46 / 45 (rows kernel 82), two tokens 74 / 79 / - (96); four wavefronts to a block
 // instead of one 55.  Every output is the same chain of MFMAs along k as in the other bf16 kernels: the same bits.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -139,22 +140,37 @@ int launch_thin(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
 
 }  // namespace
 
-// experts with rows, on average over routings that favour none
-static double experts_with_rows(const moe_shape& s) { return s.E * (1.0 - std::pow(1.0 - (double)s.k / s.E, s.T)); }
+// experts with rows, on average over routings that favour none, and the standard deviation
+static double experts_with_rows(const moe_shape& s, double* deviation = nullptr) {
+    const double E = s.E, none = std::pow(1.0 - s.k / E, s.T);                      // an expert, two experts without a row
+    const double neither = s.E > 1 ? std::pow((E - s.k) * (E - s.k - 1.0) / (E * (E - 1.0)), s.T) : none;
+    if (deviation) *deviation = std::sqrt(std::max(0.0, E * none * (1.0 - none) + E * (E - 1.0) * (neither - none * none)));
+    return E * (1.0 - none);
+}
 
 // Where the launches of at most 16 tokens come here, by the blocks that moe_ffn_rows_bf16.hip would keep busy.
 // Gate/up: up to about one and a half blocks of 64 features per compute unit.  us, that kernel / this one: 1024 x 2816 (8 experts, 2
 // per token) 1 token (88 blocks) 13 / 11, 16 tokens (348) 25 / 22; 2048 x 4096 1 token (128) 22 / 18, 4 tokens (350) 34 / 31, 16 tokens (506)
 // 47 / 46; 64 experts of 2048 x 1024, 8 per token, 3 tokens (337) 40 / 36, 8 tokens (671) 61 / 63; Mixtral-8x7B shape 1 token (448) 76 / 79.
 bool thin_takes_gate_up(const moe_shape& s) { return s.T <= 16 && experts_with_rows(s) * (s.F / 64) <= 440; }
-// Down: with clearly fewer blocks of 128 columns than compute units, or with between one and two per compute unit, which
-// share out unevenly.  Mixtral-8x7B shape 1 token (64) 82 / 46, 2 tokens (112) 95 / 77, 4 tokens (175) 114 / 111, 16 tokens (253) 148 / 154; DBRX shape 1 token (192)
-// 83 / 85, 2 tokens (336) 157 / 126, 4 tokens (525) 196 / 204; Mixtral-8x22B shape 1 token (96) 104 / 65, 6 tokens (316) 248 / 193, 16 tokens (380)
-// 259 / 251; 2048 x 4096 8 tokens (115) 36 / 26; 1024 x 2816 8 tokens (58) 24 / 17; 64 experts of 2048 x 1024 3 tokens (337) 24 / 21, 8 tokens
-// (671) 34 / 35.
+// Down: with clearly fewer blocks of 128 columns than compute units, or with between one and one and a half per compute unit, which share
+// out unevenly; here 384 blocks' worth of wavefronts, twelve per compute unit, are the most that run at once.  us for both
+// launches, by experts with rows (blocks), that kernel / this one:
+//   k of 14336 (4096 x 14336) 2 experts (64) 153 / 114, 4 (128) 233 / 214, 6 (192) 326 / 321, 8 (256) 416 / 416, 9 (288) 515 / 468, 12 (384) 625 / 615,
+//   13 (416) 668 / 691; 10752 (6144 x 10752) 3 (144) 205 / 199, 4 (192) 254 / 253, 5 (240) 321 / 329, 6 (288) 405 / 374, 9 (432) 522 / 538;
+//   8192 (5120 x 8192) 2 (80) 100 / 85, 3 (120) 133 / 126, 5 (200) 196 / 204, 7 (280) 299 / 282, 10 (400) 378 / 416; (3072 x 8192) 6 (144) 150 / 153, 8
+//   (192) 186 / 199; 4096 (4096 x 4096) 5 (160) 91 / 89, 6 (192) 96 / 100;
+//   2048 (2048 x 2048) 8 (128) 40 / 37, 11 (176) 50 / 50, 15 (240) 64 / 66, (4096 x 2048) 9 (288) 90 / 81, 13 (416) 108 / 109, 15 (480) 119 / 118.
+// The routing is not known here.  The lower range goes by the average; the upper one by the average less half the deviation (routings that
+// fill one round or less lose as much as the others gain) and plus the deviation, or all experts.
 bool thin_takes_down(const moe_shape& s) {
-    const double blocks = experts_with_rows(s) * (s.H / 128);
-    return s.T <= 16 && (blocks < 190 || (blocks > 256 && blocks < 500));
+    if (s.T > 16) return false;
+    const double per_expert = s.H / 128;
+    double deviation;
+    const double blocks = experts_with_rows(s, &deviation) * per_expert;
+    if (s.F <= 2048) return blocks < 190 || (blocks > 256 && blocks < 500);
+    if (blocks < (s.F <= 10240 ? 130 : 190)) return true;
+    return blocks - 0.5 * deviation * per_expert > 256 && std::min(blocks + deviation * per_expert, s.E * per_expert) <= 384;
 }
 
 int launch_gate_up_thin_bf16(GemmParams& p, int F, int R, int n_exp, hipStream_t st) { return launch_thin<0, 2>(p, F, R, n_exp, st); }
