@@ -20,7 +20,7 @@
 //     The activations are split once per block and pass through LDS (two stages; the registers hold the next step or two), one
 //     barrier per step of 32 k.  Splitting eight values takes 44 vector instructions, as long as 11 MFMAs: the more rows
 //     a block has, the more MFMAs share the split of its weights, and blocks of other wavefronts on the same SIMD fill
-//     the matrix cores meanwhile (three per SIMD).  Few columns (MODE 1): KG = 2, two groups of four wavefronts with 32 k of a step each.
+//     the matrix cores meanwhile (three per SIMD).  Few columns (MODE 1) or few blocks: KG = 2, two groups of four wavefronts with 32 k of a step each.
 //     1024 x 2816, 700 tokens, against the float32 MFMA with blocks of 32 rows: gate/up 177 / 111 us, down 107 / 77, layer 289 / 202;
 //     8000 tokens 2440 / 1580; 256 x 512, 1100 tokens 64 / 47.  700 tokens: matrix cores busy 0.54 and 0.40 of the launches' cycles,
 //     vector instructions 0.63 and 0.59.
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kThreads * KG, KG == 1 ? 3 : 4) void ffn_split_f32(
     };
     if (RT > 6 && rows_here > 96) main_loop(std::integral_constant<int, RT>{});
     else if (RT > 4 && rows_here > 64) main_loop(std::integral_constant<int, RT < 6 ? RT : 6>{});
-    else if (rows_here > 32) main_loop(std::integral_constant<int, 4>{});
+    else if (RT > 2 && rows_here > 32) main_loop(std::integral_constant<int, RT < 4 ? RT : 4>{});
     else main_loop(std::integral_constant<int, 2>{});
     // the thread's coordinates once more: kept through the loop they would take registers that it does not have
     int tid_e = tid;
@@ -557,6 +557,12 @@ int launch_mode(GemmParams& p, int cols, int R, int E, int n_exp, hipStream_t st
         if constexpr (MODE == 1) {
             return launch_split<1, 4, 2>(p, cols, R, n_exp, st);
         } else {
+            // Blocks of 32 rows with KG = 2 as long as they make one round: with fewer blocks than compute units the chain along k is all that
+            // counts, and these have half of it.  us for the layer, 64 rows and KG = 1 / these (before both: 32 rows on the float32 MFMA): 512 x 128, 8
+            // experts, 100 rows each (64 blocks of 32 rows) 44 / 37 (40), 400 rows (208) 51 / 45; 2048 x 128, 4 experts, 50 rows (16) 88 / 61 (79); 8192 x
+            // 512, 4 experts, 35 rows (64) 294 / 186 (286), 250 rows (256) 380 / 349; 256 x 512, 8 experts, 125 rows (256) 41.6 / 41.4; beyond,
+            // 128 x 512, 8 experts, 200 rows (448) 38.8 / 39.7; 128 x 4096, 2 experts, 100 rows (512) 82.4 / 82.8.
+            if (column_blocks * ((rows_each + 31) / 32) <= kComputeUnits) return launch_split<0, 2, 2>(p, cols, R, n_exp, st);
             // 128 rows halve what a block spends on splitting weights, 64 make more blocks: 1024 x 2816 (352 blocks for up to 128 rows
             // each) 300 tokens 78 / 77, 700: 110 / 114, 4000: 449 / 474; 256 x 512, 300 tokens (64 blocks) 23 / 18, 1000: 26 / 21
             if (column_blocks * ((rows_each + 127) / 128) >= kComputeUnits) return launch_split<0, 8, 1>(p, cols, R, n_exp, st);

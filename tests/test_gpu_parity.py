@@ -267,6 +267,7 @@ def test_bf16_handful_of_tokens(counts, H, F):
 @pytest.mark.parametrize("counts,H,F", [
     ([1, 16, 17, 33, 64, 65, 96, 97, 128, 129, 300, 0], 128, 256),    # the split kernel's row tiles and loops; two and four k-steps
     ([260, 31, 111], 384, 640),                                         # six and ten k-steps, three row tiles of an expert
+    ([100, 40, 70, 0, 33, 64, 128, 129], 128, 1024),                    # column blocks for more than a round of 32 rows, for less of 64
     ([20] * 63 + [70], 128, 256),                                       # few rows, but column blocks for every compute unit: gate/up alone
     ([150, 40, 9, 260], 256, 4224),                                     # 264 column blocks: the blocks of 128 rows
 ])
@@ -323,7 +324,8 @@ def test_f32_split_products_of_extreme_values():
     assert np.abs(h[60].double().numpy() - (0.5 * g64 * u64).numpy()).max() <= 2.0 ** -149     # underflows: silu(g) = g / 2 there
 
 
-@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([150, 40, 9, 260], 256, 4224)])       # gate/up: 64 and 128 rows a block
+@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
+                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
 @pytest.mark.parametrize("sx,s1,s3,s2", [
     (-118, 50, 118, 0),                        # x: third parts below the last bit of a bf16 subnormal; sums of 2^-68 and of 1
     (-136, 120, 120, 0),                       # x: float32 subnormals, most of them no bf16 at all
@@ -356,7 +358,8 @@ def test_f32_split_products_of_small_operands(counts, H, F, sx, s1, s3, s2):
         assert rel_rms(out[r].numpy(), o_ref.numpy()) < 2e-6, f"out, expert {e}"
 
 
-@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([150, 40, 9, 260], 256, 4224)])       # gate/up: 64 and 128 rows a block
+@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
+                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
 @pytest.mark.parametrize("scale", [float("inf"), float("nan"), 2.0 ** -45, 2.0 ** -100])
 def test_f32_rows_do_not_depend_on_their_neighbours(counts, H, F, scale):
     """Rows of infinities, NaN or tiny values (2^-45: sums of the down launch alone) change no bit of h and out of any other row."""
