@@ -264,6 +264,23 @@ def test_bf16_handful_of_tokens(counts, H, F):
         assert torch.equal(h4[:R], h3) and torch.equal(out4[:R], out3)
 
 
+@pytest.mark.parametrize("T", [1, 4])
+def test_bf16_handful_of_tokens_with_weights_beyond_the_last_level_cache(T):
+    """403 MB of expert weights: the kernel for a handful of tokens loads them with the non-temporal hint, in both launches."""
+    cfg = MoEConfig("thin_stream", "bf16", T=T, H=2048, F=4096, E=8, k=2, page_bytes=1 << 20, seed=86)
+    case = Case(cfg, shuffle_pages=True)
+    ws = M.Workspace(case.shape)
+    ws.buf.fill_(0xFF)
+    y = torch.full((T, cfg.H), float("nan"), device="cuda")
+    M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, workspace=ws, y=y)
+    torch.cuda.synchronize()
+    assert_status_clean(ws.view("status").tolist())
+    ids, w = ws.view("topk_ids").cpu().numpy(), ws.view("topk_w").cpu().numpy()
+    same = compare_routing(cfg, ids, w, case.oracle_route())
+    ref = case.oracle_layer()
+    assert_close(y.cpu().numpy()[same], ref["y"][same], "bf16", "y")
+
+
 @pytest.mark.parametrize("counts,H,F", [
     ([1, 16, 17, 33, 64, 65, 96, 97, 128, 129, 300, 0], 128, 256),    # the split kernel's row tiles and loops; two and four k-steps
     ([260, 31, 111], 384, 640),                                         # six and ten k-steps, three row tiles of an expert
@@ -292,11 +309,14 @@ def test_f32_split_products(counts, H, F):
             assert_close(out.cpu().numpy()[lo:hi], o_ref[lo:hi], "f32", f"out, expert {e} with {c} rows")
 
 
-def test_f32_split_products_of_extreme_values():
-    """Infinities, NaN, values that bf16 rounds to infinity and values whose low parts leave its range: what the float32 products
-    give, row by row, and nothing of it in other rows."""
-    counts, H, F = [100, 40], 128, 256
-    cfg = MoEConfig("extreme32", "f32", T=sum(counts), H=H, F=F, E=2, k=1, page_bytes=96 * 1024, seed=80)
+@pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
+                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
+def test_f32_split_products_of_extreme_values(counts, H, F):
+    """Infinities, NaN, values that bf16 rounds to infinity and rows so small that their sums are formed again: h and out as the
+    float32 products give them, row by row, and nothing of it in other rows.  2e-6: a chain of F / 4 = 1056 float32 roundings at
+    most, 2^-24 * sqrt(1056 / 3) if they are random."""
+    T, E = sum(counts), len(counts)
+    cfg = MoEConfig("extreme32", "f32", T=T, H=H, F=F, E=E, k=1, page_bytes=96 * 1024, seed=80)
     case = Case(cfg)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     x = case.x.clone()
@@ -304,24 +324,30 @@ def test_f32_split_products_of_extreme_values():
     x[20, 7] = float("-inf")
     x[21, 8] = float("nan")
     x[40, 9], x[40, 10] = 3.4e38, -3.4e38
-    x[60] *= 2.0 ** -118
+    x[60] *= 2.0 ** -52                               # h about 2^-106, sums of the down launch below their limit
+    x[61] *= 2.0 ** -58                               # h about 2^-118
     x[110, 100] = float("inf")
-    h, _ = M.moe_expert_ffn(case.shape, x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev)
-    torch.cuda.synchronize()
-    ref = torch.empty_like(h, device="cpu")
-    for e in range(2):
+    w = torch.rand(T, generator=torch.Generator().manual_seed(4)) + 0.5
+    h, out = M.moe_expert_ffn(case.shape, x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=w.cuda())
+    h, out, x = h.cpu(), out.cpu(), x.cpu()
+    h_ref, o_ref = torch.empty_like(h), torch.empty_like(out)
+    h64, o64 = torch.empty_like(h, dtype=torch.float64), torch.empty_like(out, dtype=torch.float64)
+    for e in range(E):
         r = slice(int(offsets[e]), int(offsets[e + 1]))
-        g, u = x[r].cpu() @ case.inp["W1"][e].T, x[r].cpu() @ case.inp["W3"][e].T
-        ref[r] = g / (1 + torch.exp(-g)) * u
-    h = h.cpu()
-    assert torch.equal(torch.isnan(h), torch.isnan(ref)) and torch.equal(torch.isinf(h), torch.isinf(ref))
-    assert torch.equal(torch.sign(h[torch.isinf(h)]), torch.sign(ref[torch.isinf(ref)]))
-    plain = [i for i in range(140) if i not in (3, 20, 21, 40, 60, 110)]
-    assert torch.isfinite(h[plain]).all() and rel_rms(h[plain].numpy(), ref[plain].numpy()) < 1e-6
-    assert rel_rms(h[40][torch.isfinite(ref[40])].numpy(), ref[40][torch.isfinite(ref[40])].numpy()) < F32_REL_RMS
-    g64 = x[60].cpu().double() @ case.inp["W1"][0].T.double()
-    u64 = x[60].cpu().double() @ case.inp["W3"][0].T.double()
-    assert np.abs(h[60].double().numpy() - (0.5 * g64 * u64).numpy()).max() <= 2.0 ** -149     # underflows: silu(g) = g / 2 there
+        W1, W3, W2 = (case.inp[n][e] for n in ("W1", "W3", "W2"))
+        g, u = x[r] @ W1.T, x[r] @ W3.T
+        h_ref[r], o_ref[r] = g / (1 + torch.exp(-g)) * u, h[r] @ W2.T * w[r, None]
+        g, u = x[r].double() @ W1.T.double(), x[r].double() @ W3.T.double()
+        h64[r], o64[r] = g / (1 + torch.exp(-g)) * u, h[r].double() @ W2.T.double() * w[r, None].double()
+    for got, ref in ((h, h_ref), (out, o_ref)):
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+        assert torch.equal(torch.sign(got[torch.isinf(got)]), torch.sign(ref[torch.isinf(ref)]))
+    assert not torch.isfinite(out[[3, 20, 21, 110]]).any()
+    plain = [i for i in range(T) if i not in (3, 20, 21, 40, 60, 61, 110)]
+    assert torch.isfinite(h[plain]).all() and torch.isfinite(out[plain]).all()
+    for rows in (plain, [60], [61]):
+        assert rel_rms(h[rows].numpy(), h64[rows].numpy()) < 2e-6 and rel_rms(out[rows].numpy(), o64[rows].numpy()) < 2e-6, rows
+    assert rel_rms(h[40][torch.isfinite(h_ref[40])].numpy(), h_ref[40][torch.isfinite(h_ref[40])].numpy()) < F32_REL_RMS
 
 
 @pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
