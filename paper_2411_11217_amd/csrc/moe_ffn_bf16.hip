@@ -92,12 +92,17 @@ constexpr int kComputeUnits = 256;           // MI355X
 // And only where the experts' weights exceed the 256 MiB last-level cache: smaller ones may still be there from the call
 // before, and the hint keeps them out (8 experts of 1024 x 2816, 138 MB, 100 tokens: 53 without, 56 with).  Where other
 // weights pass in between it is the other way round (ten such layers in turn, 8 tokens 49 / 47, 100: 55 / 53, 400: 70 / 69).
-// The same launches store h with the hint (those of moe_ffn_rows_bf16.hip always do): lines written through as they come cost
-// the reads of the weights less than dirty lines that the end of the launch has to write back.  (Any write does: a kernel of
-// nothing but loads that reads 1.88 GB in 274 us takes 300 when its blocks also write 15 MB, wherever these go.)  Gate/up
-// launch without / with, us: Mixtral-8x7B shape 256 tokens 325 / 308, 500: 346 / 325 (and the down launch behind it 198 / 180),
-// 1000: 420 / 407; DBRX shape, 600 tokens 753 / 720.  Weights that stay in the last-level cache leave room for h there and in
-// the L2, which the hint gives up: 8 experts of 1024 x 2816, 1500 tokens 41 / 50 in the down launch; 2048 x 4096, 3000 tokens 120 / 127.
+// The same experts store h with the hint (here and in moe_ffn_rows_bf16.hip): lines written through as they come cost the reads of the
+// weights less than dirty lines that the end of the launch has to write back.  (Any write does: a kernel of nothing but loads that
+// reads 1.88 GB in 274 us takes 300 when its blocks also write 15 MB, wherever these go.)  Gate/up launch without / with, us: Mixtral-8x7B
+// shape 256 tokens 323 / 304, 1000: 443 / 435 (and the down launch behind it 257 / 251); DBRX shape, 600 tokens 784 / 762; layer of
+// the Mixtral-8x7B shape, 500 tokens 556 / 515.  An expert with several row tiles has its h read by
+// several row tiles' blocks: where the down launch does not fill the chip, the way of that h is what its longest blocks wait for, and it is
+// stored without the hint.  8 experts, 40 % of the rows on one, layer without / with for that expert: 2048 x 4096 250 tokens 111 / 118, 400: 123 /
+// 138, 2048 x 14336 400 tokens 342 / 388, 1024 x 8192 400 tokens 143 / 174; with a round of down tiles and long rows of h 4096 x 8192
+// 400 tokens 364 / 356, 4096 x 14336 250 tokens 480 / 465, 400: 614 / 587; short rows 4096 x 4096 250 tokens 138 / 142, 400: 211 / 211, 6144 x 2048 400 tokens
+// 177 / 186.  Weights that stay in the last-level cache leave room for h there and in the L2: 8 experts of 1024 x 2816, 1500 tokens
+// 41 / 50 in the down launch; 2048 x 4096, 3000 tokens 120 / 127.
 constexpr int kStreamRows = 256;
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 constexpr int kRowB = 64;                    // bytes of one weight row in a stage (32 bf16: one half-step)
@@ -750,7 +755,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     if (MODE == 0) {
         constexpr int NP = NJ / 2;             // gate/up pairs of a wavefront: fragments j and j + NP
         __bf16* h = (__bf16*)p.out + (int64_t)row0 * p.ldo + nt * (32 * NP) + wn * (16 * NP) + col_l;
-        // stream_c: the launch streams its weights, and h goes past the L2 (see kStreamRows)
+        // stream_c: h goes past the L2 (see kStreamRows)
         auto store_h = [&](auto stream_c, __bf16 v, __bf16* dst) __attribute__((always_inline)) {
             if constexpr (decltype(stream_c)::value) {
                 __builtin_nontemporal_store(v, dst);
@@ -781,7 +786,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
             else if (row_tiles == 6) store_rows(stream_c, std::false_type{}, std::integral_constant<int, 6>{});
             else store_rows(stream_c, std::false_type{}, std::integral_constant<int, 8>{});
         };
-        if (p.stream) store_tile(std::true_type{});
+        if (p.stream > 1 || (p.stream && tc.mtiles == 1)) store_tile(std::true_type{});
         else store_tile(std::false_type{});
         if (extra) {                           // the extra row tile of a tall tile
 #pragma unroll
@@ -873,7 +878,8 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     fill_common(p, s, g, a);
     fill_gate_up(p, s, g, a);
     const int64_t rows_each = R / s.E;
-    p.stream = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
+    const bool streams = rows_each <= kStreamRows && (int64_t)s.E * 3 * s.H * s.F * 2 > kStreamBytes;
+    p.stream = !streams ? 0 : s.F >= 6144 && s.E * g.dt >= kComputeUnits ? 2 : 1;       // 2: h of every expert past the L2 as well
     if (rows_kernel_takes((int)rows_each)) {
         int rc = thin_takes_gate_up(s) ? launch_gate_up_thin_bf16(p, s.F, R, n_exp, st) : launch_gate_up_rows_bf16(p, s.F, R, (int)rows_each, n_exp, st);
         if (rc != MOE_OK) return rc;

@@ -40,7 +40,7 @@ struct GemmParams {
     int32_t tall_rows;        // bf16 kernel: a row tile may be up to this many rows higher than BM (0 or 32), see locate_tile
     int32_t chunked;          // tile numbering: groups dealt to the XCDs in chunks of about this many tiles (0: single groups), see locate_tile
     int32_t tall_first;       // bf16 kernel: tile numbering with the tall tiles of a chunk of groups first, see locate_tile
-    int32_t stream;           // bf16 kernels: weights of experts with one row tile are loaded with the non-temporal hint
+    int32_t stream;           // bf16 kernels: experts with one row tile load their weights and store h with the non-temporal hint; 2: all experts h
     int32_t balance;          // 1: no XCD runs more than an eighth of the launch's tiles, see stolen_tile
 };
 

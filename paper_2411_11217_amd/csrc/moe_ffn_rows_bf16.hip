@@ -190,8 +190,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
     else run(Num<0>{});
 
     if constexpr (MODE == 0) {
-        // h leaves through LDS in whole lines, 16 bytes a lane, and past the L2 (see kStreamRows; with weights that fit the
-        // last-level cache it is the same either way at these row counts: 8 experts of 1024 x 2816, 300 tokens 65.6 without, 65.4 with)
+        // h leaves through LDS in whole lines, 16 bytes a lane, in part past the L2 (see kStreamRows)
         __syncthreads();                             // everyone has read the last stage
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
@@ -204,12 +203,21 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         __syncthreads();
         constexpr int kChunks = kCols / 8;           // 16-byte chunks of a row
         char* o = (char*)p.out + ((int64_t)row0 * p.ldo + nt * kCols) * 2;
-        for (int c = tid; c < rows_here * kChunks; c += 64 * CW * RG) {
-            const int row = c / kChunks, ch = c % kChunks;
-            const i32x4 hv = *(const i32x4*)(smem + row * kOutRow + ch * 16);
-            i32x4* dst = (i32x4*)(o + (int64_t)row * p.ldo * 2 + ch * 16);
-            __builtin_nontemporal_store(hv, dst);
-        }
+        auto store_rows = [&](auto past_l2) __attribute__((always_inline)) {
+            for (int c = tid; c < rows_here * kChunks; c += 64 * CW * RG) {
+                const int row = c / kChunks, ch = c % kChunks;
+                const i32x4 hv = *(const i32x4*)(smem + row * kOutRow + ch * 16);
+                i32x4* dst = (i32x4*)(o + (int64_t)row * p.ldo * 2 + ch * 16);
+                if constexpr (decltype(past_l2)::value) {
+                    __builtin_nontemporal_store(hv, dst);
+                    asm volatile("" ::: "memory");       // else the compiler makes one store of this one and the plain one
+                } else {
+                    *dst = hv;
+                }
+            }
+        };
+        if (p.stream > 1 || (p.stream && tc.mtiles == 1)) store_rows(Num<1>{});
+        else store_rows(Num<0>{});
     } else {
         const int col = nt * kCols + cw * 16 * FC + r;
 #pragma unroll
