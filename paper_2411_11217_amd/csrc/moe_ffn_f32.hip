@@ -563,6 +563,11 @@ int launch_mode(GemmParams& p, int cols, int R, int E, int n_exp, hipStream_t st
             // 512, 4 experts, 35 rows (64) 294 / 186 (286), 250 rows (256) 380 / 349; 256 x 512, 8 experts, 125 rows (256) 41.6 / 41.4; beyond,
             // 128 x 512, 8 experts, 200 rows (448) 38.8 / 39.7; 128 x 4096, 2 experts, 100 rows (512) 82.4 / 82.8.
             if (column_blocks * ((rows_each + 31) / 32) <= kComputeUnits) return launch_split<0, 2, 2>(p, cols, R, n_exp, st);
+            // With up to 48 rows on average blocks of 64 rows with KG = 2 are the better ones where the rows are shared out unevenly, and as good where
+            // they are not.  us for the layer, 128 rows and KG = 1 / these: 2048 x 1024, 16 experts, 2 per token, 300 tokens 146 / 129, 40 % of the rows on
+            // one expert 179 / 156, all on two 158 / 100; 1024 x 2816, 8 experts, 70 tokens, likewise 90 / 87, 99 / 96, 95 / 75; 170 tokens 113 / 114;
+            // 64 rows on average 1024 x 1024, 32 experts 174 / 190, 512 x 8192, 4 experts 172 / 181.
+            if (rows_each <= 48) return launch_split<0, 4, 2>(p, cols, R, n_exp, st);
             // 128 rows halve what a block spends on splitting weights, 64 make more blocks: 1024 x 2816 (352 blocks for up to 128 rows
             // each) 300 tokens 78 / 77, 700: 110 / 114, 4000: 449 / 474; 256 x 512, 300 tokens (64 blocks) 23 / 18, 1000: 26 / 21
             if (column_blocks * ((rows_each + 127) / 128) >= kComputeUnits) return launch_split<0, 8, 1>(p, cols, R, n_exp, st);

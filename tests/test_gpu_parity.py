@@ -286,6 +286,7 @@ def test_bf16_handful_of_tokens_with_weights_beyond_the_last_level_cache(T):
     ([260, 31, 111], 384, 640),                                         # six and ten k-steps, three row tiles of an expert
     ([100, 40, 70, 0, 33, 64, 128, 129], 128, 1024),                    # column blocks for more than a round of 32 rows, for less of 64
     ([20] * 63 + [70], 128, 256),                                       # few rows, but column blocks for every compute unit: gate/up alone
+    ([36, 20, 70, 1, 64, 33, 65, 0], 128, 4224),                        # column blocks for more than a round, at most 48 rows on average
     ([150, 40, 9, 260], 256, 4224),                                     # 264 column blocks: the blocks of 128 rows
 ])
 def test_f32_split_products(counts, H, F):
@@ -310,7 +311,7 @@ def test_f32_split_products(counts, H, F):
 
 
 @pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
-                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
+                                         ([36, 20, 70, 1, 64, 33, 65, 2], 128, 4224), ([150, 40, 9, 260], 256, 4224)])       # every kernel of gate/up
 def test_f32_split_products_of_extreme_values(counts, H, F):
     """Infinities, NaN, values that bf16 rounds to infinity and rows so small that their sums are formed again: h and out as the
     float32 products give them, row by row, and nothing of it in other rows.  2e-6: a chain of F / 4 = 1056 float32 roundings at
@@ -351,7 +352,7 @@ def test_f32_split_products_of_extreme_values(counts, H, F):
 
 
 @pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
-                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
+                                         ([36, 20, 70, 1, 64, 33, 65, 2], 128, 4224), ([150, 40, 9, 260], 256, 4224)])       # every kernel of gate/up
 @pytest.mark.parametrize("sx,s1,s3,s2", [
     (-118, 50, 118, 0),                        # x: third parts below the last bit of a bf16 subnormal; sums of 2^-68 and of 1
     (-136, 120, 120, 0),                       # x: float32 subnormals, most of them no bf16 at all
@@ -385,7 +386,7 @@ def test_f32_split_products_of_small_operands(counts, H, F, sx, s1, s3, s2):
 
 
 @pytest.mark.parametrize("counts,H,F", [([100, 40], 128, 256), ([100, 40, 70, 33, 64, 1, 128, 129], 128, 1024),
-                                         ([150, 40, 9, 260], 256, 4224)])       # gate/up: 32, 64 and 128 rows a block
+                                         ([36, 20, 70, 1, 64, 33, 65, 2], 128, 4224), ([150, 40, 9, 260], 256, 4224)])       # every kernel of gate/up
 @pytest.mark.parametrize("scale", [float("inf"), float("nan"), 2.0 ** -45, 2.0 ** -100])
 def test_f32_rows_do_not_depend_on_their_neighbours(counts, H, F, scale):
     """Rows of infinities, NaN or tiny values (2^-45: sums of the down launch alone) change no bit of h and out of any other row."""
