@@ -41,6 +41,18 @@ def cpu_model() -> str:
     return "unknown"
 
 
+def gate_up_kernel(cfg):
+    """The kernel of the gate/up launch: the library's rules (launch_mode in moe_ffn_f32.hip, launch_expert_ffn_bf16 in
+    moe_ffn_bf16.hip, thin_takes_gate_up in moe_ffn_thin_bf16.hip)."""
+    each = cfg.R // cfg.E
+    if cfg.dtype == "f32":
+        return "ffn_split_f32<0>" if each > 32 or (each > 16 and cfg.F // 64 * cfg.E >= 256) else "ffn_few_rows_f32<0>"
+    if each > 80:
+        return "ffn_gemm_bf16<0>"
+    experts = cfg.E * (1.0 - (1.0 - cfg.k / cfg.E) ** cfg.T)       # with rows, on average
+    return "ffn_thin_bf16<0>" if cfg.T <= 16 and experts * (cfg.F // 64) <= 440 else "ffn_rows_bf16<0>"
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -200,9 +212,7 @@ def main():
     if stages:
         t_gu = stages["gemm_gate_up"] * 1e-3
         achieved = flops_gu / t_gu / 1e12
-        each = cfg.R // cfg.E                              # the library's own lines between its kernels
-        kernel = ("ffn_gemm_bf16<0>" if each > 80 else "ffn_rows_bf16<0>") if cfg.dtype == "bf16" else \
-            "ffn_split_f32<0>" if each > 32 else "ffn_few_rows_f32<0>"
+        kernel = gate_up_kernel(cfg)
         roofline = {"bound": "mfma", "kernel": kernel + " (gate/up expert GEMM + SwiGLU epilogue)",
                     "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": MEASURED_TRAFFIC.get(args.config),

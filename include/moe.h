@@ -114,7 +114,8 @@ int moe_page_table_validate(const moe_shape* s, const int32_t* page_table_host, 
 typedef struct moe_workspace_layout {
     /* byte offsets into the workspace of moe_layer, each 256-byte aligned */
     size_t status;     /* int32[4]: [0] bit 0 = a page-table entry was not resident; [2], [3]: shader clock in MHz that a
-                        * block of the bf16 gate/up and down launch saw (diagnostic, 0 if none reported) */
+                        * block of the bf16 gate/up and down launch saw (diagnostic, 0 if none reported; the kernel for a
+                        * handful of tokens never does) */
     size_t topk_ids;   /* int32[T][k] */
     size_t topk_w;     /* float[T][k] */
     size_t counts;     /* int32[E] */

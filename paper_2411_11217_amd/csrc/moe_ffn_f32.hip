@@ -3,7 +3,7 @@
 //
 //   ffn_split_f32: float32 products on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, 16 times the rate of the float32 MFMA).
 //     Every value is a sum of three bf16, x = x0 + x1 + x2 with 24 bits together, and a product is the six partial products
-//     x2 y0 + x0 y2 + x1 y1 + x1 y0 + x0 y1 + x0 y0; what is left out is below 2^-25 of it.  The six MFMAs of 32 k add up in
+//     x2 y0 + x0 y2 + x1 y1 + x1 y0 + x0 y1 + x0 y0; what is left out, x1 y2 and x2 y1, is below 2^-24 of it.  The six MFMAs of 32 k add up in
 //     registers of their own, from zero, and a float32 addition takes the sum over: with all six on the accumulator itself
 //     every MFMA rounds at the size of the accumulator.  Relative error against float64 of h / of out for a given h: float32 MFMA 8.7e-7 / 9.5e-7,
 //     six MFMAs on the accumulator 7.3e-7 / 5.8e-7, this way 1.8e-7 / 1.5e-7 (1024 x 2816; 256 x 512: 4.2e-7 / 4.1e-7, 3.4e-7 /
@@ -21,9 +21,9 @@
 //     barrier per step of 32 k.  Splitting eight values takes 44 vector instructions, as long as 11 MFMAs: the more rows
 //     a block has, the more MFMAs share the split of its weights, and blocks of other wavefronts on the same SIMD fill
 //     the matrix cores meanwhile (three per SIMD).  Few columns (MODE 1) or few blocks: KG = 2, two groups of four wavefronts with 32 k of a step each.
-//     1024 x 2816, 700 tokens, against the float32 MFMA with blocks of 32 rows: gate/up 177 / 111 us, down 107 / 77, layer 289 / 202;
-//     8000 tokens 2440 / 1580; 256 x 512, 1100 tokens 64 / 47.  700 tokens: matrix cores busy 0.54 and 0.40 of the launches' cycles,
-//     vector instructions 0.63 and 0.59.
+//     1024 x 2816, 700 tokens, against the float32 MFMA with blocks of 32 rows: gate/up 186 / 132 us, down 110 / 93, layer 285 / 210;
+//     3000 tokens 954 / 657; 256 x 512, 1100 tokens 66 / 49.  700 tokens: matrix cores busy 0.52 and 0.38 of the launches' cycles,
+//     vector instructions 0.66 and 0.62.
 //   ffn_few_rows_f32: at most 32 rows x 16 columns (MODE 0: 16 features) on v_mfma_f32_16x16x4_f32, the wavefronts split k instead: every fourth
 //     k-step each, activations straight from memory, no barrier until the four partial tiles are added through LDS in a
 //     fixed order.  A lane's share of an operand is a 16-byte chunk (four consecutive k of one row): lane l holds chunk 4q +
@@ -48,7 +48,7 @@ constexpr int kFewRows = 32;                         // rows of a block of ffn_f
 
 // Where ffn_split_f32 takes a launch: with more than 32 rows per expert on average (beyond, an expert's weights are read once per row
 // tile by the other kernel, and its activations once per 16 columns), and with more than 16 where its blocks of 64 columns
-// make a round on the 256 compute units.  us for the launch, ffn_few_rows / ffn_split: gate/up of 1024 x 2816 (8 experts, 2 per
+// make a round on the 256 compute units.  us for the launch, ffn_few_rows / ffn_split with 128 rows (gate/up): gate/up of 1024 x 2816 (8 experts, 2 per
 // token; 352 blocks) 50 tokens 53 / 55, 70: 61 / 55, 110: 69 / 55, 128: 86 / 59; its down launch (128 blocks) 70: 34 / 46, 110: 40 / 48,
 // 128: 55 / 49; 256 x 512 (64 and 32 blocks) 110 tokens 13 / 16 and 11 / 16.
 inline bool split_takes(int rows_each, int64_t column_blocks) {

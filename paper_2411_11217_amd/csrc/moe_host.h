@@ -54,7 +54,7 @@ int64_t linear_pages(const moe_linear_shape& s);
 // kernel, weights where the call before left them | weights from HBM (copies that exceed the last-level cache in turn): 4096 x
 // 6144 (K x N) 1 token - | 45 / 15, 100: - | 47 / 30; 6144 x 9216 16 tokens 33 / 21 | 48 / 29, 100: 41 / 39 | 59 / 50;
 // 4096 x 16384 (one full round) 16 tokens 25 / 22 | 42 / 27, 64: 31 / 24 | 40 / 30, 128: 32 / 32 | 46 / 42; 8192 x 1024 600
-// tokens 75 / 47 | 76 / 50.
+// tokens 75 / 47 | 76 / 50 (36 with the blocks of 64 rows x 64 columns that it has now up to 256 of them).
 //   Beyond one round a block's way through all of k is paid for twice: 4096 x 18432 16 tokens 26 / 33 | 38 / 39, 128: 33 / 51 | 48
 // / 73; 4096 x 32000 64 tokens 44 / 46 | 50 / 55, 100: 47 / 64 | 53 / 75; 4096 x 128256 128 tokens 224 / 304.
 //   A short way makes the other kernel's blocks (one per compute unit, set-up and tile search of 2 us) the longer ones again:

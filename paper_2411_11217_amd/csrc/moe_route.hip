@@ -312,6 +312,8 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ x,
 
 // Few tokens of a short row: a row has one chunk of eight elements per lane at most, so a wavefront of the kernel above has all the
 // work of its block.  Here it is one of the kPlaceWaves of the only block, which then places the rows as well.  The same bits.
+// 16 wavefronts would take twice the tokens, but one block of them is slower than the launch it saves, us for the layer of 256 x 512 (8
+// experts, 2 per token), 8 / 16 wavefronts: 64 tokens 25 / 27, 65 (two launches / one) 26 / 28, 128: 30 / 35.
 constexpr int kPlaceWaves = 8, kPlaceElements = 512;
 constexpr int experts_padded(int E) { return E <= 8 ? 8 : E <= 16 ? 16 : E <= 32 ? 32 : 64; }
 
