@@ -161,16 +161,18 @@ bool thin_takes_gate_up(const moe_shape& s) { return s.T <= 16 && experts_with_r
 //   8192 (5120 x 8192) 2 (80) 100 / 85, 3 (120) 133 / 126, 5 (200) 196 / 204, 7 (280) 299 / 282, 10 (400) 378 / 416; (3072 x 8192) 6 (144) 150 / 153, 8
 //   (192) 186 / 199; 4096 (4096 x 4096) 5 (160) 91 / 89, 6 (192) 96 / 100;
 //   2048 (2048 x 2048) 8 (128) 40 / 37, 11 (176) 50 / 50, 15 (240) 64 / 66, (4096 x 2048) 9 (288) 90 / 81, 13 (416) 108 / 109, 15 (480) 119 / 118.
-// The routing is not known here.  The lower range goes by the average; the upper one by the average less half the deviation (routings that
-// fill one round or less lose as much as the others gain) and plus the deviation, or all experts.
+// The routing is not known here.  The lower range goes by the average; the upper one by the average plus the deviation, or all experts, and where
+// k is not long by the average less half the deviation (routings that fill one round or less lose as much there as the others gain; with a long
+// k they lose little: 6144 x 16384, 8 experts, 4 tokens, 262 blocks on average, layer 522 / 502 over sixteen routings).
 bool thin_takes_down(const moe_shape& s) {
     if (s.T > 16) return false;
     const double per_expert = s.H / 128;
     double deviation;
     const double blocks = experts_with_rows(s, &deviation) * per_expert;
     if (s.F <= 2048) return blocks < 190 || (blocks > 256 && blocks < 500);
-    if (blocks < (s.F <= 10240 ? 130 : 190)) return true;
-    return blocks - 0.5 * deviation * per_expert > 256 && std::min(blocks + deviation * per_expert, s.E * per_expert) <= 384;
+    const bool long_k = s.F > 10240;
+    if (blocks < (long_k ? 190 : 130)) return true;
+    return blocks - (long_k ? 0.0 : 0.5 * deviation * per_expert) > 256 && std::min(blocks + deviation * per_expert, s.E * per_expert) <= 384;
 }
 
 int launch_gate_up_thin_bf16(GemmParams& p, int F, int R, int n_exp, hipStream_t st) { return launch_thin<0, 2>(p, F, R, n_exp, st); }
