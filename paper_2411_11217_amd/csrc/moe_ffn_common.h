@@ -44,9 +44,12 @@ struct GemmParams {
     int32_t balance;          // 1: no XCD runs more than an eighth of the launch's tiles, see stolen_tile
 };
 
+constexpr int kXcdUnits = 32;                        // compute units of an XCD
+
 struct TileCoord {
     int e, mt, nt, row0, rows_here;
     int mtiles;               // row tiles of the expert
+    int half;                 // -1: the whole tile; 0, 1: the half of its columns that is mine (see tail_tile)
     bool valid;
 };
 
@@ -70,10 +73,11 @@ __device__ __forceinline__ int lane_prefix_sum(int v, int lane) {
 
 __device__ __forceinline__ int uniform_of(int v_l, int src) { return __builtin_amdgcn_readfirstlane(__shfl(v_l, src, 64)); }
 
-template <int BM>
+template <int BM, bool SPLIT = false>
 __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
     TileCoord t{};
     t.valid = false;
+    t.half = -1;
     const int lane = threadIdx.x & 63;
     const int e_l = p.e_begin + lane;
     int seg0 = 0, cnt = 0;
@@ -106,6 +110,12 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
         // no XCD runs more than its even share of the launch's tiles (see stolen_tile)
         const int total = __builtin_amdgcn_readlane(lane_prefix_sum(rt_l.mtiles * p.NT, lane), 63);
         const int A = (total + 7) >> 3;
+        if constexpr (SPLIT) {
+            const TailTile tail = tail_tile(idx, A, kXcdUnits);
+            if (tail.idx < 0) return t;
+            idx = tail.idx;
+            t.half = tail.half;
+        }
         if (idx >= min(mine, A)) {
             if (idx >= A || mine >= A) return t;                     // given away, or beyond every tile
             int T[8];
@@ -118,8 +128,14 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmParams& p) {
             tiles_l = share_of(x);
             incl = lane_prefix_sum(tiles_l, lane);
         }
-    } else if (idx >= mine) {
-        return t;
+    } else {
+        if constexpr (SPLIT) {
+            const TailTile tail = tail_tile(idx, mine, stride == 8 ? kXcdUnits : 8 * kXcdUnits);
+            if (tail.idx < 0) return t;
+            idx = tail.idx;
+            t.half = tail.half;
+        }
+        if (idx >= mine) return t;
     }
     const unsigned long long holds = __ballot(idx < incl);           // lanes of this and later experts
     const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)holds) - 1);
@@ -221,6 +237,10 @@ bool thin_takes_gate_up(const moe_shape& s);
 bool thin_takes_down(const moe_shape& s);
 int launch_gate_up_thin_bf16(GemmParams& p, int F, int R, int n_exp, hipStream_t st);
 int launch_down_thin_bf16(GemmParams& p, int H, int R, int n_exp, hipStream_t st);
+
+// the bf16 launches whose last round of tiles is computed in halves (moe_ffn_halves_bf16.hip)
+int launch_gate_up_halves_bf16(const GemmParams& p, int R, int n_exp, hipStream_t st);
+int launch_down_halves_bf16(const GemmParams& p, int R, int n_exp, hipStream_t st);
 
 inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const FfnArgs& a) {
     p.offsets = a.offsets;

@@ -6,14 +6,14 @@
 // columns; a wavefront's 16 weight rows of a half-tile are 1 KiB in a row in the page, exactly one 16-byte load per lane and
 // exactly its MFMA operand, so the weights go from the page straight into registers, D k-steps ahead (p.stream: with the
 // non-temporal hint).  The activations, which all wavefronts share, are loaded as far ahead into registers and pass through a
-// double-buffered LDS stage (one k-step, 128-byte rows, the chunk swizzle of moe_ffn_bf16.hip), one barrier per k-step.
+// double-buffered LDS stage (one k-step, 128-byte rows, the chunk swizzle of moe_ffn_gemm_bf16.h), one barrier per k-step.
 // All loads are the compiler's own, in one order, so its counted waits keep D - 1 k-steps under way across the barriers.
 // Rows beyond the tile's last pair of 16-row MFMA tiles are neither loaded nor multiplied (a copy of the loop per pair:
 // branches inside it would put an LDS latency in front of every MFMA).  Few registers and little LDS: two or more blocks share
 // a compute unit and cover each other's start and end.
 //
 // RG > 1 (linear map): RG groups of CW wavefronts share the columns and split the row tiles.  Every output is the same chain of
-// MFMAs along k as in moe_ffn_bf16.hip: the same bits.
+// MFMAs along k as in moe_ffn_gemm_bf16.h: the same bits.
 #include "moe_ffn_common.h"
 
 namespace moe {
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
 
     RowsTile tc;
     if (!locate_rows_tile<BM>(p, tc)) return;
-    // diagnostic: some blocks report the shader clock they saw, as in moe_ffn_bf16.hip
+    // diagnostic: some blocks report the shader clock they saw, as in moe_ffn_gemm_bf16.h
     const bool clock_probe = p.status && (blockIdx.x & 511) == 256 && threadIdx.x == 0;
     long long probe_c = 0, probe_w = 0;
     if (clock_probe) {
@@ -254,7 +254,7 @@ int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
 }  // namespace
 
 // Where the expert GEMMs take this kernel: up to 80 rows per expert on average (of all experts: the launches of a streamed
-// layer take what the resident layer's single launch takes).  us for the layer, moe_ffn_bf16.hip's kernel / this one:
+// layer take what the resident layer's single launch takes).  us for the layer, moe_ffn_gemm_bf16.h's kernel / this one:
 // Mixtral-8x7B shape (2 of 8 experts) 1 token 196 / 165, 4: 364 / 355, 16: 469 / 455, 64: 477 / 466, 150: 485 / 478, 256 (64
 // rows each): 522 / 511, 288: 532 / 520, 400 (100 rows): 552 / 560; 64 experts of 2048 x 1024, 8 per token, 20 tokens 192 /
 // 183, 400: 241 / 235, 600 (75 rows): 252 / 247, 777 (97 rows): 259 / 262; DBRX shape 120 tokens 1089 / 1036, 250: 1129 / 1096.

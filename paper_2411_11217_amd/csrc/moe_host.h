@@ -50,7 +50,7 @@ int64_t linear_pages(const moe_linear_shape& s);
 
 // Where the dense linear map takes the kernel for few rows (csrc/moe_ffn_rows_bf16.hip): as long as its blocks of 64 columns
 // and 128 rows make one round on the 256 compute units, and with a short k and few rows.
-//   One matrix alone has too few columns to fill the chip with 256-row blocks (moe_ffn_bf16.hip).  us, those blocks / this
+//   One matrix alone has too few columns to fill the chip with 256-row blocks (moe_ffn_gemm_bf16.h).  us, those blocks / this
 // kernel, weights where the call before left them | weights from HBM (copies that exceed the last-level cache in turn): 4096 x
 // 6144 (K x N) 1 token - | 45 / 15, 100: - | 47 / 30; 6144 x 9216 16 tokens 33 / 21 | 48 / 29, 100: 41 / 39 | 59 / 50;
 // 4096 x 16384 (one full round) 16 tokens 25 / 22 | 42 / 27, 64: 31 / 24 | 40 / 30, 128: 32 / 32 | 46 / 42; 8192 x 1024 600

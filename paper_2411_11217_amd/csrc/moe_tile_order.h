@@ -160,6 +160,27 @@ MOE_HD StolenTile stolen_tile(const int* T, int A, int x, int j) {
     return t;
 }
 
+// The last round of a sequence of n tiles on `cus` compute units (an XCD's, or all of them).  Blocks are handed out first come, first
+// served, so the tiles run in rounds of about `cus`; a last round of at most cus / 2 tiles would take as long as a full one with half
+// of the compute units idle or more.  Its tiles are cut into two halves of their columns each.
+// -> tile number and half (0, 1; -1: the whole tile) of block number q of the sequence; idx < 0: none.
+struct TailTile {
+    int idx, half;
+};
+MOE_HD TailTile tail_tile(int q, int n, int cus) {
+    const int rest = n % cus, full = n - rest;
+    TailTile t;
+    if (q < full || 2 * rest > cus) {
+        t.idx = q < n ? q : -1;
+        t.half = -1;
+    } else {
+        const int j = q - full;
+        t.idx = j < 2 * rest ? full + (j >> 1) : -1;
+        t.half = j & 1;
+    }
+    return t;
+}
+
 // First row and height of row tile mt of a segment of `rows` rows that starts at row seg.
 struct RowSpan {
     int row0, rows_here;
@@ -193,7 +214,8 @@ MOE_HD RowSpan rows_of_tile(int seg, int rows, int mt, int BM, int tall_rows) {
 // (and any position of the expert's first chunk) exceeds that by is added once per expert.  Found by evaluating the
 // kernels' own share arithmetic for every m that uses chunks.  (Blocks beyond the tiles leave at once, but each still
 // costs about a microsecond of a compute unit: the bound is kept tight.)
-inline int gemm_grid(int NT, int R, int BM, int n_experts, int chunked) {
+// `split`: the tiles of a last round may be halved (tail_tile): up to 16 blocks more for each of 8 XCDs.
+inline int gemm_grid(int NT, int R, int BM, int n_experts, int chunked, bool split = false) {
     const int64_t M = R / BM + n_experts;
     const int64_t plain_groups = (NT + 7) / 8;
     int64_t slack = 0;
@@ -210,7 +232,7 @@ inline int gemm_grid(int NT, int R, int BM, int n_experts, int chunked) {
             }
         }
     }
-    return (int)(8 * (plain_groups * M + slack * n_experts));
+    return (int)(8 * (plain_groups * M + slack * n_experts + (split ? 16 : 0)));
 }
 
 // The order of the kernel for few rows per expert (moe_ffn_rows_bf16.hip).  Its tiles are numbered expert by expert, inside an

@@ -308,6 +308,25 @@ static void rows_order() {
     }
 }
 
+// The last round of a sequence of tiles: every tile is taken whole once or as both halves, in order, and 2 * 16 blocks more than
+// the full rounds are enough wherever tiles are halved.
+static void last_rounds() {
+    using namespace moe;
+    for (int cus : {32, 256})
+        for (int n = 0; n <= 3 * cus + 1; ++n) {
+            int next = 0, blocks = 0;                              // in half tiles
+            for (int q = 0; q < n + cus / 2 + 2; ++q) {
+                const TailTile t = tail_tile(q, n, cus);
+                if (t.idx < 0) continue;
+                CHECK(q == blocks && 2 * t.idx + (t.half > 0) == next && (t.half < 0) == (q < n / cus * cus || 2 * (n % cus) > cus));
+                next += t.half < 0 ? 2 : 1;
+                ++blocks;
+            }
+            CHECK(next == 2 * n && blocks <= n + cus / 2);
+        }
+    CHECK(gemm_grid(7, 300, 256, 3, 32, true) == gemm_grid(7, 300, 256, 3, 32) + 128);
+}
+
 // Beyond one round of 256 blocks of 64 columns x 128 rows the linear map must not take the kernel for few rows (it was
 // 1.1 to 1.6 times the other kernel's time there), up to one round it must.
 static void linear_rule() {
@@ -326,6 +345,7 @@ static void linear_rule() {
 int main() {
     tile_orders();
     rows_order();
+    last_rounds();
     linear_rule();
     // packer: tiles that fill their pages exactly, pages with padding at the end of a group, one tile per page
     packer_round_trip(MOE_DTYPE_F32, 128, 256, 3, 2 * 32768);

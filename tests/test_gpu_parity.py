@@ -138,6 +138,38 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
 
 
 @pytest.mark.parametrize("counts,H,F", [
+    ([90, 100, 33, 257, 129, 64, 0, 193, 81, 288, 65, 120, 97, 1, 140, 88], 4480, 128),      # down: 18 x 16 tiles of 256 columns (an odd number of page tiles)
+    ([90, 257, 150, 193, 33, 280, 64, 256], 128, 4608),                                       # gate/up: 36 x 8 tiles
+])
+def test_bf16_tiles_of_a_last_round_in_halves(counts, H, F):
+    """More than a round of tiles and less than half of another, whose tiles are computed in halves of their columns, of every height;
+    the tiles dealt to the XCDs and evened out, or neither: the same bits."""
+    E = len(counts)
+    cfg = MoEConfig("halves", "bf16", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=64 * 1024, seed=83)
+    case = Case(cfg, shuffle_pages=True, extra_pages=1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = case.view
+    h_ref, o_ref = oracle.expert_ffn(v["x"], offsets, v["W1"], v["W3"], v["W2"], cfg.dtype_code)
+    w = np.random.default_rng(1).random(cfg.T, dtype=np.float32) + 0.5
+
+    def run():
+        res = M.moe_expert_ffn(case.shape, case.x, _dev_i32(offsets), case.pw.table_dev, case.pw.pages_dev, row_w=_dev_f32(w))
+        torch.cuda.synchronize()
+        return res
+
+    h, out = run()
+    assert_h_close(h.float().cpu().numpy(), h_ref, "bf16", "h")
+    assert_close(out.cpu().numpy(), o_ref * w[:, None], "bf16", "out")
+    for option in ("balance", "xcd_remap"):
+        M.set_option(option, 0)
+        try:
+            h0, out0 = run()
+        finally:
+            M.set_option(option, 1)
+        assert torch.equal(h0, h) and torch.equal(out0, out), option
+
+
+@pytest.mark.parametrize("counts,H,F", [
     ([1, 16, 17, 31, 32, 33, 0, 48, 63, 64, 65, 128, 129], 256, 384),       # 48 rows on average: 128-row blocks
     ([1, 15, 0, 33, 64, 65, 100, 17], 128, 640),                              # 36 rows: 64-row blocks, two and ten k-steps
     ([95, 96, 97, 112, 113, 127, 40, 1, 60], 128, 256),                      # 82 rows: beyond the kernel for few rows
