@@ -12,6 +12,7 @@
 // branches inside it would put an LDS latency in front of every MFMA).  Few registers and little LDS: two or more blocks share
 // a compute unit and cover each other's start and end.
 //
+// FC = 1 in the linear map: a block's groups of 16 columns need not be a page tile's, every wavefront walks the tile of its own.
 // RG > 1 (linear map): RG groups of CW wavefronts share the columns and split the row tiles.  Every output is the same chain of
 // MFMAs along k as in moe_ffn_gemm_bf16.h: the same bits.
 #include "moe_ffn_common.h"
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
     constexpr int BM = 16 * RT, NB = MODE == 0 ? 2 * FC : FC, kCols = 16 * CW * FC;
     constexpr int kPass = 8 * CW * RG;               // rows that one load instruction per thread fetches
     constexpr int AJ = (BM + kPass - 1) / kPass, kStage = AJ * kPass * 128;
-    static_assert(RT % 2 == 0 && RT <= 8 && 128 % kCols == 0 && (kPass <= BM || RG == 1 || kPass >= 16 * RG), "");
+    static_assert(RT % 2 == 0 && RT <= 8 && (128 % kCols == 0 || (MODE == 1 && FC == 1)) && (kPass <= BM || RG == 1 || kPass >= 16 * RG), "");
     constexpr int kOutRow = kCols * 2 + 16;          // MODE 0: bytes of a row of h in LDS, 16 of padding
     constexpr int kSmem = MODE == 0 && BM * kOutRow > 2 * kStage ? BM * kOutRow : 2 * kStage;
     static_assert(MODE == 1 || RG == 1, "the row groups are the linear map's");
@@ -69,7 +70,8 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         a_off[j] = (uint32_t)src * (uint32_t)p.lda_bytes + (tid & 7) * 16;
     }
     const char* a_base = p.a_gather ? p.A : p.A + (int64_t)row0 * p.lda_bytes;
-    const int a_wr = (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    const int a_wr0 = (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    auto a_wr = [&](int j) __attribute__((always_inline)) { return (kPass % 16 ? a_wr0 ^ ((j & 1) << 6) : a_wr0) + j * kPass * 128; };     // kPass / 2 is 4 modulo 8 or 0
     const int a_rd[2] = {r * 128 + ((g ^ ((r >> 1) & 7)) << 4), r * 128 + (((4 + g) ^ ((r >> 1) & 7)) << 4)};
 
     // weights: one page tile is walked along k, MODE 0 two (the W1 and the W3 tile of the same features)
@@ -83,9 +85,12 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         }
         return p.pool + (int64_t)slot * p.page_bytes;
     };
-    constexpr int kColTiles = 128 / kCols;                // blocks per page tile along the columns
+    // MODE 1 with FC = 1: each wavefront has the page tile of its own 16 columns (a block may begin in one and end in the next)
+    constexpr bool kOwn = MODE == 1 && FC == 1;
+    constexpr int kColTiles = kOwn ? 1 : 128 / kCols;     // blocks per page tile along the columns
+    const int group = kOwn ? min(nt * CW + cw, p.n_cols / 16 - 1) : 0;       // the last block may have wavefronts too many
     {
-        const int t0 = (nt / kColTiles) * (MODE == 0 ? 2 : 1) * p.KT;
+        const int t0 = kOwn ? (group >> 3) * p.KT : (nt / kColTiles) * (MODE == 0 ? 2 : 1) * p.KT;
         page = t0 / p.tpp;
         within = t0 - page * p.tpp;
         tile[0] = page_addr(page) + (int64_t)within * kTileBytes;
@@ -109,7 +114,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
             }
         }
     };
-    const uint32_t b_off = ((nt % kColTiles) * kCols + cw * 16 * FC + r) * 64 + ((g ^ ((r >> 2) & 2)) << 4);
+    const uint32_t b_off = ((kOwn ? (group & 7) * 16 : (nt % kColTiles) * kCols + cw * 16 * FC) + r) * 64 + ((g ^ ((r >> 2) & 2)) << 4);
 
     // row group rg: row tiles rg * (NRT / RG) ..
     constexpr int TPW = (RT + RG - 1) / RG;
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         auto step = [&](int s, int slot, bool more) __attribute__((always_inline)) {     // slot: known at compile time
             char* st = smem + buf;
 #pragma unroll
-            for (int j = 0; j < NA; ++j) *(i32x4*)(st + a_wr + j * kPass * 128) = areg[slot][j];
+            for (int j = 0; j < NA; ++j) *(i32x4*)(st + a_wr(j)) = areg[slot][j];
             __syncthreads();
             if (more) load_a(s + D, slot);
             i32x4 a[2][NT];
@@ -220,12 +225,13 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
         else store_rows(Num<0>{});
     } else {
         const int col = nt * kCols + cw * 16 * FC + r;
+        const bool mine = !kOwn || group == nt * CW + cw;
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = (tile0 + i) * 16 + g * 4 + v;
-                if (row >= rows_here || (RG > 1 && i >= tiles_mine)) continue;
+                if (row >= rows_here || !mine || (RG > 1 && i >= tiles_mine)) continue;
                 const int64_t o = (int64_t)(row0 + row) * p.ldo + col;
                 const float wgt = p.row_w ? p.row_w[row0 + row] : 1.0f;
 #pragma unroll
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(64 * CW * RG) void ffn_rows_bf16(const GemmParams p
 
 template <int MODE, int RT, int CW, int FC, int RG, int D>
 int launch_rows(GemmParams& p, int cols, int R, int n_exp, hipStream_t st) {
-    p.NT = cols / (16 * CW * FC);
+    p.NT = (cols / 16 + CW * FC - 1) / (CW * FC);
     hipLaunchKernelGGL((ffn_rows_bf16<MODE, RT, CW, FC, RG, D>), dim3(rows_grid(p.NT, R, 16 * RT, n_exp)), dim3(64 * CW * RG), 0, st, p);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
@@ -282,24 +288,31 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
     return launch_rows<1, 8, 8, 1, 1, 4>(p, H, R, n_exp, st);
 }
 
-// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here).  Up to 64 rows 32 columns as long as
-// they make one round of blocks, else 64 (6144 x 9216 50 tokens 60 / 42 us), and with 32 columns two row groups.  More rows: blocks
-// of 64 rows x 64 columns as long as they make one round.  Blocks of 128 rows x 32 columns, whose four row groups each loaded the
-// weights, brought 32 KB per k-step to a compute unit where these bring 16; us for the pre-attention task, those / these, weights where
-// the call before left them | from HBM: 4096 x 6144 70 tokens 31 / 27 | 36 / 29, 100: 32 / 27 | 37 / 31, 128: 33 / 27 | 39 / 34; 2048 x 3072 300
-// tokens (128 rows x 64 columns before) 23 / 22 | 24 / 22; the post-attention task of the Mixtral-8x7B shape, 100 tokens 490 / 478.  Beyond one round 128 rows x 64 columns:
-// 4096 x 6144 192 tokens 36 with 64 rows, 35 with 128; 6144 x 9216 70 tokens 56 and 45.
+// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here): 64 rows, and the fewest groups of 16
+// columns with which all blocks make one round.  A compute unit has some 110 lines under way; a line from HBM holds its place for about
+// 0.55 us, one from the L2 for 0.13, so a compute unit brings 25 GB/s of the one or 110 GB/s of the other, and the launch wants every
+// compute unit to take an equal share.  With one and two groups the wavefronts split the rows too (their weights meet in the L1); three
+// groups with two row groups each lost 1 - 2 us with weights from HBM (4096 x 6144 100 tokens 22.8 / 24.0).  More groups with row groups: 20 - 40 % slower.
+// us for the launch, the blocks before (32 columns, or 64, or 128 rows x 64 columns) / these, weights where the call before left them | from HBM: 4096 x 4096
+// 36 tokens 16.7 / 15.7 | 18.1 / 17.1, 100: 20.1 / 16.9 | 21.8 / 18.5; 4096 x 6144 160: 27.6 / 22.2 | 29.3 / 24.5, 256: 28.2 / 24.0 | 38.3 / 30.1; 6144 x 9216 100: 38.7 / 31.9 | 52.3 /
+// 37.7; 2048 x 3072 100: 12.3 / 10.3 | 12.9 / 10.7, 400: 17.0 / 14.7 | 17.0 / 14.9; 4096 x 512 4000: 46.2 / 27.2; 512 x 512 300: 6.6 / 5.0; equal where the blocks are what they
+// were (4096 x 6144 100: 64 columns) and with up to 16 rows (4096 x 4096 1 token 12.7 / 13.1 | 14.6 / 14.2).  Up to 64 rows four groups are the most: more
+// columns per block only leave compute units idle (6144 x 9216 40 tokens 29.1 / 27.4).
 // Temporal loads, us without / with the non-temporal hint, weights where the call before left them (one matrix fits the 256 MiB
 // last-level cache) | weights from HBM: 4096 x 6144 64 tokens 17 / 21 | 21 / 22; 6144 x 9216 64 tokens 30 / 35 | 38 / 37, 128: 40 /
-// 59 | 58 / 60.
-// Groups of wavefronts that split k were faster than the blocks of 128 rows x 32 columns too (4096 x 6144 100 tokens 33 against 39 with
-// the hint), but they change the order of the sums, which the O projection hands on to a rounding and the router.
+// 59 | 58 / 60 (with the blocks before).
+// Groups of wavefronts that split k change the order of the sums, which the O projection hands on to a rounding and the router: left out.  So are
+// two k-steps behind one barrier: within 5 % either way, the barriers are not what the launch waits for.
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
-    const bool few_columns = N / 32 * ((T + 127) / 128) <= kComputeUnits;
-    if (T <= 64 && few_columns) return launch_rows<1, 4, 2, 1, 2, 8>(p, N, T, 1, st);
-    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 8>(p, N, T, 1, st);
-    if (N / 64 * ((T + 63) / 64) <= kComputeUnits) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
-    return launch_rows<1, 8, 4, 1, 2, 4>(p, N, T, 1, st);
+    const int64_t groups = N / 16, row_tiles = ((int64_t)T + 63) / 64;
+    auto one_round = [&](int cw) { return row_tiles * ((groups + cw - 1) / cw) <= kComputeUnits; };      // blocks of 64 rows x 16 cw columns
+    if (one_round(1)) return launch_rows<1, 4, 1, 1, 4, 8>(p, N, T, 1, st);
+    if (one_round(2)) return launch_rows<1, 4, 2, 1, 2, 6>(p, N, T, 1, st);
+    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
+    if (one_round(4)) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
+    if (one_round(5)) return launch_rows<1, 4, 5, 1, 1, 4>(p, N, T, 1, st);
+    if (one_round(6)) return launch_rows<1, 4, 6, 1, 1, 4>(p, N, T, 1, st);
+    return launch_rows<1, 4, 8, 1, 1, 4>(p, N, T, 1, st);
 }
 
 }  // namespace moe

@@ -61,9 +61,12 @@ int64_t linear_pages(const moe_linear_shape& s);
 // 1024 x 65536 32 tokens 28 / 25 | 33 / 29, 64: 31 / 30 | 36 / 36, 128: 34 / 36 | 39 / 50; 1024 x 18432 32 tokens 12 / 12 | 17 / 14;
 // 1536 x 18432 32 tokens 14 / 15 | 21 / 19, 1536 x 65536: 37 / 33 | 44 / 41; 2048 x 32768 32 tokens 24 / 23 | 28 / 27, but 2048 x 18432: 16
 // / 19 | 22 / 23.
+//   With more than 128 rows, as long as its blocks of 64 rows x 128 columns make one round: us, row tiles of 128 or 256 / this kernel, 4096 x
+// 6144 300 tokens 35 / 26 | 41 / 34; 6144 x 9216 140: 44 / 35 | 53 / 43; 4096 x 10880 192: 37 / 28 | 43 / 37; 2048 x 6144 300: 23 / 16 | 27 / 20; 4096 x 4096 450: 29 / 25 | 32
+// / 29; in between 4096 x 5120 300: 28 / 25 | 30 / 33.
 inline bool linear_takes_rows_kernel(int T, int K, int N) {
     constexpr int64_t kComputeUnits = 256;           // MI355X
-    return (int64_t)(N / 64) * (((int64_t)T + 127) / 128) <= kComputeUnits || (K <= 1536 && T <= 32);
+    return (int64_t)(N / 64) * (((int64_t)T + 127) / 128) <= kComputeUnits || (K <= 1536 && T <= 32) || (T > 128 && (((int64_t)T + 63) / 64) * (N / 128) <= kComputeUnits);
 }
 
 }  // namespace moe

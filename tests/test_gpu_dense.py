@@ -69,6 +69,23 @@ def test_linear_with_few_rows(T, K, N):
     assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
 
 
+@pytest.mark.parametrize("T,K,N", [(300, 256, 384), (17, 1152, 4096), (130, 128, 2048), (64, 640, 6144), (33, 128, 9216), (300, 256, 3072), (129, 640, 6144),
+                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (192, 256, 9216)])
+def test_linear_blocks_of_one_to_eight_wavefronts(T, K, N):
+    # one, two, four, five (the last block has a wavefront too many), six (two too many, and none) and eight column groups of 16 per
+    # block; two to eighteen k-steps, last row tiles of 1 to 64 rows
+    g = torch.Generator().manual_seed(T + K)
+    x = torch.randn((T, K), generator=g)
+    W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
+    ls = M.make_linear_shape(T, K, N, 3 * 16384)
+    table, pool = paged_linear(ls, W)
+    _, xn, qkv, qkv16 = M.moe_pre_attention(ls, None, x.cuda(), torch.ones(K).cuda(), 1e-5, table, pool)
+    out = M.moe_linear(ls, xn, table, pool)
+    torch.cuda.synchronize()
+    assert torch.equal(out, qkv) and torch.equal(qkv16, qkv.to(torch.bfloat16))
+    assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
+
+
 @pytest.mark.parametrize("T,K,N", [(129, 128, 9216), (192, 640, 12800), (256, 256, 9216), (257, 384, 6144), (385, 128, 6144), (512, 256, 6144)])
 def test_linear_row_tiles_of_128(T, K, N):
     # one round of blocks of 128 rows x 128 columns: against the oracle, and bit by bit against row tiles of 256
