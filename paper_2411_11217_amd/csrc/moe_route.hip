@@ -4,7 +4,7 @@
 // The product is a tall-skinny contraction (E <= 64 outputs per token), bound
 // by reading x from HBM once.
 //
-// bf16 (route_mfma_kernel): a block of 16 wavefronts (8 beyond 32 experts) owns 16 tokens.  The
+// bf16 (route_mfma_kernel): a block of 16 wavefronts (8 beyond 32 experts) owns up to 16 tokens.  The
 // reduction over H is cut into units of 64 elements (one 128-byte line per
 // token), dealt round robin to the wavefronts; for a unit, lane (r = lane % 16,
 // g = lane / 16) loads bytes g*16 .. g*16+15 of both halves of token r's line and
@@ -27,6 +27,8 @@
 // With at most 16 tokens of bf16 data one block has all of them, and in moe_layer it does the permutation too, with the
 // counting sort of moe_permute.hip on the ids that it has in LDS: a launch less, which is 4 to 5 us of a call that can
 // be as short as 30.  With f32 data the same is done for short rows (route_place_f32_kernel).
+#include <algorithm>
+
 #include "moe_place.h"
 
 namespace moe {
@@ -42,10 +44,28 @@ __device__ __forceinline__ void load8(const float* base, size_t elem, float (&v)
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
+// The maximum over groups of EP lanes (a power of two), in all their lanes.  Inside rows of 16 lanes with data-parallel moves, which
+// answer at once where a shuffle goes through LDS.
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float v) {
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false)));
+}
+template <int EP>
+__device__ __forceinline__ float group_max(float v) {
+    static_assert(EP >= 8, "");
+    v = max_dpp<0xB1>(v);                            // lane ^ 1
+    v = max_dpp<0x4E>(v);                            // lane ^ 2
+    v = max_dpp<0x141>(v);                           // the mirror lane of eight
+    if (EP >= 16) v = max_dpp<0x140>(v);             // the mirror lane of sixteen
+    if (EP >= 32) v = fmaxf(v, __shfl_xor(v, 16, 64));
+    if (EP >= 64) v = fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)));
+    return v;
+}
+
 // Top-k of lg[0 .. E) by descending value (the lower index keeps a tie) and the softmax over the selected values, for token
 // tok, by EP lanes of one wavefront (EP = experts padded to a power of two; lane `le` of the group holds expert le): k rounds
 // of a maximum over the lanes and a ballot for its first holder.  One lane per token took k * E steps of LDS latency
-// each: with 64 experts, 8 per token, 777 tokens the launch took 34 us, now 17 (the f32 kernel with 16384 and more tokens of a power
+// each: with 64 experts, 8 per token, 777 tokens the launch took 34 us, then 17, and 15.6 with the maximum by data-parallel moves instead of shuffles (the f32 kernel with 16384 and more tokens of a power
 // of two of elements loses 2 - 5 %, 65536 tokens of 4096, 8 experts: 201 / 212; with fewer it gains as much).  A NaN is selected only when no free expert precedes it, as
 // a scan that keeps the first and replaces it by what compares greater would do.  Every lane of the wavefront calls this; `live`: the token exists.
 template <int EP>
@@ -64,8 +84,7 @@ __device__ __forceinline__ void select_top_k(const float* lg, int E, int k, int 
     for (int s = 0; s < k; ++s) {
         const int f0 = __ffsll((long long)group(__ballot(free_e))) - 1;      // s < k <= E: there is one
         float bv = free_e && !nan ? v : -INFINITY;
-#pragma unroll
-        for (int m = EP / 2; m >= 1; m >>= 1) bv = fmaxf(bv, __shfl_xor(bv, m, 64));
+        bv = group_max<EP>(bv);
         const int top = __ffsll((long long)group(__ballot(free_e && !nan && v == bv))) - 1;
         const bool take_nan = (nans >> f0) & 1;
         const int best = take_nan ? f0 : top;
@@ -150,7 +169,7 @@ __device__ __forceinline__ void place_rows(const int32_t* s_ids, const float* s_
 template <int NE, int NW, bool PLACE>
 __device__ __forceinline__ void route_mfma(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
                                            int32_t* __restrict__ ids, float* __restrict__ w, float* __restrict__ logits,
-                                           int T, int H, int E, int k, const PlaceOut& place) {
+                                           int T, int H, int E, int k, int tpb, const PlaceOut& place) {
     constexpr int EP = NE * 16;
     // Units whose loads are in flight together.  Beyond 32 experts two: with four a wavefront needs 193 registers and only one
     // block fits a compute unit; 65536 tokens of 2048, 64 experts, 8 per token: 251 us with four, 156 with two, 777 tokens 17
@@ -162,10 +181,10 @@ __device__ __forceinline__ void route_mfma(const char* __restrict__ x, const cha
     __shared__ float s_w[PLACE ? 16 * MOE_MAX_EXPERTS : 1];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.x * 16;
+    const int t0 = blockIdx.x * tpb;
     const int r = lane & 15, g = lane >> 4;
     const size_t row_bytes = (size_t)H * 2;
-    const char* xa = x + (size_t)min(t0 + r, T - 1) * row_bytes + g * 16;      // rows past the end repeat the last token
+    const char* xa = x + (size_t)min(t0 + min(r, tpb - 1), T - 1) * row_bytes + g * 16;      // rows past the block's tokens repeat the last one
     const char* wb[NE];
     bool wv[NE];
 #pragma unroll
@@ -206,7 +225,7 @@ __device__ __forceinline__ void route_mfma(const char* __restrict__ x, const cha
 #pragma unroll
         for (int i = 0; i < 4; ++i) s_part[wave][g * 4 + i][n * 16 + r] = acc[n][i];
     __syncthreads();
-    for (int v = threadIdx.x; v < 16 * EP; v += NW * 64) {
+    for (int v = threadIdx.x; v < tpb * EP; v += NW * 64) {
         const int t = v / EP, e = v % EP;
         float sum = 0.f;
 #pragma unroll
@@ -217,7 +236,7 @@ __device__ __forceinline__ void route_mfma(const char* __restrict__ x, const cha
     }
     __syncthreads();
     constexpr int TW = 64 / EP;                              // tokens a wavefront selects for at a time
-    const int live = min(16, T - t0);
+    const int live = min(tpb, T - t0);
     for (int t = wave * TW; t < live; t += NW * TW)          // the whole wavefront, as long as its first token exists
         select_top_k<EP>(s_logit[t + lane / EP], E, k, t0 + t + lane / EP, t + lane / EP < live, ids, w, PLACE ? s_ids : nullptr, PLACE ? s_w : nullptr);
     if constexpr (PLACE) {
@@ -229,15 +248,15 @@ __device__ __forceinline__ void route_mfma(const char* __restrict__ x, const cha
 template <int NE, int NW>
 __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
                                                              int32_t* __restrict__ ids, float* __restrict__ w, float* __restrict__ logits,
-                                                             int T, int H, int E, int k) {
-    route_mfma<NE, NW, false>(x, Wr, bias, ids, w, logits, T, H, E, k, PlaceOut{});
+                                                             int T, int H, int E, int k, int tpb) {
+    route_mfma<NE, NW, false>(x, Wr, bias, ids, w, logits, T, H, E, k, tpb, PlaceOut{});
 }
 
 template <int NE, int NW>
 __global__ __launch_bounds__(NW * 64) void route_place_kernel(const char* __restrict__ x, const char* __restrict__ Wr, const float* __restrict__ bias,
                                                               int32_t* __restrict__ ids, float* __restrict__ w, int T, int H, int E, int k,
                                                               const PlaceOut place) {
-    route_mfma<NE, NW, true>(x, Wr, bias, ids, w, nullptr, T, H, E, k, place);
+    route_mfma<NE, NW, true>(x, Wr, bias, ids, w, nullptr, T, H, E, k, 16, place);
 }
 
 // EP: experts padded to a compile-time bound (a power of two, 8..64).  The logits of the 64 / EP tokens from t0 on, over the chunks
@@ -359,13 +378,19 @@ int launch_f32(const moe_shape& s, const void* x, const void* Wr, const float* b
 template <int NE, int NW>
 int launch_bf16(const moe_shape& s, const void* x, const void* Wr, const float* bias, int32_t* ids, float* w,
                 float* logits, hipStream_t st, const PlaceOut* place) {
-    const dim3 grid((s.T + 15) / 16), block(NW * 64);
+    // Tokens of a block: as few as give every compute unit one, 16 at most (the rows of the MFMA beyond them repeat the last token: no more
+    // memory, the same sums).  Blocks of 16 tokens left most compute units idle below 4096 tokens, and one brings only about 25 GB/s from
+    // HBM.  us for the launch with 16 / this many, x and Wr from HBM: Mixtral-8x7B shape 36 tokens 8.6 / 6.3, 256: 9.1 / 6.4, 1000: 9.8 / 7.4, 3000: 10.4 / 9.9; DBRX shape
+    // 600 tokens 16.8 / 11.9; 64 experts of 2048, 8 per token, 777 tokens 17.5 / 13.8.  Fewer than a round of blocks needs is slower: 1000 tokens by 2: 11.8.
+    constexpr int kComputeUnits = 256;               // MI355X
+    const int tpb = std::min(16, (s.T - 1) / kComputeUnits + 1);
+    const dim3 grid((s.T + tpb - 1) / tpb), block(NW * 64);
     if (place)
         hipLaunchKernelGGL((route_place_kernel<NE, NW>), dim3(1), block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, s.T, s.H, s.E,
                            s.k, *place);
     else
         hipLaunchKernelGGL((route_mfma_kernel<NE, NW>), grid, block, 0, st, (const char*)x, (const char*)Wr, bias, ids, w, logits, s.T, s.H,
-                           s.E, s.k);
+                           s.E, s.k, tpb);
     MOE_HIP_TRY(hipGetLastError());
     return MOE_OK;
 }

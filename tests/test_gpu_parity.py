@@ -450,6 +450,25 @@ def test_router_shapes(T, H, E, k, dtype):
     compare_routing(cfg, ids.cpu().numpy(), w.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("T", [256, 257, 511, 513, 1025, 2047, 3841, 4097])
+@pytest.mark.parametrize("E,k", [(8, 2), (17, 3), (64, 8)])
+def test_router_tokens_per_block(T, E, k):
+    """Batches on both sides of one to sixteen tokens per block: against the oracle, and a token's logits, experts and weights are the
+    bits that a batch of its first 100 tokens gives."""
+    cfg = MoEConfig("tpb", "bf16", T=T, H=256, F=128, E=E, k=k, page_bytes=64 * 1024, seed=60 + E)
+    case = Case(cfg)
+    ref = case.oracle_route()
+    ids, w, logits = M.moe_route(case.shape, case.x, case.Wr, want_logits=True)
+    few = M.make_shape(100, 256, 128, E, k, "bf16", 64 * 1024)
+    for at in (0, T - 100):
+        sub = M.moe_route(few, case.x[at:at + 100].contiguous(), case.Wr, want_logits=True)
+        torch.cuda.synchronize()
+        for a, b in zip((ids, w, logits), sub):
+            assert torch.equal(a[at:at + 100], b)
+    np.testing.assert_allclose(logits.cpu().numpy(), ref["logits"], rtol=0, atol=2e-5 * max(1.0, np.abs(ref["logits"]).max()))
+    compare_routing(cfg, ids.cpu().numpy(), w.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("E,k", [(1, 1), (5, 5), (8, 3), (17, 4), (64, 8)])
 def test_router_selects_like_a_scan_with_ties_infinities_and_nan(E, k, dtype):
