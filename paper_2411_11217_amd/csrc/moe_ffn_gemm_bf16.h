@@ -888,7 +888,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 template <int MODE, int NB, int TR = BM, bool SPLIT = false>
 int launch_stages(const GemmParams& p, int R, int n_exp, hipStream_t st) {
     constexpr int lds = kLdsBytes;
-    const int grid = gemm_grid(p.NT, R, TR, n_exp, p.chunked, SPLIT);
+    const int grid = gemm_grid(p.NT, R, TR, n_exp, p.chunked, SPLIT, p.balance && p.xcd_remap);
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {

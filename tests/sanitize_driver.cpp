@@ -325,6 +325,19 @@ static void last_rounds() {
             CHECK(next == 2 * n && blocks <= n + cus / 2);
         }
     CHECK(gemm_grid(7, 300, 256, 3, 32, true) == gemm_grid(7, 300, 256, 3, 32) + 128);
+    // with the XCDs evened out the grid has every tile's block and no more than the bound on the row tiles asks for
+    std::uniform_int_distribution<int> rows(0, 900);
+    for (int rep = 0; rep < 300; ++rep) {
+        const int E = 1 + (int)(g_rng() % 64), NT = 1 + (int)(g_rng() % 120);
+        int R = 0, total = 0;
+        for (int e = 0; e < E; ++e) {
+            const int c = g_rng() % 4 ? rows(g_rng) : 0;
+            R += c;
+            total += row_tiles_of(c, 256, rep % 2 ? 32 : 0).mtiles * NT;
+        }
+        const int grid = gemm_grid(NT, R, 256, E, 32, rep % 3 == 0, true) - (rep % 3 == 0 ? 128 : 0);
+        CHECK((total + 7) / 8 <= grid / 8 && grid < NT * (R / 256 + E) + 8);
+    }
 }
 
 // Beyond one round of 256 blocks of 64 columns x 128 rows the linear map must not take the kernel for few rows (it was
