@@ -263,7 +263,12 @@ inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const 
     // chunks only when the experts have more than half a row tile of rows on average: below that the launch streams
     // the weights, single groups spread over the XCDs are the better order, and the grid needs no slack for chunks
     const int64_t rows_each = (int64_t)s.T * s.k / std::max(1, a.e_end - a.e_begin);
-    p.chunked = rows_each > 128 ? std::min(std::max(get_opt(OPT_CHUNKED), 0), 32) : 0;
+    // Up to 256 rows each most experts are one row tile and the launch still streams; an expert that the routing gives several has its
+    // weights shared in smaller chunks, on more XCDs at a time.  us for the layer with chunks of 32 / 8 tiles, 40 % of the rows on one expert: Mixtral-8x7B shape 600
+    // tokens 659 / 634, 1000: 849 / 820, DBRX shape 700 tokens 1333 / 1265; evenly shared out 623 / 624 (800 tokens), 1072 / 1073 (8x22B shape, 1000), 64 experts
+    // of 2048 x 1024, 2000 tokens 344 / 335.  With more rows 32: 8x7B shape 8192 tokens 4324 / 4413 (16).
+    const int most = rows_each > 256 ? 32 : rows_each > 128 ? 8 : 0;
+    p.chunked = std::min(std::max(get_opt(OPT_CHUNKED), 0), most);
 }
 
 // parameters of the gate/up launch (K = H, output h[R][F]) and of the down launch
