@@ -32,7 +32,7 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-pthread", "-Wall", "-I", os.path.j
 # of the kernel: a pointer came back as accumulator bits and the kernel faulted).  The kernels are written so that it
 # has no need to; this check of the assembly the compiler generates makes a build fail if it ever does, or if such a
 # kernel spills to scratch memory.  The kernels' own uses print as a[N] or a[N:M], the allocator's as aN.
-ACCUMULATOR_OWNERS = {"moe_ffn_bf16.hip", "moe_ffn_halves_bf16.hip"}
+ACCUMULATOR_OWNERS = {"moe_ffn_bf16.hip", "moe_ffn_halves_bf16.hip", "moe_ffn_narrow_bf16.hip"}
 
 
 def check_kernel_assembly(asm_path: str) -> None:

@@ -42,8 +42,12 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     // down_cols: 0 = this rule, 1 / 2 = force NB.
     const int opt = get_opt(OPT_DOWN_COLS);
     const int64_t narrow_tiles = n_exp * row_tiles_each * (int64_t)g.dt;
+    // Where even these are at most half a round: 64-wide ones, as long as the tiles that the routing makes are at most half a round
+    // (an expert with 40 % of the rows: 2048 x 4096, 1024 tokens 208 tiles, 65 us whole and 82 if halved).  us for the launch, 128 / 64 wide: 2048 x 4096 500 tokens (128
+    // tiles) 52 / 44, 1024: 73 / 65; 1024 x 2816 500 tokens (64) 30 / 25, 1024: 41 / 35, 1500 (128): 36 / 32; more tiles, halved all the same: 2048 x 4096 1400 tokens (256) 60 / 80.
     if (opt == 1 || (opt == 0 && narrow_tiles <= kComputeUnits)) {
         p.NT = (int32_t)g.dt;
+        if (narrow_tiles <= kComputeUnits / 2) return launch_down_narrow_halves_bf16(p, R, n_exp, st);
         return launch_stages<1, 1>(p, R, n_exp, st);
     }
     return half_round() ? launch_down_halves_bf16(p, R, n_exp, st) : launch_stages<1, 2>(p, R, n_exp, st);

@@ -241,6 +241,8 @@ int launch_down_thin_bf16(GemmParams& p, int H, int R, int n_exp, hipStream_t st
 // the bf16 launches whose last round of tiles is computed in halves (moe_ffn_halves_bf16.hip)
 int launch_gate_up_halves_bf16(const GemmParams& p, int R, int n_exp, hipStream_t st);
 int launch_down_halves_bf16(const GemmParams& p, int R, int n_exp, hipStream_t st);
+// the down launch with 128-wide column tiles, in its last round 64-wide ones (moe_ffn_narrow_bf16.hip)
+int launch_down_narrow_halves_bf16(const GemmParams& p, int R, int n_exp, hipStream_t st);
 
 inline void fill_common(GemmParams& p, const moe_shape& s, const Geom& g, const FfnArgs& a) {
     p.offsets = a.offsets;

@@ -250,6 +250,22 @@ __device__ __forceinline__ void mfma_extra_tile_4(f32x4 (&acc)[4], const i32x4& 
     }
 #endif
 }
+// and for the two column fragments of a block of 64 columns
+__device__ __forceinline__ void mfma_extra_tile_2(f32x4 (&acc)[2], const i32x4& a, const i32x4 (&b)[2], int which) {
+#ifdef __HIP_DEVICE_COMPILE__
+#define MOE_ZM(J, B) "v_mfma_f32_16x16x32_bf16 %" #J ", %2, %" #B ", %" #J "\n\t"
+    asm volatile("s_cmp_lg_u32 %5, 0\n\ts_cbranch_scc1 1f\n\t"
+                 MOE_ZM(0, 3) MOE_ZM(1, 4)
+                 "s_branch 3f\n1:\n\ts_cmp_lg_u32 %5, 1\n\ts_cbranch_scc1 2f\n\t"
+                 MOE_ZM(0, 3)
+                 "s_branch 3f\n2:\n\t"
+                 MOE_ZM(1, 4)
+                 "3:\n\t"
+                 : "+v"(acc[0]), "+v"(acc[1])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "s"(which)
+                 : "scc");
+#endif
+}
 __device__ __forceinline__ void load_vgpr_16(i32x4& dst, const char* ptr) {
 #ifdef __HIP_DEVICE_COMPILE__
     asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(ptr) : "memory");
@@ -288,18 +304,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // One tile of an expert.  NB: page tiles per block along the columns.  2: the 256-column block described above.  1: 256 rows x
 // 128 columns (MODE 0: 64 features, gate and up), wavefront tile 128 x 64, for launches with too few 256-wide tiles to occupy the
-// chip and for the last round of a launch (see tail_tile).  nt: column tile, in units of this block's columns.
+// chip and for the last round of a launch (see tail_tile).  0 (MODE 1): 256 rows x 64 columns, half of a page tile.  nt: column tile, in units of this block's columns.
 // TR: most rows of a row tile without its extra ones.  128 (the linear map with NB = 1): twice the blocks, none but the loops of
 // short tiles.
 template <int MODE, int NB, int TR>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& tc, const int nt) {
-    static_assert(TR == BM || (TR == 128 && NB == 1), "");
+    static_assert((TR == BM || (TR == 128 && NB == 1)) && (NB > 0 || MODE == 1), "");
     constexpr int S = kStages;
     constexpr bool TWO_WALKS = MODE == 0 || NB == 2;      // two page tiles are walked along k
-    constexpr int kPart = MODE == 0 && NB == 1 ? kHalfTile / 2 : kHalfTile;     // what a stage has of a half-tile
-    constexpr int NJ = 4 * NB;                   // 16-column MFMA tiles (B fragments) per wavefront
+    constexpr bool HALVES = NB == 0 || (MODE == 0 && NB == 1);       // half of a page tile's rows each
+    constexpr int kPart = HALVES ? kHalfTile / 2 : kHalfTile;         // what a stage has of a half-tile
+    constexpr int NJ = NB == 0 ? 2 : 4 * NB;     // 16-column MFMA tiles (B fragments) per wavefront
+    constexpr int kLB = NB == 0 ? 1 : 2 * NB;    // weight loads of a half-step per wavefront
     constexpr int NMF = 4 * NJ;                  // MFMAs of a group: four 16-row tiles x NJ
-    constexpr int kLoadsPerStage = 4 + 2 * NB;   // global_load_lds instructions per wavefront per stage
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -326,7 +343,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
 
     // ---- weight tiles through the page table -------------------------------------
     const int32_t* trow = p.table + (size_t)(p.table_row_mod ? e % p.table_row_mod : e) * p.ppe + p.group_base;
-    const int pt0 = MODE == 0 ? (NB == 2 ? nt : nt >> 1) * 2 : nt * NB;
+    const int pt0 = MODE == 0 ? (NB == 2 ? nt : nt >> 1) * 2 : NB == 0 ? nt >> 1 : nt * NB;
     const int pt1 = (pt0 + 1 < p.n_page_tiles) ? pt0 + 1 : pt0;   // odd tile count: the second half is masked (NB = 2)
     int bad = 0;
     auto page_addr = [&](int page) __attribute__((always_inline)) -> const char* {
@@ -421,8 +438,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
         const int64_t src = p.a_gather ? (int64_t)min(max(p.a_gather[row0 + er] / p.a_div, 0), p.a_rows - 1) : (int64_t)row0 + er;
         ae_ptr = p.A + src * p.lda_bytes + (lane >> 4) * 16;      // + 64 bytes per half-step
     }
-    // weight half-tiles are copied linearly (the narrow gate/up block: 64 rows of each)
-    const uint32_t b_off = (MODE == 0 && NB == 1 ? (nt & 1) * kPart : 0) + wave * 1024 + lane * 16;
+    // weight half-tiles are copied linearly (HALVES: 64 rows of each)
+    const uint32_t b_off = (HALVES ? (nt & 1) * kPart : 0) + wave * 1024 + lane * 16;
 
     // The loads issued during half-step h: activation instructions (h & 1) * 4 + i (i = 0..3) of the
     // k-step two ahead, and the weight stage of half-step h + 3 (instructions 4, 5: half-tile 0; 6, 7:
@@ -444,7 +461,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
         }
     };
     auto advance_b = [&](int kn, int odd, int i) __attribute__((always_inline)) {
-        if (i == 2 * NB - 1 && odd && kn + 1 < KH) walk_next_both();
+        if (i == kLB - 1 && odd && kn + 1 < KH) walk_next_both();
     };
     // the loads of the prologue (no MFMA to pair them with)
     auto load_a = [&](int part, int i) __attribute__((always_inline)) {
@@ -473,7 +490,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
     // activations (128-byte rows, two half-steps per stage): chunk 4*hp + lane/16 in half-step parity hp.
     const int b_frag0 = (lane & 15) * kRowB + (((lane >> 4) ^ ((lane >> 2) & 2)) << 4);
     // B fragment j: MODE 0: gate rows wn*64 + (j%4)*16 of tile 0 (j < 4), the same up rows of tile 1 (j >= 4; NB = 1: half of each);
-    //               MODE 1: rows wn*(16*NJ) + j*16 of the 128*NB rows of the block's tiles
+    //               MODE 1: rows wn*(16*NJ) + j*16 of the rows of the block's tiles
     int b_base[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -567,7 +584,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
             MOE_FENCE();
             if constexpr (!HALF) {
                 constexpr int NF1 = NJ + 4;                         // fetches of group 1: B0, A0, B1 .. B(NJ-1), A1, A2, A3
-                constexpr int LA0 = NF1 + (NB == 2 ? 2 : 1), LAS = NB == 2 ? 4 : 2;     // MFMAs with an activation load behind them
+                constexpr int LA0 = NB == 0 ? 4 : NF1 + (NB == 2 ? 2 : 1), LAS = NB == 2 ? 4 : NB == 1 ? 2 : 1;     // MFMAs with an activation load behind them
                 static_for<NMF>([&](auto mc) __attribute__((always_inline)) {
                     constexpr int m = decltype(mc)::value;
                     constexpr int r = m / NJ, j = (r & 1) ? NJ - 1 - m % NJ : m % NJ;   // back and forth: one operand stays at each row change
@@ -589,11 +606,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
                 // half-step for the one wavefront of the SIMD to issue.
                 __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0)
                 MOE_FENCE();
-                constexpr int LB0 = NB == 2 ? 8 : 6, LBS = NB == 2 ? 6 : 5;             // MFMAs with a weight load behind them
+                constexpr int LB0 = NB == 2 ? 8 : NB == 1 ? 6 : 5, LBS = NB == 2 ? 6 : 5;             // MFMAs with a weight load behind them
                 static_for<NMF>([&](auto mc) __attribute__((always_inline)) {
                     constexpr int m = decltype(mc)::value;
                     constexpr int r = m / NJ, j = (r & 1) ? NJ - 1 - m % NJ : m % NJ;   // back and forth: one operand stays at each row change
-                    constexpr bool ld = LB && m >= LB0 && (m - LB0) % LBS == 0 && (m - LB0) / LBS < 2 * NB;
+                    constexpr bool ld = LB && m >= LB0 && (m - LB0) % LBS == 0 && (m - LB0) / LBS < kLB;
                     if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, AX[r], BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, (m - LB0) / LBS>{}, integral_constant<bool, ST>{}, kn);
                     else mfma(integral_constant<int, r>{}, integral_constant<int, j>{}, AX[r], BF[HP][j]);
                     MOE_FENCE();
@@ -603,7 +620,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
                     }
                 });
                 if constexpr (TALL) {                        // tall tile: the extra row tile against the column fragments of k
-                    if constexpr (NJ == 8) mfma_extra_tile_8<MODE == 0>(accE, AE[U], BF[HP], extra_which);
+                    if constexpr (NJ == 2) mfma_extra_tile_2(accE, AE[U], BF[HP], extra_which);
+                    else if constexpr (NJ == 8) mfma_extra_tile_8<MODE == 0>(accE, AE[U], BF[HP], extra_which);
                     else mfma_extra_tile_4<MODE == 0>(accE, AE[U], BF[HP], extra_which);
                     MOE_FENCE();
                     // the fragment of half-step k + 4: there is one exactly while the activation loads go on (the last four
@@ -634,11 +652,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
                 });
                 __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): as in the full loop
                 MOE_FENCE();
-                constexpr int LBS = NG / (2 * NB);                  // every LBS-th MFMA has a weight load behind it
+                constexpr int LBS = NG / kLB;                  // every LBS-th MFMA has a weight load behind it
                 static_for<NG>([&](auto mc) __attribute__((always_inline)) {
                     constexpr int m = decltype(mc)::value;
                     constexpr int r = m / NH, j = (r & 1) ? NH - 1 - m % NH : m % NH;
-                    constexpr bool ld = LB && m % LBS == 0 && m / LBS < 2 * NB;
+                    constexpr bool ld = LB && m % LBS == 0 && m / LBS < kLB;
                     const i32x4& a_cur = HP ? AY[r] : AX[r];
                     if constexpr (ld) mfma_load_b(integral_constant<int, r>{}, integral_constant<int, j>{}, a_cur, BF[HP][j], integral_constant<int, nslot>{}, integral_constant<int, ld ? m / LBS : 0>{}, integral_constant<bool, ST>{}, kn);
                     else mfma(integral_constant<int, r>{}, integral_constant<int, j>{}, a_cur, BF[HP][j]);
@@ -651,7 +669,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
                 }
                 if (LB) {
 #pragma unroll
-                    for (int i = 0; i < 2 * NB; ++i) load_b(integral_constant<bool, ST>{}, nslot, kn, nslot & 1, i);
+                    for (int i = 0; i < kLB; ++i) load_b(integral_constant<bool, ST>{}, nslot, kn, nslot & 1, i);
                 }
             }
             if (HALF && LA && HP) {            // a short tile has no second load part: the sources of the k-step two ahead move on here
@@ -667,7 +685,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
             }
         };
 
-        constexpr int kLB = 2 * NB;                       // weight loads of a half-step
         constexpr int kL2 = HALF ? NA + 2 * kLB : 2 * (4 + kLB);   // loads of two consecutive half-steps
         const std::true_type L{};
         const std::false_type N{};
@@ -821,7 +838,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
         sw[tid] = (p.row_w && tid < rows_here) ? p.row_w[row0 + tid] : 1.0f;
         if (tid < 32) sw[BM + tid] = (p.row_w && BM + tid < rows_here) ? p.row_w[row0 + BM + tid] : 1.0f;     // a tall tile's extra rows
         __syncthreads();
-        const int d0 = nt * (128 * NB) + wn * (16 * NJ);   // n_cols is a multiple of 128: with NB = 2 a wavefront's columns are all valid or all not
+        const int d0 = nt * (32 * NJ) + wn * (16 * NJ);   // n_cols is a multiple of 128: with NB = 2 a wavefront's columns are all valid or all not
         if (d0 < p.n_cols) {
             float* o = (float*)p.out + (int64_t)row0 * p.ldo + d0 + col_l;
             auto store_rows = [&](auto full, auto n_c) __attribute__((always_inline)) {
@@ -868,17 +885,17 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
     if (bad && tid == 0 && p.status) atomicOr(p.status, 1);
 }
 
-// SPLIT: the tiles of a last, at most half full round are computed as two narrow ones each (see tail_tile).
+// SPLIT: the tiles of a last, at most half full round are computed as two each of half the columns (see tail_tile).
 template <int MODE, int NB, int TR, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
-    static_assert(!SPLIT || NB == 2, "");
+    static_assert(!SPLIT || NB == 2 || (NB == 1 && MODE == 1), "");
     const TileCoord tc = locate_tile<TR, SPLIT>(p);
     if (!tc.valid) return;
     if constexpr (SPLIT) {
         if (tc.half >= 0) {
             const int nt = 2 * tc.nt + tc.half;
-            if (MODE == 1 && nt >= p.n_page_tiles) return;            // the last tile of an odd number of page tiles
-            gemm_tile<MODE, 1, TR>(p, tc, nt);
+            if (MODE == 1 && NB == 2 && nt >= p.n_page_tiles) return; // the last tile of an odd number of page tiles
+            gemm_tile<MODE, NB - 1, TR>(p, tc, nt);
             return;
         }
     }

@@ -140,6 +140,8 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
 @pytest.mark.parametrize("counts,H,F", [
     ([90, 100, 33, 257, 129, 64, 0, 193, 81, 288, 65, 120, 97, 1, 140, 88], 4480, 128),      # down: 18 x 16 tiles of 256 columns (an odd number of page tiles)
     ([90, 257, 150, 193, 33, 280, 64, 256], 128, 4608),                                       # gate/up: 36 x 8 tiles
+    ([90, 257, 150, 193, 33, 280, 64, 289], 640, 128),       # down: 40 and 5 tiles of 128 columns, all of them in halves
+    ([800, 600, 20, 700], 4096, 128),                         # down: 128 tiles by the average, 352 of them: none in halves, a last round that is
 ])
 def test_bf16_tiles_of_a_last_round_in_halves(counts, H, F):
     """More than a round of tiles and less than half of another, whose tiles are computed in halves of their columns, of every height;
