@@ -220,6 +220,37 @@ __device__ __forceinline__ bool locate_rows_tile(const GemmParams& p, RowsTile& 
     return true;
 }
 
+// The same order with the row tiles of locate_tile: for launches that deal single groups to the XCDs (p.chunked 0) it is theirs too, every XCD
+// has its share without any evening out, and a block has its tile a microsecond earlier.
+template <int BM>
+__device__ __forceinline__ TileCoord locate_single_groups(const GemmParams& p) {
+    TileCoord t{};
+    t.valid = false;
+    t.half = -1;
+    const int lane = threadIdx.x & 63, id = blockIdx.x, e_l = p.e_begin + lane;
+    int seg0 = 0, cnt = 0;
+    if (e_l < p.e_end) {
+        seg0 = p.offsets[e_l];
+        cnt = p.offsets[e_l + 1] - seg0;
+    }
+    const int m_l = row_tiles_of(cnt, BM, p.tall_rows).mtiles;
+    const int incl = lane_prefix_sum(m_l * p.NT, lane);
+    const unsigned long long holds = __ballot(id < incl);
+    if (!holds) return t;
+    const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)holds) - 1);
+    const int m = __builtin_amdgcn_readlane(m_l, src);
+    const TileInExpert te = rows_tile_in_expert(id - __builtin_amdgcn_readlane(incl, src) + m * p.NT, m, p.NT);
+    const RowSpan rs = rows_of_tile(__builtin_amdgcn_readlane(seg0, src), __builtin_amdgcn_readlane(cnt, src), te.mt, BM, p.tall_rows);
+    t.nt = te.nt;
+    t.mt = te.mt;
+    t.mtiles = m;
+    t.e = p.e_begin + src;
+    t.row0 = rs.row0;
+    t.rows_here = rs.rows_here;
+    t.valid = t.rows_here > 0;
+    return t;
+}
+
 // silu(g) * u for the bf16 kernels, with the hardware exp2 and reciprocal (1 ulp each): far below the resolution of
 // the bf16 result; an IEEE division would cost a dozen instructions per element
 __device__ __forceinline__ float silu_mul_bf16(float g, float u) {

@@ -889,7 +889,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
 template <int MODE, int NB, int TR, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
     static_assert(!SPLIT || NB == 2 || (NB == 1 && MODE == 1), "");
-    const TileCoord tc = locate_tile<TR, SPLIT>(p);
+    // the short search: layer of 64 experts of 2048 x 1024, 777 tokens 199.7 / 193.5 us, 1024 x 2816, 350 tokens 53.0 / 50.8
+    const TileCoord tc = !SPLIT && TR == BM && p.chunked == 0 && p.offsets ? locate_single_groups<TR>(p) : locate_tile<TR, SPLIT>(p);
     if (!tc.valid) return;
     if constexpr (SPLIT) {
         if (tc.half >= 0) {
@@ -905,7 +906,7 @@ __global__ __launch_bounds__(kThreads) void ffn_gemm_bf16(const GemmParams p) {
 template <int MODE, int NB, int TR = BM, bool SPLIT = false>
 int launch_stages(const GemmParams& p, int R, int n_exp, hipStream_t st) {
     constexpr int lds = kLdsBytes;
-    const int grid = gemm_grid(p.NT, R, TR, n_exp, p.chunked, SPLIT, p.balance && p.xcd_remap);
+    const int grid = !SPLIT && TR == BM && p.chunked == 0 && p.offsets ? rows_grid(p.NT, R, TR, n_exp) : gemm_grid(p.NT, R, TR, n_exp, p.chunked, SPLIT, p.balance && p.xcd_remap);
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
