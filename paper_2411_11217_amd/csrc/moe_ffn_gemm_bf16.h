@@ -86,8 +86,7 @@ constexpr int kComputeUnits = 256;           // MI355X
 // is one row tile then, every weight is read once, and a line that will not be read again should not push others out.  A
 // kernel of nothing but loads reads 7.1 TB/s with the hint and 6.2 without (moe_probe_stream_read_nt).  Layer without / with,
 // us: Mixtral-8x7B shape 16 tokens 481 / 434, 64: 487 / 444, 256: 520 / 491 (these in the other kernel), 400: 544 / 529, 700:
-// 635 / 609, 1000: 735 / 700, 1024: 748 / 717; 64 experts of 2048 x 1024 100 tokens 172 / 158, 777: 222 / 203, 2000 (250 rows per
-// expert): 469 / 445; DBRX shape 100 tokens 1090 / 991, 400: 1206 / 1139, 900: 1474 / 1427.  With more rows hardly an expert has
+// 635 / 609, 1000: 735 / 700, 1024: 748 / 717; 64 experts of 2048 x 1024 100 tokens 172 / 158, 777: 222 / 203; DBRX shape 100 tokens 1090 / 991, 400: 1206 / 1139, 900: 1474 / 1427.  With more rows hardly an expert has
 // one row tile: 1536 tokens of the Mixtral-8x7B shape 1076 / 1075.  An expert that has several row tiles all the same reads
 // without the hint: its tiles share the weights through the L2 (8 experts of 2048 x 4096, 400 tokens, 40 % of them on one
 // expert: 129 us with the hint for all, 106 this way).
@@ -745,7 +744,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const TileCoord& 
     // Short tiles: 129 .. 192 rows: both wavefront rows, five or six row tiles each; 65 .. 128: four row tiles each; at
     // most 64: the upper wavefront row alone (the other wavefronts only load); at most 32: two row tiles instead of four.
     // us for the layer with the full loop / with five or six row tiles: DBRX shape, 550 tokens (138 rows per expert) 1338 /
-    // 1222, 700 tokens 1394 / 1307; Mixtral-8x7B shape, 600 tokens 644 / 592; 64 experts of 2048 x 1024, 1200 tokens 421 / 397.
+    // 1222, 700 tokens 1394 / 1307; Mixtral-8x7B shape, 600 tokens 644 / 592.
     const bool half_tile = TR < BM || (p.half_tiles && rows_here <= 32 * kShortTiles);
     using std::integral_constant;
     auto run = [&](auto stream_c) __attribute__((always_inline)) {
