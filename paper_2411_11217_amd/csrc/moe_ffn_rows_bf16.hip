@@ -288,8 +288,7 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
     return launch_rows<1, 8, 8, 1, 1, 4>(p, H, R, n_exp, st);
 }
 
-// Blocks of the dense linear map (linear_takes_rows_kernel in moe_host.h says when it comes here): 64 rows, and the fewest groups of 16
-// columns with which all blocks make one round.  A compute unit has some 110 lines under way; a line from HBM holds its place for about
+// The dense linear map (moe_host.h: linear_takes_rows_kernel says when it comes here, linear_rows_block with which blocks).  A compute unit has some 110 lines under way; a line from HBM holds its place for about
 // 0.55 us, one from the L2 for 0.13, so a compute unit brings 25 GB/s of the one or 110 GB/s of the other, and the launch wants every
 // compute unit to take an equal share.  With one and two groups the wavefronts split the rows too (their weights meet in the L1); three
 // groups with two row groups each lost 1 - 2 us with weights from HBM (4096 x 6144 100 tokens 22.8 / 24.0).  More groups with row groups: 20 - 40 % slower.
@@ -304,15 +303,16 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
 // Groups of wavefronts that split k change the order of the sums, which the O projection hands on to a rounding and the router: left out.  So are
 // two k-steps behind one barrier: within 5 % either way, the barriers are not what the launch waits for.
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
-    const int64_t groups = N / 16, row_tiles = ((int64_t)T + 63) / 64;
-    auto one_round = [&](int cw) { return row_tiles * ((groups + cw - 1) / cw) <= kComputeUnits; };      // blocks of 64 rows x 16 cw columns
-    if (one_round(1)) return launch_rows<1, 4, 1, 1, 4, 8>(p, N, T, 1, st);
-    if (one_round(2)) return launch_rows<1, 4, 2, 1, 2, 6>(p, N, T, 1, st);
-    if (T <= 64) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
-    if (one_round(4)) return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
-    if (one_round(5)) return launch_rows<1, 4, 5, 1, 1, 4>(p, N, T, 1, st);
-    if (one_round(6)) return launch_rows<1, 4, 6, 1, 1, 4>(p, N, T, 1, st);
-    return launch_rows<1, 4, 8, 1, 1, 4>(p, N, T, 1, st);
+    const LinearBlock b = linear_rows_block(T, p.KT * kTileK, N);
+    if (b.rows == 128) return launch_rows<1, 8, 4, 1, 2, 4>(p, N, T, 1, st);
+    switch (b.groups) {
+        case 1: return launch_rows<1, 4, 1, 1, 4, 8>(p, N, T, 1, st);
+        case 2: return launch_rows<1, 4, 2, 1, 2, 6>(p, N, T, 1, st);
+        case 4: return launch_rows<1, 4, 4, 1, 1, 4>(p, N, T, 1, st);
+        case 5: return launch_rows<1, 4, 5, 1, 1, 4>(p, N, T, 1, st);
+        case 6: return launch_rows<1, 4, 6, 1, 1, 4>(p, N, T, 1, st);
+        default: return launch_rows<1, 4, 8, 1, 1, 4>(p, N, T, 1, st);
+    }
 }
 
 }  // namespace moe

@@ -63,10 +63,35 @@ int64_t linear_pages(const moe_linear_shape& s);
 // / 19 | 22 / 23.
 //   With more than 128 rows, as long as its blocks of 64 rows x 128 columns make one round: us, row tiles of 128 or 256 / this kernel, 4096 x
 // 6144 300 tokens 35 / 26 | 41 / 34; 6144 x 9216 140: 44 / 35 | 53 / 43; 4096 x 10880 192: 37 / 28 | 43 / 37; 2048 x 6144 300: 23 / 16 | 27 / 20; 4096 x 4096 450: 29 / 25 | 32
-// / 29; in between 4096 x 5120 300: 28 / 25 | 30 / 33.
+// / 29.
 inline bool linear_takes_rows_kernel(int T, int K, int N) {
     constexpr int64_t kComputeUnits = 256;           // MI355X
     return (int64_t)(N / 64) * (((int64_t)T + 127) / 128) <= kComputeUnits || (K <= 1536 && T <= 32) || (T > 128 && (((int64_t)T + 63) / 64) * (N / 128) <= kComputeUnits);
+}
+
+// Its blocks: `rows` rows and `groups` groups of 16 columns.  64 rows, and the fewest groups with which all blocks make one round; with up to
+// 64 rows four groups are the most.
+//   With an odd number of row tiles of 64 the blocks of eight groups leave more compute units idle than blocks of 128 rows x 64 columns do, and
+// weights from HBM, which a program with more than one layer has, come at the rate of the compute units that ask for them.  us, 128 x 64 /
+// 64 x 128, weights where the call before left them | from HBM: 4096 x 5120 300 tokens 27.8 / 24.5 | 29.9 / 32.7; 4096 x 8192 192: 28.4 / 25.5 | 31.4 / 35.0;
+// 14336 x 5120 320: 85 / 71 | 92 / 99; 3072 x 1920 960: 24.4 / 23.9 | 24.9 / 25.8.  Not with at most 16 rows in the last of
+// them (8192 x 5120 257: 49 / 42 | 53 / 50; 4096 x 8192 129: 28 / 25 | 30 / 29), a short k (1024 x 5120 300: 11.1 / 10.1 | 12.0 / 12.1, 1536 x 1920 960: 15.4 / 14.6 |
+// 15.4 / 14.4), many row tiles, where one more or less is nothing (4096 x 512 4000: 46.2 / 27.2 | 46 / 27), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
+struct LinearBlock {
+    int rows, groups;
+};
+inline LinearBlock linear_rows_block(int T, int K, int N) {
+    constexpr int64_t kComputeUnits = 256;
+    const int64_t groups = N / 16, row_tiles = ((int64_t)T + 63) / 64;
+    auto one_round = [&](int g) { return row_tiles * ((groups + g - 1) / g) <= kComputeUnits; };
+    if (one_round(1)) return {64, 1};
+    if (one_round(2)) return {64, 2};
+    if (T <= 64 || one_round(4)) return {64, 4};
+    if (one_round(5)) return {64, 5};
+    if (one_round(6)) return {64, 6};
+    const bool tall_one_round = (N / 64) * (((int64_t)T + 127) / 128) <= kComputeUnits;
+    if (tall_one_round && row_tiles % 2 && row_tiles < 32 && (T - 1) % 64 >= 16 && K >= (row_tiles < 8 ? 1536 : 3072)) return {128, 4};
+    return {64, 8};
 }
 
 }  // namespace moe

@@ -353,6 +353,16 @@ static void linear_rule() {
     CHECK(linear_takes_rows_kernel(256, 4096, 8192) && !linear_takes_rows_kernel(257, 4096, 8192));
     CHECK(linear_takes_rows_kernel(32, 1536, 65536) && !linear_takes_rows_kernel(33, 1536, 65536));
     CHECK(!linear_takes_rows_kernel(2147483647, 128, 2147483520));
+    // its blocks: the fewest groups of 16 columns that make one round
+    auto block = [](int T, int K, int N, int rows, int groups) {
+        const moe::LinearBlock b = moe::linear_rows_block(T, K, N);
+        return b.rows == rows && b.groups == groups;
+    };
+    CHECK(block(64, 4096, 4096, 64, 1) && block(65, 4096, 4096, 64, 2) && block(64, 4096, 8192, 64, 2) && block(65, 4096, 8192, 64, 4));
+    CHECK(block(64, 4096, 16384, 64, 4) && block(128, 4096, 10240, 64, 5) && block(128, 4096, 10368, 64, 6) && block(128, 4096, 12416, 64, 8));
+    // an odd number of row tiles: 128 rows x 64 columns, which are on more compute units than 64 rows x 128 columns
+    CHECK(block(300, 4096, 5120, 128, 4) && block(192, 1536, 8192, 128, 4) && block(960, 3072, 1920, 128, 4));
+    CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(272, 4096, 5120, 64, 8) && block(273, 4096, 5120, 128, 4) && block(300, 1024, 5120, 64, 8) && block(960, 1536, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
 }
 
 int main() {

@@ -70,10 +70,10 @@ def test_linear_with_few_rows(T, K, N):
 
 
 @pytest.mark.parametrize("T,K,N", [(300, 256, 384), (17, 1152, 4096), (130, 128, 2048), (64, 640, 6144), (33, 128, 9216), (300, 256, 3072), (129, 640, 6144),
-                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (192, 256, 9216)])
+                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (192, 256, 9216), (145, 1536, 8192), (300, 1536, 5120)])
 def test_linear_blocks_of_one_to_eight_wavefronts(T, K, N):
     # one, two, four, five (the last block has a wavefront too many), six (two too many, and none) and eight column groups of 16 per
-    # block; two to eighteen k-steps, last row tiles of 1 to 64 rows
+    # block, and (the last two) blocks of 128 rows x 64 columns; two to 24 k-steps, last row tiles of 1 to 64 rows
     g = torch.Generator().manual_seed(T + K)
     x = torch.randn((T, K), generator=g)
     W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
