@@ -295,7 +295,7 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
 // us for the launch, the blocks before (32 columns, or 64, or 128 rows x 64 columns) / these, weights where the call before left them | from HBM: 4096 x 4096
 // 36 tokens 16.7 / 15.7 | 18.1 / 17.1, 100: 20.1 / 16.9 | 21.8 / 18.5; 4096 x 6144 160: 27.6 / 22.2 | 29.3 / 24.5, 256: 28.2 / 24.0 | 38.3 / 30.1; 6144 x 9216 100: 38.7 / 31.9 | 52.3 /
 // 37.7; 2048 x 3072 100: 12.3 / 10.3 | 12.9 / 10.7, 400: 17.0 / 14.7 | 17.0 / 14.9; 4096 x 512 4000: 46.2 / 27.2; 512 x 512 300: 6.6 / 5.0; equal where the blocks are what they
-// were (4096 x 6144 100: 64 columns) and with up to 16 rows (4096 x 4096 1 token 12.7 / 13.1 | 14.6 / 14.2).  Up to 64 rows four groups are the most: more
+// were (4096 x 6144 100: 64 columns).  Up to 64 rows four groups are the most: more
 // columns per block only leave compute units idle (6144 x 9216 40 tokens 29.1 / 27.4).
 // Temporal loads, us without / with the non-temporal hint, weights where the call before left them (one matrix fits the 256 MiB
 // last-level cache) | weights from HBM: 4096 x 6144 64 tokens 17 / 21 | 21 / 22; 6144 x 9216 64 tokens 30 / 35 | 38 / 37, 128: 40 /
@@ -305,6 +305,7 @@ int launch_down_rows_bf16(GemmParams& p, int H, int R, int rows_each, int n_exp,
 int launch_linear_rows_bf16(GemmParams& p, int N, int T, hipStream_t st) {
     const LinearBlock b = linear_rows_block(T, p.KT * kTileK, N);
     if (b.rows == 128) return launch_rows<1, 8, 4, 1, 2, 4>(p, N, T, 1, st);
+    if (b.rows == 32) return b.groups == 1 ? launch_rows<1, 2, 1, 1, 2, 8>(p, N, T, 1, st) : launch_rows<1, 2, 2, 1, 2, 8>(p, N, T, 1, st);
     switch (b.groups) {
         case 1: return launch_rows<1, 4, 1, 1, 4, 8>(p, N, T, 1, st);
         case 2: return launch_rows<1, 4, 2, 1, 2, 6>(p, N, T, 1, st);

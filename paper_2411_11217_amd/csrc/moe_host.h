@@ -71,6 +71,9 @@ inline bool linear_takes_rows_kernel(int T, int K, int N) {
 
 // Its blocks: `rows` rows and `groups` groups of 16 columns.  64 rows, and the fewest groups with which all blocks make one round; with up to
 // 64 rows four groups are the most.
+//   With up to 32 rows and one or two groups 32 rows: the blocks of 64 have four (two) groups of wavefronts for the rows, and those without any load the weights all the
+// same.  us, 64 rows / 32, weights where the call before left them | from HBM: 4096 x 4096 1 token 13.2 / 12.6 | 14.2 / 12.9, 32: 13.8 / 13.0 | 14.6 / 13.6; 14336 x 4096 8: 38.2 /
+// 37.1 | 39.5 / 37.7; 512 x 512 16: 4.5 / 4.3; 1024 x 6144 1: 5.4 / 5.2 | 7.0 / 6.2; 8192 x 4224 1: 22.0 / 22.2 | 24.8 / 24.4.
 //   With an odd number of row tiles of 64 the blocks of eight groups leave more compute units idle than blocks of 128 rows x 64 columns do, and
 // weights from HBM, which a program with more than one layer has, come at the rate of the compute units that ask for them.  us, 128 x 64 /
 // 64 x 128, weights where the call before left them | from HBM: 4096 x 5120 300 tokens 27.8 / 24.5 | 29.9 / 32.7; 4096 x 8192 192: 28.4 / 25.5 | 31.4 / 35.0;
@@ -84,8 +87,9 @@ inline LinearBlock linear_rows_block(int T, int K, int N) {
     constexpr int64_t kComputeUnits = 256;
     const int64_t groups = N / 16, row_tiles = ((int64_t)T + 63) / 64;
     auto one_round = [&](int g) { return row_tiles * ((groups + g - 1) / g) <= kComputeUnits; };
-    if (one_round(1)) return {64, 1};
-    if (one_round(2)) return {64, 2};
+    const int rows = T <= 32 ? 32 : 64;
+    if (one_round(1)) return {rows, 1};
+    if (one_round(2)) return {rows, 2};
     if (T <= 64 || one_round(4)) return {64, 4};
     if (one_round(5)) return {64, 5};
     if (one_round(6)) return {64, 6};

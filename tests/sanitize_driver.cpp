@@ -360,6 +360,9 @@ static void linear_rule() {
     };
     CHECK(block(64, 4096, 4096, 64, 1) && block(65, 4096, 4096, 64, 2) && block(64, 4096, 8192, 64, 2) && block(65, 4096, 8192, 64, 4));
     CHECK(block(64, 4096, 16384, 64, 4) && block(128, 4096, 10240, 64, 5) && block(128, 4096, 10368, 64, 6) && block(128, 4096, 12416, 64, 8));
+    // up to 32 rows: blocks of 32, whose wavefronts have no more rows than that
+    CHECK(block(1, 4096, 4096, 32, 1) && block(32, 4096, 4096, 32, 1) && block(33, 4096, 4096, 64, 1) && block(16, 4096, 4224, 32, 2));
+    CHECK(block(32, 128, 8192, 32, 2) && block(33, 128, 8192, 64, 2) && block(32, 4096, 8320, 64, 4));
     // an odd number of row tiles: 128 rows x 64 columns, which are on more compute units than 64 rows x 128 columns
     CHECK(block(300, 4096, 5120, 128, 4) && block(192, 1536, 8192, 128, 4) && block(960, 3072, 1920, 128, 4));
     CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(272, 4096, 5120, 64, 8) && block(273, 4096, 5120, 128, 4) && block(300, 1024, 5120, 64, 8) && block(960, 1536, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
