@@ -74,6 +74,11 @@ inline bool linear_takes_rows_kernel(int T, int K, int N) {
 //   With up to 32 rows and one or two groups 32 rows: the blocks of 64 have four (two) groups of wavefronts for the rows, and those without any load the weights all the
 // same.  us, 64 rows / 32, weights where the call before left them | from HBM: 4096 x 4096 1 token 13.2 / 12.6 | 14.2 / 12.9, 32: 13.8 / 13.0 | 14.6 / 13.6; 14336 x 4096 8: 38.2 /
 // 37.1 | 39.5 / 37.7; 512 x 512 16: 4.5 / 4.3; 1024 x 6144 1: 5.4 / 5.2 | 7.0 / 6.2; 8192 x 4224 1: 22.0 / 22.2 | 24.8 / 24.4.
+//   Up to eight column tiles of a row tile run on as many XCDs, each of which fetches the rows for itself.  More than 216 blocks of one or two groups then ask for
+// more of them than arrive, and half as many have it done sooner, except with a short k.  us, one / two / four groups: 4096 x 128 1700 tokens (216 blocks of one) 21.0 / 17.9 /
+// 21.2, 2000: 23.2 / 18.1 / 21.1, 3300 (208 of two) - / 20.8 / 21.5, 4000: - / 24.0 / 21.7; 2048 x 256 1700 (216 of two) - / 13.0 / 13.0, 2000: - / 14.4 / 13.3; 8192 x 128 4000: - / 52 / 41;
+// 1152 x 128 4000: - / 9.6 / 10.2.  The line is late by 5 to 15 % for some k (2048 x 128 2500: - / 13.0 / 12.5, 3000: - / 14.7 / 12.8;
+// 8192 x 256 1600: - / 36.1 / 34.8) and early for none by as much.
 //   With an odd number of row tiles of 64 the blocks of eight groups leave more compute units idle than blocks of 128 rows x 64 columns do, and
 // weights from HBM, which a program with more than one layer has, come at the rate of the compute units that ask for them.  us, 128 x 64 /
 // 64 x 128, weights where the call before left them | from HBM: 4096 x 5120 300 tokens 27.8 / 24.5 | 29.9 / 32.7; 4096 x 8192 192: 28.4 / 25.5 | 31.4 / 35.0;
@@ -88,8 +93,9 @@ inline LinearBlock linear_rows_block(int T, int K, int N) {
     const int64_t groups = N / 16, row_tiles = ((int64_t)T + 63) / 64;
     auto one_round = [&](int g) { return row_tiles * ((groups + g - 1) / g) <= kComputeUnits; };
     const int rows = T <= 32 ? 32 : 64;
-    if (one_round(1)) return {rows, 1};
-    if (one_round(2)) return {rows, 2};
+    auto crowded = [&](int g) { return K >= 1536 && groups <= 8 * g && row_tiles * ((groups + g - 1) / g) > 216; };
+    if (one_round(1) && !crowded(1)) return {rows, 1};
+    if (one_round(2) && !crowded(2)) return {rows, 2};
     if (T <= 64 || one_round(4)) return {64, 4};
     if (one_round(5)) return {64, 5};
     if (one_round(6)) return {64, 6};

@@ -363,6 +363,9 @@ static void linear_rule() {
     // up to 32 rows: blocks of 32, whose wavefronts have no more rows than that
     CHECK(block(1, 4096, 4096, 32, 1) && block(32, 4096, 4096, 32, 1) && block(33, 4096, 4096, 64, 1) && block(16, 4096, 4224, 32, 2));
     CHECK(block(32, 128, 8192, 32, 2) && block(33, 128, 8192, 64, 2) && block(32, 4096, 8320, 64, 4));
+    // few column tiles and many rows: up to 216 blocks of one or two groups
+    CHECK(block(1728, 4096, 128, 64, 1) && block(1729, 4096, 128, 64, 2) && block(3456, 4096, 128, 64, 2) && block(3457, 4096, 128, 64, 4));
+    CHECK(block(1728, 1536, 256, 64, 2) && block(1729, 1536, 256, 64, 4) && block(2048, 1408, 128, 64, 1) && block(1300, 4096, 384, 64, 2));
     // an odd number of row tiles: 128 rows x 64 columns, which are on more compute units than 64 rows x 128 columns
     CHECK(block(300, 4096, 5120, 128, 4) && block(192, 1536, 8192, 128, 4) && block(960, 3072, 1920, 128, 4));
     CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(272, 4096, 5120, 64, 8) && block(273, 4096, 5120, 128, 4) && block(300, 1024, 5120, 64, 8) && block(960, 1536, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
