@@ -366,6 +366,9 @@ static void linear_rule() {
     // few column tiles and many rows: up to 216 blocks of one or two groups
     CHECK(block(1728, 4096, 128, 64, 1) && block(1729, 4096, 128, 64, 2) && block(3456, 4096, 128, 64, 2) && block(3457, 4096, 128, 64, 4));
     CHECK(block(1728, 1536, 256, 64, 2) && block(1729, 1536, 256, 64, 4) && block(2048, 1408, 128, 64, 1) && block(1300, 4096, 384, 64, 2));
+    // up to 96 rows and a short k: 128 rows x 64 columns instead of five, six and eight groups
+    CHECK(block(96, 512, 12288, 128, 4) && block(97, 512, 12288, 64, 6) && block(65, 512, 10240, 128, 4) && block(65, 640, 10240, 64, 5));
+    CHECK(block(65, 640, 16384, 64, 8) && block(65, 512, 16384, 128, 4) && block(65, 256, 8192, 64, 4) && block(300, 128, 5120, 64, 8));
     // an odd number of row tiles: 128 rows x 64 columns, which are on more compute units than 64 rows x 128 columns
     CHECK(block(300, 4096, 5120, 128, 4) && block(192, 1536, 8192, 128, 4) && block(960, 3072, 1920, 128, 4));
     CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(272, 4096, 5120, 64, 8) && block(273, 4096, 5120, 128, 4) && block(300, 1024, 5120, 64, 8) && block(960, 1536, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
