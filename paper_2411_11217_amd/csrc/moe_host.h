@@ -85,6 +85,9 @@ inline bool linear_takes_rows_kernel(int T, int K, int N) {
 // 14336 x 5120 320: 85 / 71 | 92 / 99; 3072 x 1920 960: 24.4 / 23.9 | 24.9 / 25.8.  Not with at most 16 rows in the last of
 // them (8192 x 5120 257: 49 / 42 | 53 / 50; 4096 x 8192 129: 28 / 25 | 30 / 29), a short k (1024 x 5120 300: 11.1 / 10.1 | 12.0 / 12.1, 1536 x 1920 960: 15.4 / 14.6 |
 // 15.4 / 14.4), many row tiles, where one more or less is nothing (4096 x 512 4000: 46.2 / 27.2 | 46 / 27), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
+//   Where the two sides differ, weights from HBM decide: 65 to 96 rows with six groups lose where a matrix of 80 MB and more is in the last-level cache (the second row
+// tile's blocks, with 32 rows at most, run ahead of the first one's and read the weights again), 128 x 64 / six / eight groups: 4096 x 12288 72 tokens 26.5 / 32.8 / 24.3 | 34.4 / 28.4 / 32.5, 8192 x
+// 12288 65: 47.8 / 58.8 / 41.8 | 60.6 / 53.8 / 56.0, 1024 x 12288 65: 9.9 / 10.3 / 9.7 | 12.4 / 11.5 / 12.2.
 //   Up to 96 rows and a short k have the blocks of 128 rows in place of five, six and eight groups too: the set-up of the second row tile's blocks is what
 // counts.  us, 128 x 64 / 64 rows: 128 x 9216 72 tokens 5.6 / 6.0 | 6.4 / 6.6, 128 x 16384 65: 5.8 / 6.2 | 6.6 / 7.2; 512 x 12288 65: 7.3 / 7.7 | 8.9 / 8.9, 96: 7.9 / 7.9 | 9.4 / 9.1; but
 // 256 x 16384 100: 7.1 / 7.0 | 8.1 / 7.9, 512 x 16384 100: 9.2 / 8.9 | 10.6 / 10.2, 1024 x 12288 65: 9.9 / 10.4 | 12.5 / 11.5.
