@@ -9,7 +9,7 @@ import torch
 import paper_2411_11217_amd as M
 from moe_workloads import MoEConfig, scaled
 from oracle import dense
-from util import Case, assert_close, assert_h_close, say, shape_of, assert_status_clean
+from util import Case, assert_close, assert_h_close, linear_takes_rows_kernel, say, shape_of, assert_status_clean
 
 pytestmark = pytest.mark.gpu
 
@@ -30,9 +30,11 @@ def paged_linear(ls, W, extra=3, seed=0):
 @pytest.mark.parametrize("T,K,N,page", [
     (300, 256, 384, 3 * 16384),        # ragged rows, odd number of 128-wide column tiles, tiles not dividing pages evenly
     (64, 128, 128, 16384),             # smallest shape: one column tile, 4 half-steps
-    (270, 256, 256, 16384),            # one tall row tile: the 14 rows behind the first 256 ride along
-    (800, 512, 384, 2 * 16384),        # three full row tiles, the last one with 32 more rows
+    (270, 256, 256, 16384),            # five row tiles of 64, the last with 14 rows
+    (800, 512, 384, 2 * 16384),
     (1000, 1024, 2048, 1 << 20),       # several row and column tiles
+    (270, 128, 12800, 5 * 16384),      # row tiles of 256, 128-wide column tiles, one tall row tile: the 14 rows behind the first 256 ride along
+    (540, 128, 44032, 5 * 16384),      # 256-wide column tiles, two tall row tiles
     (4096, 4096, 4096, 2 << 20),       # the O projection of the Mixtral-8x7B shape: 256-wide column tiles
 ])
 def test_linear_matches_the_oracle(T, K, N, page):
@@ -53,8 +55,8 @@ def test_linear_matches_the_oracle(T, K, N, page):
 @pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 96, 97, 128, 129, 300])
 @pytest.mark.parametrize("K,N", [(128, 128), (384, 640), (256, 9216), (1152, 16512)])
 def test_linear_with_few_rows(T, K, N):
-    # row counts around the row-tile pairs and blocks; two, four and six k-steps; column tiles of
-    # 32 and of 64, one and several row tiles; the bf16 copy of the pre-attention task; 16512 columns: the kernel with
+    # row counts around the row-tile pairs and blocks; two to eighteen k-steps; column tiles of 16 to
+    # 96 (linear_rows_block), one and several row tiles; the bf16 copy of the pre-attention task; 16512 columns: the kernel with
     # 256-row blocks from 33 rows on
     g = torch.Generator().manual_seed(T + K)
     x = torch.randn((T, K), generator=g)
@@ -70,7 +72,7 @@ def test_linear_with_few_rows(T, K, N):
 
 
 @pytest.mark.parametrize("T,K,N", [(300, 256, 384), (17, 1152, 4096), (1, 640, 6144), (32, 128, 8192), (16, 128, 128), (33, 1152, 4096), (1729, 1536, 128), (3457, 1536, 128), (130, 128, 2048), (64, 640, 6144), (33, 128, 9216), (300, 256, 3072), (129, 640, 6144),
-                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (128, 640, 9216), (65, 640, 12288), (192, 256, 9216), (145, 1536, 8192), (300, 1536, 5120), (65, 512, 9216), (96, 128, 16384)])
+                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (128, 640, 9216), (65, 640, 12288), (192, 256, 9216), (129, 128, 9216), (257, 384, 6144), (145, 1536, 8192), (300, 1536, 5120), (65, 512, 9216), (96, 128, 16384)])
 def test_linear_blocks_of_one_to_eight_wavefronts(T, K, N):
     # one, two, four, five (the last block has a wavefront too many), six (two too many, and none) and eight column groups of 16 per
     # block; blocks of 32 rows (up to 32 tokens) and of 128 (the last four); two to 24 k-steps, last row tiles of 1 to 64 rows
@@ -86,9 +88,12 @@ def test_linear_blocks_of_one_to_eight_wavefronts(T, K, N):
     assert_close(out.cpu().numpy(), dense.linear(bits(xn), bits(W)), "bf16", f"linear {T}x{K}x{N}")
 
 
-@pytest.mark.parametrize("T,K,N", [(129, 128, 9216), (192, 640, 12800), (256, 256, 9216), (257, 384, 6144), (385, 128, 6144), (512, 256, 6144)])
+@pytest.mark.parametrize("T,K,N", [(129, 128, 12800), (192, 640, 12800), (256, 256, 9216), (257, 384, 6656), (385, 128, 6144), (512, 256, 6144), (160, 128, 16384),
+                                   (144, 2176, 14720)])
 def test_linear_row_tiles_of_128(T, K, N):
-    # one round of blocks of 128 rows x 128 columns: against the oracle, and bit by bit against row tiles of 256
+    # one round of blocks of 128 rows x 128 columns (the last: beyond the lines for 129 to 160 rows, a short tile of 256): against the
+    # oracle, and bit by bit against row tiles of 256 with the full loop
+    assert not linear_takes_rows_kernel(T, K, N) and -(-T // 128) * (N // 128) <= 256
     g = torch.Generator().manual_seed(T + K)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)
     W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)

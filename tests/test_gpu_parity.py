@@ -11,7 +11,8 @@ import torch
 import oracle
 import paper_2411_11217_amd as M
 from moe_workloads import CONFIGS, MoEConfig, make_inputs, scaled
-from util import F32_REL_RMS, Case, assert_close, assert_h_close, assert_status_clean, check_permutation_valid, compare_routing, rel_rms, say, shape_of
+from util import (F32_REL_RMS, Case, assert_close, assert_h_close, assert_status_clean, bf16_launches, check_permutation_valid, compare_routing, rel_rms, row_tiles, say,
+                  shape_of)
 
 pytestmark = pytest.mark.gpu
 
@@ -24,6 +25,10 @@ MED = {
     "bf16_top4_of_16": MoEConfig("m3", "bf16", T=200, H=256, F=256, E=16, k=4, page_bytes=32 * 1024, seed=23),
     "bf16_top4_of_16_more_rows": MoEConfig("m6", "bf16", T=420, H=256, F=256, E=16, k=4, page_bytes=32 * 1024, seed=26),   # beyond the kernel for few rows
     "f32_top2_of_5": MoEConfig("m4", "f32", T=150, H=128, F=256, E=5, k=2, page_bytes=96 * 1024, seed=24),
+    # launches whose tiles are all whole, three column tiles, one expert with several row tiles: short search (chunks off), chunks of 8, chunks of 32
+    "bf16_single_groups": MoEConfig("m7", "bf16", T=2200, H=384, F=384, E=44, k=2, page_bytes=48 * 1024, seed=27, bias=((3, 0.5), (9, 0.25))),
+    "bf16_chunks_of_8": MoEConfig("m8", "bf16", T=3300, H=384, F=384, E=44, k=2, page_bytes=48 * 1024, seed=28, bias=((3, 0.5), (9, 0.25))),
+    "bf16_chunks_of_32": MoEConfig("m9", "bf16", T=6200, H=384, F=384, E=44, k=2, page_bytes=48 * 1024, seed=29, bias=((3, 0.4), (9, 0.2))),
     "bf16_skewed": MoEConfig("m5", "bf16", T=600, H=256, F=256, E=8, k=2, page_bytes=64 * 1024, seed=25,
                              bias=((0, 3.0), (7, -3.0))),
 }
@@ -98,14 +103,16 @@ def run_layer(case: Case, ref=None):
     return y, ws
 
 
-@pytest.mark.parametrize("down_cols", [0, 1, 2])
-def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
+@pytest.mark.parametrize("down_cols,H,down", [(0, 256, "128 columns, halves"), (1, 256, "128 columns, halves"), (2, 256, "256 columns, halves"), (1, 1024, "128 columns"), (0, 1024, "256 columns")])
+def test_expert_ffn_row_counts_across_the_tile_variants(down_cols, H, down):
     """Segments of 1 .. 300 rows, one per expert, on both sides of every threshold of the bf16 kernel's row-tile
     variants (32, 64, 128, 192 rows, the 256-row tile boundary, tiles that take a remainder of up to 32 rows along) and an
-    empty one, against the oracle row by row; with the tall tiles switched off every bit stays the same."""
+    empty one, against the oracle row by row; with the tall tiles switched off every bit stays the same.  In each of the four down
+    launches (H = 256: all tiles of the only round in halves)."""
     counts = [1, 16, 17, 32, 33, 0, 64, 65, 127, 128, 129, 160, 192, 193, 255, 256, 257, 300, 31, 449, 272, 273, 288, 289, 532,
               544, 576, 577, 800, 863, 865, 1061]
-    E, H, F = len(counts), 256, 384
+    E, F = len(counts), 384
+    assert bf16_launches(counts, H, F, down_cols) == ("whole", down, 32)
     cfg = MoEConfig("rows", "bf16", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=64 * 1024, seed=77)
     case = Case(cfg, shuffle_pages=True, extra_pages=1)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
@@ -137,15 +144,19 @@ def test_expert_ffn_row_counts_across_the_tile_variants(down_cols):
         assert_close(out.cpu().numpy()[lo:hi], o_ref[lo:hi], "bf16", f"out, expert {e} with {c} rows")
 
 
-@pytest.mark.parametrize("counts,H,F", [
-    ([90, 100, 33, 257, 129, 64, 0, 193, 81, 288, 65, 120, 97, 1, 140, 88], 4480, 128),      # down: 18 x 16 tiles of 256 columns (an odd number of page tiles)
-    ([90, 257, 150, 193, 33, 280, 64, 256], 128, 4608),                                       # gate/up: 36 x 8 tiles
-    ([90, 257, 150, 193, 33, 280, 64, 289], 640, 128),       # down: 40 and 5 tiles of 128 columns, all of them in halves
-    ([800, 600, 20, 700], 4096, 128),                         # down: 128 tiles by the average, 352 of them: none in halves, a last round that is
+@pytest.mark.parametrize("counts,H,F,down,tiles", [
+    ([90, 100, 33, 257, 129, 64, 0, 193, 81, 288, 65, 120, 97, 1, 140, 88], 4480, 128, "256 columns, halves", 15 * 18),    # an odd number of page tiles
+    ([90, 257, 150, 193, 33, 280, 64, 256], 128, 4608, "128 columns, halves", 8),               # gate/up: 36 x 8 tiles
+    ([90, 257, 150, 193, 33, 280, 64, 289], 640, 128, "128 columns, halves", 9 * 5),             # all of them in halves
+    ([800, 20, 20, 280], 4096, 128, "128 columns, halves", 6 * 32),                              # 24 per XCD: all of them whole
+    ([4608] + [1] * 15, 1024, 128, "128 columns, halves", 33 * 8),                               # 33 per XCD: 32 whole, one in halves
+    ([800, 600, 20, 700], 4096, 128, "128 columns", 10 * 32),
 ])
-def test_bf16_tiles_of_a_last_round_in_halves(counts, H, F):
-    """More than a round of tiles and less than half of another, whose tiles are computed in halves of their columns, of every height;
-    the tiles dealt to the XCDs and evened out, or neither: the same bits."""
+def test_bf16_tiles_of_a_last_round_in_halves(counts, H, F, down, tiles):
+    """A last round of at most half a round of tiles, which are computed in halves of their columns, of every height (`tiles`: those of the
+    down launch); the tiles dealt to the XCDs and evened out, or neither: the same bits."""
+    gate, launch, _ = bf16_launches(counts, H, F)
+    assert gate == "halves" and launch == down and tiles == row_tiles(counts) * (H // 128 if down.startswith("128") else (H // 128 + 1) // 2)
     E = len(counts)
     cfg = MoEConfig("halves", "bf16", T=sum(counts), H=H, F=F, E=E, k=1, page_bytes=64 * 1024, seed=83)
     case = Case(cfg, shuffle_pages=True, extra_pages=1)
@@ -571,22 +582,29 @@ def test_reduced_cases_stagewise_and_layer(name, down_cols):
     try:
         case = Case(MED[name], shuffle_pages=True, extra_pages=3)
         ref = run_stagewise(case)
+        if name == "bf16_single_groups" and down_cols == 0:
+            counts = ref["counts"].tolist()
+            assert bf16_launches(counts, case.cfg.H, case.cfg.F) == ("whole", "128 columns", 0) and max(counts) > 512 and any(c > 256 and c % 256 <= 32 for c in counts)
         run_layer(case, ref)
     finally:
         M.set_option("down_cols", 0)
 
 
-@pytest.mark.parametrize("name", ["bf16_top2_of_4", "bf16_two_experts_ragged", "f32_top2_of_5"])
+@pytest.mark.parametrize("name", ["bf16_top2_of_4", "bf16_two_experts_ragged", "f32_top2_of_5", "bf16_chunks_of_8", "bf16_chunks_of_32"])
 @pytest.mark.parametrize("option,default,other", [("xcd_remap", 1, 0), ("fuse_gather", 1, 0), ("half_tiles", 1, 0), ("tall_tiles", 1, 0),
                                                   ("down_cols", 0, 1), ("down_cols", 0, 2), ("chunked", 32, 0), ("chunked", 32, 8),
                                                   ("tall_first", 1, 0), ("balance", 1, 0)])
 def test_kernel_options_give_identical_bits(option, default, other, name):
     # which block computes which tile, the tile variant, and who gathers the rows of x do not change any arithmetic
     case = Case(MED[name])
-    y1, _ = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev)
+    y1, ws = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, bias=case.bias)
+    if name.startswith("bf16_chunks"):
+        counts = ws.view("counts").cpu().tolist()
+        whole, down, chunk = bf16_launches(counts, case.cfg.H, case.cfg.F)
+        assert whole == "whole" and "halves" not in down and name.endswith("of_%d" % chunk) and max(counts) > 512
     M.set_option(option, other)
     try:
-        y0, _ = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev)
+        y0, _ = M.moe_layer(case.shape, case.x, case.Wr, case.pw.table_dev, case.pw.pages_dev, bias=case.bias)
     finally:
         M.set_option(option, default)
     assert torch.equal(y0, y1)

@@ -74,6 +74,37 @@ def assert_h_close(got, ref, dtype: str, what: str):
         assert rr <= F32_REL_RMS, what
 
 
+def linear_takes_rows_kernel(T, K, N):
+    """The rule of that name in csrc/moe_host.h, so that a test of one of the linear map's kernels can say that its shape reaches it."""
+    return (N // 64) * -(-T // 128) <= 256 or (K <= 1536 and T <= 32) or (T > 128 and -(-T // 64) * (N // 128) <= 256)
+
+
+def row_tiles(counts):
+    """Row tiles of 256 rows that the experts' rows make; a remainder of up to 32 rows per full tile rides along."""
+    n = 0
+    for c in counts:
+        q, r = divmod(int(c), 256)
+        n += q if q and 0 < r <= 32 * q else q + (r > 0)
+    return n
+
+
+def bf16_launches(counts, H, F, down_cols=0):
+    """What launch_expert_ffn_bf16 (csrc/moe_ffn_bf16.hip) takes for gate/up and for down beyond the kernel for few rows, and the
+    number of tiles per XCD that stay together, by its own formulas."""
+    E, each = len(counts), int(sum(counts)) // len(counts)
+    assert each > 80, "the kernel for few rows"
+    tiles, dt = E * max(1, (each - 32 + 255) // 256), H // 128
+
+    def half(n):
+        return 0 < n % 256 <= 128
+
+    if down_cols == 1 or (down_cols == 0 and tiles * dt <= 256):
+        down = "128 columns, halves" if tiles * dt <= 128 else "128 columns"
+    else:
+        down = "256 columns, halves" if half(tiles * ((dt + 1) // 2)) else "256 columns"
+    return "halves" if half(tiles * (F // 128)) else "whole", down, 32 if each > 256 else 8 if each > 128 else 0
+
+
 class Case:
     """A workload on both sides: CPU tensors + oracle views, device tensors + paged weights."""
 
