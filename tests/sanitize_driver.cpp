@@ -159,14 +159,14 @@ static void oracle_layer(int dtype, int T, int H, int F, int E, int k, bool with
 
 // The tile order of the expert GEMMs, evaluated the way the kernels do (per expert: row tiles, chunk plan, the share of
 // every XCD; per block: the expert by cumulative tile counts, the row block, the tile): every tile of every expert is
-// taken by exactly one block (also when the XCDs even out their shares), the row tiles partition the segments, and no XCD
-// has more tiles than the grid gives it.
-static void tile_order(const std::vector<int>& counts, int NT, int BM, int tall_rows, int chunked, int stride, bool tall_first, bool balance = true) {
+// taken by exactly one block (also when the XCDs even out their shares), or its two halves by one each where the last round is
+// computed in halves (`split`), the row tiles partition the segments, and no XCD has more tiles than the grid gives it.
+static void tile_order(const std::vector<int>& counts, int NT, int BM, int tall_rows, int chunked, int stride, bool tall_first, bool balance = true, bool split = false) {
     using namespace moe;
     const int E = (int)counts.size();
     int R = 0;
     for (int c : counts) R += c;
-    const int grid = gemm_grid(NT, R, BM, E, chunked);
+    const int grid = gemm_grid(NT, R, BM, E, chunked, split, balance && stride == 8);
     CHECK(grid % 8 == 0);
     std::vector<RowTiles> rt((size_t)E);
     std::vector<ChunkPlan> plan((size_t)E);
@@ -193,7 +193,7 @@ static void tile_order(const std::vector<int>& counts, int NT, int BM, int tall_
     }
     std::vector<std::vector<char>> seen((size_t)E);
     for (int e = 0; e < E; ++e) seen[(size_t)e].assign((size_t)rt[(size_t)e].mtiles * NT, 0);
-    size_t taken = 0;
+    size_t taken = 0;                                                     // half tiles
     // what every XCD was dealt, and - with the balancing - the even share A that none exceeds
     auto share = [&](int x, int e) {
         int n = 0;
@@ -204,21 +204,29 @@ static void tile_order(const std::vector<int>& counts, int NT, int BM, int tall_
     for (int x = 0; x < stride; ++x)
         for (int e = 0; e < E; ++e) T[x] += share(x, e);
     const int A = (int)((total + 7) / 8);
+    const bool even = balance && stride == 8;
+    const int per_seq = stride == 8 ? grid / 8 : grid, cus = stride == 8 ? 32 : 256;       // blocks and compute units of an XCD, or all
     for (int xb = 0; xb < stride; ++xb) {
-        CHECK(T[xb] <= (stride == 8 ? grid / 8 : grid));                  // the grid reaches every tile of this XCD
+        if (!even) CHECK(T[xb] <= per_seq);                               // the grid reaches every tile of this XCD
         // the blocks of XCD xb in their order; with the balancing those beyond min(T, A) take tiles of other XCDs or leave
-        const int blocks = balance && stride == 8 ? std::max(T[xb], A) : T[xb];
         int ran = 0;
-        for (int blk = 0; blk < blocks; ++blk) {
-            int x = xb, idx = blk;
-            if (balance && stride == 8 && blk >= std::min(T[xb], A)) {
-                if (blk >= A || T[xb] >= A) continue;                      // given away, or beyond every tile
-                const StolenTile st = stolen_tile(T, A, xb, blk - T[xb]);
+        for (int blk = 0; blk < per_seq; ++blk) {
+            int x = xb, idx = blk, half = -1;
+            if (split) {
+                const TailTile tail = tail_tile(blk, even ? A : T[xb], cus);
+                if (tail.idx < 0) continue;
+                idx = tail.idx;
+                half = tail.half;
+            }
+            if (even && idx >= std::min(T[xb], A)) {
+                if (idx >= A || T[xb] >= A) continue;                      // given away, or beyond every tile
+                const StolenTile st = stolen_tile(T, A, xb, idx - T[xb]);
                 if (st.idx < 0) continue;
                 CHECK(st.x != xb && T[st.x] > A && st.idx >= A && st.idx < T[st.x]);
                 x = st.x;
                 idx = st.idx;
             }
+            if (!even && idx >= T[xb]) continue;
             ++ran;
             std::vector<int> tiles((size_t)E, 0);
             for (int e = 0; e < E; ++e) tiles[(size_t)e] = share(x, e);
@@ -236,30 +244,31 @@ static void tile_order(const std::vector<int>& counts, int NT, int BM, int tall_
             const TileInExpert te = tile_in_block(c, b, s, rem, stride, rt[(size_t)e].mtiles, rt[(size_t)e].tall, tall_first);
             CHECK(te.mt >= 0 && te.mt < rt[(size_t)e].mtiles && te.nt >= 0 && te.nt < NT);
             char& flag = seen[(size_t)e][(size_t)te.mt * NT + te.nt];
-            CHECK(flag == 0);
-            flag = 1;
-            ++taken;
+            const char bits = half < 0 ? 3 : half == 0 ? 1 : 2;
+            CHECK((flag & bits) == 0);
+            flag |= bits;
+            taken += half < 0 ? 2 : 1;
         }
-        if (balance && stride == 8) CHECK(ran <= A);                      // no XCD runs more than the even share
+        if (even) CHECK(ran <= A + (split ? cus / 2 : 0));                // no XCD runs more than the even share
     }
-    CHECK(taken == total);
+    CHECK(taken == 2 * total);
 }
 
 static void tile_orders() {
     std::uniform_int_distribution<int> small(0, 700), large(0, 20000), pick(0, 9);
     int cases = 0;
     for (int NT : {1, 2, 7, 16, 24, 56, 112}) {
-        for (int chunked : {0, 32}) {
+        for (int chunked : {0, 8, 32}) {
             for (int stride : {8, 1}) {
                 for (int tall_rows : {0, 32}) {
-                    for (int rep = 0; rep < 6; ++rep) {
+                    for (int rep = 0; rep < 8; ++rep) {
                         const int E = 1 + (int)(g_rng() % 17);
                         std::vector<int> counts((size_t)E);
                         for (int& c : counts) {
                             const int kind = pick(g_rng);
                             c = kind == 0 ? 0 : kind < 6 ? small(g_rng) : kind < 9 ? 256 * (1 + (int)(g_rng() % 40)) + (int)(g_rng() % 64) : large(g_rng);
                         }
-                        tile_order(counts, NT, 256, tall_rows, chunked, stride, rep % 2 == 0, rep % 3 != 0);
+                        tile_order(counts, NT, 256, tall_rows, chunked, stride, rep % 2 == 0, rep % 3 != 0, rep >= 4);
                         ++cases;
                     }
                 }
@@ -272,6 +281,7 @@ static void tile_orders() {
     tile_order({6500, 3000, 2500, 1800, 1200, 800, 400, 184}, 128, 256, 32, 32, 8, true);
     tile_order({1024, 1024, 1024, 1024}, 16, 256, 32, 32, 8, true);
     tile_order({4096}, 24, 256, 32, 32, 8, true);
+    tile_order({4608, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, 8, 256, 32, 32, 8, true, true, true);        // 33 tiles per XCD: the last one in halves
     tile_order({300, 200, 100}, 4, 64, 0, 32, 8, false);                 // the f32 kernel's row tile
     // the float32 kernels: row tiles of 32 rows, none of them tall, column tiles of 64 or 16 features or columns
     std::uniform_int_distribution<int> any_nt(1, 1000), rows32(0, 300), many32(0, 3000);
@@ -281,7 +291,7 @@ static void tile_orders() {
         tile_order(counts, rep % 4 == 0 ? 1 + (int)(g_rng() % 24) : any_nt(g_rng), 32, 0, rep % 2 ? 32 : 0, rep % 5 ? 8 : 1, false, rep % 3 != 0);
         ++cases;
     }
-    std::printf("tile order: %d random cases and 6 fixed ones ok\n", cases);
+    std::printf("tile order: %d random cases and 7 fixed ones ok\n", cases);
 }
 
 // The order of the kernel for few rows per expert: every (expert, row tile, column tile) exactly once, inside the grid.
@@ -305,6 +315,17 @@ static void rows_order() {
             total += m * NT;
         }
         CHECK(rows_grid(NT, R, BM, E) >= total);
+    }
+    // the row tiles of the 256-row kernel in the same order (locate_single_groups): inside its grid as well
+    for (int rep = 0; rep < 200; ++rep) {
+        const int NT = any_nt(g_rng), E = 1 + (int)(g_rng() % 64);
+        int R = 0, total = 0;
+        for (int e = 0; e < E; ++e) {
+            const int c = g_rng() % 4 ? few(g_rng) : many(g_rng);
+            R += c;
+            total += row_tiles_of(c, 256, rep % 2 ? 32 : 0).mtiles * NT;
+        }
+        CHECK(rows_grid(NT, R, 256, E) >= total);
     }
 }
 
@@ -340,8 +361,8 @@ static void last_rounds() {
     }
 }
 
-// Beyond one round of 256 blocks of 64 columns x 128 rows the linear map must not take the kernel for few rows (it was
-// 1.1 to 1.6 times the other kernel's time there), up to one round it must.
+// The linear map takes the kernel for few rows as long as blocks of 64 columns x 128 rows make one round of 256 (beyond it took 1.1 to 1.6 times the other kernel's time),
+// with a short k up to 32 rows, and with more than 128 rows as long as blocks of 128 columns x 64 rows make one round.
 static void linear_rule() {
     using moe::linear_takes_rows_kernel;
     for (int K : {1664, 2048, 4096, 16384})
@@ -351,6 +372,8 @@ static void linear_rule() {
             for (int N : {16512, 18432, 32000, 128256}) CHECK(!linear_takes_rows_kernel(T, K, N));
         }
     CHECK(linear_takes_rows_kernel(256, 4096, 8192) && !linear_takes_rows_kernel(257, 4096, 8192));
+    CHECK(linear_takes_rows_kernel(300, 4096, 6144) && linear_takes_rows_kernel(320, 4096, 6144) && !linear_takes_rows_kernel(321, 4096, 6144));
+    CHECK(linear_takes_rows_kernel(129, 4096, 10880) && !linear_takes_rows_kernel(129, 4096, 11008) && !linear_takes_rows_kernel(128, 4096, 16512));
     CHECK(linear_takes_rows_kernel(32, 1536, 65536) && !linear_takes_rows_kernel(33, 1536, 65536));
     CHECK(!linear_takes_rows_kernel(2147483647, 128, 2147483520));
     // its blocks: the fewest groups of 16 columns that make one round
