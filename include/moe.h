@@ -355,16 +355,18 @@ int moe_pre_attention(const moe_linear_shape* qkv_proj, const float* hidden, con
  *   "xcd_remap"   1: column-tile groups of the expert GEMMs are dealt round robin to the
  *                 8 XCDs; 0: block b computes tile b.                       default 1
  *   "half_tiles"  1: bf16 row tiles with at most 192 rows run shorter loops.   default 1
- *   "down_cols"   column tiles of the bf16 down GEMM: 0 = by grid size, 1 = 128 wide,
- *                 2 = 256 wide.                                              default 0
- *   "gate_cols"   accepted and ignored (the bf16 gate/up GEMM has one width of column tiles, 128
- *                 features).                                                 default 0
+ *   "down_cols"   column tiles of the bf16 down GEMM: 0 = by grid size, 1 = 128 wide, 2 = 256
+ *                 wide; with each of them the tiles of a last round that is at most half full
+ *                 may be computed in halves of their columns.               default 0
+ *   "gate_cols"   accepted and ignored (the width of the bf16 gate/up GEMM's column tiles is no
+ *                 choice: 128 features, in halves in such a last round).      default 0
  *   "tall_tiles"  1: bf16: row tiles may be up to 32 rows higher than 256, so that a small
  *                 remainder of an expert's rows needs no tile of its own.        default 1
  *   "fuse_gather" 1: moe_layer's gate/up GEMM gathers the rows of x itself (bf16: no x_perm
  *                 copy; f32: no copy kernel).                                default 1
  *   "chunked"     tile order of the expert GEMMs: the column tiles of an expert go to the XCDs
- *                 in chunks of about this many tiles (at most 32); 0: one by one.  default 32
+ *                 in chunks of about this many tiles (at most 32, with 129 to 256 rows per expert
+ *                 on average 8, with fewer single ones); 0: one by one.        default 32
  *   "tall_first"  1: inside a chunk the tall row tiles are numbered first.       default 1
  *   "balance"     1: no XCD runs more than an eighth of the tiles of an expert-GEMM launch: one
  *                 that was dealt more gives its last tiles to XCDs with fewer.   default 1

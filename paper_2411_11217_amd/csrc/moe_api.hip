@@ -16,14 +16,14 @@ void set_hip_error(hipError_t e) { g_last_hip_error = (int)e; }
 static int g_opts[OPT_COUNT] = {
     /*OPT_XCD_REMAP*/ 1,     // 1: the column tiles of the expert GEMMs are dealt round robin to the 8 XCDs
     /*OPT_PROFILE*/ 0,       // 1: moe_layer records stage events (see moe_profile_read)
-    /*OPT_DOWN_COLS*/ 0,     // column tiles of the bf16 down GEMM: 0 = by grid size, 1 = 128 wide, 2 = 256 wide
+    /*OPT_DOWN_COLS*/ 0,     // column tiles of the bf16 down GEMM: 0 = by grid size, 1 = 128 wide, 2 = 256 wide (a last round of at most half the compute units: half as wide)
     /*OPT_HALF_TILES*/ 1,    // 1: bf16 row tiles with at most 192 rows run the loop of their height
     /*OPT_FUSE_GATHER*/ 1,   // 1: the bf16 gate/up GEMM of moe_layer reads the rows of x through row_src (no x_perm copy)
     /*OPT_TALL_TILES*/ 1,    // 1: bf16: row tiles may be up to 32 rows higher than 256 (a small remainder needs no tile of its own)
     /*OPT_TALL_FIRST*/ 1,    // 1: bf16 tile numbering: inside a chunk of column-tile groups the tall row tiles come first
-    /*OPT_CHUNKED*/ 32,      // tile numbering: the column-tile groups of an expert go to the XCDs in chunks of about this many tiles (at most 32; 0: single groups)
+    /*OPT_CHUNKED*/ 32,      // tile numbering: the column-tile groups of an expert go to the XCDs in chunks of about this many tiles (at most 32, 8 up to 256 rows per expert on average; 0: single groups)
     /*OPT_BALANCE*/ 1,       // 1: an XCD with more than an eighth of a launch's tiles gives the rest to XCDs with fewer
-    /*OPT_GATE_COLS*/ 0,     // no effect (the bf16 gate/up GEMM has one width of column tiles)
+    /*OPT_GATE_COLS*/ 0,     // no effect (the width of the bf16 gate/up GEMM's column tiles is no choice: 128 features, in a half-full last round 64)
 };
 static const char* g_opt_names[OPT_COUNT] = {"xcd_remap", "profile", "down_cols", "half_tiles", "fuse_gather", "tall_tiles", "tall_first", "chunked", "balance", "gate_cols"};
 int get_opt(int id) { return g_opts[id]; }

@@ -39,7 +39,7 @@ int launch_expert_ffn_bf16(const moe_shape& s, const Geom& g, const FfnArgs& a, 
     // upper bound as ever).  us for the launch, narrow / wide: Mixtral-8x7B shape 1000 tokens (256 narrow tiles) 247 / 312, 1200 (512) 453 / 367;
     // Mixtral-8x22B shape 600 tokens (384) 384 / 295, 1000: 472 / 377; 2048 x 4096 1500 tokens (256) 74 / 92, 2500 (384) 108 / 95; 1024 x 2816
     // 2000 tokens (128) 55 / 69; DBRX shape 600 tokens (768) 435 / 405.
-    // down_cols: 0 = this rule, 1 / 2 = force NB.
+    // down_cols: 0 = this rule, 1 / 2 = force 128 / 256 columns.
     const int opt = get_opt(OPT_DOWN_COLS);
     const int64_t narrow_tiles = n_exp * row_tiles_each * (int64_t)g.dt;
     // Where even these are at most half a round: 64-wide ones, as long as the tiles that the routing makes are at most half a round
@@ -93,8 +93,8 @@ int launch_linear_bf16(const LinearArgs& a, hipStream_t st) {
     if ((int64_t)(a.T / BM + 1) * wide_tiles < 2 * kComputeUnits) {       // too few 256-wide tiles to fill the chip
         p.NT = p.n_page_tiles;
         // Row tiles of 128 as long as they make one round: a tile of 256 rows x 128 columns is a chain of some 0.6 us per k-step
-        // whatever else the chip does, one of 128 rows 0.4.  us for the pre-attention task, 256 / 128 rows: 4096 x 6144 270 tokens (144
-        // tiles of 128) 60 / 42, 300: 53 / 45, 512: 56 / 46; 6144 x 9216 256 tokens (144) 72 / 57; 2048 x 3072 700 tokens (144) 38 / 34,
+        // whatever else the chip does, one of 128 rows 0.4.  us for the pre-attention task, 256 / 128 rows: 4096 x 6144 512
+        // tokens (192 tiles of 128) 56 / 46; 6144 x 9216 256 tokens (144) 72 / 57; 2048 x 3072 700 tokens (144) 38 / 34,
         // 1000 (192) 40 / 34.  With up to 160 rows, a short tile of 256, they read the weights twice to have twice the blocks, which wide
         // matrices with a long k do not win back: 129 rows, 4096 x 13312 (208 tiles of 128) 37 / 34, 4096 x 14336 (224) 37 / 37, 4096 x 15360 (240) 37 / 38, 4096 x
         // 16384 (256) 35 / 40, 6144 x 13312 50 / 50, 6144 x 16384 47 / 55, but 2048 x 16384 21.4 / 20.4; 161 rows 4096 x 16384 39 / 36.

@@ -48,8 +48,9 @@ inline bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
 int validate_linear(const moe_linear_shape* s);
 int64_t linear_pages(const moe_linear_shape& s);
 
-// Where the dense linear map takes the kernel for few rows (csrc/moe_ffn_rows_bf16.hip): as long as its blocks of 64 columns
-// and 128 rows make one round on the 256 compute units, and with a short k and few rows.
+// Where the dense linear map takes the kernel for few rows (csrc/moe_ffn_rows_bf16.hip): as long as blocks of 64 columns and 128
+// rows, or with more than 128 rows of 128 columns and 64 rows, make one round on the 256 compute units (which blocks it has
+// then is linear_rows_block's choice), and with a short k and few rows.
 //   One matrix alone has too few columns to fill the chip with 256-row blocks (moe_ffn_gemm_bf16.h).  us, those blocks / this
 // kernel, weights where the call before left them | weights from HBM (copies that exceed the last-level cache in turn): 4096 x
 // 6144 (K x N) 1 token - | 45 / 15, 100: - | 47 / 30; 6144 x 9216 16 tokens 33 / 21 | 48 / 29, 100: 41 / 39 | 59 / 50;
@@ -61,7 +62,7 @@ int64_t linear_pages(const moe_linear_shape& s);
 // 1024 x 65536 32 tokens 28 / 25 | 33 / 29, 64: 31 / 30 | 36 / 36, 128: 34 / 36 | 39 / 50; 1024 x 18432 32 tokens 12 / 12 | 17 / 14;
 // 1536 x 18432 32 tokens 14 / 15 | 21 / 19, 1536 x 65536: 37 / 33 | 44 / 41; 2048 x 32768 32 tokens 24 / 23 | 28 / 27, but 2048 x 18432: 16
 // / 19 | 22 / 23.
-//   With more than 128 rows, as long as its blocks of 64 rows x 128 columns make one round: us, row tiles of 128 or 256 / this kernel, 4096 x
+//   With more than 128 rows and blocks of 64 rows x 128 columns: us, row tiles of 128 or 256 / this kernel, 4096 x
 // 6144 300 tokens 35 / 26 | 41 / 34; 6144 x 9216 140: 44 / 35 | 53 / 43; 4096 x 10880 192: 37 / 28 | 43 / 37; 2048 x 6144 300: 23 / 16 | 27 / 20; 4096 x 4096 450: 29 / 25 | 32
 // / 29.
 inline bool linear_takes_rows_kernel(int T, int K, int N) {
@@ -84,7 +85,7 @@ inline bool linear_takes_rows_kernel(int T, int K, int N) {
 // 64 x 128, weights where the call before left them | from HBM: 4096 x 5120 300 tokens 27.8 / 24.5 | 29.9 / 32.7; 4096 x 8192 192: 28.4 / 25.5 | 31.4 / 35.0;
 // 14336 x 5120 320: 85 / 71 | 92 / 99; 3072 x 1920 960: 24.4 / 23.9 | 24.9 / 25.8.  Not with at most 16 rows in the last of
 // them (8192 x 5120 257: 49 / 42 | 53 / 50; 4096 x 8192 129: 28 / 25 | 30 / 29), a short k (1024 x 5120 300: 11.1 / 10.1 | 12.0 / 12.1, 1536 x 1920 960: 15.4 / 14.6 |
-// 15.4 / 14.4), many row tiles, where one more or less is nothing (4096 x 512 4000: 46.2 / 27.2 | 46 / 27), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
+// 15.4 / 14.4), many row tiles, where one more or less is nothing (4096 x 512 4000: 42.8 / 26.2 | 42.8 / 26.9), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
 //   Where the two sides differ, weights from HBM decide: 65 to 96 rows with six groups lose where a matrix of 80 MB and more is in the last-level cache (the second row
 // tile's blocks, with 32 rows at most, run ahead of the first one's and read the weights again), 128 x 64 / six / eight groups: 4096 x 12288 72 tokens 26.5 / 32.8 / 24.3 | 34.4 / 28.4 / 32.5, 8192 x
 // 12288 65: 47.8 / 58.8 / 41.8 | 60.6 / 53.8 / 56.0, 1024 x 12288 65: 9.9 / 10.3 / 9.7 | 12.4 / 11.5 / 12.2.

@@ -5,8 +5,8 @@
 // An expert with `mtiles` row tiles and NT column tiles has mtiles x NT tiles.  The row tiles of one
 // column tile form a GROUP: they read the same weight tiles.  Blocks that run at the same time on one
 // XCD (32 compute units, one L2) should read few distinct operand tiles, so the tiles are dealt to the
-// XCDs in CHUNKS of about `chunked` (32) tiles, as square as possible:
-//   * up to 8 row tiles: a chunk is all row tiles of G = clamp(32 / mtiles, 1, 8) consecutive groups;
+// XCDs in CHUNKS of about `chunked` tiles (32; 8 up to 256 rows per expert on average, see fill_common), as square as possible:
+//   * up to 8 row tiles: a chunk is all row tiles of G = clamp(chunked / mtiles, 1, 8) consecutive groups;
 //   * 9 .. 256 row tiles: the row tiles are cut into nb ROW BLOCKS of at most max(8, ceil(mtiles / 16))
 //     row tiles (equal sizes, the first `rbig` blocks one tile more), and a chunk is the row tiles of one
 //     row block in G consecutive groups, G from the row-block height as above;
