@@ -83,9 +83,9 @@ inline bool linear_takes_rows_kernel(int T, int K, int N) {
 //   With an odd number of row tiles of 64 the blocks of eight groups leave more compute units idle than blocks of 128 rows x 64 columns do, and
 // weights from HBM, which a program with more than one layer has, come at the rate of the compute units that ask for them.  us, 128 x 64 /
 // 64 x 128, weights where the call before left them | from HBM: 4096 x 5120 300 tokens 27.8 / 24.5 | 29.9 / 32.7; 4096 x 8192 192: 28.4 / 25.5 | 31.4 / 35.0;
-// 14336 x 5120 320: 85 / 71 | 92 / 99; 3072 x 1920 960: 24.4 / 23.9 | 24.9 / 25.8.  Not with at most 16 rows in the last of
-// them (8192 x 5120 257: 49 / 42 | 53 / 50; 4096 x 8192 129: 28 / 25 | 30 / 29), a short k (1024 x 5120 300: 11.1 / 10.1 | 12.0 / 12.1, 1536 x 1920 960: 15.4 / 14.6 |
-// 15.4 / 14.4), many row tiles, where one more or less is nothing (4096 x 512 4000: 42.8 / 26.2 | 42.8 / 26.9), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
+// 14336 x 5120 320: 85 / 71 | 92 / 99; 2048 x 3072 576: 17.2 / 15.6 | 18.0 / 19.0; 3072 x 1920 960: 24.4 / 23.9 | 24.9 / 25.8.  Not with at most 24 rows in the last of
+// them (4096 x 5120 264: 27.4 / 24.2 | 29.7 / 29.5; 8192 x 8192 150: 51 / 42 | 60 / 55; 4096 x 3072 530: 28.3 / 24.5 | 29.5 / 29.0), a short k (1536 x 5120 300: 14.2 / 12.9 | 15.5 / 15.9, 1536 x 3072 576: 14.2 / 12.8 |
+// 14.8 / 14.2, 2048 x 1920 960: 17.7 / 15.8 | 17.7 / 15.9), many row tiles, where one more or less is nothing (4096 x 512 4000: 42.8 / 26.2 | 42.8 / 26.9), or an even number (4096 x 16384 100: 32 / 29 | 39 / 37).
 //   Where the two sides differ, weights from HBM decide: 65 to 96 rows with six groups lose where a matrix of 80 MB and more is in the last-level cache (the second row
 // tile's blocks, with 32 rows at most, run ahead of the first one's and read the weights again), 128 x 64 / six / eight groups: 4096 x 12288 72 tokens 26.5 / 32.8 / 24.3 | 34.4 / 28.4 / 32.5, 8192 x
 // 12288 65: 47.8 / 58.8 / 41.8 | 60.6 / 53.8 / 56.0, 1024 x 12288 65: 9.9 / 10.3 / 9.7 | 12.4 / 11.5 / 12.2.
@@ -108,7 +108,7 @@ inline LinearBlock linear_rows_block(int T, int K, int N) {
     if (tall_one_round && T <= 96 && K <= 512) return {128, 4};
     if (one_round(5)) return {64, 5};
     if (one_round(6)) return {64, 6};
-    if (tall_one_round && row_tiles % 2 && row_tiles < 32 && (T - 1) % 64 >= 16 && K >= (row_tiles < 8 ? 1536 : 3072)) return {128, 4};
+    if (tall_one_round && row_tiles % 2 && row_tiles < 32 && (T - 1) % 64 >= 24 && K >= (row_tiles < 10 ? 2048 : 3072)) return {128, 4};
     return {64, 8};
 }
 

@@ -393,8 +393,8 @@ static void linear_rule() {
     CHECK(block(96, 512, 12288, 128, 4) && block(97, 512, 12288, 64, 6) && block(65, 512, 10240, 128, 4) && block(65, 640, 10240, 64, 5));
     CHECK(block(65, 640, 16384, 64, 8) && block(65, 512, 16384, 128, 4) && block(65, 256, 8192, 64, 4) && block(300, 128, 5120, 64, 8));
     // an odd number of row tiles: 128 rows x 64 columns, which are on more compute units than 64 rows x 128 columns
-    CHECK(block(300, 4096, 5120, 128, 4) && block(192, 1536, 8192, 128, 4) && block(960, 3072, 1920, 128, 4));
-    CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(272, 4096, 5120, 64, 8) && block(273, 4096, 5120, 128, 4) && block(300, 1024, 5120, 64, 8) && block(960, 1536, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
+    CHECK(block(300, 4096, 5120, 128, 4) && block(192, 2048, 8192, 128, 4) && block(576, 2048, 3072, 128, 4) && block(960, 3072, 1920, 128, 4));
+    CHECK(block(300, 4096, 6144, 64, 8) && block(384, 4096, 5120, 64, 8) && block(280, 4096, 5120, 64, 8) && block(281, 4096, 5120, 128, 4) && block(300, 1536, 5120, 64, 8) && block(960, 2944, 1920, 64, 8) && block(4000, 4096, 512, 64, 8));
 }
 
 int main() {

@@ -72,10 +72,10 @@ def test_linear_with_few_rows(T, K, N):
 
 
 @pytest.mark.parametrize("T,K,N", [(300, 256, 384), (17, 1152, 4096), (1, 640, 6144), (32, 128, 8192), (16, 128, 128), (33, 1152, 4096), (1729, 1536, 128), (3457, 1536, 128), (130, 128, 2048), (64, 640, 6144), (33, 128, 9216), (300, 256, 3072), (129, 640, 6144),
-                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (128, 640, 9216), (65, 640, 12288), (192, 256, 9216), (129, 128, 9216), (257, 384, 6144), (145, 1536, 8192), (300, 1536, 5120), (65, 512, 9216), (96, 128, 16384)])
+                                   (700, 256, 2176), (193, 1152, 6144), (320, 128, 6144), (128, 640, 9216), (65, 640, 12288), (192, 256, 9216), (129, 128, 9216), (257, 384, 6144), (153, 2048, 8192), (300, 2048, 5120), (65, 512, 9216), (96, 128, 16384)])
 def test_linear_blocks_of_one_to_eight_wavefronts(T, K, N):
     # one, two, four, five (the last block has a wavefront too many), six (two too many, and none) and eight column groups of 16 per
-    # block; blocks of 32 rows (up to 32 tokens) and of 128 (the last four); two to 24 k-steps, last row tiles of 1 to 64 rows
+    # block; blocks of 32 rows (up to 32 tokens) and of 128 (the last four); two to 32 k-steps, last row tiles of 1 to 64 rows
     g = torch.Generator().manual_seed(T + K)
     x = torch.randn((T, K), generator=g)
     W = (torch.randn((N, K), generator=g) * 0.05).to(torch.bfloat16)
